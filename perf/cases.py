@@ -33,7 +33,7 @@ def listed():
         _seq("one_small", 1, 32, 1, 3200, 1000, 500, value="free", sigma=0.6),
         # a mixed bag of candidates, values unrelated to times, ragged lists, fill order given
         _seq("mixed_bag", 777, 203, 3, 21000, 7001, 3500, value="free", sigma=0.9, ragged=True),
-        # GPT-2 windows in 10 us units with priorities: the longest rows that stay on chip
+        # GPT-2 windows in 10 us units with priorities: rows at the border of what a compute unit's LDS holds
         _seq("gpt2_10us", 256, 148, 1, 54640, 38100, 16900, value="priority", sigma=0.8),
         # the ResNet-101 candidate set, every k = 1..4 in one call, on a plain handle (bench.py's headline)
         _seq("resnet101_sweep", 4096, 314, 4, 24200, 11800, 5900),
