@@ -90,18 +90,13 @@ typedef struct {
  * treat a window as the subset-sum problem it is (Sec. III.B, Problem 1 with profit = time):
  * the DP row is the set of reachable sums, one bit per cell, an item is one shift-and-or
  * of the set (32 cells per instruction), and the canonical selection - the one the exact DP
- * walks back, smallest mask among the optima - is read off a per-cell record of the first
- * item that reached each sum.  One wavefront per instance, everything in LDS, no scratch
- * memory.  max_items decides the width of that record and with it how many instances share
- * a compute unit: 8-bit cells up to 255 items, 8-bit cells plus one snapshot of the set up
- * to 511, 16-bit cells beyond (create returns DEFT_ERR_LIMIT when set, record and item list
- * exceed a compute unit's LDS).  Algorithm 1's levels are read off the same set (a level's
- * answer is the largest reachable sum not above its remaining time, taken before the item
- * that ends the level is added), and so are the capacity sweep's answers (the final set at
- * the largest capacity, one walk per capacity).  Results are bit-identical to those of a
- * handle without flags.  Where the one more item list those two modes need does not fit
- * the LDS, they run as under DEFT_FLAG_VALUES_ARE_WEIGHTS when max_capacity <= 26623 and on
- * the 32-bit rows above that.  deft_knapsack_get_info reports seq_path 4.
+ * walks back, smallest mask among the optima - is read off a record of the first item that
+ * reached each sum.  One wavefront per instance, set and record in registers and LDS, no
+ * scratch memory (create returns DEFT_ERR_LIMIT when an item list beside them exceeds a compute
+ * unit's LDS).  max_items decides the width of the record: 6, 9 or 12 bits per cell for up to
+ * 64, 512 or 4096 items.  Algorithm 1's levels and the capacity sweep's answers are read off
+ * the same set and record.  Results are bit-identical to those of a handle without flags.
+ * deft_knapsack_get_info reports seq_path 4.
  */
 #define DEFT_FLAG_SUBSET_SUM 2u
 

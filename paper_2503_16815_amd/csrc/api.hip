@@ -51,8 +51,7 @@ struct deft_knapsack {
     unsigned long long *glob_streamed = nullptr;  // device counter read by get_profile
     unsigned long long *lds_swept = nullptr;      // device counter read by get_profile (LDS path)
 
-    bool use_bits = false;        // SEQUENTIAL mode runs on the bit-set kernels (DEFT_FLAG_SUBSET_SUM)
-    bool use_bits_rec = false;    // and so do RECURSIVE and CAPACITY_SWEEP
+    bool use_bits = false;        // the sequential-layout modes run on the bit-set kernels (DEFT_FLAG_SUBSET_SUM)
     SeqBitsPlan bits_plan{};
 
     void *sim_buffers = nullptr;  // task-queue simulation: allocated by its first call
@@ -192,17 +191,13 @@ extern "C" deft_status_t deft_knapsack_create(const deft_knapsack_config_t *cfg,
     if (st == DEFT_OK && subset_sum) {
         const int lds_wg = (int)prop.sharedMemPerBlockOptin > 0 ? (int)prop.sharedMemPerBlockOptin
                                                                 : (int)prop.sharedMemPerBlock;
-        if (!seq_bits_plan(cfg->max_capacity, cfg->max_items, lds_wg, &h->bits_plan)) {
+        if (!seq_bits_plan(cfg->max_capacity, cfg->max_items, lds_wg, h->compute_units, &h->bits_plan)) {
             st = DEFT_ERR_LIMIT;  // (an item list too long for the LDS beside the row)
         } else if (seq_bits_prepare(h->bits_plan) != hipSuccess) {
             (void)hipGetLastError();
             st = DEFT_ERR_DEVICE;
-        } else if (h->bits_plan.lds_bytes_rec > 0 && seq_bits_rec_prepare(h->bits_plan) != hipSuccess) {
-            (void)hipGetLastError();
-            st = DEFT_ERR_DEVICE;
         } else {
             h->use_bits = true;
-            h->use_bits_rec = h->bits_plan.lds_bytes_rec > 0;
         }
     }
     if (st == DEFT_OK && want_joint) {
@@ -280,13 +275,9 @@ extern "C" deft_status_t deft_knapsack_solve_batch(deft_knapsack_t *h, const def
     if (prof && !prof->begin(st)) return DEFT_ERR_DEVICE;
 
     hipError_t e = hipSuccess;
-    if (b->mode == DEFT_MODE_SEQUENTIAL && h->use_bits) {
+    if ((b->mode == DEFT_MODE_SEQUENTIAL || probing) && h->use_bits) {
         if (prof) prof->sweep_begin(st);
-        e = seq_bits_launch(h->bits_plan, a, st);
-        if (prof) prof->sweep_end(st);
-    } else if ((b->mode == DEFT_MODE_RECURSIVE || b->mode == DEFT_MODE_CAPACITY_SWEEP) && h->use_bits_rec) {
-        if (prof) prof->sweep_begin(st);
-        e = seq_bits_rec_launch(h->bits_plan, a, st);
+        e = seq_bits_launch(h->bits_plan, a, st, nullptr);
         if (prof) prof->sweep_end(st);
     } else if (b->mode == DEFT_MODE_SEQUENTIAL || (probing && !on_lds)) {
         if (h->seq_path == 3) {
@@ -355,10 +346,9 @@ extern "C" deft_status_t deft_knapsack_simulate_schedule(deft_knapsack_t *h, con
     Profiler *prof = h->profiling ? &h->prof : nullptr;
     if (prof && !prof->begin(st)) return DEFT_ERR_DEVICE;
     const auto solve = [&](const BatchArgs &x) -> hipError_t {
-        if ((h->use_bits && x.mode == DEFT_MODE_SEQUENTIAL) || (h->use_bits_rec && x.mode == DEFT_MODE_RECURSIVE)) {
+        if (h->use_bits) {
             if (prof) prof->sweep_begin(st);
-            const hipError_t rc = x.mode == DEFT_MODE_SEQUENTIAL ? seq_bits_launch(h->bits_plan, x, st)
-                                                                 : seq_bits_rec_launch(h->bits_plan, x, st);
+            const hipError_t rc = seq_bits_launch(h->bits_plan, x, st, nullptr);
             if (prof) prof->sweep_end(st);
             return rc;
         }

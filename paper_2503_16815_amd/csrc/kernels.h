@@ -68,21 +68,23 @@ hipError_t seq_lds_rec_launch(const SeqLdsPlan &plan, const BatchArgs &args, voi
 
 // ---- sequential layout, value = weight, one bit per cell (seq_bits_kernel.h) -----
 // One wavefront per instance; the reachable sums as a bit set in registers and LDS, the
-// selection from a per-cell "first item that reached this sum" array in LDS.  No scratch.
+// selection from a bit-sliced "first item that reached this sum" table in registers.  No scratch.
 struct SeqBitsPlan {
-    int32_t variant;         // index into the compiled words-per-lane table
+    int32_t variant;         // index into the compiled (words per lane, planes) table
     int32_t words_per_lane;  // K: capacities up to 2048 K - 1
-    int32_t row_words;       // 64 K
-    int32_t first_ints;      // LDS ints of the per-cell array (8-bit cells for at most 255 items, else 16-bit)
+    int32_t planes;          // NP: lists of up to 2^NP items
+    int32_t row_words;       // 64 x the slots max_capacity needs
     int32_t n_pad;           // entries of the stage's item list in LDS
-    int32_t lds_bytes;       // dynamic LDS per workgroup (= per instance)
-    int32_t lds_bytes_rec;   // the same for the Algorithm 1 kernels (0: they do not fit)
+    int32_t lds_limit;       // most dynamic LDS a workgroup may ask for
+    int32_t lds_bytes;       // what one instance on its own takes
+    int32_t compute_units;
 };
-bool seq_bits_plan(int32_t max_capacity, int32_t max_items, int32_t lds_per_wg_bytes, SeqBitsPlan *plan);
+bool seq_bits_plan(int32_t max_capacity, int32_t max_items, int32_t lds_per_wg_bytes, int32_t compute_units, SeqBitsPlan *plan);
 hipError_t seq_bits_prepare(const SeqBitsPlan &plan);
-hipError_t seq_bits_launch(const SeqBitsPlan &plan, const BatchArgs &args, hipStream_t stream);
-hipError_t seq_bits_rec_prepare(const SeqBitsPlan &plan);  // DEFT_MODE_RECURSIVE (seq_bits_rec.hip)
-hipError_t seq_bits_rec_launch(const SeqBitsPlan &plan, const BatchArgs &args, hipStream_t stream);
+// DEFT_MODE_SEQUENTIAL, DEFT_MODE_RECURSIVE and DEFT_MODE_CAPACITY_SWEEP.
+// `swept_cells` (device, may be null): every stage adds the cell-updates its sweep evaluated.
+hipError_t seq_bits_launch(const SeqBitsPlan &plan, const BatchArgs &args, hipStream_t stream, unsigned long long *swept_cells);
+void *seq_bits_long_kernel(int variant);  // the kernels of the longer rows (seq_bits_long.hip)
 
 // ---- per-call HIP-event timing (profile.hip) ---------------------------------
 class Profiler {

@@ -1,39 +1,101 @@
-// The bit-set kernels of the sequential mode (DEFT_FLAG_SUBSET_SUM handles) and the plan both
-// sets of bit-set kernels share.
+// The bit-set kernels (seq_bits_kernel.h) for the shorter rows, and the plan and launch all of
+// them share.
 #include "seq_bits_kernel.h"
 
 namespace deft {
 
-bool seq_bits_plan(int32_t max_capacity, int32_t max_items, int32_t lds_per_wg_bytes, SeqBitsPlan *plan)
+namespace {
+
+// LDS is handed out in granules of 1280 bytes, 128 of them per compute unit.
+constexpr int kLdsGranule = 1280, kLdsGranulesPerCu = 128;
+
+BitsLayout bits_layout(const SeqBitsPlan &p, bool caps_sweep)
 {
-    const int32_t n_pad = (max_items + 7) & ~7;
-    // a cell holds a position in the stage's list
-    const int mode = max_items <= 255 ? 1 : max_items <= 511 ? 2 : 0;
-    const int cell_bytes = mode == 0 ? 2 : 1;
+    BitsLayout lay;
+    lay.row_words = p.row_words;
+    lay.n_pad = p.n_pad;
+    lay.mark_words = caps_sweep ? p.n_pad : p.n_pad / 4;
+    lay.plane_words = p.row_words * bits_plane_stride(p.planes);
+    lay.wave_words = 2 * p.row_words + 4 + (p.n_pad + 8) + p.n_pad / 2 + lay.mark_words;
+    return lay;
+}
+
+int64_t bits_lds_bytes(const BitsLayout &lay, int waves)
+{
+    return ((int64_t)4 + lay.plane_words + (int64_t)waves * lay.wave_words) * 4;
+}
+
+// Instances a compute unit holds when `waves` of them share a workgroup (0: they do not fit).
+int bits_per_cu(const SeqBitsPlan &p, int64_t lds, int waves)
+{
+    if (lds > p.lds_limit) return 0;
+    const int by_lds = kLdsGranulesPerCu / (int)((lds + kLdsGranule - 1) / kLdsGranule) * waves;
+    const int by_regs = 4 * bits_waves_per_simd(p.words_per_lane, p.planes) / waves * waves;
+    return by_lds < by_regs ? by_lds : by_regs;
+}
+
+BitsKernel bits_kernel(const SeqBitsPlan &p)
+{
+    switch (p.variant) {
+    case 0: return &seq_bits_kernel<2, 6>;
+    case 1: return &seq_bits_kernel<2, 9>;
+    case 2: return &seq_bits_kernel<2, 12>;
+    case 3: return &seq_bits_kernel<5, 6>;
+    case 4: return &seq_bits_kernel<5, 9>;
+    case 5: return &seq_bits_kernel<5, 12>;
+    case 6: return &seq_bits_kernel<7, 6>;
+    case 7: return &seq_bits_kernel<7, 9>;
+    case 8: return &seq_bits_kernel<7, 12>;
+    default: return reinterpret_cast<BitsKernel>(seq_bits_long_kernel(p.variant));
+    }
+}
+
+}  // namespace
+
+bool seq_bits_plan(int32_t max_capacity, int32_t max_items, int32_t lds_per_wg_bytes, int32_t compute_units, SeqBitsPlan *p)
+{
     for (int i = 0; i < kNumBitsWords; ++i) {
         const int K = kBitsWords[i];
         if ((int64_t)max_capacity > (int64_t)K * 2048 - 1) continue;
-        const int64_t row_words = (int64_t)K * 64;
-        const int64_t first_ints = (((int64_t)max_capacity + 1) * cell_bytes + 3) / 4;  // cells 0 .. max_capacity
-        const int64_t lds = (kBitsGuardWords + row_words + first_ints + 2 * (int64_t)n_pad + (mode == 2 ? row_words : 0)) * 4;
-        if (lds > lds_per_wg_bytes - 256) return false;
-        plan->variant = 3 * i + mode;
-        plan->words_per_lane = K;
-        plan->row_words = (int32_t)row_words;
-        plan->first_ints = (int32_t)first_ints;
-        plan->n_pad = n_pad;
-        plan->lds_bytes = (int32_t)lds;
-        // Algorithm 1 keeps one more list (the levels' remaining times); where that does not
-        // fit any more, the mode stays on the LDS-row kernels
-        const int64_t lds_rec = lds + (int64_t)n_pad * 4;
-        plan->lds_bytes_rec = lds_rec > lds_per_wg_bytes - 256 ? 0 : (int32_t)lds_rec;
-        return true;
+        const int which = max_items <= 64 ? 0 : max_items <= 512 ? 1 : 2, grain = bits_grain(K);
+        p->variant = 3 * i + which;
+        p->words_per_lane = K;
+        p->planes = kBitsPlanes[which];
+        p->row_words = (max_capacity / 2048 + grain) / grain * grain * 64;
+        p->n_pad = (max_items + 7) & ~7;
+        p->lds_limit = lds_per_wg_bytes - 256;
+        p->compute_units = compute_units;
+        p->lds_bytes = (int32_t)bits_lds_bytes(bits_layout(*p, true), 1);
+        return p->lds_bytes <= p->lds_limit;
     }
     return false;
 }
 
-hipError_t seq_bits_prepare(const SeqBitsPlan &plan) { return bits_prepare<false>(plan.variant); }
+hipError_t seq_bits_prepare(const SeqBitsPlan &p)
+{
+    // the attribute belongs to the kernel, not to the handle: the most any handle may ask for
+    // (a compute unit's LDS less a small allowance)
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(bits_kernel(p)), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               160 * 1024 - 256);
+}
 
-hipError_t seq_bits_launch(const SeqBitsPlan &p, const BatchArgs &a, hipStream_t st) { return bits_launch<false>(p, a, st); }
+hipError_t seq_bits_launch(const SeqBitsPlan &p, const BatchArgs &a, hipStream_t st, unsigned long long *swept_cells)
+{
+    const BitsLayout lay = bits_layout(p, a.mode == DEFT_MODE_CAPACITY_SWEEP);
+    // Instances per workgroup: they share one copy of the walk's planes, the largest part of an
+    // instance's LDS, but walk one at a time.  So: as few as still let the whole batch run at
+    // once, else as many as put the most instances on a compute unit.
+    int waves = 1, most = 0;
+    for (const int w : {1, 2, 4}) {
+        const int64_t lds = bits_lds_bytes(lay, w);
+        const int held = bits_per_cu(p, lds, w);
+        if (held > most) most = held, waves = w;
+        if ((int64_t)held * p.compute_units >= a.batch) break;
+    }
+    const size_t lds = (size_t)bits_lds_bytes(lay, waves);
+    const unsigned grid = (unsigned)((a.batch + waves - 1) / waves);
+    hipLaunchKernelGGL(bits_kernel(p), dim3(grid), dim3(64 * waves), lds, st, a, lay, swept_cells);
+    return hipGetLastError();
+}
 
 }  // namespace deft

@@ -6,19 +6,45 @@
 // the whole set, reach |= reach << w, 32 cells per instruction.  The selection the exact DP
 // walks back (take an item at a cell only when it strictly improves the value, walk from
 // the last item: among optimal subsets the one with the smallest mask) comes out of one
-// more array, first[t] = the first offered item that made the sum t reachable:
+// more table, first[t] = the first offered item that made the sum t reachable:
 //   the DP keeps item q at cell c exactly when the best sum up to c rises with item q, i.e.
 //   when the target t = row_q[c] was not reachable before q; if q is not kept the target
 //   stays, if it is the target becomes t - w_q.  So the walk is t = row[C]; while t > 0:
-//   q = first[t], take q, t -= w_q - a chain of LDS lookups, one per item taken, with no keep
-//   table and no memory round trips.
-// One wavefront owns an instance (one 64-thread workgroup; no barriers).  Word i of the set
-// (cells 32 i .. 32 i + 31) lives in lane i % 64, register slot i / 64, with a copy in LDS
-// that the shifted operand is read from; first[] (8 or 16 bits per cell, by the handle's
-// longest list) and the stage's offered items (weight, index) live in LDS too, so the kernel
-// needs no scratch memory at all.  A sweep ends as soon as the capacity itself is reachable.
-// Below the set a guard zone of zero words serves the reads of light items; heavier items
-// clamp their word index into it.
+//   q = first[t], take q, t -= w_q.
+//
+// One wavefront owns an instance.  Word i of the set (cells 32 i .. 32 i + 31) lives in lane
+// i % 64, register slot i / 64, with a copy in LDS that the shifted operand is read from
+// (below it a zone of zero words as long as the set, so that no shift needs clamping).
+//
+// first[] is kept bit-sliced, in registers, as NP planes of one bit per cell, and costs one
+// exclusive-or per word and item.  Number the items by a Gray code g: from one item to the next
+// exactly one bit j of it toggles, and the item's step is plane[j] ^= set (as it stands after
+// the item).  A sum t first reached by item q is in the set from step q on, so plane j has
+// toggled once for every change of bit j from q to the last step L: the planes of t spell
+// g(q) ^ g(L).  Which bit toggles follows from the item's number alone (the trailing zeros of
+// q + 1), so four items are unrolled with planes 0, 1, 0 fixed and the fourth item's plane
+// picked by a uniform branch.  (An array of first[] cells in LDS, written where an
+// item reached a fresh sum, took half of the kernel - the fresh words are few and found by
+// ballots, bit by bit - and its LDS held a compute unit to eight instances.  The ResNet-101-shaped
+// sweep of 4096 schedules took 0.469 ms with it and one lookup per taken item in the walk, and
+// takes 0.096 ms now; 1024 candidates of the task queues over eight iterations 2.03 and 0.75 ms.)
+//
+// What bounds it: a chain of one LDS write and one LDS read per item and, with the compute unit
+// full of instances, the LDS pipeline (two words read and one written per 32 cells).
+//
+// Items only ever reach as far as the sum of the weights so far, so a block of four items works
+// on the register slots below that, a compile-time count moved up as the sum grows: on average
+// a little more than half of the slots.
+//
+// The walk reads its planes from LDS, where they are put once the sweep is over.  It does not
+// follow the chain item by item: 64 lanes suppose that the next 64 items down the list are
+// all taken, each looks first[] up at the target this leaves it, and a ballot finds the first
+// lane whose item was not the one; the lanes before it take theirs.  A sweep that fills the
+// window from the front takes long runs (all but a handful of the items in front of the
+// last one), so a walk is a few rounds where it was a chain of a hundred dependent lookups.
+// The planes are the largest part of the LDS an instance needs, and only during its walk: the
+// wavefronts of a workgroup share one copy under a lock (held for one walk at a time; the
+// holder waits for nobody).
 #pragma once
 
 #include "instance_check.h"
@@ -27,7 +53,17 @@ namespace deft {
 
 namespace {
 
-constexpr int kBitsGuardWords = 128;  // zero words below the set: items up to 32 * 126 cells read without clamping
+constexpr int kBitsEnumItems = 6;  // stages offered at most this many items are settled by enumeration
+
+// words-per-lane counts are compiled for; a block of items works on a multiple of bits_grain(K) slots
+constexpr int bits_grain(int k) { return k <= 7 ? 1 : k <= 14 ? 2 : 4; }
+constexpr int bits_plane_stride(int np) { return np | 1; }  // odd: a lane's planes are spread over the LDS banks
+// wavefronts per SIMD the register budget is held to: planes, set, and about fifty others
+constexpr int bits_waves_per_simd(int k, int np)
+{
+    const int regs = k * (np + 1) + 50;
+    return regs <= 64 ? 8 : regs <= 80 ? 6 : regs <= 96 ? 5 : regs <= 128 ? 4 : regs <= 168 ? 3 : regs <= 256 ? 2 : 1;
+}
 
 __device__ __forceinline__ void wave_lds_sync()
 {
@@ -36,6 +72,15 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
+// The lane index as a value the compiler knows nothing about: what follows from the index alone (a
+// slot's address, its mask, for every slot) is cheap to compute where it is used; left visible it is
+// all computed once at kernel entry and parked in scratch memory.
+__device__ __forceinline__ int bits_local(int lane)
+{
+    asm volatile("" : "+v"(lane));
+    return lane;
 }
 
 template <class Op>
@@ -60,208 +105,357 @@ __device__ __forceinline__ int bits_wave_suffix_sum(int x, int lane)
               t3 = __builtin_amdgcn_readlane(x, 48);
     return x + (lane < 16 ? t1 : 0) + (lane < 32 ? t2 : 0) + (lane < 48 ? t3 : 0);
 }
+// Sum over the lanes at and below `lane`, the same way from the other side.
+__device__ __forceinline__ int bits_wave_prefix_sum(int x, int lane)
+{
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);  // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);  // row_shr:2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);  // row_shr:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);  // row_shr:8
+    const int t0 = __builtin_amdgcn_readlane(x, 15), t1 = __builtin_amdgcn_readlane(x, 31),
+              t2 = __builtin_amdgcn_readlane(x, 47);
+    return x + (lane >= 16 ? t0 : 0) + (lane >= 32 ? t1 : 0) + (lane >= 48 ? t2 : 0);
+}
 __device__ __forceinline__ int bits_wave_sum(int x) { return bits_wave_reduce(x, [](int a, int b) { return a + b; }); }
 __device__ __forceinline__ int bits_wave_max(int x) { return bits_wave_reduce(x, [](int a, int b) { return max(a, b); }); }
 
-// One stage's sweep over `nact` offered items (weights in lw[], LDS) at capacity C, NB words
-// per lane.  Returns the stage's value (largest reachable sum <= C); first[t] is set for
-// every reachable t in 1 .. C (when the sweep ends early: for every t reached so far).
-// The sweep ends as soon as C itself is reachable: the value is final, and the walk from C
-// only follows sums that were reached by earlier items.
-// SNAP (8-bit cells, lists of 256 .. 511 items): a cell keeps the low eight bits of the
-// position, and `snap` keeps the set as it stood after the item at position 255: a sum in it
-// was first reached by a position below 256, any other by 256 + the cell.
-// REC (Algorithm 1): lp[q] is the remaining time P_q of the level made of the items before q
-// (-1 if that is negative).  The set before item q is exactly that level's, so its answer is
-// the largest reachable sum <= P_q: the word that holds P_q read from LDS and, where that one
-// has nothing at or below P_q, a search of the words below.  Levels are met deepest first and
-// a shallower one replaces the incumbent only when strictly greater, as the recursion does
-// on its way back up.  With `levels` the sweep ends, as in the sequential mode, once C (the
-// whole remaining time) is reachable: no level is worth more, the levels so far are worth
-// less (their sets did not hold C), and a later level is worth C exactly when its remaining
-// time is C (nothing is dropped after it) - the first such entry, else the whole list, is
-// the answer.  Without `levels` (the capacity sweep) it goes through the whole list.
-struct BitsLevel {
-    int value, length, remain;
+// LDS of a workgroup, in 32-bit words: [lock: 4][planes: plane_words] and per wavefront
+// [zeros: row_words][set: row_words][pad: 4][prefix: n_pad + 8][index: n_pad / 2][marks: mark_words].
+struct BitsLayout {
+    int32_t row_words, n_pad, mark_words, plane_words, wave_words;
 };
-template <int NB>
-__device__ __forceinline__ int largest_sum_up_to(const uint32_t *set, const uint32_t (&own)[NB], int lane, int limit)
+// One instance's share of it.
+struct BitsLds {
+    uint32_t *set;      // reachable sums, zeros below
+    int32_t *prefix;    // prefix[p]: weight of the stage's first p offered items
+    uint16_t *index;    // the item at position p of the stage's list
+    uint32_t *marks;    // sequential modes: a byte per item, its knapsack (255: none); capacity sweep: a word per item
+    uint32_t *planes;   // first[] of the walk in progress (shared by the workgroup)
+    int32_t *lock;
+};
+
+// The state of a stage's sweep.
+template <int K, int NP>
+struct BitsRows {
+    uint32_t own[K];
+    uint32_t plane[NP][K];
+};
+
+// A sweep in progress: the stage's list, where it may end, and how far it has come.
+struct BitsSweep {
+    int cnt, cap;             // items listed; the capacity
+    int stop_slot, stop_lane; // where cell `cap` lives; slot -1: the sweep does not end there
+    uint32_t stop_bit;
+    int check_mask;           // looked at after the items whose number has these bits set: every eighth, or every
+                              // second one of a list of at most 64
+    bool caps_sweep;          // the sweep ends once every lane's capacity `goal` is reachable
+    int goal;
+    int q;                    // items gone through so far (Gray steps taken)
+    int items;                // the same without the empty steps that fill up the last block
+    int wchunk, upto;         // lane x: weight of item (q & ~63) + x, and the list's weight up to and with it
+    bool reached;
+};
+
+// plane[k] ^= set[k] for M slots, if h == J (uniform).  The branch is inside the asm: as a branch of the
+// program every plane is merged behind it, and the merges of a chain of them cost the compiler
+// half of the registers again in copies.
+template <int J, int M>
+__device__ __forceinline__ void bits_toggle_if(int h, uint32_t *plane, const uint32_t *set)
 {
-    const int wi = limit >> 5;
-    const uint32_t x = set[wi] & (0xffffffffu >> (31 - (limit & 31)));  // every lane reads the same word
-    if (x != 0) return wi * 32 + 31 - __builtin_clz(x);               // (the same in every lane)
-    int best = 0;
-#pragma unroll
-    for (int k = 0; k < NB; ++k)
-        if (own[k] != 0 && k * 64 + lane < wi) best = max(best, (k * 64 + lane) * 32 + 31 - __builtin_clz(own[k]));
-    return bits_wave_max(best);
+    static_assert(M >= 1 && M <= 7, "slots per branch");
+    if constexpr (M == 1)
+        asm volatile("s_cmp_lg_u32 %2, %3\n\ts_cbranch_scc1 .Lkeep%=\n\t"
+                     "v_xor_b32 %0, %0, %1\n.Lkeep%=:"
+                     : "+v"(plane[0]) : "v"(set[0]), "s"(h), "n"(J) : "scc");
+    else if constexpr (M == 2)
+        asm volatile("s_cmp_lg_u32 %4, %5\n\ts_cbranch_scc1 .Lkeep%=\n\t"
+                     "v_xor_b32 %0, %0, %2\n\tv_xor_b32 %1, %1, %3\n.Lkeep%=:"
+                     : "+v"(plane[0]), "+v"(plane[1]) : "v"(set[0]), "v"(set[1]), "s"(h), "n"(J) : "scc");
+    else if constexpr (M == 3)
+        asm volatile("s_cmp_lg_u32 %6, %7\n\ts_cbranch_scc1 .Lkeep%=\n\t"
+                     "v_xor_b32 %0, %0, %3\n\tv_xor_b32 %1, %1, %4\n\tv_xor_b32 %2, %2, %5\n.Lkeep%=:"
+                     : "+v"(plane[0]), "+v"(plane[1]), "+v"(plane[2]) : "v"(set[0]), "v"(set[1]), "v"(set[2]), "s"(h), "n"(J) : "scc");
+    else if constexpr (M == 4)
+        asm volatile("s_cmp_lg_u32 %8, %9\n\ts_cbranch_scc1 .Lkeep%=\n\t"
+                     "v_xor_b32 %0, %0, %4\n\tv_xor_b32 %1, %1, %5\n\tv_xor_b32 %2, %2, %6\n\tv_xor_b32 %3, %3, %7\n.Lkeep%=:"
+                     : "+v"(plane[0]), "+v"(plane[1]), "+v"(plane[2]), "+v"(plane[3]) : "v"(set[0]), "v"(set[1]), "v"(set[2]), "v"(set[3]), "s"(h), "n"(J) : "scc");
+    else if constexpr (M == 5)
+        asm volatile("s_cmp_lg_u32 %10, %11\n\ts_cbranch_scc1 .Lkeep%=\n\t"
+                     "v_xor_b32 %0, %0, %5\n\tv_xor_b32 %1, %1, %6\n\tv_xor_b32 %2, %2, %7\n\tv_xor_b32 %3, %3, %8\n\tv_xor_b32 %4, %4, %9\n.Lkeep%=:"
+                     : "+v"(plane[0]), "+v"(plane[1]), "+v"(plane[2]), "+v"(plane[3]), "+v"(plane[4]) : "v"(set[0]), "v"(set[1]), "v"(set[2]), "v"(set[3]), "v"(set[4]), "s"(h), "n"(J) : "scc");
+    else if constexpr (M == 6)
+        asm volatile("s_cmp_lg_u32 %12, %13\n\ts_cbranch_scc1 .Lkeep%=\n\t"
+                     "v_xor_b32 %0, %0, %6\n\tv_xor_b32 %1, %1, %7\n\tv_xor_b32 %2, %2, %8\n\tv_xor_b32 %3, %3, %9\n\tv_xor_b32 %4, %4, %10\n\tv_xor_b32 %5, %5, %11\n.Lkeep%=:"
+                     : "+v"(plane[0]), "+v"(plane[1]), "+v"(plane[2]), "+v"(plane[3]), "+v"(plane[4]), "+v"(plane[5]) : "v"(set[0]), "v"(set[1]), "v"(set[2]), "v"(set[3]), "v"(set[4]), "v"(set[5]), "s"(h), "n"(J) : "scc");
+    else if constexpr (M == 7)
+        asm volatile("s_cmp_lg_u32 %14, %15\n\ts_cbranch_scc1 .Lkeep%=\n\t"
+                     "v_xor_b32 %0, %0, %7\n\tv_xor_b32 %1, %1, %8\n\tv_xor_b32 %2, %2, %9\n\tv_xor_b32 %3, %3, %10\n\tv_xor_b32 %4, %4, %11\n\tv_xor_b32 %5, %5, %12\n\tv_xor_b32 %6, %6, %13\n.Lkeep%=:"
+                     : "+v"(plane[0]), "+v"(plane[1]), "+v"(plane[2]), "+v"(plane[3]), "+v"(plane[4]), "+v"(plane[5]), "+v"(plane[6]) : "v"(set[0]), "v"(set[1]), "v"(set[2]), "v"(set[3]), "v"(set[4]), "v"(set[5]), "v"(set[6]), "s"(h), "n"(J) : "scc");
 }
-template <int NB, class FirstT, bool SNAP, bool REC>
-__device__ __forceinline__ int sweep_bits(uint32_t *set, FirstT *first, uint32_t *snap, const int32_t *lw, const int32_t *lp,
-                                          int lane, int nact, int C, BitsLevel &best, bool levels)
+template <int J, int KK>
+__device__ __forceinline__ void bits_toggle_slots(int h, uint32_t *plane, const uint32_t *set)
 {
-    uint32_t own[NB], need[NB];  // need: the cells of the word that are <= C
-#pragma unroll
-    for (int k = 0; k < NB; ++k) {
-        const int cell0 = (k * 64 + lane) * 32;
-        need[k] = cell0 + 31 <= C ? 0xffffffffu : cell0 > C ? 0u : (1u << (C - cell0 + 1)) - 1u;
-        own[k] = (k == 0 && lane == 0) ? 1u : 0u;  // the empty sum
-        set[k * 64 + lane] = own[k];
-        if constexpr (SNAP) snap[k * 64 + lane] = 0xffffffffu;  // until position 255 has been swept: everything
+    if constexpr (KK <= 7) {
+        bits_toggle_if<J, KK>(h, plane, set);
+    } else {
+        bits_toggle_if<J, 4>(h, plane, set);
+        bits_toggle_slots<J, KK - 4>(h, plane + 4, set + 4);
     }
-    wave_lds_sync();
-    const int c_lane = (C >> 5) & 63;
-    const uint32_t c_bit = 1u << (C & 31);
-    for (int q0 = 0; q0 < nact; q0 += 64) {
-        const int wchunk = q0 + lane < nact ? lw[q0 + lane] : 0;  // 64 weights in a register
-        const int pchunk = REC && q0 + lane < nact ? lp[q0 + lane] : -1;
-        const int q1 = min(q0 + 64, nact);
-        for (int q = q0; q < q1; ++q) {
-            const int w = __builtin_amdgcn_readlane(wchunk, q & 63);
-            if constexpr (REC) {
-                const int probe_at = __builtin_amdgcn_readlane(pchunk, q & 63);
-                if (probe_at >= 0) {
-                    const int level_value = largest_sum_up_to<NB>(set, own, lane, probe_at);
-                    if (level_value > best.value) best = BitsLevel{level_value, q, probe_at};
+}
+// The same for planes J .. NP - 1.
+template <int J, int NP, int KK, int K>
+__device__ __forceinline__ void bits_toggle_from(int h, uint32_t (&plane)[NP][K], const uint32_t (&set)[K])
+{
+    if constexpr (J < NP) {
+        bits_toggle_slots<J, KK>(h, plane[J], set);
+        bits_toggle_from<J + 1, NP, KK, K>(h, plane, set);
+    }
+}
+
+// Items until the list ends, the sweep may end, or slots beyond the first KK are needed; then on to
+// the next slot count.
+template <int KK, int K, int NP>
+__device__ __forceinline__ void bits_run(const BitsLds &l, BitsRows<K, NP> &r, int lane, BitsSweep &w)
+{
+    constexpr int GS = bits_grain(K);
+    uint32_t *set = l.set;
+    auto look = [&]() {
+        uint32_t word = 0;
+#pragma unroll
+        for (int k = KK - GS; k < KK; ++k)
+            if (k == w.stop_slot) word = (uint32_t)__builtin_amdgcn_readlane((int)r.own[k], w.stop_lane);
+        return (word & w.stop_bit) != 0;
+    };
+    while (w.q < w.cnt) {
+        if ((w.q & 63) == 0) {
+            const int p = w.q + lane;
+            w.upto = l.prefix[min(p + 1, w.cnt)];
+            w.wchunk = p < w.cnt ? w.upto - l.prefix[p] : 0;
+        }
+        if (KK < K && min(__builtin_amdgcn_readlane(w.upto, (w.q & 63) + 3), w.cap) >= KK * 2048) break;
+        bool early = false;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            int wt = __builtin_amdgcn_readlane(w.wchunk, (w.q & 63) + i);
+            if (i >= 2) wt = early ? 0 : wt;  // (an item of no weight changes nothing)
+            // new word i = old cells 32 i - wt .. 32 i - wt + 31, of the old words i - ws and i - ws - 1
+            // with ws = (wt - 1) / 32: a funnel shift by -wt mod 32 (the instruction takes the low five bits)
+            const uint32_t *src = set + (lane - ((wt - 1) >> 5));
+            uint32_t lo[KK], hi[KK];
+#pragma unroll
+            for (int k = 0; k < KK; ++k) {
+                lo[k] = src[k * 64 - 1];
+                hi[k] = src[k * 64];
+            }
+            wave_lds_sync();
+#pragma unroll
+            for (int k = 0; k < KK; ++k) {
+                r.own[k] |= __builtin_amdgcn_alignbit(hi[k], lo[k], (uint32_t)-wt);
+                set[k * 64 + lane] = r.own[k];
+                if (i < 3) {
+                    r.plane[i & 1][k] ^= r.own[k];
+                    asm volatile("" : "+v"(r.plane[i & 1][k]));  // (here: sunk to the end of the block it keeps three sets alive)
                 }
             }
-            // new word i = old cells 32 i - w .. 32 i - w + 31: two neighbouring old words, funnel-shifted
-            const int ws = w >> 5, bs = w & 31;
-            const int sh = (32 - bs) & 31;
-            const int base = lane - ws - (bs ? 1 : 0);  // old word below the pair of slot 0
-            uint32_t fresh[NB];
-            uint32_t any = 0;
-            if (ws + 2 <= kBitsGuardWords) {
-#pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    const uint32_t lo = set[base + k * 64], hi = set[base + k * 64 + 1];
-                    const uint32_t nw = own[k] | __builtin_amdgcn_alignbit(hi, lo, sh);
-                    fresh[k] = nw & ~own[k] & need[k];
-                    own[k] = nw;
-                    any |= fresh[k];
-                }
-            } else {
-#pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    const uint32_t lo = set[max(base + k * 64, -kBitsGuardWords)];
-                    const uint32_t hi = set[max(base + k * 64 + 1, -kBitsGuardWords)];
-                    const uint32_t nw = own[k] | __builtin_amdgcn_alignbit(hi, lo, sh);
-                    fresh[k] = nw & ~own[k] & need[k];
-                    own[k] = nw;
-                    any |= fresh[k];
-                }
-            }
-            wave_lds_sync();  // the old set has been read
-            if (__builtin_amdgcn_ballot_w64(any != 0) != 0ull) {
-#pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    unsigned long long who = __builtin_amdgcn_ballot_w64(fresh[k] != 0);
-                    if (who == 0ull) continue;  // nobody reached anything in this slot
-                    set[k * 64 + lane] = own[k];
-                    // Item q is the first to reach these sums.  Few words hold fresh bits (an item
-                    // mostly extends the set by a run of sums at its top), so the words are taken
-                    // one pair at a time and their bits are spread over the lanes: lane b of
-                    // either half of the wavefront marks cell b of its half's word.
-                    do {
-                        const int l0 = __builtin_ctzll(who);
-                        who &= who - 1;
-                        int l1 = l0;  // (an odd count: both halves mark the same word)
-                        if (who != 0ull) {
-                            l1 = __builtin_ctzll(who);
-                            who &= who - 1;
-                        }
-                        const uint32_t bits0 = __builtin_amdgcn_readlane(fresh[k], l0);
-                        const uint32_t bits1 = __builtin_amdgcn_readlane(fresh[k], l1);
-                        const int l = lane < 32 ? l0 : l1;
-                        const uint32_t bits = lane < 32 ? bits0 : bits1;
-                        if ((bits >> (lane & 31)) & 1u) first[(k * 64 + l) * 32 + (lane & 31)] = (FirstT)q;
-                    } while (who != 0ull);
-                }
-                // (C's word is in the last slot: NB is the smallest count that covers it)
-                const bool reached = lane == c_lane && (fresh[NB - 1] & c_bit) != 0;
-                wave_lds_sync();  // the new set is visible
-                if (__builtin_amdgcn_ballot_w64(reached) != 0ull) {
-                    if constexpr (!REC) {
-                        return C;
-                    } else if (levels) {
-                        int found = nact;  // the whole list
-                        for (int c0 = (q + 1) & ~63; c0 < nact; c0 += 64) {
-                            const int e = c0 + lane;
-                            const unsigned long long hit =
-                                __builtin_amdgcn_ballot_w64(e > q && e < nact && lp[e] == C);
-                            if (hit != 0ull) {
-                                found = c0 + __builtin_ctzll(hit);
-                                break;
-                            }
-                        }
-                        best = BitsLevel{C, found, C};
-                        return C;
-                    }
-                }
-            }
-            if constexpr (SNAP) {
-                if (q == 255) {
-#pragma unroll
-                    for (int k = 0; k < NB; ++k) snap[k * 64 + lane] = own[k];
-                }
-            }
+            wave_lds_sync();
+            if (i == 1 && w.check_mask == 1) early = look();
+        }
+        const int hp = __builtin_amdgcn_readfirstlane(__builtin_ctz((w.q >> 2) + 1) + 2);  // the plane of the fourth item
+        bits_toggle_slots<2, KK>(hp, r.plane[2], r.own);  // (half of the time)
+        if (hp > 2) bits_toggle_from<3, NP, KK, K>(hp, r.plane, r.own);
+        w.items = w.q + (early ? 2 : 4);
+        w.q += 4;
+        if (((w.q - 1) & w.check_mask) == w.check_mask) {
+            w.reached = early || look();
+            if (w.caps_sweep) w.reached = __builtin_amdgcn_ballot_w64((set[w.goal >> 5] >> (w.goal & 31) & 1u) == 0) == 0ull;
+            if (w.reached) return;
         }
     }
-    int top = 0;
+    if constexpr (KK < K) {
+        if (w.q < w.cnt) bits_run<KK + GS, K, NP>(l, r, lane, w);
+    }
+}
+
+// Sweeps the stage's list (`cnt` items, prefix sums in l.prefix) at capacity C.  Ends early once C
+// itself is reachable: the value is final, and the walk from C only follows sums that earlier
+// items reached.  (caps_sweep: once every lane's capacity `goal` is.)
+template <int K, int NP>
+__device__ __forceinline__ BitsSweep bits_sweep(const BitsLds &l, BitsRows<K, NP> &r, int lane, int cnt, int C,
+                                                bool caps_sweep, int goal)
+{
+    constexpr int GS = bits_grain(K);
+    lane = bits_local(lane);
+    const int slots_all = ((C >> 11) + GS) / GS * GS;
 #pragma unroll
-    for (int k = 0; k < NB; ++k) {
-        const uint32_t x = own[k] & need[k];
-        if (x) top = max(top, (k * 64 + lane) * 32 + 31 - __builtin_clz(x));
+    for (int k = 0; k < K; ++k) {
+        r.own[k] = (k == 0 && lane == 0) ? 1u : 0u;  // the empty sum
+        if (k < slots_all) l.set[k * 64 + lane] = r.own[k];
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            r.plane[j][k] = 0;
+        }
+    }
+    wave_lds_sync();
+    BitsSweep w{cnt, C, caps_sweep ? -1 : C >> 11, (C >> 5) & 63, 1u << (C & 31), !caps_sweep && cnt <= 64 ? 1 : 7,
+                caps_sweep, goal, 0, 0, 0, 0, false};
+    bits_run<GS, K, NP>(l, r, lane, w);
+    w.items = min(w.items, cnt);
+    return w;
+}
+
+// Largest reachable sum <= C.
+template <int K, int NP>
+__device__ __forceinline__ int bits_top(const BitsRows<K, NP> &r, int lane, int C)
+{
+    int top = 0;
+    lane = bits_local(lane);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int cell0 = (k * 64 + lane) * 32;
+        const uint32_t need = cell0 + 31 <= C ? 0xffffffffu : cell0 > C ? 0u : (1u << (C - cell0 + 1)) - 1u;
+        const uint32_t x = r.own[k] & need;
+        if (x) top = max(top, cell0 + 31 - __builtin_clz(x));
     }
     return bits_wave_max(top);
 }
 
-template <int N, class FirstT, bool SNAP, bool REC>
-__device__ __forceinline__ int sweep_bits_dispatch(int nb, uint32_t *set, FirstT *first, uint32_t *snap, const int32_t *lw,
-                                                   const int32_t *lp, int lane, int nact, int C, BitsLevel &best, bool levels)
+// The planes to LDS (taking the workgroup's lock), word by word: the NP planes of a word side by side.
+template <int K, int NP>
+__device__ __forceinline__ void bits_publish(const BitsLds &l, const BitsRows<K, NP> &r, int lane, int C)
 {
-    if (nb == N) {
-        return sweep_bits<N, FirstT, SNAP, REC>(set, first, snap, lw, lp, lane, nact, C, best, levels);
-    } else if constexpr (N > 1) {
-        return sweep_bits_dispatch<N - 1, FirstT, SNAP, REC>(nb, set, first, snap, lw, lp, lane, nact, C, best, levels);
+    constexpr int PS = bits_plane_stride(NP);
+    lane = bits_local(lane);
+    if (blockDim.x > 64) {
+        if (lane == 0) {
+            while (atomicCAS(l.lock, 0, 1) != 0) __builtin_amdgcn_s_sleep(2);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        __builtin_amdgcn_wave_barrier();
     }
-    return 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        if (k * 2048 <= C) {
+#pragma unroll
+            for (int j = 0; j < NP; ++j) l.planes[(k * 64 + lane) * PS + j] = r.plane[j][k];
+        }
+    }
+    wave_lds_sync();
+}
+__device__ __forceinline__ void bits_release(const BitsLds &l, int lane)
+{
+    wave_lds_sync();
+    if (blockDim.x > 64) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        if (lane == 0) atomicExch(l.lock, 0);
+    }
 }
 
-// K: words per lane the variant is compiled for (capacities up to 2048 K - 1).
-// LDS: [guard zeros][set: row_words][first: first_ints ints][lw: n_pad][li: n_pad]
-//      [lp: n_pad, if REC][snap: row_words, if SNAP]
-// FirstT: the cell type of first[].  An 8-bit cell serves lists of at most 255 items, with
-// SNAP (one snapshot of the set) of at most 511, and halves the instance's LDS, so that
-// about twice as many instances share a compute unit.
-// REC = false: DEFT_MODE_SEQUENTIAL.  REC = true, chosen by a.mode at run time:
-// DEFT_MODE_RECURSIVE (Algorithm 1 on one window: every item offered in generation order, the
-// best level tracked during the sweep, the walk started at that level's value) and
-// DEFT_MODE_CAPACITY_SWEEP (one sweep at the largest capacity, one walk per capacity).
-template <int K, class FirstT, bool SNAP, bool REC>
-__global__ void __launch_bounds__(64) seq_bits_kernel(BatchArgs a, int row_words, int first_ints, int n_pad)
+// first[t] after `steps` Gray steps, read off the published planes.
+template <int NP>
+__device__ __forceinline__ int bits_first(const uint32_t *planes, int t, int steps)
+{
+    const uint32_t *at = planes + (t >> 5) * bits_plane_stride(NP);
+    const int b = t & 31;
+    uint32_t code = 0;
+#pragma unroll
+    for (int j = 0; j < NP; ++j) code |= ((at[j] >> b) & 1u) << j;
+    code ^= (uint32_t)(steps ^ (steps >> 1)) & ((1u << NP) - 1u);
+    code ^= code >> 1;  // Gray code to number
+    code ^= code >> 2;
+    code ^= code >> 4;
+    if constexpr (NP > 8) code ^= code >> 8;
+    return (int)code;
+}
+
+// The walk from the sum `t`, by groups of G lanes (a power of two), each with a target of its
+// own.  Lane x of a group supposes that the x items before position `from` + 1 down the list are
+// taken.  take(p) is called by the lanes whose item (position p) is taken.  Returns what is
+// left of t (0, unless something is broken).
+template <int NP, class Take>
+__device__ __forceinline__ int bits_walk(const BitsLds &l, int lane, int G, int t, int cnt, int steps, Take &&take)
+{
+    const int x = lane & (G - 1), group = lane & ~(G - 1);
+    const unsigned long long group_mask = (G == 64 ? ~0ull : (1ull << G) - 1ull) << group;
+    int q = t > 0 ? min(bits_first<NP>(l.planes, t, steps), cnt - 1) : 0;
+    int guard = 2 * cnt + 2;  // (every round takes an item or moves down the list)
+    while (__builtin_amdgcn_ballot_w64(t > 0) != 0ull && guard-- > 0) {
+        const int p = q - x;
+        const bool in_list = t > 0 && p >= 0;
+        const int left = in_list ? t - (l.prefix[q + 1] - l.prefix[p + 1]) : 0;
+        const int first = left > 0 ? min(bits_first<NP>(l.planes, left, steps), cnt - 1) : 0;
+        const bool fits = left > 0 && first == p;
+        const unsigned long long miss = __builtin_amdgcn_ballot_w64(!fits) & group_mask;
+        const int stop = miss != 0ull ? __builtin_ctzll(miss) : group + G;  // lanes of the group before it take
+        if (lane < stop && fits) take(p);
+        // the next target: what the stopping lane was left with (nothing, once t is used up or
+        // the list is), or what follows the group's last item
+        const int src = min(stop, group + G - 1);
+        int t_next = __shfl(left, src), q_next = __shfl(first, src);
+        if (stop == group + G) {
+            const int p_last = q - (G - 1);
+            t_next = t - (l.prefix[q + 1] - l.prefix[p_last]);
+            q_next = p_last - 1;
+            if (q_next < 0) q_next = 0;
+        }
+        t = t > 0 ? max(t_next, 0) : t;
+        q = q_next;
+    }
+    return t;
+}
+
+// K: words per lane (capacities up to 2048 K - 1).  NP: planes (lists of up to 2^NP items).
+// a.mode: DEFT_MODE_SEQUENTIAL, DEFT_MODE_RECURSIVE or DEFT_MODE_CAPACITY_SWEEP.
+template <int K, int NP>
+__global__ void __launch_bounds__(256, bits_waves_per_simd(K, NP))
+seq_bits_kernel(BatchArgs a, BitsLayout lay, unsigned long long *swept_cells)
 {
     extern __shared__ __align__(16) int32_t lds_bits[];
-    const int inst = blockIdx.x, lane = threadIdx.x;
-    uint32_t *set = reinterpret_cast<uint32_t *>(lds_bits) + kBitsGuardWords;
-    FirstT *first = reinterpret_cast<FirstT *>(set + row_words);
-    int32_t *lw = reinterpret_cast<int32_t *>(set + row_words) + first_ints;
-    int32_t *li = lw + n_pad;
-    int32_t *lp = li + n_pad;
-    uint32_t *snap = reinterpret_cast<uint32_t *>(lp + (REC ? n_pad : 0));
+    const int lane_ = threadIdx.x & 63, lane = lane_;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int inst = (int)blockIdx.x * (int)(blockDim.x >> 6) + wave;
+    BitsLds l;
+    l.lock = lds_bits;
+    l.planes = reinterpret_cast<uint32_t *>(lds_bits) + 4;
+    uint32_t *zeros = l.planes + lay.plane_words + (size_t)wave * lay.wave_words;
+    l.set = zeros + lay.row_words;
+    l.prefix = reinterpret_cast<int32_t *>(l.set + lay.row_words + 4);
+    l.index = reinterpret_cast<uint16_t *>(l.prefix + lay.n_pad + 8);
+    l.marks = reinterpret_cast<uint32_t *>(l.prefix + lay.n_pad + 8 + lay.n_pad / 2);
+    if (blockDim.x > 64) {
+        if (threadIdx.x == 0) *l.lock = 0;
+        __syncthreads();
+    }
+    if (inst >= a.batch) return;  // (the whole wavefront; no barrier follows)
 
+    const bool levels = a.mode == DEFT_MODE_RECURSIVE, caps_sweep = a.mode == DEFT_MODE_CAPACITY_SWEEP;
     // Everything whose address follows from the instance number alone is fetched at once: the
-    // kernel's entry is one memory round trip (two for lists of more than 64 items).
+    // kernel's entry is one memory round trip.  The weights stay in registers (lists of up to
+    // 512 items; longer ones are read again per stage).
+    constexpr int NCH = NP <= 6 ? 1 : NP <= 9 ? 8 : 1;
     const int32_t *__restrict__ W = a.weights + (size_t)inst * a.item_stride;
     const int32_t *__restrict__ V = a.values + (size_t)inst * a.item_stride;
     const int32_t *cap = a.capacities + (size_t)inst * a.knap_stride;
     const int32_t *ord = a.fill_order ? a.fill_order + (size_t)inst * a.knap_stride : nullptr;
-    const int w_first = lane < a.item_stride ? W[lane] : 0;
-    const int v_first = lane < a.item_stride ? V[lane] : 0;
+    int wreg[NCH], vreg[NCH];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+        const bool have = c * 64 + lane < a.item_stride;
+        wreg[c] = have ? W[c * 64 + lane] : 0;
+        vreg[c] = have ? V[c * 64 + lane] : 0;
+    }
     const int cap_raw = lane < a.knap_stride ? cap[lane] : 0;
     const int ord_raw = ord && lane < a.knap_stride ? ord[lane] : lane;
     const int n = a.n_items[inst], m = a.n_knapsacks[inst];
-    const bool caps_sweep = REC && a.mode == DEFT_MODE_CAPACITY_SWEEP;  // (the REC kernels serve both modes)
+    for (int i = lane; i < lay.row_words; i += 64) zeros[i] = 0;
+    // f(first item of the chunk, this lane's weight, this lane's value) for every 64 items
+    auto chunks = [&](auto &&f) {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+            if (c * 64 < n) f(c * 64, wreg[c], vreg[c]);
+        if constexpr (NP > 9) {
+            for (int i0 = 64; i0 < n; i0 += 64) f(i0, i0 + lane < n ? W[i0 + lane] : 0, i0 + lane < n ? V[i0 + lane] : 0);
+        }
+    };
 
     // Input checks, in the order every kernel of the library reports them: invalid data, the
     // handle's limits, overflow of the value sum; then the handle's promise that every value
@@ -271,29 +465,29 @@ __global__ void __launch_bounds__(64) seq_bits_kernel(BatchArgs a, int row_words
         uint32_t flags = 0;
         unsigned long long vs = 0;
         bool differs = false;
-        if (n < 0 || n > a.item_stride || m < 0 || m > a.knap_stride || (REC && (caps_sweep ? m > 31 : m != 1))) {
+        if (n < 0 || n > a.item_stride || m < 0 || m > a.knap_stride || (levels && m != 1) || (caps_sweep && m > 31)) {
             flags = 1;
         } else {
-            for (int i0 = 0; i0 < n; i0 += 64) {
-                const int i = i0 + lane;
-                if (i < n) {
-                    const int w = i0 == 0 ? w_first : W[i], v = i0 == 0 ? v_first : V[i];
+            chunks([&](int i0, int w, int v) {
+                if (i0 + lane < n) {
                     bool bad = w < 1 || v < 0;
-                    if constexpr (REC) bad = bad || (!caps_sweep && a.drop_time[(size_t)inst * a.item_stride + i] < 0);
+                    if (levels) bad = bad || a.drop_time[(size_t)inst * a.item_stride + i0 + lane] < 0;
                     if (bad) flags |= 1; else vs += (unsigned)v;
                     differs = differs || v != w;
                 }
-            }
+            });
             unsigned long long seen = 0;
             if (lane < m) {
                 if (cap_raw < 0) flags |= 1; else if (cap_raw > a.max_capacity) flags |= 2;
                 if (ord_raw < 0 || ord_raw >= m) flags |= 1; else seen = 1ull << ord_raw;
             }
-            // a fill order names every knapsack once: m entries in range with m distinct values
-            auto bit_or = [](int x, int y) { return x | y; };
-            const int seen_lo = bits_wave_reduce((int)(uint32_t)seen, bit_or);
-            const int seen_hi = bits_wave_reduce((int)(uint32_t)(seen >> 32), bit_or);
-            if ((int)(__popc((uint32_t)seen_lo) + __popc((uint32_t)seen_hi)) != m) flags |= 1;
+            if (ord) {
+                // a fill order names every knapsack once: m entries in range with m distinct values
+                auto bit_or = [](int x, int y) { return x | y; };
+                const int seen_lo = bits_wave_reduce((int)(uint32_t)seen, bit_or);
+                const int seen_hi = bits_wave_reduce((int)(uint32_t)(seen >> 32), bit_or);
+                if ((int)(__popc((uint32_t)seen_lo) + __popc((uint32_t)seen_hi)) != m) flags |= 1;
+            }
         }
         // (a lane adds at most 64 values below 2^31: three 16-bit pieces keep the sums in range)
         const unsigned long long total_v = (unsigned long long)(unsigned)bits_wave_sum((int)(vs & 0xffffu)) +
@@ -304,237 +498,178 @@ __global__ void __launch_bounds__(64) seq_bits_kernel(BatchArgs a, int row_words
         else if (total_v >= (1ull << 31)) status = DEFT_ERR_OVERFLOW;
         else if (__builtin_amdgcn_ballot_w64(differs) != 0ull) status = DEFT_ERR_INVALID_ARG;
     }
-    clear_outputs(a, inst, status);
-    if (status != DEFT_OK) return;
-
-    for (int i = lane; i < kBitsGuardWords; i += 64) lds_bits[i] = 0;
-    const int cap_l = lane < m ? cap_raw : 0;
-    const int ord_l = lane < m ? ord_raw : lane;
     int32_t *out_asg = a.assignment + (size_t)inst * a.item_stride;
-    int32_t *out_kv = a.knap_value + (size_t)inst * a.knap_stride;
-    int32_t *out_kl = a.knap_load + (size_t)inst * a.knap_stride;
-    wave_lds_sync();
-
-    if constexpr (REC) {
-        if (caps_sweep) {
-            // The capacity sweep: one sweep over the whole list at the largest capacity; the
-            // final set answers every capacity (the largest reachable sum not above it), and the
-            // chain through first[] from that sum is the selection the DP would walk back at that
-            // capacity.  Lane x takes capacity x: all the walks run side by side, each lane
-            // following its own chain through LDS, and an item's mask collects the capacities
-            // at which it is taken.
-            const int cap_max = bits_wave_max(cap_l);
-            if (n == 0 || m == 0) return;  // (every output is already zero)
-            for (int i = lane; i < n; i += 64) {
-                lw[i] = i < 64 ? w_first : W[i];
-                lp[i] = -1;  // no level ends anywhere
-            }
-            wave_lds_sync();
-            BitsLevel unused{0, 0, 0};
-            const int nb = (cap_max / 32 + 64) / 64;
-            (void)sweep_bits_dispatch<K, FirstT, SNAP, true>(nb, set, first, snap, lw, lp, lane, n, cap_max, unused, false);
-            int t = 0;
-            if (lane < m) {
-                int wi = cap_l >> 5;
-                uint32_t x = set[wi] & (0xffffffffu >> (31 - (cap_l & 31)));
-                while (x == 0) x = set[--wi];  // (word 0 holds the empty sum)
-                t = wi * 32 + 31 - __builtin_clz(x);
-            }
-            const int value = t;
-            __threadfence_block();  // the cleared masks are in place before bits are set in them
-            int guard = n;          // (a chain is never longer than the list)
-            while (__builtin_amdgcn_ballot_w64(t > 0) != 0ull && guard-- > 0) {
-                if (t > 0) {
-                    int q = first[t];
-                    if constexpr (SNAP) q += ((snap[t >> 5] >> (t & 31)) & 1u) ? 0 : 256;
-                    q = min(q, n - 1);
-                    atomicOr(reinterpret_cast<unsigned int *>(&out_asg[q]), 1u << lane);
-                    t -= lw[q];
-                }
-            }
-            if (lane < m) {
-                out_kv[lane] = value;
-                out_kl[lane] = value;
-            }
-            const int at_largest = bits_wave_max(value);
-            const bool broken = __builtin_amdgcn_ballot_w64(t != 0) != 0ull;  // (never expected)
-            if (lane == 0) {
-                a.total_value[inst] = at_largest;
-                if (broken) a.status[inst] = DEFT_ERR_DEVICE;
-            }
-            return;
-        }
-        // Algorithm 1: the whole list is offered in generation order (an item heavier than the
-        // remaining time changes nothing, but the levels are counted in list positions).
-        // Entry i gets P_i = R - sum of drop[t] over t >= i, from a suffix sum taken 64 items at
-        // a time from the end of the list.  Only "how far below R" matters and R is at most
-        // 2^16: a drop time is clamped just above 2^24 and so is the running sum, which keeps
-        // everything in 32 bits and exact wherever the remaining time is not negative.
-        constexpr int kOver = (1 << 24) + 1;
-        const int C = __builtin_amdgcn_readlane(cap_l, 0);
-        const int32_t *drop = a.drop_time + (size_t)inst * a.item_stride;
-        int behind = 0;  // sum of drop over the chunks already done (uniform)
-        for (int i0 = (n - 1) & ~63; i0 >= 0 && n > 0; i0 -= 64) {
-            const int i = i0 + lane;
-            const int x = bits_wave_suffix_sum(i < n ? min(drop[i], kOver) : 0, lane);
-            if (i < n) {
-                const int left = C - min(x + behind, kOver);
-                lw[i] = i0 == 0 ? w_first : W[i];
-                li[i] = i;
-                lp[i] = left < 0 ? -1 : left;
-            }
-            behind = min(behind + __builtin_amdgcn_readlane(x, 0), kOver);
-        }
-        wave_lds_sync();
-        BitsLevel best{0, 0, 0};
-        int value = 0;
-        if (n > 0) {
-            const int nb = (C / 32 + 64) / 64;
-            value = sweep_bits_dispatch<K, FirstT, SNAP, true>(nb, set, first, snap, lw, lp, lane, n, C, best, true);
-        }
-        if (value > best.value) best = BitsLevel{value, n, C};  // level 0: the whole list
-        // the walk from the best level's value: its chain only meets sums first reached by
-        // items of that level (a sum reachable with the first q items was first reached by one of them)
-        int t = best.value;
-        int guard = n;
-        while (t > 0 && guard-- > 0) {
-            int q = first[t];
-            if constexpr (SNAP) q += ((snap[t >> 5] >> (t & 31)) & 1u) ? 0 : 256;
-            q = min(q, n - 1);
-            if (lane == 0) out_asg[q] = 0;
-            t -= lw[q];
+    if (status != DEFT_OK) {
+        for (int i = lane; i < a.item_stride; i += 64) out_asg[i] = caps_sweep ? 0 : -1;
+        if (lane < a.knap_stride) {
+            a.knap_value[(size_t)inst * a.knap_stride + lane] = 0;
+            a.knap_load[(size_t)inst * a.knap_stride + lane] = 0;
         }
         if (lane == 0) {
-            if (t != 0) a.status[inst] = DEFT_ERR_DEVICE;  // (never expected)
-            out_kv[0] = best.value;
-            out_kl[0] = best.value;
-            out_kv[1] = n - best.length;  // the level: items left off the list, its remaining time
-            out_kl[1] = best.value > 0 ? best.remain : 0;
-            a.total_value[inst] = best.value;
+            a.total_value[inst] = 0;
+            a.status[inst] = status;
         }
         return;
     }
-
-    // items already placed: bit (i / 64) of lane (i % 64)
-    unsigned long long placed = 0;
+    for (int i = lane; i < lay.mark_words; i += 64) l.marks[i] = caps_sweep ? 0u : 0xffffffffu;
+    uint8_t *mark8 = reinterpret_cast<uint8_t *>(l.marks);
+    const int cap_l = lane < m ? cap_raw : 0;
+    const int ord_l = lane < m ? ord_raw : lane;
+    int kv_l = 0, kl_l = 0;  // lane j: knapsack j's value and load
     long long total = 0;
-    for (int s = 0; s < m; ++s) {
+    wave_lds_sync();
+
+    BitsRows<K, NP> rows;
+    const int cap_max = caps_sweep ? bits_wave_max(cap_l) : 0;
+    const int stages = caps_sweep ? min(m, 1) : m;
+    for (int s = 0; s < stages; ++s) {
         const int j = __builtin_amdgcn_readlane(ord_l, s);
-        const int C = __builtin_amdgcn_readlane(cap_l, j);
+        const int C = caps_sweep ? cap_max : __builtin_amdgcn_readlane(cap_l, j);
+        const int lane = bits_local(lane_);
         // offered items: not yet placed and able to fit at all, ascending index
-        int cnt = 0, unplaced = 0, offered_weight = 0;
-        for (int i0 = 0; i0 < n; i0 += 64) {
+        int cnt = 0, sum = 0;
+        bool all_placed = true;
+        if (lane == 0) l.prefix[0] = 0;
+        chunks([&](int i0, int w, int) {
             const int i = i0 + lane;
-            const int w = i >= n ? 0 : i0 == 0 ? w_first : W[i];
-            const bool open = i < n && ((placed >> (i0 >> 6)) & 1ull) == 0;
-            const bool f = open && w <= C;
-            unplaced += __popcll(__builtin_amdgcn_ballot_w64(open));
-            const unsigned long long mask = __builtin_amdgcn_ballot_w64(f);
-            if (f) {
+            const bool open = i < n && (caps_sweep || mark8[i] == 0xff);
+            const bool offered = open && w <= C;
+            all_placed = all_placed && __builtin_amdgcn_ballot_w64(open) == 0ull;
+            const unsigned long long mask = __builtin_amdgcn_ballot_w64(offered);
+            const int upto = sum + bits_wave_prefix_sum(offered ? w : 0, lane);  // (4096 weights of at most 65535)
+            if (offered) {
                 const int pos = cnt + __popcll(mask & ((1ull << lane) - 1ull));
-                lw[pos] = w;
-                li[pos] = i;
-                offered_weight += w;
+                l.prefix[pos + 1] = upto;
+                l.index[pos] = (uint16_t)i;
             }
             cnt += __popcll(mask);
-        }
-        if (unplaced == 0) break;  // every item is placed: the remaining stages stay empty
-        if (cnt == 0) continue;
+            sum = __builtin_amdgcn_readlane(upto, 63);
+        });
+        if (all_placed && !levels) break;  // every item is placed: the remaining stages stay empty
         wave_lds_sync();
-        // (a lane's share is clamped just above the largest capacity, so that the sum stays in
-        // range and still exceeds C whenever the true sum does)
-        offered_weight = bits_wave_sum(min(offered_weight, (1 << 24) + 1));
-        int value;
-        if (offered_weight <= C) {
+        int value = 0, last = -1;  // last: the list position whose item completed the value
+        if (cnt == 0) {
+            // nothing is offered
+        } else if (sum <= C && !caps_sweep) {
             // everything offered fits together: the DP takes it all (every value is positive)
-            for (int p = lane; p < cnt; p += 64) {
-                const int i = li[p];
-                out_asg[i] = j;
-            }
-            for (int i0 = 0; i0 < n; i0 += 64) {
-                const int i = i0 + lane;
-                const int w = i >= n ? 0 : i0 == 0 ? w_first : W[i];
-                if (i < n && ((placed >> (i0 >> 6)) & 1ull) == 0 && w <= C) placed |= 1ull << (i0 >> 6);
-            }
-            value = offered_weight;
+            for (int p = lane; p < cnt; p += 64) mark8[l.index[p]] = (uint8_t)j;
+            value = sum;
+            last = cnt - 1;
+        } else if (cnt <= kBitsEnumItems && !caps_sweep) {
+            // A handful of items: lane x weighs the subset whose members are the set bits of x.  The
+            // DP with its walk returns the feasible subset of greatest value and, among
+            // equals, the one with the smallest such number.
+            int ws = 0;
+            for (int p = 0; p < cnt; ++p)
+                if ((lane >> p) & 1) ws += l.prefix[p + 1] - l.prefix[p];
+            const bool feasible = lane < (1 << cnt) && ws <= C;
+            value = bits_wave_max(feasible ? ws : -1);
+            const int pick = __builtin_ctzll(__builtin_amdgcn_ballot_w64(feasible && ws == value));  // (the empty set is feasible)
+            if (lane < cnt && ((pick >> lane) & 1)) mark8[l.index[lane]] = (uint8_t)j;
+            last = 31 - __builtin_clz(pick | 1);
         } else {
-            const int nb = (C / 32 + 64) / 64;  // words per lane covering cells 0 .. C
-            BitsLevel unused{0, 0, 0};
-            value = sweep_bits_dispatch<K, FirstT, SNAP, false>(nb, set, first, snap, lw, lp, lane, cnt, C, unused, false);
-            // the walk: every lane follows the same chain; the lane that owns an item's bit marks it
-            int t = value;
-            int guard = cnt;  // (a chain is never longer than the list)
-            while (t > 0 && guard-- > 0) {
-                int q = first[t];
-                if constexpr (SNAP) q += ((snap[t >> 5] >> (t & 31)) & 1u) ? 0 : 256;
-                const int w = lw[min(q, cnt - 1)], i = li[min(q, cnt - 1)];
-                if (lane == (i & 63)) placed |= 1ull << (i >> 6);
-                if (lane == 0) out_asg[i] = j;
-                t -= w;
+            const BitsSweep sw = bits_sweep<K, NP>(l, rows, lane, cnt, C, caps_sweep, cap_l);
+            const int steps = sw.q;
+            if (swept_cells && lane == 0) {
+                // measurement only: C - w + 1 per item the sweep went through
+                atomicAdd(swept_cells,
+                          (unsigned long long)sw.items * (unsigned)(C + 1) - (unsigned long long)(unsigned)l.prefix[sw.items]);
             }
-            if (t != 0 && lane == 0) a.status[inst] = DEFT_ERR_DEVICE;  // (never expected)
+            bits_publish<K, NP>(l, rows, lane, C);
+            if (!caps_sweep) {
+                value = sw.reached ? C : bits_top<K, NP>(rows, lane, C);
+                if (value > 0) last = min(bits_first<NP>(l.planes, value, steps), cnt - 1);
+                const int left = bits_walk<NP>(l, lane, 64, value, cnt, steps, [&](int p) { mark8[l.index[p]] = (uint8_t)j; });
+                if (left != 0) status = DEFT_ERR_DEVICE;  // (never expected)
+            } else {
+                // One sweep at the largest capacity answers every capacity: the largest reachable
+                // sum not above it, and the chain from that sum is the selection the DP would walk
+                // back there.  The lanes are dealt out to the capacities in groups, all walks run side
+                // by side, and an item's word collects the capacities at which it is taken.
+                int t = 0;
+                if (lane < m) {
+                    int wi = cap_l >> 5;
+                    uint32_t bits = l.set[wi] & (0xffffffffu >> (31 - (cap_l & 31)));
+                    while (bits == 0) bits = l.set[--wi];  // (word 0 holds the empty sum)
+                    t = wi * 32 + 31 - __builtin_clz(bits);
+                }
+                kv_l = kl_l = t;
+                int G = 64;
+                while (G > 1 && 64 / G < m) G >>= 1;
+                const int x = lane / G;  // this group's capacity
+                int t_group = __shfl(t, x);
+                if (x >= m) t_group = 0;
+                const int left = bits_walk<NP>(l, lane, G, t_group, cnt, steps,
+                                               [&](int p) { atomicOr(&l.marks[l.index[p]], 1u << x); });
+                if (__builtin_amdgcn_ballot_w64(left != 0) != 0ull) status = DEFT_ERR_DEVICE;  // (never expected)
+            }
+            bits_release(l, lane);
         }
-        if (lane == 0) {
-            out_kv[j] = value;
-            out_kl[j] = value;
-        }
-        total += value;
         wave_lds_sync();
+        if (!caps_sweep) {
+            if (lane == j) kv_l = kl_l = value;
+            total += value;
+        }
+        if (levels) {
+            // Algorithm 1: level d keeps the first n - d items and the remaining time R less the drop
+            // times of the others.  The levels' answers are nested (fewer items, less time), so the
+            // whole list's value is the greatest, and the recursion's answer is the deepest level
+            // that has it too: the smallest e such that the items before e reach it (e is beyond
+            // the item that completed it) and the time left for them, R - sum of drop[t] over
+            // t >= e, is not below it.  The remaining times grow with e: the list is searched from
+            // its end, 64 entries at a time, until one falls short.  (R is at most 2^16: a drop time
+            // is clamped just above 2^24 and so is the running sum, which keeps everything in 32
+            // bits and exact wherever the remaining time is not negative.)
+            constexpr int kOver = (1 << 24) + 1;
+            int length = 0, remain = 0;
+            if (value > 0) {
+                length = n;
+                remain = C;
+                const int beyond = l.index[last];
+                const int32_t *drop = a.drop_time + (size_t)inst * a.item_stride;
+                int behind = 0;
+                for (int i0 = (n - 1) & ~63; i0 >= 0; i0 -= 64) {
+                    const int e = i0 + lane;
+                    const int x = bits_wave_suffix_sum(e < n ? min(drop[e], kOver) : 0, lane);
+                    const int time_left = C - min(x + behind, kOver);
+                    const unsigned long long hit = __builtin_amdgcn_ballot_w64(e > beyond && e < n && time_left >= value);
+                    if (hit == 0ull) break;
+                    length = i0 + __builtin_ctzll(hit);
+                    remain = __builtin_amdgcn_readlane(time_left, __builtin_ctzll(hit));
+                    if ((hit & 1ull) == 0ull) break;
+                    behind = min(behind + __builtin_amdgcn_readlane(x, 0), kOver);
+                }
+            }
+            if (lane == 1) {  // slot 1 reports the level: items left off the list, its remaining time
+                kv_l = n - length;
+                kl_l = remain;
+            }
+        }
     }
-    if (lane == 0) a.total_value[inst] = total;
+    if (caps_sweep) total = bits_wave_max(kv_l);
+
+    for (int i = lane; i < a.item_stride; i += 64) {
+        int asg = caps_sweep ? 0 : -1;
+        if (i < n) asg = caps_sweep ? (int)l.marks[i] : (int)(int8_t)mark8[i];
+        out_asg[i] = asg;
+    }
+    if (lane < a.knap_stride) {
+        a.knap_value[(size_t)inst * a.knap_stride + lane] = kv_l;
+        a.knap_load[(size_t)inst * a.knap_stride + lane] = kl_l;
+    }
+    if (lane == 0) {
+        a.total_value[inst] = total;
+        a.status[inst] = status;
+    }
 }
 
-// Compiled words-per-lane counts (capacities up to 2048 K - 1), each with the three layouts of first[].
-constexpr int kBitsWords[] = {2, 5, 7, 10, 13, 19, 32};
+// Compiled words-per-lane counts (capacities up to 2048 K - 1) and plane counts (lists of up to
+// 2^NP items).
+constexpr int kBitsWords[] = {2, 5, 7, 10, 14, 20, 32};
 constexpr int kNumBitsWords = 7;
+constexpr int kBitsPlanes[] = {6, 9, 12};
 
-// mode: 0 = 16-bit cells, 1 = 8-bit cells, 2 = 8-bit cells and the snapshot
-template <int K, bool REC, class F>
-auto with_bits_mode(int mode, F &&f)
-{
-    switch (mode) {
-    case 0: return f(&seq_bits_kernel<K, uint16_t, false, REC>);
-    case 1: return f(&seq_bits_kernel<K, uint8_t, false, REC>);
-    default: return f(&seq_bits_kernel<K, uint8_t, true, REC>);
-    }
-}
-template <bool REC, class F>
-auto with_bits_kernel(int variant, F &&f)
-{
-    switch (variant / 3) {
-    case 0: return with_bits_mode<2, REC>(variant % 3, f);
-    case 1: return with_bits_mode<5, REC>(variant % 3, f);
-    case 2: return with_bits_mode<7, REC>(variant % 3, f);
-    case 3: return with_bits_mode<10, REC>(variant % 3, f);
-    case 4: return with_bits_mode<13, REC>(variant % 3, f);
-    case 5: return with_bits_mode<19, REC>(variant % 3, f);
-    case 6: return with_bits_mode<32, REC>(variant % 3, f);
-    default: return f(static_cast<void (*)(BatchArgs, int, int, int)>(nullptr));
-    }
-}
-
-template <bool REC>
-hipError_t bits_prepare(int variant)
-{
-    // the attribute belongs to the kernel, not to the handle: the most any handle may ask for
-    // (a compute unit's LDS less a small allowance)
-    return with_bits_kernel<REC>(variant, [](auto fn) {
-        if (!fn) return hipErrorInvalidValue;
-        return hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   160 * 1024 - 256);
-    });
-}
-
-template <bool REC>
-hipError_t bits_launch(const SeqBitsPlan &p, const BatchArgs &a, hipStream_t st)
-{
-    return with_bits_kernel<REC>(p.variant, [&](auto fn) {
-        if (!fn) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(fn, dim3((unsigned)a.batch), dim3(64), (size_t)(REC ? p.lds_bytes_rec : p.lds_bytes), st, a,
-                           p.row_words, p.first_ints, p.n_pad);
-        return hipGetLastError();
-    });
-}
+typedef void (*BitsKernel)(BatchArgs, BitsLayout, unsigned long long *);
 
 }  // namespace
 
