@@ -112,22 +112,21 @@ private:
 };
 
 // ---- sequential mode, rows in global memory (seq_global.hip) -------------------
-// For capacities whose row does not fit LDS.  One launch per offered item: the
-// row ping-pongs between two global buffers, keep bits go out as 64-bit words.
+// For capacities whose row does not fit LDS: the row streams through LDS rings, several items per
+// pass, one workgroup per instance (Algorithm 1: one launch per item, rows in two buffers).
 struct SeqGlobalPlan {
-    int32_t threads, cells_per_thread;
+    int32_t threads, cells_per_thread;  // of the launch per item
     int32_t row_len;           // int32 cells per row buffer (multiple of the tile)
     int32_t keep_words;        // 64-bit keep words per item
     int32_t max_items, max_batch;
-    int32_t ring_segs;         // persistent sweep: 256-cell segments of the old row resident in LDS
+    int32_t ring_cells;        // streamed sweep: cells of its rings in LDS
     int32_t lds_bytes;         // its dynamic LDS
-    int32_t persistent_min_batch;  // batches at least this large take the persistent sweep
-    int64_t scratch_bytes;     // rows + keep + offered-item lists + per-instance state
+    int64_t scratch_bytes;     // rows + keep + item lists + per-instance state
 };
 void seq_global_plan(int32_t max_capacity, int32_t max_items, int32_t max_batch, int32_t lds_per_wg_bytes,
-                     int32_t compute_units, SeqGlobalPlan *plan);
+                     SeqGlobalPlan *plan);
 hipError_t seq_global_prepare(const SeqGlobalPlan &plan);
-// `streamed_cells` (device, may be null): the persistent sweep adds the row cells it fetched.
+// `streamed_cells` (device, may be null): the streamed sweep adds the row cells it reads and writes.
 hipError_t seq_global_launch(const SeqGlobalPlan &plan, const BatchArgs &args, void *scratch,
                              hipStream_t stream, Profiler *prof, unsigned long long *streamed_cells);
 

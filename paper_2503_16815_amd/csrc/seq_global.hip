@@ -1,30 +1,45 @@
 // Sequential multiple-knapsack solve for capacities whose row does not fit LDS
-// (Sec. III.B, Problem 1 per window).  The row lives in global memory in two
-// buffers; offered item q reads buffer q & 1 and writes the other:
-//   new[c] = max(old[c], old[c - w] + v)   for c >= w,   new[c] = old[c] below,
-// with the take bit (old[c - w] + v > old[c]) collected per 64 cells by a
-// wavefront ballot and stored as one 64-bit keep word.  The first offered item
-// of a stage reads zeros instead of a buffer.
-// Two ways to run a stage's sweeps:
-//  * batches with at least one instance per two compute units: one persistent
-//    workgroup per instance walks all offered items; the row streams once per
-//    item through a ring in LDS, so each old cell is fetched from global memory
-//    exactly once and both operands of a cell come from LDS (sg_sweep_all);
-//  * smaller batches: one launch per offered-item rank, the row cut into tiles
-//    over many workgroups (sg_sweep; the host cannot know how many items each
-//    instance still offers, so it launches item_stride of them and a workgroup
-//    whose instance has fewer exits); the shifted read hits cache lines another
-//    wavefront has just fetched.
-// Traffic per cell: 4 B read + 4 B write + 1/8 B keep.
+// (Sec. III.B, Problem 1 per window): the row lives in global memory.
+//
+// The streamed sweep (sg_stream; the sequential mode and the capacity sweep): one launch, one
+// workgroup per instance for all stages, lists and walks included.
+//
+// What is kept of a cell is how far it falls short: D[c] = (value of the items so far) - row[c], so
+//   D'[c] = min(D[c] + v, D[c - w]),   item taken where D[c - w] < D[c] + v,   D[c < 0] = infinity.
+// Every cell at or above the weight of the items so far holds all of them: D = 0 there, in no need of
+// being stored or computed, and its keep bit is known to be set.  And a walk that starts at C has at
+// most the items behind q to lower it: cells of the row after item q below C - (their weight) are
+// never looked at.  What is swept of a row is the band between the two, at most the smaller of C and
+// (weight offered) - C wide: on the GPT-2 shape 30 % of the cells up to C.
+//
+// The band streams through LDS in ascending blocks of R cells, and a pass over it serves up to
+// seven consecutive items.  Level l (item q + l) has a ring in LDS with the row before its item, long
+// enough to reach w cells back; at step t it computes block t - l from its ring into level l + 1's, the
+// last level stores to global memory, in place, behind the loads, and one wavefront keeps the loads
+// of level 0 two or three blocks ahead.  The levels work on different blocks, so one barrier per step
+// is all the ordering there is, and a step is one task of 512 cells for each of up to fifteen
+// wavefronts.  The shifted operand of an item of at least a block's weight lies in blocks that have long
+// been complete: it is read one step ahead, behind the barrier's wait.  A cell-update costs 8 / levels + 1/8
+// bytes of global traffic, 12 bytes of LDS, four vector instructions and a share of about
+// twenty vector and forty scalar instructions per task.
+// Measured on the GPT-2 shape (256 instances, C = 381000, one window swept): 2.36 ms, with nine
+// instances 2.19 ms; one persistent workgroup per instance over all cells up to C, three items per pass,
+// and launches of their own for lists and walks took 11.5 ms, one launch per item 3.55 ms.  What bounds
+// it: a step is read, compute, write, barrier for all wavefronts at once (about 1850 cycles for fourteen
+// tasks, of which the vector units are busy 740 and LDS 680).
+//
+// Algorithm 1 reads a cell of every intermediate row, so it takes sweeps that leave each of them in
+// global memory: one launch per offered-item rank, two row buffers, the row cut into tiles over
+// many workgroups (sg_sweep), keep bits by wavefront ballots.
 #include <limits.h>
-
-#include <type_traits>
 
 #include "instance_check.h"
 
 namespace deft {
 
 namespace {
+
+constexpr int kMaxItemsPlaced = 4096;  // longest item list (create-time limit)
 
 constexpr int kThreads = 256;
 constexpr int kIter = 32;                       // 64-cell groups per wavefront
@@ -34,10 +49,15 @@ constexpr int kTileCells = kWaveCells * (kThreads / 64);
 // per-instance state kept between launches
 struct InstState {
     int32_t status, n_act, knap, cap;
-    int64_t total;
-    int32_t buf;   // row buffer holding the stage's final row; -1: the parity of n_act says
     // Algorithm 1: the best level met so far (its value, the length of its list, its remaining time)
     int32_t best_value, best_length, best_remain;
+};
+
+// One offered item of the streamed sweep.
+struct alignas(8) StreamItem {
+    int32_t w, v;
+    int64_t upto;  // weight of the stage's list up to and with this item
+    int32_t index, pad;
 };
 
 struct Scratch {
@@ -46,6 +66,7 @@ struct Scratch {
     int32_t *act;       // [batch][max_items]
     int32_t *probe;     // [batch][max_items]  Algorithm 1: remaining time of the level that ends before entry q
     InstState *state;   // [batch]
+    StreamItem *items;  // [batch][max_items]  the streamed sweep's lists
 };
 
 __host__ __device__ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -63,6 +84,8 @@ Scratch carve(const SeqGlobalPlan &p, void *base, int32_t max_batch)
     s.probe = reinterpret_cast<int32_t *>(c);
     c += align256((size_t)max_batch * p.max_items * 4);
     s.state = reinterpret_cast<InstState *>(c);
+    c += align256((size_t)max_batch * sizeof(InstState));
+    s.items = reinterpret_cast<StreamItem *>(c);
     return s;
 }
 
@@ -74,12 +97,9 @@ __global__ void __launch_bounds__(kThreads) sg_init(BatchArgs a, InstState *stat
     if (threadIdx.x == 0) {
         state[inst].status = status;
         state[inst].n_act = 0;
-        state[inst].total = 0;
     }
 }
 
-// Stage s: knapsack id, capacity and the ascending list of offered items
-// (not yet placed, weight <= capacity).
 // Algorithm 1 (one stage): the whole list is offered in its order, and entry q gets the
 // remaining time of the level that ends before it, R - sum of drop_time over the entries
 // from q on (-1 if negative), from a suffix sum taken 64 entries at a time from the end.
@@ -89,7 +109,7 @@ __global__ void __launch_bounds__(64) sg_levels_setup(BatchArgs a, InstState *st
     const int inst = blockIdx.x, lane = threadIdx.x;
     InstState *st = &state[inst];
     if (st->status != DEFT_OK) {
-        if (lane == 0) st->n_act = 0, st->knap = -1, st->buf = -1;
+        if (lane == 0) st->n_act = 0, st->knap = -1;
         return;
     }
     const int n = a.n_items[inst];
@@ -112,78 +132,9 @@ __global__ void __launch_bounds__(64) sg_levels_setup(BatchArgs a, InstState *st
         behind += __shfl(x, 0);
     }
     if (lane == 0) {
-        st->n_act = n; st->knap = 0; st->cap = C; st->buf = -1;
+        st->n_act = n; st->knap = 0; st->cap = C;
         st->best_value = 0; st->best_length = 0; st->best_remain = 0;
     }
-}
-
-__global__ void __launch_bounds__(64) sg_stage_setup(BatchArgs a, int s, InstState *state, int32_t *act,
-                                                     int max_items)
-{
-    const int inst = blockIdx.x, lane = threadIdx.x;
-    InstState *st = &state[inst];
-    const int m = a.n_knapsacks[inst];
-    if (st->status != DEFT_OK || s >= m) {
-        if (lane == 0) st->n_act = 0, st->knap = -1, st->buf = -1;
-        return;
-    }
-    const int n = a.n_items[inst];
-    // Capacity sweep (Sec. IV.C feedback): one stage, swept at the largest of the instance's
-    // capacities; every item is offered and nothing is settled here (the smaller capacities
-    // are read off the same final row).
-    const bool caps_sweep = a.mode == DEFT_MODE_CAPACITY_SWEEP;
-    const int j = caps_sweep ? 0 : a.fill_order ? a.fill_order[(size_t)inst * a.knap_stride + s] : s;
-    int C = a.capacities[(size_t)inst * a.knap_stride + j];
-    if (caps_sweep)
-        for (int x = 1; x < m; ++x) C = max(C, a.capacities[(size_t)inst * a.knap_stride + x]);
-    const int32_t *W = a.weights + (size_t)inst * a.item_stride;
-    const int32_t *asg = a.assignment + (size_t)inst * a.item_stride;
-    int32_t *list = act + (size_t)inst * max_items;
-    int cnt = 0;
-    long long offered_weight = 0;
-    for (int i0 = 0; i0 < n; i0 += 64) {
-        const int i = i0 + lane;
-        const bool f = i < n && (caps_sweep || asg[i] < 0) && W[i] <= C;
-        const unsigned long long mask = __ballot(f);
-        if (f) {
-            list[cnt + __popcll(mask & ((1ull << lane) - 1ull))] = i;
-            offered_weight += W[i];
-        }
-        cnt += __popcll(mask);
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) offered_weight += __shfl_down(offered_weight, off);
-    offered_weight = __shfl(offered_weight, 0);
-    if (!caps_sweep && offered_weight <= C) {
-        // Nothing is offered, or everything offered fits together: the DP and its walk would
-        // take exactly the offered items of positive value (at every step of the walk the
-        // capacity left still holds all earlier items, and a zero-value item never strictly
-        // improves a cell).  The stage is settled here; no sweep, no walk.
-        const int32_t *V = a.values + (size_t)inst * a.item_stride;
-        long long vsum = 0, lsum = 0;
-        for (int i = lane; i < n; i += 64) {
-            const int w = W[i], v = V[i];
-            if (asg[i] < 0 && w <= C && v > 0) {
-                a.assignment[(size_t)inst * a.item_stride + i] = j;
-                vsum += v;
-                lsum += w;
-            }
-        }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            vsum += __shfl_down(vsum, off);
-            lsum += __shfl_down(lsum, off);
-        }
-        if (lane == 0) {
-            a.knap_value[(size_t)inst * a.knap_stride + j] = (int)vsum;
-            a.knap_load[(size_t)inst * a.knap_stride + j] = (int)lsum;
-            st->total += vsum;
-            a.total_value[inst] = st->total;
-            st->n_act = 0, st->knap = -1, st->buf = -1;
-        }
-        return;
-    }
-    if (lane == 0) { st->n_act = cnt; st->knap = j; st->cap = C; st->buf = -1; }
 }
 
 // Offered item q of every instance: one pass over the row.
@@ -195,7 +146,7 @@ sg_sweep(BatchArgs a, int q, InstState *state, const int32_t *__restrict__ act, 
     const InstState st = state[inst];
     if (q >= st.n_act) return;
     const int C = st.cap;
-    if (a.mode == DEFT_MODE_RECURSIVE && tile == 0 && threadIdx.x == 0 && q > 0) {
+    if (tile == 0 && threadIdx.x == 0 && q > 0) {
         // Algorithm 1: the row before item q is the row of the level that ends here; a
         // shallower level replaces the best one only when strictly greater.  (Nobody else
         // touches the instance's best level during this launch; before the first item the
@@ -236,296 +187,8 @@ sg_sweep(BatchArgs a, int q, InstState *state, const int32_t *__restrict__ act, 
     if (lane < kIter) kw[lane] = mine;
 }
 
-constexpr int kAllThreads = 1024;   // persistent sweep: one workgroup per instance
-constexpr int kAllWaves = kAllThreads / 64;
-constexpr int kAllLoadWaves = 2;    // wavefronts that only move old cells from global memory into LDS
-constexpr int kAllComputeWaves = kAllWaves - kAllLoadWaves;
-constexpr int kSegCells = 256;      // one task / one 16-byte-per-lane LDS-direct load
-constexpr int kMaxItemsPerPass = 3; // temporal blocking depth of the persistent sweep
-constexpr int kMinBlockSegs = 14;   // smallest block worth an extra level: one task per computing wavefront
-
-typedef __attribute__((address_space(3))) int32_t lds_i32;
-typedef const __attribute__((address_space(1))) int32_t global_ci32;
-
-// Block hand-over barriers of sg_sweep_all: a loading wavefront arrives when its LDS-direct
-// loads have landed, a computing wavefront when its LDS reads have (its row and keep stores
-// stay in flight until the end of the item).  Asm, because the compiler puts a wait for all
-// vector memory in front of every barrier it knows of once a kernel has LDS-direct loads.
-__device__ __forceinline__ void barrier_after_loads() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-__device__ __forceinline__ void barrier_after_lds_reads() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
-// All offered items of one stage, one workgroup per instance.  The row is walked in
-// ascending blocks of R segments (256 cells each); a ring of LDS segments holds the part
-// of the old row the block needs (segment g in slot g % ring size), so that every old cell
-// is fetched from global memory once and both operands of a cell come from LDS.
-//
-// Two kinds of pass over the row:
-//  * one item: old row in buffer `cur`, new row into the other buffer.  The ring holds the
-//    block being computed, the block being loaded and the cells up to w below:
-//    2 R + ceil(w / 256) + 1 <= ring_segs.  Items too heavy for that read their shifted
-//    operand from global memory (separate instantiation).
-//  * g = 2 or 3 items (temporal blocking): the rows between the items exist only in LDS.
-//    Ring 0 holds the old row (2 R + s0 segments), ring l the row after item l - 1
-//    (R + sl + 1 segments), sl = ceil(wl / 256) + 1; per block, level l computes item l's
-//    block from ring l into ring l + 1, and the last level stores it - into the buffer
-//    being read, behind the loads - so a cell-update costs 1/g of the HBM traffic.
-// A compute task is one segment: lane l covers cells seg*256 + 64 j + l, j = 0..3, so the
-// v_cmp masks are the keep words of the segment.
-__global__ void __launch_bounds__(kAllThreads)
-sg_sweep_all(BatchArgs a, InstState *__restrict__ state, const int32_t *__restrict__ act, int32_t *rows,
-             uint64_t *keep, int row_len, int keep_words, int max_items, int ring_segs,
-             unsigned long long *streamed_cells)
-{
-    extern __shared__ __align__(16) int32_t ring[];  // [ring_segs][256]
-    const int inst = blockIdx.x;
-    const InstState st = state[inst];
-    if (st.status != DEFT_OK || st.knap < 0 || st.n_act <= 0) return;
-    const int C = st.cap;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const bool loader = wave < kAllLoadWaves;
-    const int nseg = C / kSegCells + 1;  // segments holding cells 0 .. C (all inside row_len)
-    const int32_t *W = a.weights + (size_t)inst * a.item_stride;
-    const int32_t *V = a.values + (size_t)inst * a.item_stride;
-    const int32_t *list = act + (size_t)inst * max_items;
-    int32_t *const buf0 = rows + (size_t)inst * 2 * row_len;
-    const std::true_type yes{};
-    const std::false_type no{};
-
-    // the first offered item sees an all-zero row: the ring is cleared once and not loaded
-    for (int i = threadIdx.x; i < ring_segs * kSegCells; i += kAllThreads) ring[i] = 0;
-    __syncthreads();
-
-    // segments [lo, lo + n) of `src` -> ring slots slot_lo .. of a ring of rn segments at rbase
-    auto load_segs = [&](const int32_t *src, int lo, int n, int rbase, int rn, int slot_lo) {
-        for (int g = wave; g < n; g += kAllLoadWaves) {
-            int slot = slot_lo + g;
-            if (slot >= rn) slot -= rn;
-            __builtin_amdgcn_global_load_lds((global_ci32 *)(src + (size_t)(lo + g) * kSegCells + lane * 4),
-                                             (lds_i32 *)(ring + (size_t)(rbase + slot) * kSegCells), 16, 0, 0);
-        }
-    };
-
-    // One task = one segment `seg`, held in slot `slot` of the source ring (rn segments at
-    // segment offset rbase).  IN_RING: the shifted operand comes from the ring, else from
-    // `src` in global memory.  KIND 0: the whole segment lies at or above w; 1: w falls
-    // inside it (cells below w keep their value); 2: the whole segment lies below w (copied
-    // through).  TO_LDS: the new cells go to slot `oslot` of the ring at obase, else to `dst`.
-    auto task = [&](auto in_ring_tag, auto kind_tag, auto to_lds_tag, int rbase, int rn, int w, int v, int seg,
-                    int slot, const int32_t *src, bool first, int32_t *dst, int obase, int oslot, uint64_t *kw) {
-        constexpr bool IN_RING = decltype(in_ring_tag)::value;
-        constexpr int KIND = decltype(kind_tag)::value;
-        constexpr bool TO_LDS = decltype(to_lds_tag)::value;
-        const int32_t *rg = ring + (size_t)rbase * kSegCells;
-        const int rcells = rn * kSegCells;
-        const int32_t *own = rg + (size_t)slot * kSegCells + lane;
-        const int c0 = seg * kSegCells + lane;
-        int cen[4], sh[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) cen[j] = own[j * 64];
-        if (KIND != 2) {
-            if (IN_RING) {
-                // ring position of the segment's first cell minus w, brought into [0, rcells)
-                int base = slot * kSegCells - w;
-                base += base < 0 ? rcells : 0;
-                if (base + kSegCells <= rcells) {
-                    // the 256 shifted cells are contiguous in the ring: immediate offsets
-                    const int32_t *shp = rg + base + lane;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) sh[j] = shp[j * 64];
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        unsigned o = (unsigned)(base + lane + j * 64);
-                        o = min(o, o - (unsigned)rcells);  // wraps past the ring's end
-                        sh[j] = rg[o];
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int c = c0 + j * 64;
-                    sh[j] = (c >= w && !first) ? src[c - w] : 0;
-                }
-            }
-        }
-        unsigned long long m[4];
-        int32_t *lds_out = ring + (size_t)(obase + oslot) * kSegCells + lane;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            int best = cen[j];
-            m[j] = 0;
-            if (KIND != 2) {
-                int cand = sh[j] + v;
-                if (KIND == 1 || !IN_RING) cand = c0 + j * 64 < w ? INT_MIN : cand;
-                m[j] = __ballot(cand > best);
-                best = max(best, cand);
-            }
-            if (TO_LDS) lds_out[j * 64] = best;
-            else dst[(size_t)c0 + j * 64] = best;
-        }
-        if (lane < 4) {
-            unsigned long long wsel = 0;
-#pragma unroll
-            for (int jj = 0; jj < 4; ++jj)
-                if (jj == lane) wsel = m[jj];
-            kw[seg * 4 + lane] = wsel;
-        }
-    };
-    // picks the KIND for the segment
-    auto run_task = [&](auto in_ring_tag, auto to_lds_tag, int rbase, int rn, int w, int v, int seg, int slot,
-                        const int32_t *src, bool first, int32_t *dst, int obase, int oslot, uint64_t *kw) {
-        const int c_first = seg * kSegCells;
-        if (c_first >= w)
-            task(in_ring_tag, std::integral_constant<int, 0>{}, to_lds_tag, rbase, rn, w, v, seg, slot, src, first, dst,
-                 obase, oslot, kw);
-        else if (c_first + kSegCells > w)
-            task(in_ring_tag, std::integral_constant<int, 1>{}, to_lds_tag, rbase, rn, w, v, seg, slot, src, first, dst,
-                 obase, oslot, kw);
-        else
-            task(yes, std::integral_constant<int, 2>{}, to_lds_tag, rbase, rn, w, v, seg, slot, src, first, dst, obase,
-                 oslot, kw);
-    };
-
-    int cur = 0;  // buffer holding the row before item q (all zeros for q == 0, wherever it is)
-    int q = 0;
-    int row_transfers = 0;  // rows read from plus rows written to global memory
-    while (q < st.n_act) {
-        const bool first = q == 0;
-        row_transfers += first ? 1 : 2;  // every pass writes the row, all but the stage's first read it
-        int32_t *src = buf0 + (size_t)cur * row_len;
-        // the next up to kMaxItemsPerPass items: weight, value, reach in segments, keep row
-        int w[kMaxItemsPerPass], v[kMaxItemsPerPass], sg[kMaxItemsPerPass];
-        uint64_t *kw[kMaxItemsPerPass];
-#pragma unroll
-        for (int l = 0; l < kMaxItemsPerPass; ++l) {
-            const int t = list[min(q + l, st.n_act - 1)];
-            w[l] = W[t];
-            v[l] = V[t];
-            sg[l] = (w[l] + kSegCells - 1) / kSegCells + 1;  // segments the shifted operand reaches back
-            kw[l] = keep + ((size_t)inst * max_items + t) * keep_words;
-        }
-        // as many items per pass as leave blocks of at least kMinBlockSegs segments:
-        // (g + 1) R + sum of reaches + (g - 1) <= ring_segs
-        int g = 1, R = 0;
-        {
-            int reach = sg[0];
-#pragma unroll
-            for (int l = 1; l < kMaxItemsPerPass; ++l) {
-                reach += sg[l];
-                const int r = (ring_segs - l - reach) / (l + 2);
-                if (q + l < st.n_act && r >= kMinBlockSegs) { g = l + 1; R = r; }
-            }
-        }
-        if (g >= 2) {
-            // ---- g items per pass: ring 0 holds the old row (2 R + reach of item 0), ring l
-            // the row after item l - 1 (R + reach of item l + 1); level l reads ring l and
-            // writes ring l + 1, the last level stores to the buffer being read ------------
-            int rbase[kMaxItemsPerPass], rn[kMaxItemsPerPass], slot[kMaxItemsPerPass];
-            {
-                int at = 0;
-#pragma unroll
-                for (int l = 0; l < kMaxItemsPerPass; ++l) {
-                    rbase[l] = at;
-                    rn[l] = l == 0 ? 2 * R + sg[0] : R + sg[l] + 1;
-                    at += rn[l];
-                    slot[l] = 0;  // lo % rn[l]
-                }
-            }
-            if (loader) {
-                if (!first) load_segs(src, 0, min(R, nseg), 0, rn[0], 0);
-                barrier_after_loads();
-            } else {
-                barrier_after_lds_reads();
-            }
-            for (int lo = 0; lo < nseg; lo += R) {
-                int slot_next[kMaxItemsPerPass];
-#pragma unroll
-                for (int l = 0; l < kMaxItemsPerPass; ++l) {
-                    slot_next[l] = slot[l] + R;
-                    if (slot_next[l] >= rn[l]) slot_next[l] -= rn[l];
-                }
-                const int ns = min(R, nseg - lo);
-                if (loader) {
-                    if (!first && lo + R < nseg) load_segs(src, lo + R, min(R, nseg - lo - R), 0, rn[0], slot_next[0]);
-                    for (int l = 0; l + 1 < g; ++l) barrier_after_lds_reads();  // (levels of this block)
-                    barrier_after_loads();  // the next block of the old row is in ring 0
-                } else {
-#pragma unroll
-                    for (int l = 0; l < kMaxItemsPerPass; ++l) {
-                        if (l < g) {
-                            const bool last = l + 1 == g;
-                            for (int i = wave - kAllLoadWaves; i < ns; i += kAllComputeWaves) {
-                                int s_in = slot[l] + i;
-                                if (s_in >= rn[l]) s_in -= rn[l];
-                                if (last) {
-                                    run_task(yes, no, rbase[l], rn[l], w[l], v[l], lo + i, s_in, src, first && l == 0, src, 0,
-                                             0, kw[l]);
-                                } else {
-                                    int s_out = slot[l + 1 < kMaxItemsPerPass ? l + 1 : l] + i;
-                                    const int rn_out = rn[l + 1 < kMaxItemsPerPass ? l + 1 : l];
-                                    if (s_out >= rn_out) s_out -= rn_out;
-                                    run_task(yes, yes, rbase[l], rn[l], w[l], v[l], lo + i, s_in, src, first && l == 0, src,
-                                             rbase[l + 1 < kMaxItemsPerPass ? l + 1 : l], s_out, kw[l]);
-                                }
-                            }
-                            barrier_after_lds_reads();  // level l of the block is complete
-                        }
-                    }
-                }
-#pragma unroll
-                for (int l = 0; l < kMaxItemsPerPass; ++l) slot[l] = slot_next[l];
-            }
-            q += g;  // the new row replaced the old one in buffer `cur`
-        } else {
-            // ---- one item per pass --------------------------------------------------
-            int32_t *dst = buf0 + (size_t)(cur ^ 1) * row_len;
-            const int wA = w[0], vA = v[0], sA = sg[0];
-            uint64_t *kwA = kw[0];
-            const bool shifted_in_ring = sA + 2 <= ring_segs;
-            const int R1 = max(1, (shifted_in_ring ? ring_segs - sA : ring_segs) / 2);
-            if (loader) {
-                if (!first) load_segs(src, 0, min(R1, nseg), 0, ring_segs, 0);
-                barrier_after_loads();
-            } else {
-                barrier_after_lds_reads();
-            }
-            int slot_lo = 0;  // lo % ring_segs
-            for (int lo = 0; lo < nseg; lo += R1) {
-                int slot_next = slot_lo + R1;
-                if (slot_next >= ring_segs) slot_next -= ring_segs;
-                if (loader) {
-                    if (!first && lo + R1 < nseg)
-                        load_segs(src, lo + R1, min(R1, nseg - lo - R1), 0, ring_segs, slot_next);
-                    barrier_after_loads();  // the next block is in the ring
-                } else {
-                    const int ns = min(R1, nseg - lo);
-                    for (int i = wave - kAllLoadWaves; i < ns; i += kAllComputeWaves) {
-                        int sl = slot_lo + i;
-                        if (sl >= ring_segs) sl -= ring_segs;
-                        if (shifted_in_ring)
-                            run_task(yes, no, 0, ring_segs, wA, vA, lo + i, sl, src, first, dst, 0, 0, kwA);
-                        else
-                            run_task(no, no, 0, ring_segs, wA, vA, lo + i, sl, src, first, dst, 0, 0, kwA);
-                    }
-                    barrier_after_lds_reads();  // this block's slots may be reused
-                }
-                slot_lo = slot_next;
-            }
-            cur ^= 1;
-            q += 1;
-        }
-        // the next pass reads what this one wrote (other wavefronts' cells included)
-        __threadfence_block();
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        state[inst].buf = cur;
-        if (streamed_cells) atomicAdd(streamed_cells, (unsigned long long)row_transfers * nseg * kSegCells);
-    }
-}
-
-// One thread per instance walks the keep words back from (last offered item, C).
+// Algorithm 1: one thread per instance walks the keep words back from the best level's last item and
+// remaining time.
 __global__ void __launch_bounds__(64)
 sg_traceback(BatchArgs a, InstState *state, const int32_t *__restrict__ act, const int32_t *rows,
              const uint64_t *keep, int row_len, int keep_words, int max_items)
@@ -538,19 +201,13 @@ sg_traceback(BatchArgs a, InstState *state, const int32_t *__restrict__ act, con
     const int32_t *W = a.weights + (size_t)inst * a.item_stride;
     const int32_t *list = act + (size_t)inst * max_items;
     int value = 0;
-    if (nact > 0) value = rows[((size_t)inst * 2 + (st->buf >= 0 ? st->buf : (nact & 1))) * row_len + C];
-    int c = C, from = nact - 1;
-    const bool levels = a.mode == DEFT_MODE_RECURSIVE;
-    int length = nact;
-    if (levels) {  // the whole list is the last level met; the walk starts at the best level's end
-        if (value > st->best_value) { st->best_value = value; st->best_length = nact; st->best_remain = C; }
-        value = st->best_value;
-        length = st->best_length;
-        from = length - 1;
-        c = st->best_remain;
-    }
-    const int start = c;
-    for (int q = from; q >= 0; --q) {
+    if (nact > 0) value = rows[((size_t)inst * 2 + (nact & 1)) * row_len + C];
+    // the whole list is the last level met
+    if (value > st->best_value) { st->best_value = value; st->best_length = nact; st->best_remain = C; }
+    value = st->best_value;
+    const int length = st->best_length, start = st->best_remain;
+    int c = start;
+    for (int q = length - 1; q >= 0; --q) {
         const int t = list[q];
         const int w = W[t];
         if (w <= c) {
@@ -563,59 +220,529 @@ sg_traceback(BatchArgs a, InstState *state, const int32_t *__restrict__ act, con
     }
     a.knap_value[(size_t)inst * a.knap_stride + j] = value;
     a.knap_load[(size_t)inst * a.knap_stride + j] = start - c;
-    if (levels) {  // slot 1 reports the level: items left off the list, its remaining time
-        a.knap_value[(size_t)inst * a.knap_stride + 1] = a.n_items[inst] - length;
-        a.knap_load[(size_t)inst * a.knap_stride + 1] = value > 0 ? start : 0;
-    }
-    st->total += value;
-    a.total_value[inst] = st->total;
+    // slot 1 reports the level: items left off the list, its remaining time
+    a.knap_value[(size_t)inst * a.knap_stride + 1] = a.n_items[inst] - length;
+    a.knap_load[(size_t)inst * a.knap_stride + 1] = value > 0 ? start : 0;
+    a.total_value[inst] = value;
 }
 
-// Capacity sweep: one thread per (instance, capacity) reads the value at its capacity off the
-// final row and walks the keep words back from (last offered item, that capacity); an item's
-// output word collects the capacities at which it is taken.
-__global__ void __launch_bounds__(64)
-sg_traceback_caps(BatchArgs a, InstState *state, const int32_t *__restrict__ act, const int32_t *rows,
-                  const uint64_t *keep, int row_len, int keep_words, int max_items)
+// ---- the streamed sweep -----------------------------------------------------------------
+
+constexpr int kStreamThreads = 1024;  // one workgroup per instance, all stages
+constexpr int kStreamWaves = kStreamThreads / 64;  // the last one moves old cells from global memory into LDS
+constexpr int kTaskCells = 512;       // what a wavefront computes at a time: eight cells per lane
+constexpr int kTaskSlots = kTaskCells / 64;
+constexpr int kMaxLevels = 7;         // items per pass over the row
+constexpr int kMiscBytes = 1024;      // LDS in front of the rings: StreamShared and the placed-item bits
+
+typedef __attribute__((address_space(3))) int32_t lds_i32;
+typedef const __attribute__((address_space(1))) int32_t global_ci32;
+
+struct StreamShared {
+    int32_t cnt, knap, cap, cap_min;
+    int64_t weight;            // of the whole list
+    int32_t value;             // of the whole list
+    int32_t settled;
+    uint32_t placed[kMaxItemsPlaced / 32];
+};
+static_assert(sizeof(StreamShared) <= kMiscBytes, "fits in front of the rings");
+
+// How a pass is cut: `levels` items over blocks of `block` cells, `ahead` blocks of the old row in flight.
+struct PassShape {
+    int16_t levels, block, ahead;
+};
+// Fifteen computing wavefronts, block / 512 tasks per level and step: the shapes that keep most of them
+// busy.  A cell costs 8 / levels bytes of global traffic, which is what bounds a pass of few
+// items, so more levels come before larger blocks; the rings limit both.
+constexpr PassShape kShapes[] = {{7, 1024, 3}, {6, 1024, 3}, {5, 1536, 2}, {5, 1024, 3}, {4, 1536, 2}, {4, 1024, 3},
+                                 {3, 2560, 2}, {3, 1024, 3}, {2, 3584, 2}, {2, 1024, 3}, {1, 7680, 2}, {1, 2560, 2},
+                                 {1, 1024, 3}};
+constexpr int kNumShapes = sizeof(kShapes) / sizeof(kShapes[0]);
+
+// Block hand-over: the loading wavefront arrives when the block that the next step reads has landed,
+// a computing one when its LDS accesses have; its stores stay in flight until the end of the pass.
+// Asm, because the compiler puts a wait for all vector memory in front of every barrier it
+// knows of once a kernel has LDS-direct loads.
+__device__ __forceinline__ void step_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+// Waits until at most n of the wavefront's loads are in flight (n is one of the counts the shapes give).
+__device__ __forceinline__ void wait_loads(int n)
 {
-    const int idx = blockIdx.x * 64 + threadIdx.x;
-    const int inst = idx / a.knap_stride, j = idx % a.knap_stride;
-    if (inst >= a.batch) return;
-    const InstState *st = &state[inst];
-    if (st->status != DEFT_OK || st->knap < 0 || j >= a.n_knapsacks[inst]) return;
-    const int nact = st->n_act, C = a.capacities[(size_t)inst * a.knap_stride + j];
-    const int32_t *W = a.weights + (size_t)inst * a.item_stride;
-    const int32_t *list = act + (size_t)inst * max_items;
-    int value = 0;
-    if (nact > 0) value = rows[((size_t)inst * 2 + (st->buf >= 0 ? st->buf : (nact & 1))) * row_len + C];
-    int c = C;
-    for (int q = nact - 1; q >= 0; --q) {
-        const int t = list[q];
-        const int w = W[t];
-        if (w <= c) {
-            const uint64_t word = keep[((size_t)inst * max_items + t) * keep_words + (c >> 6)];
-            if ((word >> (c & 63)) & 1ull) {
-                atomicOr(reinterpret_cast<unsigned int *>(&a.assignment[(size_t)inst * a.item_stride + t]), 1u << j);
-                c -= w;
+    switch (n) {
+    case 4: asm volatile("s_waitcnt vmcnt(4)" ::: "memory"); break;
+    case 6: asm volatile("s_waitcnt vmcnt(6)" ::: "memory"); break;
+    case 8: asm volatile("s_waitcnt vmcnt(8)" ::: "memory"); break;
+    case 10: asm volatile("s_waitcnt vmcnt(10)" ::: "memory"); break;
+    case 14: asm volatile("s_waitcnt vmcnt(14)" ::: "memory"); break;
+    case 30: asm volatile("s_waitcnt vmcnt(30)" ::: "memory"); break;
+    default: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
+    }
+}
+
+// acc = 2 acc + (sh < own): compare into vcc, add-with-carry.
+__device__ __forceinline__ uint32_t shift_in_less(uint32_t acc, int sh, int own)
+{
+    uint32_t out;
+    asm("v_cmp_lt_i32 vcc, %2, %3\n\tv_addc_co_u32 %0, vcc, %1, %1, vcc" : "=v"(out) : "v"(acc), "v"(sh), "v"(own) : "vcc");
+    return out;
+}
+
+__device__ __forceinline__ StreamItem load_item(const StreamItem *e)
+{
+    // written earlier in the launch by another wavefront of the workgroup (same compute unit, same L1)
+    StreamItem it;
+    const unsigned long long *u = reinterpret_cast<const unsigned long long *>(e);
+    const unsigned long long a = __hip_atomic_load(u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    it.upto = (int64_t)__hip_atomic_load(u + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    const unsigned long long c = __hip_atomic_load(u + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    it.w = (int)(uint32_t)a;
+    it.v = (int)(uint32_t)(a >> 32);
+    it.index = (int)(uint32_t)c;
+    it.pad = 0;
+    return it;
+}
+
+// The keep bit of (item q of the list, cell c): byte (c / 512) * 64 + c % 64 of the item's row, bit
+// 7 - (c / 64) % 8.
+__device__ __forceinline__ size_t keep_byte(int c) { return ((size_t)(c >> 9) << 6) + (c & 63); }
+
+// What a computing wavefront does in one pass: one task of one level per step.
+struct StreamTask {
+    int w, v;          // the level's item
+    int len, len_out;  // lengths of the ring read and of the ring written
+    int32_t *rg;       // the ring read
+    int32_t *rg_out;   // the ring written (not the last level)
+    int32_t *row;      // the row (last level)
+    uint8_t *keep;     // the item's keep row, this lane's byte
+    int low, top;      // cells of the level's row outside these do not matter
+    int c, at;         // the task's first cell at the level's first step, and its place in the rings
+    int first;         // the level's first step
+};
+// AHEAD: the item weighs at least a block, so that the next step's shifted operand is complete and is
+// read before this step's barrier.  LAST: the level stores to the row.
+template <bool AHEAD, bool LAST>
+__device__ __forceinline__ void stream_task(const StreamTask &k, int R, int steps, int lane)
+{
+    int p = k.at, po = k.at, c0 = k.c;
+    int shd[kTaskSlots];
+    auto read_shifted = [&](int at) {
+        int from = at - k.w;
+        if (from < 0) from += k.len;
+        if (from + kTaskCells <= k.len) {
+            const int32_t *s = k.rg + from + lane;
+#pragma unroll
+            for (int x = 0; x < kTaskSlots; ++x) shd[x] = s[x * 64];
+        } else {
+#pragma unroll
+            for (int x = 0; x < kTaskSlots; ++x) {
+                const unsigned o = (unsigned)(from + lane + x * 64);
+                shd[x] = k.rg[min(o, o - (unsigned)k.len)];  // wraps past the ring's end
             }
         }
+    };
+    step_barrier();
+    for (int t = 0; t < k.first; ++t) step_barrier();
+    if (AHEAD) read_shifted(p);
+    for (int t = k.first; t < steps; ++t) {
+        const bool here = c0 <= k.top && c0 + kTaskCells > k.low;
+        if (here) {
+            int own[kTaskSlots];
+            const int32_t *s = k.rg + p + lane;
+#pragma unroll
+            for (int x = 0; x < kTaskSlots; ++x) own[x] = s[x * 64];
+            if (!AHEAD) read_shifted(p);
+            if (c0 < k.w) {
+#pragma unroll
+                for (int x = 0; x < kTaskSlots; ++x)
+                    if (c0 + x * 64 + lane < k.w) shd[x] = INT_MAX;
+            }
+            uint32_t bits = 0;
+            int32_t *o = (LAST ? k.row + c0 : k.rg_out + po) + lane;
+#pragma unroll
+            for (int x = 0; x < kTaskSlots; ++x) {
+                const int passed = (int)((uint32_t)own[x] + (uint32_t)k.v);
+                bits = shift_in_less(bits, shd[x], passed);
+                o[x * 64] = min(passed, shd[x]);
+            }
+            k.keep[(size_t)(c0 >> 9) << 6] = (uint8_t)bits;
+        }
+        c0 += R;
+        p += R;
+        if (p >= k.len) p -= k.len;
+        po += R;
+        if (po >= k.len_out) po -= k.len_out;
+        if (AHEAD) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (what the step wrote)
+            read_shifted(p);
+            asm volatile("s_barrier" ::: "memory");
+        } else {
+            step_barrier();
+        }
     }
-    a.knap_value[(size_t)inst * a.knap_stride + j] = value;
-    a.knap_load[(size_t)inst * a.knap_stride + j] = C - c;
-    if (C == st->cap) a.total_value[inst] = value;  // the largest capacity (equal ones agree)
+}
+
+// All stages of one instance (see the head of this file).
+__global__ void __launch_bounds__(kStreamThreads)
+sg_stream(BatchArgs a, StreamItem *lists, int32_t *rows, uint8_t *keep, int row_len, int max_items, int ring_cells,
+          unsigned long long *streamed_cells)
+{
+    extern __shared__ __align__(16) char lds_stream[];
+    StreamShared *sh = reinterpret_cast<StreamShared *>(lds_stream);
+    int32_t *ring = reinterpret_cast<int32_t *>(lds_stream + kMiscBytes);
+    const int inst = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int status = check_instance(a, inst, false);
+    clear_outputs(a, inst, status);
+    if (status != DEFT_OK) return;
+
+    const int n = a.n_items[inst], m = a.n_knapsacks[inst];
+    const int32_t *W = a.weights + (size_t)inst * a.item_stride;
+    const int32_t *V = a.values + (size_t)inst * a.item_stride;
+    const int32_t *cap = a.capacities + (size_t)inst * a.knap_stride;
+    int32_t *out_asg = a.assignment + (size_t)inst * a.item_stride;
+    int32_t *out_kv = a.knap_value + (size_t)inst * a.knap_stride;
+    int32_t *out_kl = a.knap_load + (size_t)inst * a.knap_stride;
+    StreamItem *list = lists + (size_t)inst * max_items;
+    int32_t *row = rows + (size_t)inst * 2 * row_len;
+    uint8_t *kp = keep + (size_t)inst * max_items * (row_len / 8);
+    const size_t keep_row = row_len / 8;
+    const bool caps_sweep = a.mode == DEFT_MODE_CAPACITY_SWEEP;
+    for (int i = tid; i < kMaxItemsPlaced / 32; i += kStreamThreads) sh->placed[i] = 0;
+    __syncthreads();
+
+    long long total = 0;
+    unsigned long long streamed = 0;
+    const int stages = caps_sweep ? min(m, 1) : m;
+    for (int s = 0; s < stages; ++s) {
+        // ---- the stage's list, built by the first wavefront ------------------------------
+        if (wave == 0) {
+            const int j = caps_sweep ? 0 : a.fill_order ? a.fill_order[(size_t)inst * a.knap_stride + s] : s;
+            int C = cap[j], C_min = C;
+            if (caps_sweep)
+                for (int x = 1; x < m; ++x) C = max(C, cap[x]), C_min = min(C_min, cap[x]);
+            // offered: not placed, able to fit at all, worth something (an item of no value never
+            // strictly improves a cell)
+            int cnt = 0;
+            long long weight = 0;
+            int value = 0;
+            for (int i0 = 0; i0 < n; i0 += 64) {
+                const int i = i0 + lane;
+                const int w = i < n ? W[i] : 0, v = i < n ? V[i] : 0;
+                const bool f = i < n && !((sh->placed[i >> 5] >> (i & 31)) & 1u) && w <= C && v > 0;
+                const unsigned long long mask = __ballot(f);
+                long long upto = f ? w : 0;
+                int vsum = f ? v : 0;
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) {
+                    const long long y = __shfl_up(upto, off);
+                    if (lane >= off) upto += y;
+                    vsum += __shfl_xor(vsum, off);
+                }
+                if (f) {
+                    StreamItem e;
+                    e.w = w; e.v = v; e.index = i; e.pad = 0;
+                    e.upto = weight + upto;
+                    list[cnt + __popcll(mask & ((1ull << lane) - 1ull))] = e;
+                }
+                cnt += __popcll(mask);
+                weight += __shfl(upto, 63);
+                value += vsum;
+            }
+            const bool settled = !caps_sweep && weight <= C;
+            if (settled && cnt > 0) {
+                // everything offered fits together: the DP takes it all
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                for (int p = lane; p < cnt; p += 64) {
+                    const int i = load_item(list + p).index;
+                    out_asg[i] = j;
+                    atomicOr(&sh->placed[i >> 5], 1u << (i & 31));
+                }
+                if (lane == 0) {
+                    out_kv[j] = value;
+                    out_kl[j] = (int)weight;
+                }
+            }
+            if (lane == 0) {
+                sh->cnt = cnt; sh->knap = j; sh->cap = C; sh->cap_min = C_min;
+                sh->weight = weight; sh->value = value; sh->settled = settled;
+            }
+        }
+        __threadfence_block();
+        __syncthreads();
+        const int cnt = sh->cnt, j = sh->knap, C = sh->cap, C_min = sh->cap_min, value_all = sh->value;
+        const long long weight_all = sh->weight;
+        if (sh->settled || cnt == 0) {
+            total += value_all;
+            __syncthreads();
+            continue;
+        }
+
+        // ---- the sweep -----------------------------------------------------------------
+        // the cells of the row after the list's first p items that matter: upto = their weight
+        auto top = [&](long long upto) { return (int)min((long long)C, upto); };
+        auto bottom = [&](long long upto) { return (int)max(0ll, C_min - (weight_all - upto)); };
+        long long before = 0;  // weight of the items gone through
+        for (int q = 0; q < cnt;) {
+            StreamItem it{};
+            if (lane < kMaxLevels && q + lane < cnt) it = load_item(list + q + lane);
+            const int room = (it.w + kTaskCells - 1) / kTaskCells * kTaskCells;
+            const int left = cnt - q;
+            int g = 0, R = 0, ahead = 0;
+#pragma unroll
+            for (int x = kNumShapes - 1; x >= 0; --x) {  // the first shape that fits
+                // a ring: w cells back from the block being written, and one more block where the
+                // shifted operand is not read a step ahead
+                int need = (kShapes[x].ahead - 1) * kShapes[x].block;
+                for (int l = 0; l < kShapes[x].levels; ++l)
+                    need += __builtin_amdgcn_readlane(room, l) + (__builtin_amdgcn_readlane(it.w, l) >= kShapes[x].block ? 1 : 2) * kShapes[x].block;
+                if (kShapes[x].levels <= left && need <= ring_cells) g = kShapes[x].levels, R = kShapes[x].block, ahead = kShapes[x].ahead;
+            }
+            const int U_in = top(before), L_in = bottom(before);
+            if (g == 0) {
+                // ---- one item too heavy for the rings: in place, both operands from global memory,
+                // from the top down in steps of at most its weight (a step's shifted operands lie
+                // below everything it writes)
+                const int w = __builtin_amdgcn_readlane(it.w, 0), v = __builtin_amdgcn_readlane(it.v, 0);
+                const int U = top(before + w), L = bottom(before + w);
+                constexpr int kStep = kStreamWaves * 2 * kTaskCells;
+                for (int hi = U / kStep * kStep; hi >= 0 && hi + kStep > L; hi -= kStep) {
+#pragma unroll
+                    for (int x = 0; x < 2; ++x) {
+                        const int c0 = hi + (wave * 2 + x) * kTaskCells;
+                        if (c0 > U || c0 + kTaskCells <= L) continue;
+                        int own[kTaskSlots], shd[kTaskSlots];
+#pragma unroll
+                        for (int k = 0; k < kTaskSlots; ++k) {
+                            const int c = c0 + k * 64 + lane;
+                            own[k] = q > 0 && c <= U_in ? row[c] : 0;
+                            shd[k] = c < w ? INT_MAX : q > 0 && c - w <= U_in ? row[c - w] : 0;
+                        }
+                        uint32_t bits = 0;
+#pragma unroll
+                        for (int k = 0; k < kTaskSlots; ++k) {
+                            const int passed = (int)((uint32_t)own[k] + (uint32_t)v);
+                            bits = shift_in_less(bits, shd[k], passed);
+                            row[c0 + k * 64 + lane] = min(passed, shd[k]);
+                        }
+                        kp[(size_t)q * keep_row + keep_byte(c0) + lane] = (uint8_t)bits;
+                    }
+                    __threadfence_block();
+                    __syncthreads();
+                }
+                streamed += (unsigned)(U_in - L_in + U - L + 2);
+                before += w;
+                q += 1;
+                continue;
+            }
+
+            // ---- g items per pass ----------------------------------------------------------
+            // lane l < g: level l's ring (length, first cell)
+            const int rlen = lane < g ? room + (it.w >= R ? 1 : 2) * R + (lane == 0 ? (ahead - 1) * R : 0) : 0;
+            int rbase = rlen;
+#pragma unroll
+            for (int off = 1; off < 8; off <<= 1) {
+                const int y = __shfl_up(rbase, off);
+                if (lane >= off) rbase += y;
+            }
+            rbase -= rlen;
+            auto upto_of = [&](int l) {  // weight of the list up to and with item q + l
+                return ((long long)__builtin_amdgcn_readlane((int)(it.upto >> 32), l) << 32) |
+                       (long long)(unsigned)__builtin_amdgcn_readlane((int)it.upto, l);
+            };
+            const long long after = upto_of(g - 1);
+            const int U_out = top(after), L_out = bottom(after);
+            const int b0 = L_in / R, nb = U_out / R - b0 + 1;
+            const int real = q > 0 ? U_in / R - b0 + 1 : 0;  // blocks of the old row that hold anything
+            const int tpl = R / kTaskCells;
+            const int steps = nb + g - 1;
+            if (wave == kStreamWaves - 1) {
+                // the loading wavefront
+                const int per_block = R / 256;
+                const int ring0 = __builtin_amdgcn_readlane(rlen, 0);
+                int at = 0;  // ring position of block `next`
+                int next = 0;
+                auto issue = [&]() {
+                    if (next < real) {
+                        const int32_t *src = row + (size_t)(b0 + next) * R + lane * 4;
+                        int p = at;
+                        for (int x = 0; x < per_block; ++x) {
+                            __builtin_amdgcn_global_load_lds((global_ci32 *)(src + x * 256), (lds_i32 *)(ring + p), 16, 0, 0);
+                            p += 256;
+                            if (p >= ring0) p -= ring0;
+                        }
+                    }
+                    ++next;
+                    at += R;
+                    if (at >= ring0) at -= ring0;
+                };
+                int ready = 0;  // ring position of the block to hand over
+                // block x is complete in the ring: loaded, zero above the old row's top
+                auto finish = [&](int x) {
+                    if (x < real) wait_loads(min(next - 1 - x, real - 1 - x) * per_block);
+                    if (x >= real) {
+                        int p = ready;
+                        for (int i = 0; i < per_block; ++i) {
+                            *reinterpret_cast<int4 *>(ring + p + lane * 4) = make_int4(0, 0, 0, 0);
+                            p += 256;
+                            if (p >= ring0) p -= ring0;
+                        }
+                    } else if (x == real - 1) {
+                        for (int i = U_in - (b0 + x) * R + 1 + lane; i < R; i += 64) {
+                            int p = ready + i;
+                            if (p >= ring0) p -= ring0;
+                            ring[p] = 0;
+                        }
+                    }
+                    ready += R;
+                    if (ready >= ring0) ready -= ring0;
+                };
+                for (int x = 0; x < ahead; ++x) issue();
+                finish(0);
+                step_barrier();
+                for (int t = 0; t < steps; ++t) {
+                    issue();  // block t + ahead
+                    if (t + 1 < nb) finish(t + 1);
+                    step_barrier();
+                }
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            } else {
+                // A computing wavefront: one task of one level per step, the same all through the pass.
+                const bool busy = wave < g * tpl;
+                const int l = min(wave / tpl, g - 1), sub = wave - wave / tpl * tpl;
+                StreamTask k;
+                k.w = __builtin_amdgcn_readlane(it.w, l);
+                k.v = __builtin_amdgcn_readlane(it.v, l);
+                k.len = __builtin_amdgcn_readlane(rlen, l);
+                k.rg = ring + __builtin_amdgcn_readlane(rbase, l);
+                k.low = bottom(upto_of(l));
+                k.top = U_out;
+                k.len_out = l + 1 == g ? 0 : __builtin_amdgcn_readlane(rlen, l + 1);
+                k.rg_out = ring + (l + 1 == g ? 0 : __builtin_amdgcn_readlane(rbase, l + 1));
+                k.row = row;
+                k.keep = kp + (size_t)(q + l) * keep_row + lane;
+                k.c = b0 * R + sub * kTaskCells;
+                k.at = sub * kTaskCells;
+                k.first = l;
+                if (!busy) {
+                    for (int t = 0; t <= steps; ++t) step_barrier();
+                } else if (l + 1 < g) {
+                    if (k.w >= R) stream_task<true, false>(k, R, steps, lane); else stream_task<false, false>(k, R, steps, lane);
+                } else {
+                    if (k.w >= R) stream_task<true, true>(k, R, steps, lane); else stream_task<false, true>(k, R, steps, lane);
+                }
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the stores of the pass)
+            }
+            streamed += (unsigned)(U_in - L_in + U_out - L_out + 2);
+            before = after;
+            q += g;
+            // the next pass reads what this one wrote (other wavefronts' cells included)
+            __threadfence_block();
+            __syncthreads();
+        }
+
+        // ---- the value and the walk ------------------------------------------------------
+        // From (last item, c) down the list: item q is taken where its keep bit is set at the capacity left,
+        // and without a look once everything up to it fits.  A chain of dependent loads, so six
+        // steps are taken per memory round trip: lane L in [2^d, 2^(d+1)) assumes the decisions
+        // spelled by the bits of L below its leading one for items q .. q-d+1 and fetches the bit of
+        // item q-d at the capacity those leave; a ballot gives all 63 answers.
+        auto walk = [&](int c, auto &&take) {
+            const int d = 31 - __clz(lane | 1), path = lane - (1 << d);
+            int q = cnt - 1;
+            while (q >= 0) {
+                StreamItem e{};
+                if (lane < 6 && q - lane >= 0) e = load_item(list + q - lane);
+                const long long upto_q = ((long long)__builtin_amdgcn_readlane((int)(e.upto >> 32), 0) << 32) |
+                                         (long long)(unsigned)__builtin_amdgcn_readlane((int)e.upto, 0);
+                if (upto_q <= c) {  // everything left fits
+                    for (int p = lane; p <= q; p += 64) take(load_item(list + p).index);
+                    return c - (int)upto_q;
+                }
+                int wv[6], iv[6];
+#pragma unroll
+                for (int i = 0; i < 6; ++i) {
+                    wv[i] = __builtin_amdgcn_readlane(e.w, i);
+                    iv[i] = __builtin_amdgcn_readlane(e.index, i);
+                }
+                int cl = c, wd = wv[0];
+                long long upto = upto_q;  // of the items up to and with q - d
+#pragma unroll
+                for (int i = 0; i < 5; ++i) {
+                    if (i < d && ((path >> (d - 1 - i)) & 1)) cl -= wv[i];
+                    if (i < d) upto -= wv[i];
+                    if (d == i + 1) wd = wv[i + 1];
+                }
+                uint32_t bit = 0;
+                if (lane >= 1 && q - d >= 0 && cl >= wd) {
+                    if (cl >= upto) {
+                        bit = 1;
+                    } else {
+                        const uint8_t byte = __hip_atomic_load(&kp[(size_t)(q - d) * keep_row + keep_byte(cl)], __ATOMIC_RELAXED,
+                                                               __HIP_MEMORY_SCOPE_WORKGROUP);
+                        bit = (byte >> (7 - ((cl >> 6) & 7))) & 1u;
+                    }
+                }
+                const unsigned long long takes = __ballot(bit != 0);
+                int node = 1;
+#pragma unroll
+                for (int i = 0; i < 6; ++i) {
+                    const int b = (int)((takes >> node) & 1ull);
+                    if (b) {
+                        if (lane == 0) take(iv[i]);
+                        c -= wv[i];
+                    }
+                    node = 2 * node + b;
+                }
+                q -= 6;
+            }
+            return c;
+        };
+        auto value_at = [&](int c) {
+            return c >= weight_all ? value_all
+                                   : value_all - __hip_atomic_load(&row[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        };
+        if (!caps_sweep) {
+            const int value = value_at(C);
+            if (wave == 0) {
+                const int left = walk(C, [&](int i) {
+                    out_asg[i] = j;
+                    atomicOr(&sh->placed[i >> 5], 1u << (i & 31));
+                });
+                if (lane == 0) {
+                    out_kv[j] = value;
+                    out_kl[j] = C - left;
+                }
+            }
+            total += value;
+        } else {
+            for (int x = wave; x < m; x += kStreamWaves) {
+                const int c = cap[x];
+                const int left = walk(c, [&](int i) { atomicOr(reinterpret_cast<unsigned int *>(&out_asg[i]), 1u << x); });
+                if (lane == 0) {
+                    out_kv[x] = value_at(c);
+                    out_kl[x] = c - left;
+                }
+            }
+            total = value_at(C);
+        }
+        __syncthreads();
+    }
+    if (tid == 0) {
+        a.total_value[inst] = total;
+        if (streamed_cells) atomicAdd(streamed_cells, streamed);
+    }
 }
 
 }  // namespace
 
 void seq_global_plan(int32_t max_capacity, int32_t max_items, int32_t max_batch, int32_t lds_per_wg_bytes,
-                     int32_t compute_units, SeqGlobalPlan *p)
+                     SeqGlobalPlan *p)
 {
     p->threads = kThreads;
     p->cells_per_thread = kIter;
-    p->ring_segs = lds_per_wg_bytes / (kSegCells * 4);
-    p->lds_bytes = p->ring_segs * kSegCells * 4;
-    // one workgroup per instance pays once the batch covers at least half the compute units
-    p->persistent_min_batch = p->ring_segs >= 8 ? (compute_units + 1) / 2 : INT_MAX;
+    // (check_instance keeps a few words of its own in LDS)
+    p->ring_cells = (lds_per_wg_bytes - 256 - kMiscBytes) / 4 / kTaskCells * kTaskCells;
+    p->lds_bytes = kMiscBytes + p->ring_cells * 4;
     const int64_t cells = (int64_t)max_capacity + 1;
     p->row_len = (int32_t)((cells + kWaveCells - 1) / kWaveCells * kWaveCells);
     p->keep_words = p->row_len / 64;
@@ -624,54 +751,41 @@ void seq_global_plan(int32_t max_capacity, int32_t max_items, int32_t max_batch,
     p->scratch_bytes = (int64_t)(align256((size_t)max_batch * 2 * p->row_len * 4) +
                                  align256((size_t)max_batch * max_items * p->keep_words * 8) +
                                  2 * align256((size_t)max_batch * max_items * 4) +
-                                 align256((size_t)max_batch * sizeof(InstState)));
+                                 align256((size_t)max_batch * sizeof(InstState)) +
+                                 align256((size_t)max_batch * max_items * sizeof(StreamItem)));
 }
 
 hipError_t seq_global_prepare(const SeqGlobalPlan &p)
 {
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(&sg_sweep_all),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, p.lds_bytes);
+    // (the attribute belongs to the kernel, not to the handle, and the plan's LDS is the device's)
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(&sg_stream), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               p.lds_bytes);
 }
 
 hipError_t seq_global_launch(const SeqGlobalPlan &p, const BatchArgs &a, void *scratch, hipStream_t st,
                              Profiler *prof, unsigned long long *streamed_cells)
 {
     const Scratch s = carve(p, scratch, p.max_batch);
-    hipLaunchKernelGGL(sg_init, dim3(a.batch), dim3(kThreads), 0, st, a, s.state);
-    const int tiles = p.row_len / kTileCells + (p.row_len % kTileCells ? 1 : 0);
-    const bool caps_sweep = a.mode == DEFT_MODE_CAPACITY_SWEEP, levels = a.mode == DEFT_MODE_RECURSIVE;
-    const int stages = caps_sweep || levels ? 1 : a.knap_stride;
-    for (int stage = 0; stage < stages; ++stage) {
-        if (levels)
-            hipLaunchKernelGGL(sg_levels_setup, dim3(a.batch), dim3(64), 0, st, a, s.state, s.act, s.probe, p.max_items);
-        else
-            hipLaunchKernelGGL(sg_stage_setup, dim3(a.batch), dim3(64), 0, st, a, stage, s.state, s.act, p.max_items);
-        // Algorithm 1 reads one cell of every intermediate row, so it takes the sweeps that
-        // leave each of them in global memory (one launch per item)
-        if (a.batch >= p.persistent_min_batch && !levels) {
-            if (prof) prof->sweep_begin(st);
-            hipLaunchKernelGGL(sg_sweep_all, dim3((unsigned)a.batch), dim3(kAllThreads), (size_t)p.lds_bytes, st, a,
-                               s.state, s.act, s.rows, s.keep, p.row_len, p.keep_words, p.max_items, p.ring_segs,
-                               prof ? streamed_cells : nullptr);
-            if (prof) prof->sweep_end(st);
-        } else {
-            for (int q = 0; q < a.item_stride; ++q) {
-                if (prof) prof->sweep_begin(st);
-                hipLaunchKernelGGL(sg_sweep, dim3((unsigned)tiles * (unsigned)a.batch), dim3(kThreads), 0, st, a, q,
-                                   s.state, s.act, s.probe, s.rows, s.keep, p.row_len, p.keep_words, p.max_items,
-                                   tiles);
-                if (prof) prof->sweep_end(st);
-            }
-        }
-        if (caps_sweep) {
-            const unsigned walks = (unsigned)a.batch * (unsigned)a.knap_stride;
-            hipLaunchKernelGGL(sg_traceback_caps, dim3((walks + 63) / 64), dim3(64), 0, st, a, s.state, s.act, s.rows,
-                               s.keep, p.row_len, p.keep_words, p.max_items);
-        } else {
-            hipLaunchKernelGGL(sg_traceback, dim3((a.batch + 63) / 64), dim3(64), 0, st, a, s.state, s.act,
-                               s.rows, s.keep, p.row_len, p.keep_words, p.max_items);
-        }
+    if (a.mode != DEFT_MODE_RECURSIVE) {
+        if (prof) prof->sweep_begin(st);
+        hipLaunchKernelGGL(sg_stream, dim3((unsigned)a.batch), dim3(kStreamThreads), (size_t)p.lds_bytes, st, a, s.items,
+                           s.rows, reinterpret_cast<uint8_t *>(s.keep), p.row_len, p.max_items, p.ring_cells,
+                           prof ? streamed_cells : nullptr);
+        if (prof) prof->sweep_end(st);
+        return hipGetLastError();
     }
+    hipLaunchKernelGGL(sg_init, dim3(a.batch), dim3(kThreads), 0, st, a, s.state);
+    hipLaunchKernelGGL(sg_levels_setup, dim3(a.batch), dim3(64), 0, st, a, s.state, s.act, s.probe, p.max_items);
+    const int tiles = p.row_len / kTileCells + (p.row_len % kTileCells ? 1 : 0);
+    // (the host cannot know how many items an instance has: a workgroup whose instance has fewer exits)
+    for (int q = 0; q < a.item_stride; ++q) {
+        if (prof) prof->sweep_begin(st);
+        hipLaunchKernelGGL(sg_sweep, dim3((unsigned)tiles * (unsigned)a.batch), dim3(kThreads), 0, st, a, q, s.state, s.act,
+                           s.probe, s.rows, s.keep, p.row_len, p.keep_words, p.max_items, tiles);
+        if (prof) prof->sweep_end(st);
+    }
+    hipLaunchKernelGGL(sg_traceback, dim3((a.batch + 63) / 64), dim3(64), 0, st, a, s.state, s.act, s.rows, s.keep,
+                       p.row_len, p.keep_words, p.max_items);
     return hipGetLastError();
 }
 
