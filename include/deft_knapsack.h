@@ -71,11 +71,11 @@ typedef struct {
  * DEFT_FLAG_VALUES_ARE_WEIGHTS: the caller promises that in every instance given to this
  * handle each item's value equals its weight - the paper's own objective (Sec. III.B,
  * Problem 1: the profit of a bucket is its communication time).  Requires 1 <= max_capacity
- * <= 26623 (create returns DEFT_ERR_LIMIT otherwise, also when max_items is too long for the
- * smaller rows' LDS).  The sequential-layout modes (SEQUENTIAL, RECURSIVE, CAPACITY_SWEEP,
- * deft_knapsack_simulate_schedule) then run kernels that keep the DP row as 16-bit cells
- * (row[c] - c lies in [-c, 0]), two per 32-bit word: half the LDS per instance, half the LDS
- * instructions and packed 16-bit arithmetic per cell.  Results are bit-identical to those of a
+ * <= 26623 (create returns DEFT_ERR_LIMIT otherwise).  The sequential-layout modes (SEQUENTIAL,
+ * RECURSIVE, CAPACITY_SWEEP, deft_knapsack_simulate_schedule) then run on the kernels that
+ * DEFT_FLAG_SUBSET_SUM names, alone and without scratch memory; a handle without flags asks
+ * every instance for v == w first and solves those that have it there too (capacities up to
+ * 65535), the others on rows of values.  Results are bit-identical to those of a
  * handle without the flag.  An instance that breaks the promise (some value != its weight)
  * gets status DEFT_ERR_INVALID_ARG like any other bad input.  The joint and greedy modes are
  * not affected.
@@ -329,7 +329,9 @@ typedef struct {
     int32_t seq_path;          /* 0 none, 1 wavefront-per-instance LDS, 2 workgroup-per-
                                   instance LDS, 3 rows in global memory, 4 bit-set rows
                                   (DEFT_FLAG_SUBSET_SUM; what SEQUENTIAL, RECURSIVE and
-                                  CAPACITY_SWEEP calls run on)                             */
+                                  CAPACITY_SWEEP calls run on).  1, 2 and 3 and the four
+                                  figures below name the rows that max_capacity asks for,
+                                  which on those handles serve instances with v != w       */
     int32_t seq_threads;       /* threads cooperating on one instance                      */
     int32_t seq_cells_per_thread;
     int32_t seq_lds_bytes;     /* LDS per workgroup                                        */
@@ -353,7 +355,8 @@ typedef struct {
     int64_t swept_cell_updates; /* rows in LDS (seq_path 1 or 2): cell-updates the sweeps
                               evaluated, C - w + 1 for every item a stage's sweep went
                               through (stages settled without a sweep and the items after
-                              a full row add nothing); 0 on the other paths               */
+                              a full row add nothing), and the same count from the bit-set
+                              rows on those handles; 0 on the other paths                 */
 } deft_knapsack_profile_t;
 
 /* Turn HIP-event timing of solve calls on (1) or off (0); off by default.

@@ -51,8 +51,12 @@ struct deft_knapsack {
     unsigned long long *glob_streamed = nullptr;  // device counter read by get_profile
     unsigned long long *lds_swept = nullptr;      // device counter read by get_profile (LDS path)
 
-    bool use_bits = false;        // the sequential-layout modes run on the bit-set kernels (DEFT_FLAG_SUBSET_SUM)
+    // The bit-set kernels: promised - the handle's creator said that values are weights, and the
+    // sequential-layout modes run on them alone; otherwise, where bits_ready, they answer the
+    // instances of which that holds and flag the others in `left` for the kernels with rows of values.
+    bool bits_ready = false, promised = false;
     SeqBitsPlan bits_plan{};
+    int32_t *left = nullptr;      // [max_batch]
 
     void *sim_buffers = nullptr;  // task-queue simulation: allocated by its first call
 
@@ -66,6 +70,8 @@ struct deft_knapsack {
 
 namespace {
 
+bool subset_sum(const deft_knapsack *h) { return (h->cfg.flags & DEFT_FLAG_SUBSET_SUM) != 0; }
+
 void free_handle(deft_knapsack *h)
 {
     if (!h) return;
@@ -75,6 +81,7 @@ void free_handle(deft_knapsack *h)
     if (h->glob_streamed) (void)hipFree(h->glob_streamed);
     if (h->lds_swept) (void)hipFree(h->lds_swept);
     if (h->joint_scratch) (void)hipFree(h->joint_scratch);
+    if (h->left) (void)hipFree(h->left);
     if (h->sim_buffers) (void)hipFree(h->sim_buffers);
     h->prof.destroy();
     delete h;
@@ -116,9 +123,8 @@ extern "C" deft_status_t deft_knapsack_create(const deft_knapsack_config_t *cfg,
     if (want_joint && cfg->max_knapsacks < 2) return DEFT_ERR_INVALID_ARG;
     const bool subset_sum = (cfg->flags & DEFT_FLAG_SUBSET_SUM) != 0;
     if (subset_sum && (!want_seq || cfg->max_capacity > kMaxSubsetSumCapacity)) return DEFT_ERR_LIMIT;
-    // what a subset-sum handle does not run on the bit-set kernels (the greedy mode; Algorithm 1
-    // and the capacity sweep where their extra list does not fit the LDS) runs on rows of 16-bit
-    // cells where those reach, on the 32-bit rows beyond
+    // rows of 16-bit cells: what such a handle would run on if its list did not fit beside the bit set
+    // (every list of at most kMaxItems does)
     const bool packed16 = (cfg->flags & DEFT_FLAG_VALUES_ARE_WEIGHTS) != 0 ||
                           (subset_sum && cfg->max_capacity <= kMaxPacked16Capacity);
     if ((cfg->flags & DEFT_FLAG_VALUES_ARE_WEIGHTS) != 0 && (!want_seq || cfg->max_capacity > kMaxPacked16Capacity))
@@ -146,14 +152,31 @@ extern "C" deft_status_t deft_knapsack_create(const deft_knapsack_config_t *cfg,
     h->compute_units = prop.multiProcessorCount;
 
     deft_status_t st = DEFT_OK;
-    if (want_seq) {
-        const int lds_wg = (int)prop.sharedMemPerBlockOptin > 0 ? (int)prop.sharedMemPerBlockOptin
-                                                                : (int)prop.sharedMemPerBlock;
+    const int lds_wg = (int)prop.sharedMemPerBlockOptin > 0 ? (int)prop.sharedMemPerBlockOptin
+                                                            : (int)prop.sharedMemPerBlock;
+    if (want_seq && cfg->max_capacity <= kMaxSubsetSumCapacity) {
+        if (!seq_bits_plan(cfg->max_capacity, cfg->max_items, lds_wg, h->compute_units, &h->bits_plan)) {
+            if (subset_sum) st = DEFT_ERR_LIMIT;  // (an item list too long for the LDS beside the row)
+        } else if (seq_bits_prepare(h->bits_plan) != hipSuccess) {
+            (void)hipGetLastError();
+            st = DEFT_ERR_DEVICE;
+        } else {
+            h->bits_ready = true;
+            h->promised = cfg->flags != 0;
+        }
+    }
+    if (st == DEFT_OK && want_seq) {
         if (seq_lds_plan(cfg->max_capacity, cfg->max_items, cfg->max_knapsacks, cfg->max_batch, lds_wg, packed16,
                          &h->lds_plan) &&
             seq_lds_prepare(&h->lds_plan) == hipSuccess && seq_lds_rec_prepare(h->lds_plan) == hipSuccess) {
             h->seq_path = h->lds_plan.threads == 64 ? 1 : 2;
-            st = alloc(&h->keep, h->lds_plan.scratch_bytes, &h->scratch_bytes);
+            // (the row kernels of a handle that was promised values equal to weights never run)
+            if (!h->promised) st = alloc(&h->keep, h->lds_plan.scratch_bytes, &h->scratch_bytes);
+            if (st == DEFT_OK && !h->promised && h->bits_ready) {
+                void *c = nullptr;
+                st = alloc(&c, (int64_t)cfg->max_batch * 4, &h->scratch_bytes);
+                h->left = static_cast<int32_t *>(c);
+            }
             if (st == DEFT_OK) {
                 void *c = nullptr;
                 st = alloc(&c, 8, &h->scratch_bytes);
@@ -174,7 +197,7 @@ extern "C" deft_status_t deft_knapsack_create(const deft_knapsack_config_t *cfg,
                 (void)hipGetLastError();
                 st = DEFT_ERR_DEVICE;
             } else {
-                st = alloc(&h->glob_scratch, h->glob_plan.scratch_bytes, &h->scratch_bytes);
+                if (!h->promised) st = alloc(&h->glob_scratch, h->glob_plan.scratch_bytes, &h->scratch_bytes);
                 if (st == DEFT_OK) {
                     void *c = nullptr;
                     st = alloc(&c, 8, &h->scratch_bytes);
@@ -187,22 +210,8 @@ extern "C" deft_status_t deft_knapsack_create(const deft_knapsack_config_t *cfg,
             }
         }
     }
-    if (st == DEFT_OK && subset_sum) {
-        const int lds_wg = (int)prop.sharedMemPerBlockOptin > 0 ? (int)prop.sharedMemPerBlockOptin
-                                                                : (int)prop.sharedMemPerBlock;
-        if (!seq_bits_plan(cfg->max_capacity, cfg->max_items, lds_wg, h->compute_units, &h->bits_plan)) {
-            st = DEFT_ERR_LIMIT;  // (an item list too long for the LDS beside the row)
-        } else if (seq_bits_prepare(h->bits_plan) != hipSuccess) {
-            (void)hipGetLastError();
-            st = DEFT_ERR_DEVICE;
-        } else {
-            h->use_bits = true;
-        }
-    }
     if (st == DEFT_OK && want_joint) {
         h->joint_path = 1;
-        const int lds_wg = (int)prop.sharedMemPerBlockOptin > 0 ? (int)prop.sharedMemPerBlockOptin
-                                                                : (int)prop.sharedMemPerBlock;
         joint_plan(cfg->max_c1, cfg->max_c2, cfg->max_items, cfg->max_batch, lds_wg, &h->joint_plan);
         if (joint_prepare(h->joint_plan) != hipSuccess) {
             (void)hipGetLastError();
@@ -274,16 +283,31 @@ extern "C" deft_status_t deft_knapsack_solve_batch(deft_knapsack_t *h, const def
     if (prof && !prof->begin(st)) return DEFT_ERR_DEVICE;
 
     hipError_t e = hipSuccess;
-    if ((b->mode == DEFT_MODE_SEQUENTIAL || probing) && h->use_bits) {
+    unsigned long long *swept = prof && !subset_sum(h) ? h->lds_swept : nullptr;
+    a.left = nullptr;
+    // A plain handle's instances may still have values equal to weights: the bit-set kernels answer those
+    // (measured on 4096 ResNet-101-shaped schedules: 0.100 ms, rows of values 1.66 ms) and the rows take
+    // what is left.  Where none qualifies that is a launch for nothing, 2.2 us for one instance and 4 us
+    // for four thousand, which a call of a few short instances would notice (one of 32 items at
+    // capacity 1000: 19.4 us on the rows alone; values equal to weights save it 9 us): those go to the
+    // rows at once.
+    const bool small = b->batch < 64 && (int64_t)b->item_stride * h->cfg.max_capacity < (1 << 17);
+    const bool by_sums = (b->mode == DEFT_MODE_SEQUENTIAL || probing) && h->bits_ready &&
+                         (h->promised || (h->left && !small));
+    if (by_sums) {
+        a.left = h->left;
         if (prof) prof->sweep_begin(st);
-        e = seq_bits_launch(h->bits_plan, a, st, nullptr);
+        e = seq_bits_launch(h->bits_plan, a, st, swept);
         if (prof) prof->sweep_end(st);
+    }
+    if (e != hipSuccess || (by_sums && h->promised)) {
+        // (nothing is left to do)
     } else if (b->mode == DEFT_MODE_SEQUENTIAL || (probing && !on_lds)) {
         if (h->seq_path == 3) {
             e = seq_global_launch(h->glob_plan, a, h->glob_scratch, st, prof, h->glob_streamed);
         } else {
             if (prof) prof->sweep_begin(st);
-            e = seq_lds_launch(h->lds_plan, a, h->keep, st, prof ? h->lds_swept : nullptr);
+            e = seq_lds_launch(h->lds_plan, a, h->keep, st, swept);
             if (prof) prof->sweep_end(st);
         }
     } else if (b->mode == DEFT_MODE_GREEDY || b->mode == DEFT_MODE_GREEDY2) {
@@ -292,7 +316,7 @@ extern "C" deft_status_t deft_knapsack_solve_batch(deft_knapsack_t *h, const def
         if (prof) prof->sweep_end(st);
     } else if (probing) {  // on the LDS-resident row
         if (prof) prof->sweep_begin(st);
-        e = seq_lds_rec_launch(h->lds_plan, a, h->keep, st, prof ? h->lds_swept : nullptr);
+        e = seq_lds_rec_launch(h->lds_plan, a, h->keep, st, swept);
         if (prof) prof->sweep_end(st);
     } else {
         e = joint_launch(h->joint_plan, a, h->joint_scratch, st, prof);
@@ -345,9 +369,9 @@ extern "C" deft_status_t deft_knapsack_simulate_schedule(deft_knapsack_t *h, con
     Profiler *prof = h->profiling ? &h->prof : nullptr;
     if (prof && !prof->begin(st)) return DEFT_ERR_DEVICE;
     const auto solve = [&](const BatchArgs &x) -> hipError_t {
-        if (h->use_bits) {
+        if (h->bits_ready) {  // a bucket's value is its communication time
             if (prof) prof->sweep_begin(st);
-            const hipError_t rc = seq_bits_launch(h->bits_plan, x, st, nullptr);
+            const hipError_t rc = seq_bits_launch(h->bits_plan, x, st, prof && !subset_sum(h) ? h->lds_swept : nullptr);
             if (prof) prof->sweep_end(st);
             return rc;
         }
@@ -385,7 +409,7 @@ extern "C" deft_status_t deft_knapsack_get_info(const deft_knapsack_t *h, deft_k
         info->seq_threads = h->glob_plan.threads;
         info->seq_cells_per_thread = h->glob_plan.cells_per_thread;
     }
-    if (h->use_bits) {  // what SEQUENTIAL calls run on
+    if (subset_sum(h)) {  // what SEQUENTIAL calls run on
         info->seq_path = 4;
         info->seq_threads = 64;
         info->seq_cells_per_thread = h->bits_plan.words_per_lane * 32;

@@ -20,6 +20,9 @@ struct BatchArgs {
     const int32_t *drop_time;  // recursive mode only
     int64_t *total_value;
     int32_t *knap_value, *knap_load, *assignment, *status;
+    // [batch] or null.  The bit-set kernels write 1 for an instance whose values are not all its
+    // weights and leave it alone, 0 for one they answered; the LDS-row kernels then skip those.
+    int32_t *left;
 };
 
 // ---- sequential mode, capacity row resident in LDS (seq_lds.hip) ------------

@@ -244,6 +244,7 @@ hipError_t schedule_sim_launch(const ScheduleArgs &s, void *sim_buffers, hipStre
     a.knap_load = buf.kl;
     a.assignment = buf.asg;
     a.status = buf.status;
+    a.left = nullptr;
 
     const dim3 grid((unsigned)s.batch), block(64);
     hipLaunchKernelGGL(sim_init, grid, block, 0, st, s, buf);

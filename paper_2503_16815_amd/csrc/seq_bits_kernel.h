@@ -497,6 +497,12 @@ seq_bits_kernel(BatchArgs a, BitsLayout lay, unsigned long long *swept_cells)
         else if (__builtin_amdgcn_ballot_w64((flags & 2) != 0) != 0ull) status = DEFT_ERR_LIMIT;
         else if (total_v >= (1ull << 31)) status = DEFT_ERR_OVERFLOW;
         else if (__builtin_amdgcn_ballot_w64(differs) != 0ull) status = DEFT_ERR_INVALID_ARG;
+        if (a.left) {
+            // no promise was made: an instance in order that is not a subset-sum problem is the next kernel's
+            const bool not_mine = status == DEFT_ERR_INVALID_ARG && __builtin_amdgcn_ballot_w64((flags & 1) != 0) == 0ull;
+            if (lane == 0) a.left[inst] = not_mine ? 1 : 0;
+            if (not_mine) return;
+        }
     }
     int32_t *out_asg = a.assignment + (size_t)inst * a.item_stride;
     if (status != DEFT_OK) {

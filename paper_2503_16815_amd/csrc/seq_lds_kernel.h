@@ -793,6 +793,7 @@ seq_lds_kernel(BatchArgs a, LdsLayout lay, uint32_t *keep, int64_t keep_words_pe
     const int tid = (T == 64) ? (int)(threadIdx.x & 63) : (int)threadIdx.x;
     const int inst = (T == 64) ? (int)blockIdx.x * 4 + sub : (int)blockIdx.x;
     if (inst >= a.batch) return;  // whole wavefront (T == 64) or never (grid == batch)
+    if (a.left && a.left[inst] == 0) return;  // (the same: all lanes of the instance, before any barrier)
     // One wavefront of the instance does everything that is serial: the stage set-up, the
     // stages settled without a sweep, the walk.  Its instructions all issue on the one SIMD
     // it lives on, next to that SIMD's share of the sweeps; which wavefront it is rotates

@@ -140,6 +140,7 @@ extern "C" deft_status_t deft_knapsack_solve_batch_static(int32_t device, int32_
     a.knap_load = b->knap_load;
     a.assignment = b->assignment;
     a.status = b->status;
+    a.left = nullptr;
     // Nothing in the array has to start at zero: a stage writes its item list before any
     // lane reads it, and a keep-row part is read only when the flag its writer set in
     // registers says it was written in this launch.  What the last call left is never read.
