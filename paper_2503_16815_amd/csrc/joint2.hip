@@ -13,6 +13,16 @@
 // The 2-bit choice is stored as two bit planes (took link 0 / took link 1),
 // one 64-bit ballot word per 64 consecutive b.  The first item reads zeros
 // instead of a table.
+//
+// Two runs of rows need no computing.  Row a with all of the items so far light enough
+// together for link 0 (a >= the sum of their w0) holds all of them at every b, and its
+// choice is link 0 (the first that reaches the full value): the row is a constant, neither
+// computed nor stored, and its LDS copy is filled instead of loaded.  And a walk from C1 has
+// at most the items behind q to lower it, so rows of the table after item q below C1 - (the
+// sum of their w0) are never looked at.  Between the two a row is needed; what such a row
+// reads, a row at a - w0 included, was needed (or constant) one item earlier.
+// Two-link batch (256 instances, 64 items of 1 to 64, C1 = C2 = 512; a quarter of the rows is
+// outside): 8.01 -> 6.42 ms.
 #include <limits.h>
 
 #include <type_traits>
@@ -98,7 +108,7 @@ __global__ void __launch_bounds__(kSweepThreads)
 jt_sweep_all(BatchArgs a, const InstState *__restrict__ state, int32_t *tab, uint64_t *choice, int rows, int pitch,
              int max_items, int ring_rows, int lds_pitch)
 {
-    extern __shared__ __align__(16) int32_t ring[];  // [ring_rows][lds_pitch], row a lives in slot a % ring_rows
+    extern __shared__ __align__(16) int32_t ring[];  // [ring_rows][lds_pitch], row a lives in slot (a - base) % ring_rows
     const int inst = blockIdx.x;
     const InstState st = state[inst];
     if (st.status != DEFT_OK || st.n <= 0) return;
@@ -122,8 +132,22 @@ jt_sweep_all(BatchArgs a, const InstState *__restrict__ state, int32_t *tab, uin
     for (int i = threadIdx.x; i < ring_rows * lds_pitch; i += kSweepThreads) ring[i] = 0;
     __syncthreads();
 
+    long long behind = 0;  // weight on link 0 of the items behind the current one
+    for (int i = lane; i < st.n; i += 64) behind += W0[i];
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) behind += __shfl_xor(behind, off);
+    int held = 0, held_value = 0;  // weight on link 0 (at most nrow) and value of the items before it
+
     for (int q = 0; q < st.n; ++q) {
         const int w0 = W0[q], w1 = W1[q], v = V[q];
+        behind -= w0;
+        // rows [need, end) are computed, [base, end) loaded, those from `constant` on filled
+        const int need = __builtin_amdgcn_readfirstlane(behind < st.c1 ? st.c1 - (int)behind : 0);
+        const int constant = held, fill = held_value;
+        const int end = held = min(nrow, held + min(w0, nrow));
+        const int base = max(0, need - w0);
+        held_value += v;
+        if (need >= end) continue;
         const int32_t *__restrict__ src = tab + ((size_t)inst * 2 + (q & 1)) * tsz;
         int32_t *__restrict__ dst = tab + ((size_t)inst * 2 + ((q & 1) ^ 1)) * tsz;
         uint64_t *ch = choice + ((size_t)inst * max_items + q) * ((size_t)rows * segs * 2);
@@ -138,7 +162,7 @@ jt_sweep_all(BatchArgs a, const InstState *__restrict__ state, int32_t *tab, uin
         // (row, segment) pairs are dealt round-robin to the loading wavefronts.
         auto load_rows = [&](int lo, int slot_lo) {
             if (first) return;
-            const int nr = min(R, nrow - lo);
+            const int nr = min(R, end - lo);
             // whole rows, dealt round-robin to the loading wavefronts; a row is ntile parts of
             // 256 columns, 16 bytes per lane.  Kept lean: a loading wavefront shares its SIMD with
             // computing ones, so the instructions it spends per load bound the rate it loads at.
@@ -149,6 +173,11 @@ jt_sweep_all(BatchArgs a, const InstState *__restrict__ state, int32_t *tab, uin
                 int32_t *l = ring + (size_t)slot * lds_pitch;
                 // a lane's four columns may run past the instance's last column, never past the
                 // row pitch of the table or of the ring (both are multiples of four)
+                if (lo + r >= constant) {
+                    for (int col = lane * 4; col < ncol; col += 256)
+                        *reinterpret_cast<int4 *>(ring + (size_t)slot * lds_pitch + col) = make_int4(fill, fill, fill, fill);
+                    continue;
+                }
                 for (int part = 0; part < ntile; ++part) {
                     if (part * 256 + lane * 4 < ncol)
                         __builtin_amdgcn_global_load_lds((global_ci32 *)(g + part * 256), (lds_i32 *)(l + part * 256), 16, 0, 0);
@@ -157,17 +186,17 @@ jt_sweep_all(BatchArgs a, const InstState *__restrict__ state, int32_t *tab, uin
         };
 
         if (loader) {
-            load_rows(0, 0);
+            load_rows(base, 0);
             barrier_after_loads();
         } else {
             barrier_after_lds_reads();
         }
-        int slot_a0 = 0;  // a0 % ring_rows
-        for (int a0 = 0; a0 < nrow; a0 += R) {
+        int slot_a0 = 0;  // (a0 - base) % ring_rows
+        for (int a0 = base; a0 < end; a0 += R) {
             int slot_next = slot_a0 + R;
             if (slot_next >= ring_rows) slot_next -= ring_rows;
             if (loader) {
-                if (a0 + R < nrow) load_rows(a0 + R, slot_next);
+                if (a0 + R < end) load_rows(a0 + R, slot_next);
                 barrier_after_loads();  // the next block is in the ring
             } else {
                 // One task.  IN_RING: the row-shifted operand comes from the ring; otherwise
@@ -256,8 +285,8 @@ jt_sweep_all(BatchArgs a, const InstState *__restrict__ state, int32_t *tab, uin
                         ch[((size_t)ar * segs + (col >> 6)) * 2 + 1] = t1;
                     }
                 };
-                const int nr = min(R, nrow - a0);
-                int r = 0, tile = wave - kLoadWaves;
+                const int nr = min(R, end - a0);
+                int r = max(0, need - a0), tile = wave - kLoadWaves;
                 while (true) {
                     while (tile >= ntile_tasks) { tile -= ntile_tasks; ++r; }
                     if (r >= nr) break;
@@ -295,8 +324,7 @@ jt_sweep_all(BatchArgs a, const InstState *__restrict__ state, int32_t *tab, uin
 }
 
 __global__ void __launch_bounds__(64)
-jt_traceback(BatchArgs a, const InstState *__restrict__ state, const int32_t *tab, const uint64_t *choice,
-             int rows, int pitch, int max_items)
+jt_traceback(BatchArgs a, const InstState *__restrict__ state, const uint64_t *choice, int rows, int pitch, int max_items)
 {
     const int inst = blockIdx.x * 64 + threadIdx.x;
     if (inst >= a.batch) return;
@@ -306,10 +334,18 @@ jt_traceback(BatchArgs a, const InstState *__restrict__ state, const int32_t *ta
     const int32_t *W0 = a.weights + (size_t)inst * 2 * a.item_stride;
     const int32_t *W1 = W0 + a.item_stride;
     const int32_t *V = a.values + (size_t)inst * a.item_stride;
-    int total = 0;
-    if (st.n > 0) total = tab[((size_t)inst * 2 + (st.n & 1)) * ((size_t)rows * pitch) + (size_t)st.c1 * pitch + st.c2];
+    long long held = 0;  // weight on link 0 of the items up to and with i
+    for (int i = 0; i < st.n; ++i) held += W0[i];
     int ar = st.c1, b = st.c2, val0 = 0, val1 = 0;
-    for (int i = st.n - 1; i >= 0; --i) {
+    for (int i = st.n - 1; i >= 0; held -= W0[i], --i) {
+        if (ar >= held) {  // a constant row: link 0 takes whatever is worth something
+            if (V[i] > 0) {
+                a.assignment[(size_t)inst * a.item_stride + i] = 0;
+                ar -= W0[i];
+                val0 += V[i];
+            }
+            continue;
+        }
         const uint64_t *ch = choice + ((size_t)inst * max_items + i) * ((size_t)rows * segs * 2) +
                              ((size_t)ar * segs + (b >> 6)) * 2;
         const unsigned bit = b & 63;
@@ -327,7 +363,7 @@ jt_traceback(BatchArgs a, const InstState *__restrict__ state, const int32_t *ta
     int32_t *kl = a.knap_load + (size_t)inst * a.knap_stride;
     kv[0] = val0; kv[1] = val1;
     kl[0] = st.c1 - ar; kl[1] = st.c2 - b;
-    a.total_value[inst] = total;
+    a.total_value[inst] = (int64_t)val0 + val1;
 }
 
 }  // namespace
@@ -365,8 +401,8 @@ hipError_t joint_launch(const JointPlan &p, const BatchArgs &a, void *scratch, h
     hipLaunchKernelGGL(jt_sweep_all, dim3((unsigned)a.batch), dim3(kSweepThreads), (size_t)p.lds_bytes, st, a, s.state,
                        s.tab, s.choice, p.rows, p.pitch, p.max_items, p.ring_rows, p.lds_pitch);
     if (prof) prof->sweep_end(st);
-    hipLaunchKernelGGL(jt_traceback, dim3((a.batch + 63) / 64), dim3(64), 0, st, a, s.state, s.tab, s.choice,
-                       p.rows, p.pitch, p.max_items);
+    hipLaunchKernelGGL(jt_traceback, dim3((a.batch + 63) / 64), dim3(64), 0, st, a, s.state, s.choice, p.rows,
+                       p.pitch, p.max_items);
     return hipGetLastError();
 }
 
