@@ -175,12 +175,15 @@ def run_schedule(args):
         for _ in range(args.warmup):
             binding.simulate_schedule(h, ds, stream)
         stream.synchronize()
-        h.set_profiling(True)
         t0 = time.perf_counter()
         for _ in range(args.steps):
             out = binding.simulate_schedule(h, ds, stream)
         stream.synchronize()
         t1 = time.perf_counter()
+        h.set_profiling(True)   # the same steps again, untimed, for the kernels' own times and counts
+        for _ in range(args.steps):
+            out = binding.simulate_schedule(h, ds, stream)
+        stream.synchronize()
         prof = h.get_profile()
         got = {k: getattr(out, k).cpu().numpy() for k in ("stage_case", "stage_count", "stage_time", "update_k",
                                                           "tail", "status")}
@@ -193,14 +196,13 @@ def run_schedule(args):
     sweep_s = float(prof.sweep_ms) * 1e-3
     launches = int(prof.sweep_launches)
     swept_step = int(prof.swept_cell_updates) // args.steps   # counted by the library: what the sweeps evaluated
+    # every stage runs on the bit-set kernels, 12 LDS bytes and about four vector instructions per 32
+    # cells; on a handle that promises a subset-sum problem they count nothing, and the one-sweep cells
+    # the oracle's sample gives stand in
     bitset = bool(getattr(args, "subset_sum", False))
-    bytes_per_cell, ops_per_cell = (4.0, 1.75) if packed16 else (8.0, 3.0)
+    bytes_per_cell, ops_per_cell = 0.375, 0.125
     if bitset:
-        # every stage on the bit-set kernels, which count nothing: the one-sweep cells the oracle's
-        # sample gives (what the int32 kernels would be offered), at the bit-set kernels' own 12 LDS
-        # bytes and four vector instructions per 32 cells - for the record, the kernels are bound by latency
         swept_step = int(cells_step)
-        bytes_per_cell, ops_per_cell = 0.375, 0.125
     achieved = swept_step * args.steps * bytes_per_cell / sweep_s / 1e9 if sweep_s > 0 else 0.0
     ops = swept_step * args.steps * ops_per_cell / sweep_s if sweep_s > 0 else 0.0
     upd = got["update_k"]
@@ -210,7 +212,7 @@ def run_schedule(args):
         vs_baseline=None, dtype="int32", data="synthetic",
         config=dict(workload=f"task-queue simulation (Cases 1-4), ResNet-101-shaped: {sb.batch} candidates x "
                              f"{sb.n_buckets} buckets x {sb.iterations} iterations, windows 5900 / 11800 +-10%"
-                             + (" [rows of 16-bit cells]" if packed16 else "")
+                             + (" [handle promises values equal to weights]" if packed16 else "")
                              + (" [bit-set rows; cell-updates as the oracle's sample counts them for one sweep per stage]"
                                 if bitset else ""),
                     value_counts=("one-sweep cell-updates per stage as estimated from the oracle's sample (the bit-set "
@@ -227,7 +229,7 @@ def run_schedule(args):
         profile=dict(total_ms_per_step=float(prof.total_ms) / args.steps,
                      sweep_ms_per_step=float(prof.sweep_ms) / args.steps),
         roofline=dict(bound="lds", achieved=achieved, peak=PEAK_LDS_GBS, unit="GB/s", frac=achieved / PEAK_LDS_GBS,
-                      traffic=None, kernel="seq_bits_kernel" if bitset else "seq_lds_kernel",
+                      traffic=None, kernel="seq_bits_kernel",
                       bytes_per_cell=bytes_per_cell, launches=launches,
                       avg_launch_ms=float(prof.sweep_ms) / max(launches, 1),
                       swept_cell_updates_per_s=swept_step * args.steps / sweep_s if sweep_s > 0 else 0.0,
@@ -252,6 +254,24 @@ def subset(kb, rows):
                            fill_order=pick(kb.fill_order), meta=dict(kb.meta), drop_time=pick(kb.drop_time))
 
 
+def values_are_weights(kb):
+    listed = np.arange(kb.item_stride)[None, :] < kb.n_items[:, None]
+    return kb.weights.shape == kb.values.shape and bool((kb.weights == kb.values)[listed].all())
+
+
+def joint_cells_computed(kb):
+    """Cells of the rows that the two-link sweep computes: after an item, from C1 less the link-0 weight of
+    the items behind it up to the link-0 weight of the items so far."""
+    cells = 0
+    for b in range(kb.batch):
+        w = kb.weights[b, 0, :kb.n_items[b]].astype(np.int64)
+        c1, c2 = (int(c) for c in kb.capacities[b, :2])
+        held = np.cumsum(w)
+        need = np.maximum(0, c1 - (held[-1:] - held))
+        cells += int(np.maximum(0, np.minimum(c1 + 1, held) - need).sum()) * (c2 + 1)
+    return cells
+
+
 def run_solver(args):
     """One workload through deft_knapsack_solve_batch.  Returns (line, parity)."""
     import torch
@@ -274,20 +294,16 @@ def run_solver(args):
     packed16 = bool(getattr(args, "packed16", False))
     if packed16:
         limits["flags"] = 1
-        desc += " [rows of 16-bit cells]"
-        # two 16-bit cells per LDS word and per packed instruction: 2 B read + 2 B written per cell
-        # (LDS bound 128 B / 4 B = 32 cells per clock and CU); subtract and max per pair of cells,
-        # permute + shift + bit-field insert per two pairs = 1.75 vector instructions per cell (ALU
-        # bound 64 / 1.75 = 36.6; lanes below the item's shift add a byte permute per pair): LDS is
-        # the nearer bound and the one the fraction is taken against
-        algo = dict(bound="lds", bytes_per_cell=4.0, ops_per_cell=1.75)
+        desc += " [handle promises values equal to weights]"
     subset_sum = bool(getattr(args, "subset_sum", False))
     if subset_sum:
         limits["flags"] = 2
-        desc += " [bit-set rows]"
-        # one bit per cell: two 4-byte words read and one written per 32 cells, four vector instructions
-        # per 32 cells; a latency-bound kernel (one wavefront per instance), stated against the LDS peak
-        # at its own bytes for the record
+        desc += " [handle promises a subset-sum problem]"
+    # instances whose values are their weights are solved on the bit-set kernels, whatever the handle
+    by_sums = seq and calls[0].mode in (0, 2, 5) and cap <= 65535 and all(values_are_weights(kb) for kb in calls)
+    if by_sums:
+        # one bit per cell: two 4-byte words read and one written per 32 cells, and about four
+        # vector instructions, per 32 cells
         algo = dict(bound="lds", bytes_per_cell=0.375, ops_per_cell=0.125)
     if seq:
         limits["max_capacity"] = cap
@@ -379,13 +395,19 @@ def run_solver(args):
             step()
         stream.synchronize()
         torch.cuda.synchronize(dev)
-        h.set_profiling(True)
         t0 = time.perf_counter()
         for _ in range(args.steps):
             step()
         stream.synchronize()
         torch.cuda.synchronize(dev)
         t1 = time.perf_counter()
+        # the same steps again, untimed, for the kernels' own times and the counted cells: the events, and
+        # one counter that every instance adds to, would be half of the shortest steps (0.19 ms, 0.10 without)
+        h.set_profiling(True)
+        for _ in range(args.steps):
+            step()
+        stream.synchronize()
+        torch.cuda.synchronize(dev)
         prof = h.get_profile()
         h.set_profiling(False)
 
@@ -402,6 +424,8 @@ def run_solver(args):
     # rows in LDS: the library counts the cell-updates its sweeps evaluated (C - w + 1 per swept
     # item); value and roofline are priced on that count.  For the sequential mode the same number
     # follows from the oracle's results and the two rules (swept_step above): both are reported.
+    if not seq:   # the rows outside the band that the two-link sweep computes
+        swept_step = sum(joint_cells_computed(kb) for kb in calls)
     replayed_swept = swept_step
     counted_swept = int(prof.swept_cell_updates) // args.steps if seq and info.seq_path in (1, 2) else None
     if counted_swept is not None:
@@ -422,8 +446,8 @@ def run_solver(args):
     # committed rocprofv3 counter passes of this same command (FETCH_SIZE and WRITE_SIZE scaled
     # by a copy of known size); only for the unmodified workload.
     traffic = traffic_source = None
-    kernel = ("seq_bits_kernel" if (seq and info.seq_path == 4 and calls[0].mode in (0, 2, 5)) else
-              "seq_lds_kernel" if (seq and info.seq_path in (1, 2, 4)) else ("sg_sweep_all" if seq else "jt_sweep_all"))
+    kernel = ("seq_bits_kernel" if by_sums else
+              "seq_lds_kernel" if (seq and info.seq_path in (1, 2, 4)) else ("sg_stream" if seq else "jt_sweep_all"))
     tf = os.path.join(ROOT, "profiles", f"{kernel}_{args.workload}_traffic.txt")
     if plain_run and os.path.exists(tf):
         try:
@@ -454,8 +478,12 @@ def run_solver(args):
         steps=args.steps, warmup=args.warmup, ms_per_step=ms_step, higher_is_better=True, scaling="weak",
         vs_baseline=None, dtype="int32", data="synthetic",
         config=dict(workload=desc,
-                    value_counts="cell-updates the kernels evaluate (cell_updates_swept_per_step); the job as the "
-                                 "oracle performs it holds cell_updates_per_step, see effective_cell_updates_per_s",
+                    value_counts=("cells up to the capacity of the items the sweeps go through (cell_updates_swept_per_step), "
+                                  + ("32 of them an instruction on the bit-set kernels; " if by_sums else
+                                     "of which the streamed sweep computes a band; " if kernel == "sg_stream" else
+                                     "every one evaluated; ")
+                                  + "the job as the oracle performs it holds cell_updates_per_step, see "
+                                    "effective_cell_updates_per_s"),
                     instances_per_step=inst_step, cell_updates_per_step=cells_step,
                     cell_updates_swept_per_step=swept_step,
                     cell_updates_swept_per_step_replayed_from_oracle=replayed_swept if calls[0].mode == 0 else None,
@@ -534,11 +562,9 @@ def main() -> int:
                     help="default workload only: skip the other configurations and the peak calibration "
                          "(profiling runs: keeps the kernel statistics to the headline launches)")
     ap.add_argument("--packed16", action="store_true",
-                    help="value-equals-weight workloads: create the handle with DEFT_FLAG_VALUES_ARE_WEIGHTS "
-                         "(rows of 16-bit cells)")
+                    help="value-equals-weight workloads: create the handle with DEFT_FLAG_VALUES_ARE_WEIGHTS")
     ap.add_argument("--subset-sum", action="store_true",
-                    help="value-equals-weight workloads: create the handle with DEFT_FLAG_SUBSET_SUM (bit-set "
-                         "rows, one wavefront per instance)")
+                    help="value-equals-weight workloads: create the handle with DEFT_FLAG_SUBSET_SUM")
     ap.add_argument("--max-stages", type=int, default=0, help="clamp n_knapsacks (debug only)")
     ap.add_argument("--only-k", type=int, default=0, help="keep only the call with this k (debug only)")
     args = ap.parse_args()
@@ -563,16 +589,14 @@ def main() -> int:
                             ("vgg19", {}), ("gpt2", {}), ("hetero", {}), ("backward", {}), ("inflation", {}),
                             ("schedule", {}),
                             # the value-equals-weight workloads again on handles created with
-                            # DEFT_FLAG_VALUES_ARE_WEIGHTS (rows of 16-bit cells), priced on their own roofline
-                            # (4 LDS bytes per cell instead of 8)
+                            # DEFT_FLAG_VALUES_ARE_WEIGHTS: the bit-set kernels alone, no look at the values left over
                             ("resnet101_rows16", dict(workload="resnet101", packed16=True)),
                             ("resnet101_one_call_per_k_rows16", dict(workload="resnet101", per_k_calls=True, packed16=True)),
                             ("vgg19_rows16", dict(workload="vgg19", packed16=True)),
                             ("backward_rows16", dict(workload="backward", packed16=True)),
                             ("inflation_rows16", dict(workload="inflation", packed16=True)),
                             ("schedule_rows16", dict(workload="schedule", packed16=True)),
-                            # the value-equals-weight workloads on handles created with DEFT_FLAG_SUBSET_SUM
-                            # (bit-set rows, one wavefront per instance)
+                            # and on handles created with DEFT_FLAG_SUBSET_SUM: the same kernels
                             ("resnet101_bitset", dict(workload="resnet101", subset_sum=True)),
                             ("resnet101_one_call_per_k_bitset", dict(workload="resnet101", per_k_calls=True, subset_sum=True)),
                             ("vgg19_bitset", dict(workload="vgg19", subset_sum=True)),
