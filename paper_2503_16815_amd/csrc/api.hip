@@ -288,10 +288,10 @@ extern "C" deft_status_t deft_knapsack_solve_batch(deft_knapsack_t *h, const def
     // A plain handle's instances may still have values equal to weights: the bit-set kernels answer those
     // (measured on 4096 ResNet-101-shaped schedules: 0.100 ms, rows of values 1.66 ms) and the rows take
     // what is left.  Where none qualifies that is a launch for nothing, 2.2 us for one instance and 4 us
-    // for four thousand, which a call of a few short instances would notice (one of 32 items at
-    // capacity 1000: 19.4 us on the rows alone; values equal to weights save it 9 us): those go to the
-    // rows at once.
-    const bool small = b->batch < 64 && (int64_t)b->item_stride * h->cfg.max_capacity < (1 << 17);
+    // for four thousand, which a call of short instances would notice (one of 32 items at capacity
+    // 1000: 19.4 us on the rows alone; 909 of 43 items at capacity 820, unrelated values: 32.5 us on the rows
+    // alone, 35.1 us with the look): fewer than 1024 of those go to the rows at once.
+    const bool small = b->batch < 1024 && (int64_t)b->item_stride * h->cfg.max_capacity < (1 << 17);
     const bool by_sums = (b->mode == DEFT_MODE_SEQUENTIAL || probing) && h->bits_ready &&
                          (h->promised || (h->left && !small));
     if (by_sums) {
