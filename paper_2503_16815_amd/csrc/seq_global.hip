@@ -18,10 +18,10 @@
 // last level stores to global memory, in place, behind the loads, and one wavefront keeps the loads
 // of level 0 two or three blocks ahead.  The levels work on different blocks, so one barrier per step
 // is all the ordering there is, and a step is one task of 512 cells for each of up to fifteen
-// wavefronts.  The shifted operand of an item of at least a block's weight lies in blocks that have long
-// been complete: it is read one step ahead, behind the barrier's wait.  A cell-update costs 8 / levels + 1/8
-// bytes of global traffic, 12 bytes of LDS, four vector instructions and a share of about
-// twenty vector and forty scalar instructions per task.
+// wavefronts.  The shifted operand of an item of at least a block's weight lies in blocks that were
+// complete a step ago: it is read one step ahead, while the step's own cells are computed.  A cell-update
+// costs 8 / levels + 1/8 bytes of global traffic, 12 bytes of LDS, four vector instructions and a share
+// of about thirty vector and forty scalar instructions per task.
 // Measured on the GPT-2 shape (256 instances, C = 381000, one window swept): 2.36 ms, with nine
 // instances 2.19 ms; one persistent workgroup per instance over all cells up to C, three items per pass,
 // and launches of their own for lists and walks took 11.5 ms, one launch per item 3.55 ms.  What bounds
@@ -260,7 +260,8 @@ constexpr PassShape kShapes[] = {{7, 1024, 3}, {6, 1024, 3}, {5, 1536, 2}, {5, 1
 constexpr int kNumShapes = sizeof(kShapes) / sizeof(kShapes[0]);
 
 // Block hand-over: the loading wavefront arrives when the block that the next step reads has landed,
-// a computing one when its LDS accesses have; its stores stay in flight until the end of the pass.
+// a computing one when its LDS accesses have (the ones for its next step included: what they read may be
+// overwritten behind the barrier); its stores stay in flight until the end of the pass.
 // Asm, because the compiler puts a wait for all vector memory in front of every barrier it
 // knows of once a kernel has LDS-direct loads.
 __device__ __forceinline__ void step_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
@@ -317,39 +318,49 @@ struct StreamTask {
     int c, at;         // the task's first cell at the level's first step, and its place in the rings
     int first;         // the level's first step
 };
-// AHEAD: the item weighs at least a block, so that the next step's shifted operand is complete and is
-// read before this step's barrier.  LAST: the level stores to the row.
+// AHEAD: the item weighs at least a block, so that the next step's shifted operand is complete when this
+// step begins and is read then; it has arrived by the step's barrier.  (Read behind the stores instead: 2.39 ms
+// on the GPT-2 shape, 2.30 so.)  LAST: the level stores to the row.
+// Why a ring is long enough: while block b is computed from it, cells from b R - w (AHEAD: (b + 1) R - w,
+// at most b R) are read, and block b + 1 is written, up to cell (b + 2) R (level 0: up to
+// (b + 1 + ahead) R).  That is w + 2 R cells and, AHEAD, w + R (level 0: ahead - 1 blocks more).
+// (AHEAD reads the operand of a level's first block beside that of its second; it lies below the band.)
 template <bool AHEAD, bool LAST>
 __device__ __forceinline__ void stream_task(const StreamTask &k, int R, int steps, int lane)
 {
     int p = k.at, po = k.at, c0 = k.c;
-    int shd[kTaskSlots];
-    auto read_shifted = [&](int at) {
+    int shd[kTaskSlots], nxt[kTaskSlots];
+    auto read_shifted = [&](int at, int (&to)[kTaskSlots]) {
         int from = at - k.w;
         if (from < 0) from += k.len;
         if (from + kTaskCells <= k.len) {
             const int32_t *s = k.rg + from + lane;
 #pragma unroll
-            for (int x = 0; x < kTaskSlots; ++x) shd[x] = s[x * 64];
+            for (int x = 0; x < kTaskSlots; ++x) to[x] = s[x * 64];
         } else {
 #pragma unroll
             for (int x = 0; x < kTaskSlots; ++x) {
                 const unsigned o = (unsigned)(from + lane + x * 64);
-                shd[x] = k.rg[min(o, o - (unsigned)k.len)];  // wraps past the ring's end
+                to[x] = k.rg[min(o, o - (unsigned)k.len)];  // wraps past the ring's end
             }
         }
     };
     step_barrier();
     for (int t = 0; t < k.first; ++t) step_barrier();
-    if (AHEAD) read_shifted(p);
+    if (AHEAD) read_shifted(p, shd);
     for (int t = k.first; t < steps; ++t) {
         const bool here = c0 <= k.top && c0 + kTaskCells > k.low;
+        int own[kTaskSlots];
         if (here) {
-            int own[kTaskSlots];
             const int32_t *s = k.rg + p + lane;
 #pragma unroll
             for (int x = 0; x < kTaskSlots; ++x) own[x] = s[x * 64];
-            if (!AHEAD) read_shifted(p);
+            if (!AHEAD) read_shifted(p, shd);
+        }
+        p += R;
+        if (p >= k.len) p -= k.len;
+        if (AHEAD) read_shifted(p, nxt);
+        if (here) {
             if (c0 < k.w) {
 #pragma unroll
                 for (int x = 0; x < kTaskSlots; ++x)
@@ -366,16 +377,12 @@ __device__ __forceinline__ void stream_task(const StreamTask &k, int R, int step
             k.keep[(size_t)(c0 >> 9) << 6] = (uint8_t)bits;
         }
         c0 += R;
-        p += R;
-        if (p >= k.len) p -= k.len;
         po += R;
         if (po >= k.len_out) po -= k.len_out;
+        step_barrier();
         if (AHEAD) {
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (what the step wrote)
-            read_shifted(p);
-            asm volatile("s_barrier" ::: "memory");
-        } else {
-            step_barrier();
+#pragma unroll
+            for (int x = 0; x < kTaskSlots; ++x) shd[x] = nxt[x];
         }
     }
 }
@@ -491,7 +498,7 @@ sg_stream(BatchArgs a, StreamItem *lists, int32_t *rows, uint8_t *keep, int row_
 #pragma unroll
             for (int x = kNumShapes - 1; x >= 0; --x) {  // the first shape that fits
                 // a ring: w cells back from the block being written, and one more block where the
-                // shifted operand is not read a step ahead
+                // shifted operand is not read a step ahead (see stream_task)
                 int need = (kShapes[x].ahead - 1) * kShapes[x].block;
                 for (int l = 0; l < kShapes[x].levels; ++l)
                     need += __builtin_amdgcn_readlane(room, l) + (__builtin_amdgcn_readlane(it.w, l) >= kShapes[x].block ? 1 : 2) * kShapes[x].block;
