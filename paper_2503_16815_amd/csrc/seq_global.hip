@@ -489,7 +489,9 @@ sg_stream(BatchArgs a, StreamItem *lists, int32_t *rows, uint8_t *keep, int row_
         auto top = [&](long long upto) { return (int)min((long long)C, upto); };
         auto bottom = [&](long long upto) { return (int)max(0ll, C_min - (weight_all - upto)); };
         long long before = 0;  // weight of the items gone through
-        for (int q = 0; q < cnt;) {
+        // (a capacity sweep whose every capacity holds the whole list has no band: the walks below never
+        // meet a cell that is not known)
+        for (int q = weight_all <= C_min ? cnt : 0; q < cnt;) {
             StreamItem it{};
             if (lane < kMaxLevels && q + lane < cnt) it = load_item(list + q + lane);
             const int room = (it.w + kTaskCells - 1) / kTaskCells * kTaskCells;

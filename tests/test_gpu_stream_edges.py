@@ -49,3 +49,24 @@ def test_capacity_sweeps(binding, oracle):
     for seed, w_hi in ((1, 2000), (2, 9000), (3, 30000)):
         kb = _batch(45000 + seed, 5, 25, lambda r, s: r.integers(1, w_hi, size=s), caps, W.MODE_CAPACITY_SWEEP)
         run(binding, oracle, kb, max_capacity=70000)
+
+
+@pytest.mark.parametrize("n", [1, 6, 7, 12, 40])
+@pytest.mark.parametrize("over", [-1, 0, 1, 5000])
+def test_capacity_sweeps_whose_every_capacity_is_near_or_beyond_the_weight(binding, oracle, n, over):
+    """The least capacity one short of the list's weight, the weight itself, and beyond: from the
+    weight on there is no row to sweep, and no row cell is counted."""
+    import torch
+    weight = 50000 // n * n
+    kb = _batch(46000 + n, 4, n, lambda r, s: np.full(s, weight // n), [weight + over + 9000, weight + over, weight + over + 1],
+                W.MODE_CAPACITY_SWEEP)
+    kb.weights[:, 0] += 2 * (n > 1)
+    kb.weights[:, -1] -= 2 * (n > 1)
+    run(binding, oracle, kb, max_capacity=70000)
+    with binding.DeftKnapsack(max_batch=kb.batch, max_items=kb.item_stride, max_knapsacks=kb.knap_stride, max_capacity=70000) as h:
+        db = h.upload(kb)
+        h.set_profiling(True)
+        h.solve_batch(db)
+        torch.cuda.synchronize()
+        cells = int(h.get_profile().streamed_row_cells)
+    assert cells == 0 if over >= 0 else 0 < cells <= 4 * n * 2 * (weight + 1), cells
