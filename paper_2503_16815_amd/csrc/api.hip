@@ -192,20 +192,19 @@ extern "C" deft_status_t deft_knapsack_create(const deft_knapsack_config_t *cfg,
         } else {
             (void)hipGetLastError();
             h->seq_path = 3;
-            seq_global_plan(cfg->max_capacity, cfg->max_items, cfg->max_batch, lds_wg, &h->glob_plan);
-            if (seq_global_prepare(h->glob_plan) != hipSuccess) {
+            seq_global_plan(cfg->max_capacity, cfg->max_items, cfg->max_batch, lds_wg, h->compute_units, &h->glob_plan);
+            if (!h->promised) st = alloc(&h->glob_scratch, h->glob_plan.scratch_bytes, &h->scratch_bytes);
+            if (st == DEFT_OK && !h->promised && seq_global_prepare(h->glob_plan, h->glob_scratch) != hipSuccess) {
                 (void)hipGetLastError();
                 st = DEFT_ERR_DEVICE;
-            } else {
-                if (!h->promised) st = alloc(&h->glob_scratch, h->glob_plan.scratch_bytes, &h->scratch_bytes);
-                if (st == DEFT_OK) {
-                    void *c = nullptr;
-                    st = alloc(&c, 8, &h->scratch_bytes);
-                    h->glob_streamed = static_cast<unsigned long long *>(c);
-                    if (st == DEFT_OK && hipMemset(c, 0, 8) != hipSuccess) {
-                        (void)hipGetLastError();
-                        st = DEFT_ERR_DEVICE;
-                    }
+            }
+            if (st == DEFT_OK) {
+                void *c = nullptr;
+                st = alloc(&c, 8, &h->scratch_bytes);
+                h->glob_streamed = static_cast<unsigned long long *>(c);
+                if (st == DEFT_OK && hipMemset(c, 0, 8) != hipSuccess) {
+                    (void)hipGetLastError();
+                    st = DEFT_ERR_DEVICE;
                 }
             }
         }

@@ -116,7 +116,8 @@ private:
 
 // ---- sequential mode, rows in global memory (seq_global.hip) -------------------
 // For capacities whose row does not fit LDS: the row streams through LDS rings, several items per
-// pass, one workgroup per instance (Algorithm 1: one launch per item, rows in two buffers).
+// pass, one workgroup per instance, which idle compute units help where instances are few (Algorithm 1:
+// one launch per item, rows in two buffers).
 struct SeqGlobalPlan {
     int32_t threads, cells_per_thread;  // of the launch per item
     int32_t row_len;           // int32 cells per row buffer (multiple of the tile)
@@ -124,11 +125,13 @@ struct SeqGlobalPlan {
     int32_t max_items, max_batch;
     int32_t ring_cells;        // streamed sweep: cells of its rings in LDS
     int32_t lds_bytes;         // its dynamic LDS
+    int32_t compute_units;
     int64_t scratch_bytes;     // rows + keep + item lists + per-instance state
 };
 void seq_global_plan(int32_t max_capacity, int32_t max_items, int32_t max_batch, int32_t lds_per_wg_bytes,
-                     SeqGlobalPlan *plan);
-hipError_t seq_global_prepare(const SeqGlobalPlan &plan);
+                     int32_t compute_units, SeqGlobalPlan *plan);
+// Sets the kernels' dynamic-LDS attribute and clears what calls expect cleared in the scratch.
+hipError_t seq_global_prepare(const SeqGlobalPlan &plan, void *scratch);
 // `streamed_cells` (device, may be null): the streamed sweep adds the row cells it reads and writes.
 hipError_t seq_global_launch(const SeqGlobalPlan &plan, const BatchArgs &args, void *scratch,
                              hipStream_t stream, Profiler *prof, unsigned long long *streamed_cells);

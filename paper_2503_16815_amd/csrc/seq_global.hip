@@ -28,6 +28,25 @@
 // it: a step is read, compute, write, barrier for all wavefronts at once (about 1850 cycles for fourteen
 // tasks, of which the vector units are busy 740 and LDS 680).
 //
+// Teams.  A batch of at most half as many instances as there are compute units, on rows of 131072 cells or
+// more, is launched with helpers: workgroups behind the batch's own, as many per instance as fill the chip.
+// An instance's own workgroup (the owner) runs everything above; where that is expected to be quicker
+// (kTeamJobNs and its like) it cuts the next item's band into tiles instead, every workgroup of the team
+// takes some, both operands straight from global memory, from one row buffer into the other, and the owner
+// waits for the tiles that helpers took.  Nobody waits for a workgroup that has not begun: a tile is
+// asked for by whoever is there (the owner would do them all), an owner waits only for helpers that are at a
+// tile, and a helper waits only for an owner that has begun, else it leaves after a few
+// milliseconds.  So no order or number of workgroups on the chip, another team's included, can hold one up.
+// The helpers hold their compute units until the owner dismisses them: before its last walk, or at
+// once where no window of the instance is that long.
+// Row cells go out as device-scope stores, which leave nothing in an XCD's L2 for the release to write
+// back (2000000 cells, 4 instances of 148 items: 3.06 ms, with plain stores 3.56); counters
+// are striped (see TeamStripe; one instance of that: 2.24 ms, one counter for all 3.40).
+// Measured, 148 items in two windows, lists twice the first window: one instance of 381000 cells 1.33 ms,
+// alone 3.68, a launch per item over all compute units 3.26; 2000000 cells 2.24, 34.5 and 3.63 ms; sixteen of
+// 381000 cells 2.37, 3.82 and 4.17 ms; lists that barely exceed the window, one of 160000 cells: 0.59, 0.58
+// and 2.00 ms.  A call with nothing to sweep pays 3 to 5 us for its helpers.
+//
 // Algorithm 1 reads a cell of every intermediate row, so it takes sweeps that leave each of them in
 // global memory: one launch per offered-item rank, two row buffers, the row cut into tiles over
 // many workgroups (sg_sweep), keep bits by wavefront ballots.
@@ -60,6 +79,23 @@ struct alignas(8) StreamItem {
     int32_t index, pad;
 };
 
+// What the workgroups of a team tell each other (see the head of this file).  Every access is an atomic one
+// of the whole device.  A team of some size has kTeamStripes counters of each kind, a cache line to itself,
+// with every kTeamStripes-th tile and workgroup: 255 workgroups at one address wait 20 ns for each other.
+constexpr int kTeamStripes = 8;
+struct alignas(128) TeamStripe {
+    // 0: the owner has not begun.  Else the tiles of the job in the upper half (none: there is no job)
+    // and how often a tile was asked for in the lower; kTeamOver: there will be no more jobs.
+    unsigned long long ticket;
+    uint32_t done;  // tiles that helpers have finished, all jobs
+    uint32_t gone;  // workgroups that have left the team
+};
+struct alignas(128) TeamJob {
+    TeamStripe stripe[kTeamStripes];
+    uint32_t word[8];  // the job: w, v, low, top, top_in, q, buffer read, tasks per wavefront and tile
+    uint32_t gone;     // stripes whose workgroups have all left; the last one leaves all at 0 for the next call
+};
+
 struct Scratch {
     int32_t *rows;      // [batch][2][row_len]
     uint64_t *keep;     // [batch][max_items][keep_words]
@@ -67,6 +103,7 @@ struct Scratch {
     int32_t *probe;     // [batch][max_items]  Algorithm 1: remaining time of the level that ends before entry q
     InstState *state;   // [batch]
     StreamItem *items;  // [batch][max_items]  the streamed sweep's lists
+    TeamJob *jobs;      // [batch]  the streamed sweep's teams
 };
 
 __host__ __device__ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -86,6 +123,8 @@ Scratch carve(const SeqGlobalPlan &p, void *base, int32_t max_batch)
     s.state = reinterpret_cast<InstState *>(c);
     c += align256((size_t)max_batch * sizeof(InstState));
     s.items = reinterpret_cast<StreamItem *>(c);
+    c += align256((size_t)max_batch * p.max_items * sizeof(StreamItem));
+    s.jobs = reinterpret_cast<TeamJob *>(c);
     return s;
 }
 
@@ -233,6 +272,18 @@ constexpr int kStreamWaves = kStreamThreads / 64;  // the last one moves old cel
 constexpr int kTaskCells = 512;       // what a wavefront computes at a time: eight cells per lane
 constexpr int kTaskSlots = kTaskCells / 64;
 constexpr int kMaxLevels = 7;         // items per pass over the row
+// Teams: a job is cut into tiles of one task per wavefront.
+constexpr int kTeamCells = kStreamWaves * kTaskCells;
+// Instances of shorter rows do without: on 80000 cells a team gained a tenth on lists of 12 items and cost
+// every other call its 3 to 7 us.
+constexpr int kTeamMinCells = 1 << 17;
+constexpr int kTeamStartPolls = 1 << 12;     // how often a helper looks for an owner that has not begun
+constexpr unsigned long long kTeamOver = 1ull << 63;
+// What is expected, in ns, of a job (besides its tiles), of a task of every wavefront of the team, of a step of
+// a pass and of a step of an item too heavy for the rings.  All items by the team or none (148 items, two
+// windows, lists twice the first window): one instance of 160000 cells 1.52 and 1.58 ms, by this
+// estimate 1.25; 64 of them 3.13 and 1.70, so 1.67; one of 381000 1.72 and 3.67, so 1.33.
+constexpr int kTeamJobNs = 5000, kTeamTileNs = 2500, kStepNs = 780, kHeavyStepNs = 1400;
 constexpr int kMiscBytes = 1024;      // LDS in front of the rings: StreamShared and the placed-item bits
 
 typedef __attribute__((address_space(3))) int32_t lds_i32;
@@ -243,6 +294,8 @@ struct StreamShared {
     int64_t weight;            // of the whole list
     int32_t value;             // of the whole list
     int32_t settled;
+    unsigned long long ticket;  // of the team's job
+    int32_t job[8], stripe;
     uint32_t placed[kMaxItemsPlaced / 32];
 };
 static_assert(sizeof(StreamShared) <= kMiscBytes, "fits in front of the rings");
@@ -387,20 +440,212 @@ __device__ __forceinline__ void stream_task(const StreamTask &k, int R, int step
     }
 }
 
-// All stages of one instance (see the head of this file).
+// ---- teams ----
+template <class T>
+__device__ __forceinline__ T team_load(const T *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <class T>
+__device__ __forceinline__ void team_store(T *p, T x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// One item's cells of the task at c0, both operands from global memory: `src` holds the row before
+// the item up to cell top_in, all cells above it are 0.
+template <bool SHARED = false>
+__device__ __forceinline__ void row_task(const int32_t *src, int32_t *dst, uint8_t *keep, int c0, int w, int v, int top_in, int lane)
+{
+    int own[kTaskSlots], shd[kTaskSlots];
+#pragma unroll
+    for (int k = 0; k < kTaskSlots; ++k) {
+        const int c = c0 + k * 64 + lane;
+        own[k] = c <= top_in ? src[c] : 0;
+        shd[k] = c < w ? INT_MAX : c - w <= top_in ? src[c - w] : 0;
+    }
+    uint32_t bits = 0;
+#pragma unroll
+    for (int k = 0; k < kTaskSlots; ++k) {
+        const int passed = (int)((uint32_t)own[k] + (uint32_t)v);
+        bits = shift_in_less(bits, shd[k], passed);
+        if (SHARED) team_store(&dst[c0 + k * 64 + lane], min(passed, shd[k]));
+        else dst[c0 + k * 64 + lane] = min(passed, shd[k]);
+    }
+    keep[keep_byte(c0) + lane] = (uint8_t)bits;
+}
+
+__device__ __forceinline__ uint32_t team_count(uint32_t *p)
+{
+    return __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long team_ask(TeamStripe *s)
+{
+    return __hip_atomic_fetch_add(&s->ticket, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// (of helpers + 1 workgroups, the owner being number 0)
+__device__ __forceinline__ int team_stripes(int helpers) { return helpers >= 4 * kTeamStripes ? kTeamStripes : 1; }
+// How many of 0 .. n - 1 are stripe s's.
+__device__ __forceinline__ int striped(int n, int s, int stripes) { return (n - s + stripes - 1) / stripes; }
+__device__ __forceinline__ uint32_t ticket_tiles(unsigned long long t) { return (uint32_t)(t >> 32); }
+__device__ __forceinline__ uint32_t ticket_number(unsigned long long t) { return (uint32_t)t; }
+
+// Tile `tile` of a job, by the whole workgroup; returns when its stores have been made.
+__device__ __forceinline__ void team_tile(int32_t *buffers, int row_len, uint8_t *kp, size_t keep_row, const int32_t *job, int tile,
+                                          int wave, int lane)
+{
+    int j[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) j[i] = __builtin_amdgcn_readfirstlane(job[i]);
+    const int low = j[2], top = j[3], span = j[7];
+    const int32_t *src = buffers + (size_t)j[6] * row_len;
+    int32_t *dst = buffers + (size_t)(j[6] ^ 1) * row_len;
+    int c0 = low / kTeamCells * kTeamCells + __builtin_amdgcn_readfirstlane(tile) * span * kTeamCells + wave * kTaskCells;
+#pragma unroll 1
+    for (int x = 0; x < span; ++x, c0 += kTeamCells)
+        if (c0 <= top && c0 + kTaskCells > low) row_task<true>(src, dst, kp + (size_t)j[5] * keep_row, c0, j[0], j[1], j[4], lane);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+}
+
+// Workgroup `number` will not look at the team's words again.
+__device__ __forceinline__ void team_leave(TeamJob *job, int number, int helpers)
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (what it has said itself)
+    const int stripes = team_stripes(helpers), s = number % stripes;
+    if (team_count(&job->stripe[s].gone) + 1 != (uint32_t)striped(helpers + 1, s, stripes)) return;
+    if (team_count(&job->gone) + 1 != (uint32_t)stripes) return;
+    for (int i = 0; i < stripes; ++i) {
+        team_store(&job->stripe[i].ticket, 0ull);
+        team_store(&job->stripe[i].done, 0u);
+        team_store(&job->stripe[i].gone, 0u);
+    }
+    team_store(&job->gone, 0u);
+}
+
+// A helper: takes tiles of the instance's jobs until there are no more, or leaves if the instance's owner
+// does not begin.
+__device__ __forceinline__ void team_help(StreamShared *sh, TeamJob *job, int number, int helpers, int32_t *buffers, int row_len,
+                                          uint8_t *kp, size_t keep_row, int wave, int lane)
+{
+    const int stripes = team_stripes(helpers), s = number % stripes;
+    TeamStripe *mine = &job->stripe[s];
+    while (true) {
+        if (wave == 0) {
+            unsigned long long t = kTeamOver;
+            if (lane == 0) {
+                for (int polls = 0; polls < kTeamStartPolls;) {
+                    t = team_load(&mine->ticket);
+                    if (t == 0) ++polls;
+                    if (t >> 63) break;
+                    // (the first of a stripe for its first tile, and so on; the others would only stand in the way)
+                    if (ticket_number(t) < ticket_tiles(t) && (uint32_t)(number / stripes) < ticket_tiles(t)) {
+                        t = team_ask(mine);
+                        if (t >> 63 || ticket_number(t) < ticket_tiles(t)) break;
+                    }
+                    __builtin_amdgcn_s_sleep(2);
+                    t = kTeamOver;
+                }
+                sh->ticket = t;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            if (lane < 8) sh->job[lane] = (int)team_load(&job->word[lane]);
+        }
+        __syncthreads();
+        const unsigned long long t = sh->ticket;
+        if (t >> 63) {
+            if (threadIdx.x == 0) team_leave(job, number, helpers);
+            return;
+        }
+        team_tile(buffers, row_len, kp, keep_row, sh->job, (int)ticket_number(t) * stripes + s, wave, lane);
+        if (threadIdx.x == 0) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            team_count(&mine->done);
+        }
+    }
+}
+
+// The owner says the same to every stripe.
+__device__ __forceinline__ void team_tell(TeamJob *job, int helpers, unsigned long long ticket)
+{
+    if ((int)threadIdx.x < team_stripes(helpers)) team_store(&job->stripe[threadIdx.x].ticket, ticket);
+}
+
+// The owner: one item as a job of `tiles` tiles.  `done`, lane x of the first wavefront: the tiles of
+// stripe x that helpers took, all jobs.
+__device__ __forceinline__ void team_lead(StreamShared *sh, TeamJob *job, int helpers, const int (&words)[8], int tiles, uint32_t &done,
+                                          int32_t *buffers, int row_len, uint8_t *kp, size_t keep_row, int wave, int lane)
+{
+    const int stripes = team_stripes(helpers);
+    const bool counts = wave == 0 && lane < stripes;
+    if (wave == 0) {
+        if (lane == 0) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                sh->job[i] = words[i];
+                team_store(&job->word[i], (uint32_t)words[i]);
+            }
+        }
+        // (the row as the workgroup has left it, too: a barrier lies behind the stores)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        if (counts) {
+            const int part = striped(tiles, lane, stripes);
+            team_store(&job->stripe[lane].ticket, (unsigned long long)part << 32 | (part > 0 ? 0u : 1u));
+            done += part;
+        }
+    }
+    // The first tile, then whatever no helper has asked for.
+    int s = 0;
+    while (s >= 0) {
+        if (threadIdx.x == 0) sh->ticket = team_ask(&job->stripe[s]);
+        __syncthreads();
+        const unsigned long long t = sh->ticket;
+        if (ticket_number(t) < ticket_tiles(t)) {
+            if (wave == 0 && lane == s) --done;
+            team_tile(buffers, row_len, kp, keep_row, sh->job, (int)ticket_number(t) * stripes + s, wave, lane);
+        }
+        if (wave == 0) {
+            const unsigned long long left = counts ? team_load(&job->stripe[lane].ticket) : 0ull;
+            const unsigned long long open = __ballot(counts && ticket_number(left) < ticket_tiles(left));
+            if (lane == 0) sh->stripe = open ? __builtin_ctzll(open) : -1;
+        }
+        __syncthreads();
+        s = sh->stripe;
+    }
+    if (wave == 0) {
+        while (__ballot(counts && team_load(&job->stripe[lane].done) != done) != 0ull) __builtin_amdgcn_s_sleep(1);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    }
+    __syncthreads();
+}
+
+// All stages of one instance (see the head of this file), with the `helpers` workgroups of each instance behind the batch's own.
+template <bool TEAMS>
 __global__ void __launch_bounds__(kStreamThreads)
-sg_stream(BatchArgs a, StreamItem *lists, int32_t *rows, uint8_t *keep, int row_len, int max_items, int ring_cells,
-          unsigned long long *streamed_cells)
+sg_stream(BatchArgs a, StreamItem *lists, int32_t *rows, uint8_t *keep, TeamJob *jobs, int helpers, int row_len, int max_items,
+          int ring_cells, unsigned long long *streamed_cells)
 {
     extern __shared__ __align__(16) char lds_stream[];
     StreamShared *sh = reinterpret_cast<StreamShared *>(lds_stream);
     int32_t *ring = reinterpret_cast<int32_t *>(lds_stream + kMiscBytes);
-    const int inst = blockIdx.x;
+    const int inst = TEAMS ? blockIdx.x % a.batch : blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int32_t *buffers = rows + (size_t)inst * 2 * row_len;
+    uint8_t *kp = keep + (size_t)inst * max_items * (row_len / 8);
+    const size_t keep_row = row_len / 8;
+    TeamJob *job = jobs + inst;
+    if (TEAMS && (int)blockIdx.x >= a.batch) {
+        team_help(sh, job, blockIdx.x / a.batch, helpers, buffers, row_len, kp, keep_row, wave, lane);
+        return;
+    }
     const int status = check_instance(a, inst, false);
     clear_outputs(a, inst, status);
-    if (status != DEFT_OK) return;
+    // (may be said twice; the owner leaves at the very end)
+    bool team = TEAMS;
+    auto dismiss = [&]() {
+        if (team) team_tell(job, helpers, kTeamOver);
+        team = false;
+    };
+    if (status != DEFT_OK) {
+        dismiss();
+        if (TEAMS && tid == 0) team_leave(job, 0, helpers);
+        return;
+    }
 
     const int n = a.n_items[inst], m = a.n_knapsacks[inst];
     const int32_t *W = a.weights + (size_t)inst * a.item_stride;
@@ -410,9 +655,8 @@ sg_stream(BatchArgs a, StreamItem *lists, int32_t *rows, uint8_t *keep, int row_
     int32_t *out_kv = a.knap_value + (size_t)inst * a.knap_stride;
     int32_t *out_kl = a.knap_load + (size_t)inst * a.knap_stride;
     StreamItem *list = lists + (size_t)inst * max_items;
-    int32_t *row = rows + (size_t)inst * 2 * row_len;
-    uint8_t *kp = keep + (size_t)inst * max_items * (row_len / 8);
-    const size_t keep_row = row_len / 8;
+    int cur = 0;  // the buffer that holds the row
+    uint32_t done = 0;
     const bool caps_sweep = a.mode == DEFT_MODE_CAPACITY_SWEEP;
     for (int i = tid; i < kMaxItemsPlaced / 32; i += kStreamThreads) sh->placed[i] = 0;
     __syncthreads();
@@ -420,6 +664,12 @@ sg_stream(BatchArgs a, StreamItem *lists, int32_t *rows, uint8_t *keep, int row_
     long long total = 0;
     unsigned long long streamed = 0;
     const int stages = caps_sweep ? min(m, 1) : m;
+    if (team) {
+        int most = 0;
+        for (int x = 0; x < m; ++x) most = max(most, cap[x]);
+        if (most < kTeamMinCells) dismiss();
+        else team_tell(job, helpers, 1ull);  // (begun)
+    }
     for (int s = 0; s < stages; ++s) {
         // ---- the stage's list, built by the first wavefront ------------------------------
         if (wave == 0) {
@@ -507,6 +757,27 @@ sg_stream(BatchArgs a, StreamItem *lists, int32_t *rows, uint8_t *keep, int row_
                 if (kShapes[x].levels <= left && need <= ring_cells) g = kShapes[x].levels, R = kShapes[x].block, ahead = kShapes[x].ahead;
             }
             const int U_in = top(before), L_in = bottom(before);
+            int32_t *row = buffers + (size_t)cur * row_len;
+            if (team) {
+                // ---- one item by the team, where that is expected to be quicker than the owner alone
+                const int w = __builtin_amdgcn_readlane(it.w, 0), v = __builtin_amdgcn_readlane(it.v, 0);
+                const int U = top(before + w), L = bottom(before + w);
+                // as many tiles as the team has workgroups, or fewer
+                const int span = (U / kTeamCells - L / kTeamCells + 1 + helpers) / (helpers + 1);
+                const int tiles = (U / kTeamCells - L / kTeamCells) / span + 1;
+                const int together = kTeamJobNs + span * kTeamTileNs;
+                const int alone = g == 0 ? ((U - L) / (kStreamWaves * 2 * kTaskCells) + 1) * kHeavyStepNs
+                                         : ((U - L) / R + g) * kStepNs / g;
+                if (together < alone) {
+                    const int words[8] = {w, v, L, U, q > 0 ? U_in : -1, q, cur, span};
+                    team_lead(sh, job, helpers, words, tiles, done, buffers, row_len, kp, keep_row, wave, lane);
+                    cur ^= 1;
+                    streamed += (unsigned)(U_in - L_in + U - L + 2);
+                    before += w;
+                    q += 1;
+                    continue;
+                }
+            }
             if (g == 0) {
                 // ---- one item too heavy for the rings: in place, both operands from global memory,
                 // from the top down in steps of at most its weight (a step's shifted operands lie
@@ -519,21 +790,7 @@ sg_stream(BatchArgs a, StreamItem *lists, int32_t *rows, uint8_t *keep, int row_
                     for (int x = 0; x < 2; ++x) {
                         const int c0 = hi + (wave * 2 + x) * kTaskCells;
                         if (c0 > U || c0 + kTaskCells <= L) continue;
-                        int own[kTaskSlots], shd[kTaskSlots];
-#pragma unroll
-                        for (int k = 0; k < kTaskSlots; ++k) {
-                            const int c = c0 + k * 64 + lane;
-                            own[k] = q > 0 && c <= U_in ? row[c] : 0;
-                            shd[k] = c < w ? INT_MAX : q > 0 && c - w <= U_in ? row[c - w] : 0;
-                        }
-                        uint32_t bits = 0;
-#pragma unroll
-                        for (int k = 0; k < kTaskSlots; ++k) {
-                            const int passed = (int)((uint32_t)own[k] + (uint32_t)v);
-                            bits = shift_in_less(bits, shd[k], passed);
-                            row[c0 + k * 64 + lane] = min(passed, shd[k]);
-                        }
-                        kp[(size_t)q * keep_row + keep_byte(c0) + lane] = (uint8_t)bits;
+                        row_task(row, row, kp + (size_t)q * keep_row, c0, w, v, q > 0 ? U_in : -1, lane);
                     }
                     __threadfence_block();
                     __syncthreads();
@@ -649,7 +906,10 @@ sg_stream(BatchArgs a, StreamItem *lists, int32_t *rows, uint8_t *keep, int row_
             __syncthreads();
         }
 
+        if (TEAMS && s + 1 == stages) team_tell(job, helpers, kTeamOver);
+
         // ---- the value and the walk ------------------------------------------------------
+        const int32_t *row = buffers + (size_t)cur * row_len;
         // From (last item, c) down the list: item q is taken where its keep bit is set at the capacity left,
         // and without a look once everything up to it fits.  A chain of dependent loads, so six
         // steps are taken per memory round trip: lane L in [2^d, 2^(d+1)) assumes the decisions
@@ -736,17 +996,20 @@ sg_stream(BatchArgs a, StreamItem *lists, int32_t *rows, uint8_t *keep, int row_
         }
         __syncthreads();
     }
+    dismiss();
     if (tid == 0) {
         a.total_value[inst] = total;
         if (streamed_cells) atomicAdd(streamed_cells, streamed);
+        if (TEAMS) team_leave(job, 0, helpers);
     }
 }
 
 }  // namespace
 
 void seq_global_plan(int32_t max_capacity, int32_t max_items, int32_t max_batch, int32_t lds_per_wg_bytes,
-                     SeqGlobalPlan *p)
+                     int32_t compute_units, SeqGlobalPlan *p)
 {
+    p->compute_units = compute_units;
     p->threads = kThreads;
     p->cells_per_thread = kIter;
     // (check_instance keeps a few words of its own in LDS)
@@ -761,14 +1024,22 @@ void seq_global_plan(int32_t max_capacity, int32_t max_items, int32_t max_batch,
                                  align256((size_t)max_batch * max_items * p->keep_words * 8) +
                                  2 * align256((size_t)max_batch * max_items * 4) +
                                  align256((size_t)max_batch * sizeof(InstState)) +
-                                 align256((size_t)max_batch * max_items * sizeof(StreamItem)));
+                                 align256((size_t)max_batch * max_items * sizeof(StreamItem)) +
+                                 align256((size_t)max_batch * sizeof(TeamJob)));
 }
 
-hipError_t seq_global_prepare(const SeqGlobalPlan &p)
+hipError_t seq_global_prepare(const SeqGlobalPlan &p, void *scratch)
 {
+    const Scratch s = carve(p, scratch, p.max_batch);
+    hipError_t e = hipMemset(s.jobs, 0, (size_t)p.max_batch * sizeof(TeamJob));  // (every call leaves them so)
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    if (e != hipSuccess) return e;
     // (the attribute belongs to the kernel, not to the handle, and the plan's LDS is the device's)
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(&sg_stream), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               p.lds_bytes);
+    for (const void *kernel : {reinterpret_cast<const void *>(&sg_stream<false>), reinterpret_cast<const void *>(&sg_stream<true>)}) {
+        e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, p.lds_bytes);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t seq_global_launch(const SeqGlobalPlan &p, const BatchArgs &a, void *scratch, hipStream_t st,
@@ -776,10 +1047,16 @@ hipError_t seq_global_launch(const SeqGlobalPlan &p, const BatchArgs &a, void *s
 {
     const Scratch s = carve(p, scratch, p.max_batch);
     if (a.mode != DEFT_MODE_RECURSIVE) {
+        int helpers = 0;
+        if (p.row_len > kTeamMinCells) {
+            helpers = p.compute_units / a.batch - 1;
+            const int tiles = p.row_len / kTeamCells;
+            if (helpers > tiles) helpers = tiles;
+        }
         if (prof) prof->sweep_begin(st);
-        hipLaunchKernelGGL(sg_stream, dim3((unsigned)a.batch), dim3(kStreamThreads), (size_t)p.lds_bytes, st, a, s.items,
-                           s.rows, reinterpret_cast<uint8_t *>(s.keep), p.row_len, p.max_items, p.ring_cells,
-                           prof ? streamed_cells : nullptr);
+        hipLaunchKernelGGL(helpers > 0 ? &sg_stream<true> : &sg_stream<false>, dim3((unsigned)a.batch * (unsigned)(helpers + 1)), dim3(kStreamThreads), (size_t)p.lds_bytes, st,
+                           a, s.items, s.rows, reinterpret_cast<uint8_t *>(s.keep), s.jobs, helpers, p.row_len, p.max_items,
+                           p.ring_cells, prof ? streamed_cells : nullptr);
         if (prof) prof->sweep_end(st);
         return hipGetLastError();
     }
