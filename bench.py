@@ -164,9 +164,9 @@ def run_schedule(args):
     t_cpu = time.perf_counter() - t0
     dev = torch.device("cuda", 0)
     stream = torch.cuda.Stream(device=dev)
-    packed16 = bool(getattr(args, "packed16", False))
+    promised = bool(getattr(args, "values_are_weights", False))
     with binding.DeftKnapsack(device=0, max_batch=sb.batch, max_items=sb.n_buckets, max_knapsacks=2,
-                              max_capacity=cap, flags=2 if getattr(args, "subset_sum", False) else 1 if packed16 else 0) as h:
+                              max_capacity=cap, flags=2 if getattr(args, "subset_sum", False) else 1 if promised else 0) as h:
         info = h.info()
         ds = binding.DeviceSchedules(sb, dev)
         torch.cuda.synchronize(dev)
@@ -212,7 +212,7 @@ def run_schedule(args):
         vs_baseline=None, dtype="int32", data="synthetic",
         config=dict(workload=f"task-queue simulation (Cases 1-4), ResNet-101-shaped: {sb.batch} candidates x "
                              f"{sb.n_buckets} buckets x {sb.iterations} iterations, windows 5900 / 11800 +-10%"
-                             + (" [handle promises values equal to weights]" if packed16 else "")
+                             + (" [handle promises values equal to weights]" if promised else "")
                              + (" [bit-set rows; cell-updates as the oracle's sample counts them for one sweep per stage]"
                                 if bitset else ""),
                     value_counts=("one-sweep cell-updates per stage as estimated from the oracle's sample (the bit-set "
@@ -286,13 +286,13 @@ def run_solver(args):
             kb.n_knapsacks[:] = np.minimum(kb.n_knapsacks, args.max_stages)
         desc += f" [n_knapsacks clamped to {args.max_stages}]"
     plain_run = args.batch_scale == 1.0 and not (args.per_k_calls or args.only_k or args.max_stages or
-                                                 getattr(args, "packed16", False) or getattr(args, "subset_sum", False))
+                                                 getattr(args, "values_are_weights", False) or getattr(args, "subset_sum", False))
     seq = calls[0].mode != 1
     cap = max(int(kb.capacities.max()) for kb in calls)
     limits = dict(max_batch=max(kb.batch for kb in calls), max_items=max(kb.item_stride for kb in calls),
                   max_knapsacks=max(kb.knap_stride for kb in calls))
-    packed16 = bool(getattr(args, "packed16", False))
-    if packed16:
+    promised = bool(getattr(args, "values_are_weights", False))
+    if promised:
         limits["flags"] = 1
         desc += " [handle promises values equal to weights]"
     subset_sum = bool(getattr(args, "subset_sum", False))
@@ -561,7 +561,7 @@ def main() -> int:
     ap.add_argument("--no-per-config", "--no-per-k", dest="no_per_config", action="store_true",
                     help="default workload only: skip the other configurations and the peak calibration "
                          "(profiling runs: keeps the kernel statistics to the headline launches)")
-    ap.add_argument("--packed16", action="store_true",
+    ap.add_argument("--values-are-weights", action="store_true",
                     help="value-equals-weight workloads: create the handle with DEFT_FLAG_VALUES_ARE_WEIGHTS")
     ap.add_argument("--subset-sum", action="store_true",
                     help="value-equals-weight workloads: create the handle with DEFT_FLAG_SUBSET_SUM")
@@ -590,12 +590,12 @@ def main() -> int:
                             ("schedule", {}),
                             # the value-equals-weight workloads again on handles created with
                             # DEFT_FLAG_VALUES_ARE_WEIGHTS: the bit-set kernels alone, no look at the values left over
-                            ("resnet101_rows16", dict(workload="resnet101", packed16=True)),
-                            ("resnet101_one_call_per_k_rows16", dict(workload="resnet101", per_k_calls=True, packed16=True)),
-                            ("vgg19_rows16", dict(workload="vgg19", packed16=True)),
-                            ("backward_rows16", dict(workload="backward", packed16=True)),
-                            ("inflation_rows16", dict(workload="inflation", packed16=True)),
-                            ("schedule_rows16", dict(workload="schedule", packed16=True)),
+                            ("resnet101_promised", dict(workload="resnet101", values_are_weights=True)),
+                            ("resnet101_one_call_per_k_promised", dict(workload="resnet101", per_k_calls=True, values_are_weights=True)),
+                            ("vgg19_promised", dict(workload="vgg19", values_are_weights=True)),
+                            ("backward_promised", dict(workload="backward", values_are_weights=True)),
+                            ("inflation_promised", dict(workload="inflation", values_are_weights=True)),
+                            ("schedule_promised", dict(workload="schedule", values_are_weights=True)),
                             # and on handles created with DEFT_FLAG_SUBSET_SUM: the same kernels
                             ("resnet101_bitset", dict(workload="resnet101", subset_sum=True)),
                             ("resnet101_one_call_per_k_bitset", dict(workload="resnet101", per_k_calls=True, subset_sum=True)),
@@ -604,7 +604,7 @@ def main() -> int:
                             ("inflation_bitset", dict(workload="inflation", subset_sum=True)),
                             ("schedule_bitset", dict(workload="schedule", subset_sum=True))):
             sub = argparse.Namespace(**vars(args))
-            sub.workload, sub.no_cpu = name, args.no_cpu or "rows16" in name or "bitset" in name
+            sub.workload, sub.no_cpu = name, args.no_cpu or "promised" in name or "bitset" in name
             sub.steps, sub.warmup, sub.single_thread = max(3, min(args.steps, 20)), 3, False
             for k, v in extra.items():
                 setattr(sub, k, v)

@@ -19,7 +19,7 @@ constexpr int32_t kMaxBatch = 1 << 20;
 constexpr int32_t kMaxCapacity = 1 << 24;
 constexpr int32_t kMaxJointCapacity = 4095;
 constexpr int32_t kMaxIterations = 4096;
-constexpr int32_t kMaxPacked16Capacity = 26623;  // the longest row of 16-bit cells that is compiled
+constexpr int32_t kMaxValuesAreWeightsCapacity = 26623;
 constexpr int32_t kMaxSubsetSumCapacity = 65535;  // the longest bit-set row that is compiled
 
 struct DeviceGuard {
@@ -123,11 +123,7 @@ extern "C" deft_status_t deft_knapsack_create(const deft_knapsack_config_t *cfg,
     if (want_joint && cfg->max_knapsacks < 2) return DEFT_ERR_INVALID_ARG;
     const bool subset_sum = (cfg->flags & DEFT_FLAG_SUBSET_SUM) != 0;
     if (subset_sum && (!want_seq || cfg->max_capacity > kMaxSubsetSumCapacity)) return DEFT_ERR_LIMIT;
-    // rows of 16-bit cells: what such a handle would run on if its list did not fit beside the bit set
-    // (every list of at most kMaxItems does)
-    const bool packed16 = (cfg->flags & DEFT_FLAG_VALUES_ARE_WEIGHTS) != 0 ||
-                          (subset_sum && cfg->max_capacity <= kMaxPacked16Capacity);
-    if ((cfg->flags & DEFT_FLAG_VALUES_ARE_WEIGHTS) != 0 && (!want_seq || cfg->max_capacity > kMaxPacked16Capacity))
+    if ((cfg->flags & DEFT_FLAG_VALUES_ARE_WEIGHTS) != 0 && (!want_seq || cfg->max_capacity > kMaxValuesAreWeightsCapacity))
         return DEFT_ERR_LIMIT;
 
     int ndev = 0;
@@ -156,7 +152,7 @@ extern "C" deft_status_t deft_knapsack_create(const deft_knapsack_config_t *cfg,
                                                             : (int)prop.sharedMemPerBlock;
     if (want_seq && cfg->max_capacity <= kMaxSubsetSumCapacity) {
         if (!seq_bits_plan(cfg->max_capacity, cfg->max_items, lds_wg, h->compute_units, &h->bits_plan)) {
-            if (subset_sum) st = DEFT_ERR_LIMIT;  // (an item list too long for the LDS beside the row)
+            if (cfg->flags != 0) st = DEFT_ERR_LIMIT;  // (an item list too long for the LDS beside the row)
         } else if (seq_bits_prepare(h->bits_plan) != hipSuccess) {
             (void)hipGetLastError();
             st = DEFT_ERR_DEVICE;
@@ -166,7 +162,7 @@ extern "C" deft_status_t deft_knapsack_create(const deft_knapsack_config_t *cfg,
         }
     }
     if (st == DEFT_OK && want_seq) {
-        if (seq_lds_plan(cfg->max_capacity, cfg->max_items, cfg->max_knapsacks, cfg->max_batch, lds_wg, packed16,
+        if (seq_lds_plan(cfg->max_capacity, cfg->max_items, cfg->max_knapsacks, cfg->max_batch, lds_wg,
                          &h->lds_plan) &&
             seq_lds_prepare(&h->lds_plan) == hipSuccess && seq_lds_rec_prepare(h->lds_plan) == hipSuccess) {
             h->seq_path = h->lds_plan.threads == 64 ? 1 : 2;
@@ -186,9 +182,6 @@ extern "C" deft_status_t deft_knapsack_create(const deft_knapsack_config_t *cfg,
                     st = DEFT_ERR_DEVICE;
                 }
             }
-        } else if (packed16) {
-            (void)hipGetLastError();
-            st = DEFT_ERR_LIMIT;   // (an item list too long for the packed row's LDS)
         } else {
             (void)hipGetLastError();
             h->seq_path = 3;
@@ -374,13 +367,7 @@ extern "C" deft_status_t deft_knapsack_simulate_schedule(deft_knapsack_t *h, con
             if (prof) prof->sweep_end(st);
             return rc;
         }
-        if (h->seq_path == 3) return seq_global_launch(h->glob_plan, x, h->glob_scratch, st, prof, h->glob_streamed);
-        if (prof) prof->sweep_begin(st);
-        const hipError_t rc = x.mode == DEFT_MODE_SEQUENTIAL
-                                  ? seq_lds_launch(h->lds_plan, x, h->keep, st, prof ? h->lds_swept : nullptr)
-                                  : seq_lds_rec_launch(h->lds_plan, x, h->keep, st, prof ? h->lds_swept : nullptr);
-        if (prof) prof->sweep_end(st);
-        return rc;
+        return seq_global_launch(h->glob_plan, x, h->glob_scratch, st, prof, h->glob_streamed);
     };
     const hipError_t e = schedule_sim_launch(a, h->sim_buffers, st, solve);
     if (prof) prof->end(st);

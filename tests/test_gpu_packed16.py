@@ -1,7 +1,7 @@
-"""GPU parity of the kernels with rows of 16-bit cells (handles created with
-DEFT_FLAG_VALUES_ARE_WEIGHTS: every value equals its weight, capacities up to 26623),
-through the C ABI, bit-exact against the oracle on every output: every compiled variant,
-every mode that runs on them, the paper's shapes at full size."""
+"""GPU parity of handles created with DEFT_FLAG_VALUES_ARE_WEIGHTS (every value equals its weight,
+capacities up to 26623): the bit-set kernels alone, over the capacities at which one kernel build hands
+over to the next, every mode that runs on them, the paper's shapes at full size.  Through the C
+ABI, bit-exact against the oracle on every output."""
 import numpy as np
 import pytest
 
@@ -13,23 +13,22 @@ pytestmark = pytest.mark.gpu
 
 FLAG = 1   # DEFT_FLAG_VALUES_ARE_WEIGHTS
 
-VARIANTS = [
-    (700, 1023),       # one wavefront per instance
-    (3000, 4095),      # 256 x 16
-    (8000, 8191),      # 256 x 32
-    (9500, 9599),      # 320 x 30 (five wavefronts)
-    (10000, 10239),    # 512 x 20
-    (13000, 13311),    # 512 x 26
-    (19900, 19967),    # 768 x 26
-    (26000, 26623),    # 1024 x 26
+VARIANTS = [           # words per lane of the kernel that runs, and register slots of the row
+    (700, 1023),       # 2, 1 slot
+    (3000, 4095),      # 2, 2 slots
+    (8000, 8191),      # 5, 4 slots
+    (9500, 9599),      # 5, 5 slots
+    (10000, 10239),    # 5, the longest
+    (13000, 13311),    # 7, 7 slots
+    (19900, 19967),    # 10, 10 slots
+    (26000, 26623),    # 14, 14 slots: the longest the flag allows
 ]
 
 
 @pytest.mark.parametrize("cap_hi,max_capacity", VARIANTS)
 def test_random_ragged_every_variant(binding, oracle, cap_hi, max_capacity):
-    """Ragged n and m, random fill order, capacities from 0 up: light items (below one lane
-    row), items around the lane count (lanes on both sides of the shift) and items of several
-    lane rows (the per-lane word offsets of the heavy path), odd and even pair counts."""
+    """Ragged n and m, random fill order, capacities from 0 up: items of a few cells, of a few words of
+    the set, and as heavy as the window."""
     for seed, n_max, w_hi in ((1, 60, max(9, cap_hi // 40)), (2, 45, max(20, cap_hi // 6)), (3, 30, cap_hi)):
         kb = W.random_sequential(11000 + 7 * cap_hi + seed, batch=37, n_max=n_max, m_max=4, w_hi=w_hi, v_hi=9,
                                  cap_hi=cap_hi, ties=True)
