@@ -228,7 +228,9 @@ def test_rows_that_fill_early_every_lds_variant(binding, oracle, max_capacity, n
     well before its list ends, so the sweep's early end, the write-back of a row that uses the
     variant's highest slots, the partial keep-row flags and the walk that starts at the last
     swept item all run together; the library's swept-cell count must equal the replay of the
-    early end from the oracle's results (which also shows that rows did fill)."""
+    early end from the oracle's results (which also shows that rows did fill).  (Calls of this size
+    look at the values and are answered by the bit-set kernels, which keep the same count; the row
+    kernels themselves are put through these lists by test_gpu_rows_that_fill.py.)"""
     import torch
     import bench
     kb = W.filling_rows(8000 + max_capacity, batch=batch, n_max=n_max, m_max=3, w_hi=w_hi,
