@@ -73,9 +73,11 @@ typedef struct {
  * Problem 1: the profit of a bucket is its communication time).  Requires 1 <= max_capacity
  * <= 26623 (create returns DEFT_ERR_LIMIT otherwise).  The sequential-layout modes (SEQUENTIAL,
  * RECURSIVE, CAPACITY_SWEEP, deft_knapsack_simulate_schedule) then run on the kernels that
- * DEFT_FLAG_SUBSET_SUM names, alone and without scratch memory; a handle without flags asks
- * every instance for v == w first and solves those that have it there too (capacities up to
- * 65535), the others on rows of values.  Results are bit-identical to those of a
+ * DEFT_FLAG_SUBSET_SUM names, alone and without scratch memory.  A handle without flags
+ * solves the instances that have v == w there too, the others on rows of values, as long as
+ * max_capacity is at most 38911 (rows in LDS); solve calls of fewer than 1024 instances with
+ * item_stride * max_capacity below 2^17 do not look for such instances, and the task queues, whose
+ * every stage has v == w, run there up to 65535.  Results are bit-identical to those of a
  * handle without the flag.  An instance that breaks the promise (some value != its weight)
  * gets status DEFT_ERR_INVALID_ARG like any other bad input.  The joint and greedy modes are
  * not affected.
@@ -348,10 +350,10 @@ typedef struct {
     float sweep_ms;        /* summed duration of the DP sweep kernel launches              */
     int32_t sweep_launches;
     float other_ms;        /* total_ms - sweep_ms: set-up, traceback, launch gaps          */
-    int64_t streamed_row_cells; /* sequential mode with rows in global memory, persistent
-                              sweep: row cells read from plus row cells written to global
-                              memory by the sweeps, summed over instances and stages (a
-                              pass over a row may serve two items); 0 on the other paths   */
+    int64_t streamed_row_cells; /* SEQUENTIAL and CAPACITY_SWEEP with rows in global memory:
+                              row cells read from plus row cells written to global memory
+                              by the sweeps, summed over instances and stages (a pass over a
+                              row may serve seven items); 0 on the other paths             */
     int64_t swept_cell_updates; /* rows in LDS (seq_path 1 or 2): cell-updates the sweeps
                               evaluated, C - w + 1 for every item a stage's sweep went
                               through (stages settled without a sweep and the items after

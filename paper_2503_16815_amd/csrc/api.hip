@@ -280,9 +280,12 @@ extern "C" deft_status_t deft_knapsack_solve_batch(deft_knapsack_t *h, const def
     // A plain handle's instances may still have values equal to weights: the bit-set kernels answer those
     // (measured on 4096 ResNet-101-shaped schedules: 0.100 ms, rows of values 1.66 ms) and the rows take
     // what is left.  Where none qualifies that is a launch for nothing, 2.2 us for one instance and 4 us
-    // for four thousand, which a call of short instances would notice (one of 32 items at capacity
-    // 1000: 19.4 us on the rows alone; 909 of 43 items at capacity 820, unrelated values: 32.5 us on the rows
-    // alone, 35.1 us with the look): fewer than 1024 of those go to the rows at once.
+    // for four thousand, a hundredth of most calls but a tenth of one of short instances.  Fewer than
+    // 1024 of those go to the rows at once, so that no call of unrelated values pays that much.  What it costs
+    // where values are weights, rows and look, us (unrelated values in brackets): one instance of 32 items at
+    // capacity 1000 17.9 and 12.1 (21.2, 23.6); 64 of 43 at 820 24.8 and 15.3 (29.5, 32.2); 1023 of 43 at 820
+    // 27.1 and 17.3 (31.3, 34.1); 1023 of 120 at 1000 56.7 and 26.7 (74.3, 77.8); 1023 of 9 at 600 13.2 and
+    // 12.0 (10.1, 13.3).  A caller who knows its values says so with a flag and gets the shorter time.
     const bool small = b->batch < 1024 && (int64_t)b->item_stride * h->cfg.max_capacity < (1 << 17);
     const bool by_sums = (b->mode == DEFT_MODE_SEQUENTIAL || probing) && h->bits_ready &&
                          (h->promised || (h->left && !small));
