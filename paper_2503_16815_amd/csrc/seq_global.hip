@@ -27,8 +27,8 @@
 // it: a step is read, compute, write, barrier for all wavefronts at once (counters: vector units busy 41 % of
 // the cycles, LDS 39 %, a wavefront waiting 52 % of its own).
 //
-// Teams.  A batch of at most half as many instances as there are compute units, on rows of 131072 cells or
-// more, is launched with helpers: workgroups behind the batch's own, as many per instance as fill the chip.
+// Teams.  A batch of at most half as many instances as there are compute units, on long rows (kTeamRows), is
+// launched with helpers: workgroups behind the batch's own, as many per instance as fill the chip.
 // An instance's own workgroup (the owner) runs everything above; where that is expected to be quicker
 // (kTeamJobNs and its like) it cuts the next item's band into tiles instead, every workgroup of the team
 // takes some, both operands straight from global memory, from one row buffer into the other, and the owner
@@ -36,15 +36,14 @@
 // asked for by whoever is there (the owner would do them all), an owner waits only for helpers that are at a
 // tile, and a helper waits only for an owner that has begun, else it leaves after a few
 // milliseconds.  So no order or number of workgroups on the chip, another team's included, can hold one up.
-// The helpers hold their compute units until the owner dismisses them: before its last walk, or at
-// once where no window of the instance is that long.
+// The helpers hold their compute units until the owner dismisses them: before its last walk, or when a
+// list shows that no band worth a job is left (kTeamMinBand).
 // Row cells go out as device-scope stores, which leave nothing in an XCD's L2 for the release to write
 // back (2000000 cells, 4 instances of 148 items: 3.06 ms, with plain stores 3.56); counters
 // are striped (see TeamStripe; one instance of that: 2.24 ms, one counter for all 3.40).
-// Measured, 148 items in two windows, lists twice the first window: one instance of 381000 cells 1.33 ms,
-// alone 3.68, a launch per item over all compute units 3.26; 2000000 cells 2.24, 34.5 and 3.63 ms; sixteen of
-// 381000 cells 2.37, 3.82 and 4.17 ms; lists that barely exceed the window, one of 160000 cells: 0.59, 0.58
-// and 2.00 ms.  A call with nothing to sweep pays 3 to 5 us for its helpers.
+// Measured, 148 items in two windows, lists twice the first window: one instance of 381000 cells 1.38 ms,
+// alone 3.68, a launch per item over all compute units 3.26; 2000000 cells 2.42, 34.5 and 3.63 ms; sixteen of
+// 381000 cells 2.37, 3.82 and 4.17 ms.  A call with nothing to sweep pays 3 to 5 us for its helpers.
 //
 // Algorithm 1 reads a cell of every intermediate row, so it takes sweeps that leave each of them in
 // global memory: one launch per offered-item rank, two row buffers, the row cut into tiles over
@@ -273,9 +272,18 @@ constexpr int kTaskSlots = kTaskCells / 64;
 constexpr int kMaxLevels = 7;         // items per pass over the row
 // Teams: a job is cut into tiles of one task per wavefront.
 constexpr int kTeamCells = kStreamWaves * kTaskCells;
-// Instances of shorter rows do without: on 80000 cells a team gained a tenth on lists of 12 items and cost
-// every other call its 3 to 7 us.
-constexpr int kTeamMinCells = 1 << 17;
+// Which launches get helpers: rows of kTeamRows cells, or of kTeamRowsHeavy and kTeamCellsPerItem cells per item
+// listed (heavy items, for which a team does most).  The host cannot see how wide a band will be; what decides is that
+// a call whose bands are too narrow for a team loses 4 to 7 us to the larger kernel.  One window, then two fifths of
+// it, lists 1.2 and 1.7 times the first (narrow and wide), 1 to 64 instances, gain by the team: 140000 cells
+// and 20 items 0.98-1.05 and 1.10-1.39, 24 items 0.96-1.03 and 1.08-1.23; 160000 and 12 1.08-1.18 and 1.34-1.61, 24
+// 0.97 and 1.12-1.43, 60 0.98 and 1.01-1.18; 200000 and 24 1.03-1.13 and 1.20-1.63, 60 0.98 and 1.05-1.44; 300000 and
+// 60 1.02-1.13 and 1.18-2.1, 148 0.995-1.01 and 1.00-1.72.  On 80000 cells 0.9 and 1.1 with 12 items.
+constexpr int kTeamRows = 1 << 18, kTeamRowsHeavy = 1 << 17, kTeamCellsPerItem = 7000;
+// The narrowest band in which the estimate below can favour the team: where passes serve seven items, and where
+// items are so heavy that a pass serves one (lists of more than kTeamHeavy on average are taken for such).
+// 160000 cells with 33000 of band: 148 items gain nothing, 12 go from 141 to 121 us.
+constexpr int kTeamMinBand = 60000, kTeamMinBandHeavy = 9500, kTeamHeavy = 4000;
 constexpr int kTeamStartPolls = 1 << 12;     // how often a helper looks for an owner that has not begun
 constexpr unsigned long long kTeamOver = 1ull << 63;
 // What is expected, in ns, of a job (besides its tiles), of a task of every wavefront of the team, of a step of
@@ -294,7 +302,7 @@ struct StreamShared {
     int32_t value;             // of the whole list
     int32_t settled;
     unsigned long long ticket;  // of the team's job
-    int32_t job[8], stripe;
+    int32_t job[8], stripe, team;
     uint32_t placed[kMaxItemsPlaced / 32];
 };
 static_assert(sizeof(StreamShared) <= kMiscBytes, "fits in front of the rings");
@@ -635,10 +643,8 @@ sg_stream(BatchArgs a, StreamItem *lists, int32_t *rows, uint8_t *keep, TeamJob 
     const int status = check_instance(a, inst, false);
     clear_outputs(a, inst, status);
     // (may be said twice; the owner leaves at the very end)
-    bool team = TEAMS;
     auto dismiss = [&]() {
-        if (team) team_tell(job, helpers, kTeamOver);
-        team = false;
+        if (TEAMS) team_tell(job, helpers, kTeamOver);
     };
     if (status != DEFT_OK) {
         dismiss();
@@ -663,11 +669,9 @@ sg_stream(BatchArgs a, StreamItem *lists, int32_t *rows, uint8_t *keep, TeamJob 
     long long total = 0;
     unsigned long long streamed = 0;
     const int stages = caps_sweep ? min(m, 1) : m;
-    if (team) {
-        int most = 0;
-        for (int x = 0; x < m; ++x) most = max(most, cap[x]);
-        if (most < kTeamMinCells) dismiss();
-        else team_tell(job, helpers, 1ull);  // (begun)
+    if (TEAMS) {
+        if (tid == 0) sh->team = 1;
+        team_tell(job, helpers, 1ull);  // (begun)
     }
     for (int s = 0; s < stages; ++s) {
         // ---- the stage's list, built by the first wavefront ------------------------------
@@ -705,6 +709,16 @@ sg_stream(BatchArgs a, StreamItem *lists, int32_t *rows, uint8_t *keep, TeamJob 
                 value += vsum;
             }
             const bool settled = !caps_sweep && weight <= C;
+            if (TEAMS && sh->team != 0) {
+                // no band worth a job, now (at most weight - C_min wide) or later
+                int widest = weight <= C_min ? 0 : (int)min((long long)C, weight - C_min);
+                for (int x = s + 1; x < stages; ++x)
+                    widest = max(widest, cap[a.fill_order ? a.fill_order[(size_t)inst * a.knap_stride + x] : x]);
+                if (widest < (weight > (long long)cnt * kTeamHeavy ? kTeamMinBandHeavy : kTeamMinBand)) {
+                    dismiss();
+                    if (lane == 0) sh->team = 0;
+                }
+            }
             if (settled && cnt > 0) {
                 // everything offered fits together: the DP takes it all
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -727,6 +741,7 @@ sg_stream(BatchArgs a, StreamItem *lists, int32_t *rows, uint8_t *keep, TeamJob 
         __syncthreads();
         const int cnt = sh->cnt, j = sh->knap, C = sh->cap, C_min = sh->cap_min, value_all = sh->value;
         const long long weight_all = sh->weight;
+        const bool team = TEAMS && __builtin_amdgcn_readfirstlane(sh->team) != 0;
         if (sh->settled || cnt == 0) {
             total += value_all;
             __syncthreads();
@@ -757,9 +772,11 @@ sg_stream(BatchArgs a, StreamItem *lists, int32_t *rows, uint8_t *keep, TeamJob 
             }
             const int U_in = top(before), L_in = bottom(before);
             int32_t *row = buffers + (size_t)cur * row_len;
-            if (team) {
-                // ---- one item by the team, where that is expected to be quicker than the owner alone
-                const int w = __builtin_amdgcn_readlane(it.w, 0), v = __builtin_amdgcn_readlane(it.v, 0);
+            // ---- one item by the team, where that is expected to be quicker than the owner alone.  Most passes are
+            // too narrow for it by far, and what they pay for the question counts: no divisions, nothing in 64 bits.
+            const int w_next = __builtin_amdgcn_readlane(it.w, 0);
+            if (__builtin_expect(team && U_in - L_in + w_next > (g == 0 ? 4 * kStreamWaves * 2 * kTaskCells : 8 * g * R), 0)) {
+                const int w = w_next, v = __builtin_amdgcn_readlane(it.v, 0);
                 const int U = top(before + w), L = bottom(before + w);
                 // as many tiles as the team has workgroups, or fewer
                 const int span = (U / kTeamCells - L / kTeamCells + 1 + helpers) / (helpers + 1);
@@ -1047,7 +1064,7 @@ hipError_t seq_global_launch(const SeqGlobalPlan &p, const BatchArgs &a, void *s
     const Scratch s = carve(p, scratch, p.max_batch);
     if (a.mode != DEFT_MODE_RECURSIVE) {
         int helpers = 0;
-        if (p.row_len > kTeamMinCells) {
+        if (p.row_len >= kTeamRows || (p.row_len > kTeamRowsHeavy && p.row_len >= (int64_t)kTeamCellsPerItem * a.item_stride)) {
             helpers = p.compute_units / a.batch - 1;
             const int tiles = p.row_len / kTeamCells;
             if (helpers > tiles) helpers = tiles;

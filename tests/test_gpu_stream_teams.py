@@ -40,7 +40,13 @@ def test_tiles_and_helpers(binding, oracle, cap, batch):
     heavy = lambda r, s: r.integers(36000, 90000, size=s)  # noqa: E731
     mixed = lambda r, s: np.where(r.random(s) < 0.2, r.integers(36000, 60000, size=s), r.integers(1, 12000, size=s))  # noqa: E731
     _run(binding, oracle, _batch(51000 + cap + batch, batch, 9, heavy, [cap, cap // 3]), cap)
-    _run(binding, oracle, _batch(52000 + cap + batch, min(batch, 8), 24, mixed, [cap // 2, cap]), cap)
+    _run(binding, oracle, _batch(52000 + cap + batch, min(batch, 8), 18, mixed, [cap // 2, cap]), cap)
+
+
+@pytest.mark.parametrize("cap,n", [(139999, 20), (139999, 21), (260095, 40), (260096, 40), (262143, 40), (262144, 40)])
+def test_which_rows_get_helpers(binding, oracle, cap, n):
+    """Both sides of 7000 cells per item and of 262144 cells."""
+    _run(binding, oracle, _batch(53500 + cap + n, 3, n, lambda r, s: r.integers(1, 4 * cap // n, size=s), [cap, cap * 2 // 5]), cap)
 
 
 @pytest.mark.parametrize("batch,cap", [(1, 2200000), (1, 2097151), (1, 2097152), (5, 600000), (16, 400000)])
