@@ -56,7 +56,7 @@ struct deft_knapsack {
     // instances of which that holds and flag the others in `left` for the kernels with rows of values.
     bool bits_ready = false, promised = false;
     SeqBitsPlan bits_plan{};
-    int32_t *left = nullptr;      // [max_batch]
+    int32_t *left = nullptr;      // [max_batch]; rows in global memory: for the enumeration ahead of them
 
     void *sim_buffers = nullptr;  // task-queue simulation: allocated by its first call
 
@@ -187,7 +187,13 @@ extern "C" deft_status_t deft_knapsack_create(const deft_knapsack_config_t *cfg,
             h->seq_path = 3;
             seq_global_plan(cfg->max_capacity, cfg->max_items, cfg->max_batch, lds_wg, h->compute_units, &h->glob_plan);
             if (!h->promised) st = alloc(&h->glob_scratch, h->glob_plan.scratch_bytes, &h->scratch_bytes);
-            if (st == DEFT_OK && !h->promised && seq_global_prepare(h->glob_plan, h->glob_scratch) != hipSuccess) {
+            if (st == DEFT_OK && !h->promised) {
+                void *c = nullptr;
+                st = alloc(&c, (int64_t)cfg->max_batch * 4, &h->scratch_bytes);
+                h->left = static_cast<int32_t *>(c);
+            }
+            if (st == DEFT_OK && !h->promised &&
+                (seq_global_prepare(h->glob_plan, h->glob_scratch) != hipSuccess || seq_enum_prepare() != hipSuccess)) {
                 (void)hipGetLastError();
                 st = DEFT_ERR_DEVICE;
             }
@@ -288,7 +294,7 @@ extern "C" deft_status_t deft_knapsack_solve_batch(deft_knapsack_t *h, const def
     // 12.0 (10.1, 13.3).  A caller who knows its values says so with a flag and gets the shorter time.
     const bool small = b->batch < 1024 && (int64_t)b->item_stride * h->cfg.max_capacity < (1 << 17);
     const bool by_sums = (b->mode == DEFT_MODE_SEQUENTIAL || probing) && h->bits_ready &&
-                         (h->promised || (h->left && !small));
+                         (h->promised || (on_lds && h->left && !small));
     if (by_sums) {
         a.left = h->left;
         if (prof) prof->sweep_begin(st);
@@ -299,7 +305,13 @@ extern "C" deft_status_t deft_knapsack_solve_batch(deft_knapsack_t *h, const def
         // (nothing is left to do)
     } else if (b->mode == DEFT_MODE_SEQUENTIAL || (probing && !on_lds)) {
         if (h->seq_path == 3) {
-            e = seq_global_launch(h->glob_plan, a, h->glob_scratch, st, prof, h->glob_streamed);
+            if (b->mode == DEFT_MODE_SEQUENTIAL) {
+                a.left = h->left;
+                if (prof) prof->sweep_begin(st);
+                e = seq_enum_launch(a, h->compute_units, st);
+                if (prof) prof->sweep_end(st);
+            }
+            if (e == hipSuccess) e = seq_global_launch(h->glob_plan, a, h->glob_scratch, st, prof, h->glob_streamed);
         } else {
             if (prof) prof->sweep_begin(st);
             e = seq_lds_launch(h->lds_plan, a, h->keep, st, swept);

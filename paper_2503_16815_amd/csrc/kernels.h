@@ -21,7 +21,8 @@ struct BatchArgs {
     int64_t *total_value;
     int32_t *knap_value, *knap_load, *assignment, *status;
     // [batch] or null.  The bit-set kernels write 1 for an instance whose values are not all its
-    // weights and leave it alone, 0 for one they answered; the LDS-row kernels then skip those.
+    // weights and leave it alone, 0 for one they answered; the LDS-row kernels then skip those.  The
+    // enumeration ahead of rows in global memory does the same for the streamed sweep.
     int32_t *left;
 };
 
@@ -78,6 +79,11 @@ hipError_t seq_bits_prepare(const SeqBitsPlan &plan);
 // `swept_cells` (device, may be null): every stage adds the cell-updates its sweep evaluated.
 hipError_t seq_bits_launch(const SeqBitsPlan &plan, const BatchArgs &args, hipStream_t stream, unsigned long long *swept_cells);
 void *seq_bits_long_kernel(int variant);  // the kernels of the longer rows (seq_bits_long.hip)
+
+// ---- sequential mode by enumeration, ahead of rows in global memory (seq_enum.hip) ----------
+// Answers the instances it can (args.left 0) and flags the others (1).  No scratch.
+hipError_t seq_enum_prepare();
+hipError_t seq_enum_launch(const BatchArgs &args, int32_t compute_units, hipStream_t stream);
 
 // ---- per-call HIP-event timing (profile.hip) ---------------------------------
 class Profiler {

@@ -1,8 +1,8 @@
 // Sequential multiple-knapsack solve for capacities whose row does not fit LDS
 // (Sec. III.B, Problem 1 per window): the row lives in global memory.
 //
-// The streamed sweep (sg_stream; the sequential mode and the capacity sweep): one launch, one
-// workgroup per instance for all stages, lists and walks included.
+// The streamed sweep (sg_stream; the sequential mode, for the instances that the enumeration ahead of it leaves, and
+// the capacity sweep): one launch, one workgroup per instance for all stages, lists and walks included.
 //
 // What is kept of a cell is how far it falls short: D[c] = (value of the items so far) - row[c], so
 //   D'[c] = min(D[c] + v, D[c - w]),   item taken where D[c - w] < D[c] + v,   D[c < 0] = infinity.
@@ -640,8 +640,9 @@ sg_stream(BatchArgs a, StreamItem *lists, int32_t *rows, uint8_t *keep, TeamJob 
         team_help(sh, job, blockIdx.x / a.batch, helpers, buffers, row_len, kp, keep_row, wave, lane);
         return;
     }
-    const int status = check_instance(a, inst, false);
-    clear_outputs(a, inst, status);
+    const bool answered = a.left && a.left[inst] == 0;  // (by the enumeration)
+    const int status = answered ? -1 : check_instance(a, inst, false);
+    if (!answered) clear_outputs(a, inst, status);
     // (may be said twice; the owner leaves at the very end)
     auto dismiss = [&]() {
         if (TEAMS) team_tell(job, helpers, kTeamOver);

@@ -1,0 +1,66 @@
+"""Stages settled by enumeration of the selections that can be optimal: one wavefront ahead of rows in global
+memory, the set-up wavefront of the LDS-row kernels, and the stages these reduce.  Lists around the pool's 64 items, values
+that tie (the smallest mask has to come out), items of no value, a few items that hold most of the weight, values and
+weights of very different sizes, windows that hold all but a little, lists that run over.  Bit-exact against the oracle."""
+import numpy as np
+import pytest
+
+from paper_2503_16815_amd import workloads as W
+from tests.test_gpu_parity import binding, run  # noqa: F401  (binding is a fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def _batch(seed, batch, n, cap, kind, m=3):
+    r = np.random.Generator(np.random.PCG64(seed))
+    mean = 2.0 * cap / n
+    w = np.maximum(1, np.rint(r.lognormal(0.0, 0.9, size=(batch, n)) * mean / 1.5)).astype(np.int64)
+    v = np.rint(w * r.uniform(1.0, 4.0, size=w.shape)).astype(np.int64)
+    if kind == "free":
+        v = r.integers(0, 1001, size=w.shape)                   # some items of no value
+    elif kind == "alike":                                        # few kinds of items: many selections are as good
+        at = r.integers(0, 4, size=w.shape)
+        w, v = np.maximum(1, (mean * np.array([0.5, 0.9, 1.1, 1.4])))[at].astype(np.int64), np.array([3, 5, 6, 8])[at]
+    elif kind == "rates":                                        # two rates of value, many weights
+        v = w * r.integers(1, 3, size=w.shape)
+    elif kind == "heavy":                                        # three items hold 85 % of the weight
+        w[:, :3] = np.rint(1.9 * cap * 0.28 * r.uniform(0.9, 1.1, size=(batch, min(3, n)))) if n >= 3 else w[:, :3]
+        v = np.rint(w * r.uniform(1.0, 4.0, size=w.shape)).astype(np.int64)
+    elif kind == "great":                                        # values far above the weights
+        v = r.integers(1, (1 << 30) // n, size=w.shape)
+    elif kind == "light":                                        # and far below
+        v = r.integers(1, 4, size=w.shape)
+    w = np.minimum(w, cap + 3)                                   # (some fit no window)
+    caps = np.maximum(1, np.rint(cap * r.uniform(0.2, 1.0, size=(batch, m)))).astype(np.int64)
+    caps[0] = np.minimum(cap, w[0].sum() - 1)                    # all but one unit, all, one unit too many
+    if batch > 2:
+        caps[1], caps[2] = np.minimum(cap, w[1].sum()), np.minimum(cap, w[2].sum() + 1)
+    kb = W._sequential(f"enumeration_{kind}_{n}_{cap}", w.astype(np.int32), v.astype(np.int32), caps.astype(np.int32))
+    kb.fill_order = np.argsort(r.random((batch, m)), axis=1).astype(np.int32)
+    return kb
+
+
+KINDS = ["priority", "free", "alike", "rates", "heavy", "great", "light"]
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("n", [1, 7, 24, 63, 64, 65, 130, 300])
+def test_ahead_of_rows_in_global_memory(binding, oracle, kind, n):
+    run(binding, oracle, _batch(71000 + n, 6, n, 45000, kind), max_capacity=45000)
+
+
+def test_more_instances_than_compute_units(binding, oracle):
+    """Shorter lists, two instances on a compute unit."""
+    run(binding, oracle, _batch(72000, 300, 40, 41000, "priority", m=2), max_capacity=41000)
+
+
+def test_faults_beside_good_instances(binding, oracle):
+    kb = _batch(75000, 8, 50, 45000, "priority")
+    kb.weights[1, 3] = 0
+    kb.values[2, 4] = -1
+    kb.capacities[3, 0] = 45001
+    kb.n_items[4] = 0
+    kb.n_knapsacks[5] = 0
+    kb.values[6] = 2 ** 30
+    kb.fill_order[7] = 0
+    run(binding, oracle, kb, max_capacity=45000)
