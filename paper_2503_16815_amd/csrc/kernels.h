@@ -55,6 +55,10 @@ hipError_t seq_lds_prepare(SeqLdsPlan *plan);
 // `swept_cells` (device, may be null): every stage adds the cell-updates its sweep evaluated.
 hipError_t seq_lds_launch(const SeqLdsPlan &plan, const BatchArgs &args, void *scratch,
                           hipStream_t stream, unsigned long long *swept_cells);
+// Its kernels that try a stage by enumeration first (seq_lds_pool.hip); seq_lds_prepare and seq_lds_launch see to them.
+hipError_t seq_lds_pool_prepare(const SeqLdsPlan &plan);
+hipError_t seq_lds_pool_launch(const SeqLdsPlan &plan, const BatchArgs &args, void *scratch,
+                               hipStream_t stream, unsigned long long *swept_cells);
 // Algorithm 1 (recursive mode) under the same plan and scratch (seq_lds_rec.hip).
 hipError_t seq_lds_rec_prepare(const SeqLdsPlan &plan);
 hipError_t seq_lds_rec_launch(const SeqLdsPlan &plan, const BatchArgs &args, void *scratch,

@@ -268,7 +268,7 @@ __device__ __forceinline__ PoolOutcome pool_stage(const int2 *items, char *space
         const bool leap = may_leap && left > G && left <= G_pool;
         if (leap || left <= G) G = left;
         if (G <= last_G) {
-            if (G >= G_pool) return kPoolFailed;
+            if (G >= G_pool) break;
             ++round;
             continue;
         }
@@ -318,31 +318,7 @@ __device__ __forceinline__ PoolOutcome pool_stage(const int2 *items, char *space
             if (both) size_b = grow(list_b, size_b, 2 * p + 1, first_b);
         }
         if (over) {
-            if (REDUCE && left <= G_pool) {
-                const bool is_open = s_loss <= left;
-                unsigned long long chosen = 0, open_items = 0;
-                int load = 0, value = 0;
-                for (int c = 0; c < chunks; ++c) {
-                    const int f = loss_of[c * 64 + lane];
-                    if (is_offered(c) && f < 0) chosen |= 1ull << c;
-                }
-                const unsigned long long is_open_mask = __ballot(is_open);
-                for (int j = 0; j < kPool; ++j) {
-                    if (((is_open_mask >> j) & 1ull) == 0) break;  // (sorted by loss)
-                    const int i = __builtin_amdgcn_readlane(index, __builtin_amdgcn_readlane(s_place, j));
-                    if (lane == (i & 63)) {
-                        chosen &= ~(1ull << (i >> 6));
-                        open_items |= 1ull << (i >> 6);
-                    }
-                }
-                for (int c = 0; c < chunks; ++c) {
-                    const int2 it = items[c * 64 + lane];
-                    if ((chosen >> c) & 1ull) load += it.x, value += it.y;
-                }
-                answer = PoolAnswer{pool_sum(value), pool_sum(load), chosen, open_items};
-                return kPoolReduced;
-            }
-            if (!leap) return kPoolFailed;
+            if (!leap || REDUCE) break;
             may_leap = false;
             continue;
         }
@@ -461,7 +437,7 @@ __device__ __forceinline__ PoolOutcome pool_stage(const int2 *items, char *space
             }
         }
         if (!met) {
-            if (G >= G_pool) return kPoolFailed;
+            if (G >= G_pool) break;
             continue;
         }
         answer.value = worth + best;
@@ -476,7 +452,25 @@ __device__ __forceinline__ PoolOutcome pool_stage(const int2 *items, char *space
         answer.chosen = chosen;
         return kPoolFound;
     }
-    return kPoolFailed;
+    if (!REDUCE || least >= 1ll << 62) return kPoolFailed;
+    // What loses more than the selection known is treated the same in every one as good.
+    const int open_limit = __float_as_int((float)least * (1.0f + 0x1p-22f));  // (rounding included)
+    unsigned long long chosen = 0, open_items = 0;
+    int load = 0, value = 0;
+    for (int c = 0; c < chunks; ++c) {
+        const int f = loss_of[c * 64 + lane];
+        const int2 it = items[c * 64 + lane];
+        if (!is_offered(c)) continue;
+        if ((f & 0x7fffffff) <= open_limit) {
+            open_items |= 1ull << c;
+        } else if (f < 0) {
+            chosen |= 1ull << c;
+            load += it.x;
+            value += it.y;
+        }
+    }
+    answer = PoolAnswer{pool_sum(value), pool_sum(load), chosen, open_items};
+    return kPoolReduced;
 }
 
 // A selection's items as numbers to compare: whether x comes before y (the last item that one of them alone takes is

@@ -31,12 +31,13 @@
 //
 // Not every stage is swept: the first wavefront settles stages that are offered
 // nothing, whose offered items all fit together, or that are offered at most
-// six items, and where every value equals its weight a sweep ends as soon as
+// six items (POOL kernels: also those of unrelated values that enumeration settles, see
+// seq_enum.h, and what it does not settle it may reduce), and where every value equals its weight a sweep ends as soon as
 // every sum up to C can be reached.
 //
-// This header holds the kernel and its launcher as templates; seq_lds.hip instantiates
-// them for the sequential mode and seq_lds_rec.hip for Algorithm 1 (REC = true), so the
-// two sets of kernels compile side by side.
+// This header holds the kernel and its launcher as templates; seq_lds.hip and seq_lds_pool.hip
+// instantiate them for the sequential mode and seq_lds_rec.hip for Algorithm 1 (REC = true), so the
+// sets of kernels compile side by side.
 #pragma once
 
 #include <limits.h>
@@ -45,6 +46,7 @@
 #include <type_traits>
 
 #include "kernels.h"
+#include "seq_enum.h"
 
 namespace deft {
 
@@ -230,6 +232,14 @@ struct LdsLayout {
 constexpr int kMiscInts = 8;
 // Stages that are offered at most this many items are settled by enumeration of their subsets.
 constexpr int kEnumItems = 6;
+// Stages of this many items, or cells (items offered times capacity), are tried by enumeration: 12 us a stage, where a
+// sweep takes 0.35 us an item; with lists of up to kPoolEntries (a stage of longer ones is reduced to the
+// items that are open, some 20 to 50, and swept).  A mixed bag of 777 instances of up to 203 items: 0.125 ms, from 96 items on
+// 0.166, by cells from 500000 on alone 0.205, 0.36 without.  Not those with an item of a fifth of the weight offered (the bound is far from the optimum then:
+// 15 us for nothing, on the 185 us of 7 instances of 385 items at capacity 2619 of which three hold 85 % of the weight).
+constexpr int kPoolItems = 48;
+constexpr int64_t kPoolCells = 1200000;
+constexpr int kPoolEntries = 192;
 // Second M0 base of the add-TID write-back, in bytes above the first.
 constexpr int kSecondBase = 60416;
 
@@ -498,6 +508,8 @@ __device__ __forceinline__ int sweep_dispatch(int nchunk, int32_t *row, uint32_t
     return 0;
 }
 
+// POOL: stages of unrelated values are tried by enumeration first (seq_enum.h), in kernels of their own, since its
+// registers cost the calls that have no use for it 2 us.
 // WPE = wavefronts per SIMD the register budget is held to (LDS allows that many).
 // REC = false: the sequential mode.  REC = true: the modes that read more than row[C] off
 // one sweep, chosen by a.mode at run time:
@@ -506,7 +518,7 @@ __device__ __forceinline__ int sweep_dispatch(int nchunk, int32_t *row, uint32_t
 //   the capacity sweep (Sec. IV.C feedback): one sweep at the largest of the instance's
 //   capacities, then the value at each capacity is a cell of the final row and each
 //   capacity gets a walk of its own, the wavefronts of the instance sharing the walks.
-template <int T, int K, int G, int WPE, bool REC>
+template <int T, int K, int G, int WPE, bool REC, bool POOL>
 __global__ void __launch_bounds__(T == 64 ? 256 : T, WPE)
 seq_lds_kernel(BatchArgs a, LdsLayout lay, uint32_t *keep, int64_t keep_words_per_inst, OfferedItem *lists,
                int list_stride, unsigned long long *swept_cells)
@@ -546,7 +558,7 @@ seq_lds_kernel(BatchArgs a, LdsLayout lay, uint32_t *keep, int64_t keep_words_pe
     int32_t *row = misc + lay.guard_cells;
     const uint32_t row_off = lds_offset(row);
     // misc: [0] fault flags (bit 2: some value differs from its weight), [1] offered-item count,
-    //       [2..3] value sum, [4..5] fill-order seen mask, [6] the stage being swept, [7] tag of the
+    //       [2..3] value sum, then [2] the capacity it is swept at, [4..5] fill-order seen mask, [6] the stage being swept, [7] tag of the
     //       last row-is-full check that found an unfinished cell
 
     const int n = a.n_items[inst];
@@ -679,6 +691,12 @@ seq_lds_kernel(BatchArgs a, LdsLayout lay, uint32_t *keep, int64_t keep_words_pe
     // weight and value of item i0 + lane, as the serial wavefront's stage loop reads them
     auto item_w = [&](int i0, int i) { return i >= n ? 0 : i0 == 0 ? w_first : W[i]; };
     auto item_v = [&](int i0, int i) { return i >= n ? 0 : i0 == 0 ? v_first : V[i]; };
+    // (where the row's LDS holds the items and lists of some length)
+    int2 *const pool_items = reinterpret_cast<int2 *>(row);
+    const int pool_room = lay.row_cells * 4 - pool_items_bytes(n);
+    const bool pooled = POOL && !veqw && pool_room >= pool_space_bytes(n, kPool);
+    // A stage that is reduced: what is taken in any case, and the window left for the sweep (serial wavefront).
+    int fixed_value = 0, fixed_load = 0, sweep_C = 0;
     int s = 0;
     while (true) {
         // The serial wavefront prepares stages one after the other, settling those that need
@@ -688,9 +706,11 @@ seq_lds_kernel(BatchArgs a, LdsLayout lay, uint32_t *keep, int64_t keep_words_pe
         if (serial) {
             const int tid = sl;  // (the lane: this block addresses items as i0 + lane)
             int cnt = -1;
+            fixed_value = fixed_load = 0;
             for (; s < stages; ++s) {
                 const int j = stage_knapsack(s);
                 const int C = stage_capacity(j);
+                sweep_C = C;
                 OfferedItem *list = inst_lists + (size_t)s * list_stride;
                 if (levels) {
                     // Algorithm 1: the whole list is offered in generation order (an item heavier
@@ -720,13 +740,21 @@ seq_lds_kernel(BatchArgs a, LdsLayout lay, uint32_t *keep, int64_t keep_words_pe
                 // offered items: not yet placed and able to fit at all, ascending index
                 cnt = 0;
                 int unplaced = 0;
+                int heaviest = 0;
                 int offered_weight = 0;  // per lane at most 64 items of at most 2^24 each
+                unsigned long long worth = 0;  // what is open and of some value, laid out like `placed`
                 for (int i0 = 0; i0 < n; i0 += 64) {
                     const int i = i0 + tid;
                     const int w = item_w(i0, i);
                     const int v = item_v(i0, i);
                     const bool open = i < n && ((placed >> (i0 >> 6)) & 1ull) == 0;
                     const bool f = open && w <= C;
+                    if constexpr (POOL) {
+                        if (pooled) {
+                            pool_items[i] = make_int2(w, v);
+                            if (open && v > 0) worth |= 1ull << (i0 >> 6);
+                        }
+                    }
                     unplaced += __popcll(__ballot(open));
                     const unsigned long long mask = __ballot(f);
                     if (f) {
@@ -734,6 +762,7 @@ seq_lds_kernel(BatchArgs a, LdsLayout lay, uint32_t *keep, int64_t keep_words_pe
                         e.w = w; e.v = v; e.index = i; e.pad = -1;  // no level ends here
                         list[cnt + __popcll(mask & ((1ull << tid) - 1ull))] = e;
                         offered_weight += w;
+                        heaviest = max(heaviest, w);
                     }
                     cnt += __popcll(mask);
                 }
@@ -819,6 +848,44 @@ seq_lds_kernel(BatchArgs a, LdsLayout lay, uint32_t *keep, int64_t keep_words_pe
                             total += best_value;
                         }
                         cnt = -1;
+                    } else if constexpr (POOL) {
+                        pool_sync();
+                        PoolAnswer answer;
+                        const PoolOutcome outcome =
+                            pooled && (cnt >= kPoolItems || (int64_t)cnt * C >= kPoolCells) && pool_max(heaviest) <= offered_weight / 5
+                                ? pool_stage<true>(pool_items, reinterpret_cast<char *>(row) + pool_items_bytes(n), pool_room,
+                                                   kPoolEntries, n, C, worth, -1, tid, answer)
+                                : kPoolFailed;
+                        if (outcome == kPoolFound || outcome == kPoolReduced) {
+                            // (reduced: these are taken in any case)
+                            placed |= answer.chosen;
+                            for (unsigned long long bits = answer.chosen; bits; bits &= bits - 1)
+                                out_asg[__builtin_ctzll(bits) * 64 + tid] = j;
+                            if (tid == 0) {
+                                out_kv[j] = answer.value;
+                                out_kl[j] = answer.load;
+                                total += answer.value;
+                            }
+                            cnt = -1;
+                        }
+                        if (outcome == kPoolReduced) {
+                            fixed_value = answer.value;
+                            fixed_load = answer.load;
+                            sweep_C = C - answer.load;
+                            cnt = 0;
+                            for (int i0 = 0; i0 < n; i0 += 64) {
+                                const int2 it = pool_items[i0 + tid];
+                                const bool f = ((answer.open >> (i0 >> 6)) & 1ull) != 0 && it.x <= sweep_C;
+                                const unsigned long long mask = __ballot(f);
+                                if (f) {
+                                    OfferedItem e;
+                                    e.w = it.x; e.v = it.y; e.index = i0 + tid; e.pad = -1;
+                                    list[cnt + __popcll(mask & ((1ull << tid) - 1ull))] = e;
+                                }
+                                cnt += __popcll(mask);
+                            }
+                            if (cnt == 0) cnt = -1;
+                        }
                     }
                 }
                 if (cnt >= 0) break;  // this stage needs its sweep
@@ -826,6 +893,7 @@ seq_lds_kernel(BatchArgs a, LdsLayout lay, uint32_t *keep, int64_t keep_words_pe
             if (tid == 0) {
                 misc[1] = s < stages ? cnt : -1;
                 misc[6] = s;
+                if constexpr (POOL) misc[2] = sweep_C;
                 misc[7] = 0;  // no check of this stage has run yet
             }
         }
@@ -833,7 +901,7 @@ seq_lds_kernel(BatchArgs a, LdsLayout lay, uint32_t *keep, int64_t keep_words_pe
         if (uniform(misc[1]) < 0) break;
         s = uniform(misc[6]);
         const int j = stage_knapsack(s);
-        const int C = stage_capacity(j);
+        const int C = POOL ? uniform(misc[2]) : stage_capacity(j);
         OfferedItem *list = inst_lists + (size_t)s * list_stride;
 
         const int nchunk = uniform((C / T + G) / G);  // G-slot chunks covering cells 0 .. C
@@ -977,8 +1045,8 @@ seq_lds_kernel(BatchArgs a, LdsLayout lay, uint32_t *keep, int64_t keep_words_pe
                     out_asg[b * 64 + L] = j;
                 }
                 if (L == 0) {
-                    out_kv[j] = value;
-                    out_kl[j] = walk_cap - c;
+                    out_kv[j] = value + fixed_value;
+                    out_kl[j] = walk_cap - c + fixed_load;
                     if constexpr (REC) {  // slot 1 reports the level: items left off the list, its remaining time
                         out_kv[1] = n - best.length;
                         out_kl[1] = value > 0 ? walk_cap : 0;
@@ -1019,8 +1087,8 @@ struct Variant {
 };
 
 #define DEFT_VARIANT(T, K, G, WPE, GUARD) \
-    { T, K, G, GUARD, reinterpret_cast<const void *>(&seq_lds_kernel<T, K, G, WPE, REC>) }
-template <bool REC>
+    { T, K, G, GUARD, reinterpret_cast<const void *>(&seq_lds_kernel<T, K, G, WPE, REC, POOL>) }
+template <bool REC, bool POOL = false>
 const Variant *variant_table()
 {
     static const Variant table[] = {
@@ -1038,7 +1106,7 @@ const Variant *variant_table()
 #undef DEFT_VARIANT
 constexpr int kNumVariants = 8;
 
-template <int T, int K, int G, int WPE, bool REC>
+template <int T, int K, int G, int WPE, bool REC, bool POOL>
 hipError_t launch_one(const SeqLdsPlan &p, const BatchArgs &a, void *scratch, hipStream_t st,
                       unsigned long long *swept_cells)
 {
@@ -1046,24 +1114,24 @@ hipError_t launch_one(const SeqLdsPlan &p, const BatchArgs &a, void *scratch, hi
     const unsigned grid = (unsigned)((a.batch + p.inst_per_wg - 1) / p.inst_per_wg);
     uint32_t *keep = static_cast<uint32_t *>(scratch);
     OfferedItem *lists = reinterpret_cast<OfferedItem *>(static_cast<char *>(scratch) + p.keep_bytes);
-    hipLaunchKernelGGL((seq_lds_kernel<T, K, G, WPE, REC>), dim3(grid), dim3(p.wg_threads), (size_t)p.lds_bytes, st,
+    hipLaunchKernelGGL((seq_lds_kernel<T, K, G, WPE, REC, POOL>), dim3(grid), dim3(p.wg_threads), (size_t)p.lds_bytes, st,
                        a, lay, keep, p.keep_words_per_inst, lists, p.n_pad, swept_cells);
     return hipGetLastError();
 }
 
-template <bool REC>
+template <bool REC, bool POOL = false>
 hipError_t launch_variant(const SeqLdsPlan &p, const BatchArgs &a, void *scratch, hipStream_t st,
                           unsigned long long *swept_cells)
 {
     switch (p.variant) {
-    case 0: return launch_one<64, 16, 4, 5, REC>(p, a, scratch, st, swept_cells);
-    case 1: return launch_one<256, 16, 4, 7, REC>(p, a, scratch, st, swept_cells);
-    case 2: return launch_one<256, 32, 4, 4, REC>(p, a, scratch, st, swept_cells);
-    case 3: return launch_one<512, 20, 1, 8, REC>(p, a, scratch, st, swept_cells);
-    case 4: return launch_one<512, 26, 1, 6, REC>(p, a, scratch, st, swept_cells);
-    case 5: return launch_one<768, 26, 1, 6, REC>(p, a, scratch, st, swept_cells);
-    case 6: return launch_one<1024, 26, 1, 4, REC>(p, a, scratch, st, swept_cells);
-    case 7: return launch_one<1024, 38, 2, 4, REC>(p, a, scratch, st, swept_cells);
+    case 0: return launch_one<64, 16, 4, 5, REC, POOL>(p, a, scratch, st, swept_cells);
+    case 1: return launch_one<256, 16, 4, 7, REC, POOL>(p, a, scratch, st, swept_cells);
+    case 2: return launch_one<256, 32, 4, 4, REC, POOL>(p, a, scratch, st, swept_cells);
+    case 3: return launch_one<512, 20, 1, 8, REC, POOL>(p, a, scratch, st, swept_cells);
+    case 4: return launch_one<512, 26, 1, 6, REC, POOL>(p, a, scratch, st, swept_cells);
+    case 5: return launch_one<768, 26, 1, 6, REC, POOL>(p, a, scratch, st, swept_cells);
+    case 6: return launch_one<1024, 26, 1, 4, REC, POOL>(p, a, scratch, st, swept_cells);
+    case 7: return launch_one<1024, 38, 2, 4, REC, POOL>(p, a, scratch, st, swept_cells);
     default: return hipErrorInvalidValue;
     }
 }
@@ -1072,10 +1140,10 @@ hipError_t launch_variant(const SeqLdsPlan &p, const BatchArgs &a, void *scratch
 // workgroups the runtime would place on a compute unit.  The attribute belongs to the
 // kernel, not to the handle, so it is set to the most any handle on this variant can ask
 // for (the variant's full row): a later, smaller handle never lowers it under an earlier one.
-template <bool REC>
+template <bool REC, bool POOL = false>
 hipError_t prepare_variant(const SeqLdsPlan &plan, int *wg_per_cu)
 {
-    const Variant &v = variant_table<REC>()[plan.variant];
+    const Variant &v = variant_table<REC, POOL>()[plan.variant];
     const void *fn = v.fn;
     const int full_row = (v.guard + v.cells * v.threads) * 4 * plan.inst_per_wg;
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, full_row);

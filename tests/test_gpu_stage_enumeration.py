@@ -54,6 +54,24 @@ def test_more_instances_than_compute_units(binding, oracle):
     run(binding, oracle, _batch(72000, 300, 40, 41000, "priority", m=2), max_capacity=41000)
 
 
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("n,cap", [(600, 1000), (130, 4000), (64, 8100), (65, 10200), (200, 13000), (60, 19900), (40, 26600), (300, 38900)])
+def test_every_variant_of_rows_in_lds(binding, oracle, kind, n, cap):
+    """Items times capacity on both sides of where it is tried; stages settled, reduced and left alone."""
+    run(binding, oracle, _batch(73000 + cap, 6, n, cap, kind), max_capacity=cap)
+
+
+@pytest.mark.parametrize("kind", ["priority", "alike", "free"])
+def test_without_a_handle(binding, oracle, kind):
+    import torch
+    from tests.test_gpu_parity import assert_same
+    kb = _batch(74000, 4, 150, 9000, kind)
+    ref = oracle.solve_batch(kb, nthreads=16, cap_limit=9000)
+    out = binding.solve_batch_static(binding.DeviceBatch(kb, torch.device("cuda", 0)), 9000)
+    torch.cuda.synchronize()
+    assert_same(kb, out, ref)
+
+
 def test_faults_beside_good_instances(binding, oracle):
     kb = _batch(75000, 8, 50, 45000, "priority")
     kb.weights[1, 3] = 0
