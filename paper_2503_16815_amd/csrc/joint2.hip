@@ -1,4 +1,5 @@
-// Joint two-link solve (Sec. III.C, Problem 2 with one weight per link).  The
+// Joint two-link solve (Sec. III.C, Problem 2 with one weight per link).  Most instances are answered by enumeration
+// (joint2_enum.h); what follows is the table sweep, for those it leaves.  The
 // (C1+1) x (C2+1) table does not fit LDS, so it lives in global memory (two
 // copies, item q reads copy q & 1 and writes the other) and streams through an
 // LDS window once per item:
@@ -28,16 +29,16 @@
 #include <type_traits>
 
 #include "instance_check.h"
+#include "joint2_enum.h"
 
 namespace deft {
 
 namespace {
 
-constexpr int kThreads = 256;
-
 struct InstState {
     int32_t status, n, c1, c2;
 };
+constexpr int kAnswered = -1;  // status of an instance that the enumeration has answered: none of the codes that callers see
 
 struct Scratch {
     int32_t *tab;       // [batch][2][rows][pitch]
@@ -57,21 +58,6 @@ Scratch carve(const JointPlan &p, void *base)
     c += align256((size_t)p.max_batch * p.max_items * p.rows * (p.pitch / 64) * 16);
     s.state = reinterpret_cast<InstState *>(c);
     return s;
-}
-
-__global__ void __launch_bounds__(kThreads) jt_init(BatchArgs a, InstState *state)
-{
-    const int inst = blockIdx.x;
-    const int status = check_instance(a, inst, true);
-    clear_outputs(a, inst, status);
-    if (threadIdx.x == 0) {
-        InstState st;
-        st.status = status;
-        st.n = status == DEFT_OK ? a.n_items[inst] : 0;
-        st.c1 = status == DEFT_OK ? a.capacities[(size_t)inst * a.knap_stride] : -1;
-        st.c2 = status == DEFT_OK ? a.capacities[(size_t)inst * a.knap_stride + 1] : -1;
-        state[inst] = st;
-    }
 }
 
 constexpr int kSweepThreads = 1024;  // one workgroup per instance
@@ -389,6 +375,9 @@ void joint_plan(int32_t max_c1, int32_t max_c2, int32_t max_items, int32_t max_b
 
 hipError_t joint_prepare(const JointPlan &p)
 {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&jt_enumerate<InstState>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(EnumShared));
+    if (e != hipSuccess) return e;
     return hipFuncSetAttribute(reinterpret_cast<const void *>(&jt_sweep_all),
                                hipFuncAttributeMaxDynamicSharedMemorySize, p.lds_bytes);
 }
@@ -396,8 +385,8 @@ hipError_t joint_prepare(const JointPlan &p)
 hipError_t joint_launch(const JointPlan &p, const BatchArgs &a, void *scratch, hipStream_t st, Profiler *prof)
 {
     const Scratch s = carve(p, scratch);
-    hipLaunchKernelGGL(jt_init, dim3(a.batch), dim3(kThreads), 0, st, a, s.state);
     if (prof) prof->sweep_begin(st);
+    hipLaunchKernelGGL(jt_enumerate<InstState>, dim3((unsigned)a.batch), dim3(kEnumThreads), sizeof(EnumShared), st, a, s.state, kAnswered);
     hipLaunchKernelGGL(jt_sweep_all, dim3((unsigned)a.batch), dim3(kSweepThreads), (size_t)p.lds_bytes, st, a, s.state,
                        s.tab, s.choice, p.rows, p.pitch, p.max_items, p.ring_rows, p.lds_pitch);
     if (prof) prof->sweep_end(st);

@@ -1,0 +1,70 @@
+"""The two-link solve by enumeration of the selections that can be optimal, and what it leaves to the table sweep:
+lists around the fewest and the most items it takes, values that tie (the smallest choice number has to come out),
+items of no value, items that fit one link or none, links that hold everything, lists that run over, capacities
+around the greatest it takes.  Bit-exact against the oracle."""
+import numpy as np
+import pytest
+
+from paper_2503_16815_amd import workloads as W
+from tests.test_gpu_parity import binding, run  # noqa: F401  (binding is a fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def _batch(seed, batch, n, w_hi, c1, c2, kind="free"):
+    r = np.random.Generator(np.random.PCG64(seed))
+    kb = W.random_joint(seed, batch=batch, n_max=n, w_hi=w_hi, v_hi=1000, c1_hi=c1, c2_hi=c2, ragged=False)
+    if kind == "alike":          # few kinds of items: many selections are as good
+        at = r.integers(0, 5, size=(batch, n))
+        kb.weights[:, 0], kb.weights[:, 1] = 1 + np.array([1, 3, 4, 6, 7])[at], 2 + np.array([5, 9, 12, 14, 25])[at]
+        kb.values[:] = np.array([7, 11, 15, 22, 30])[at]
+    elif kind == "ratio":        # link 1 takes three times link 0's time throughout: moving items costs nothing
+        kb.weights[:, 1] = np.minimum(3 * kb.weights[:, 0].astype(np.int64), 2 ** 31 - 1)
+    elif kind == "time":         # values are the times on link 0
+        kb.values[:] = kb.weights[:, 0]
+    elif kind == "great":
+        kb.values[:] = r.integers(1, (1 << 30) // n, size=kb.values.shape)
+    elif kind == "nothing":      # half of the items are worth nothing, some fit no link
+        kb.values[:, ::2] = 0
+        kb.weights[:, :, 3::7] = 2 ** 31 - 1
+    kb.capacities[:, 0] = r.integers(max(1, c1 // 2), c1 + 1, size=batch)
+    kb.capacities[:, 1] = r.integers(max(1, c2 // 2), c2 + 1, size=batch)
+    kb.capacities[0] = (c1, c2)
+    return kb
+
+
+KINDS = ["free", "alike", "ratio", "time", "great", "nothing"]
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("n,w_hi,c1,c2", [(15, 20, 60, 90), (16, 20, 60, 90), (33, 30, 200, 150), (64, 40, 300, 400), (65, 12, 120, 500),
+                                          (150, 30, 180, 170)])
+def test_kinds_of_lists(binding, oracle, kind, n, w_hi, c1, c2):
+    run(binding, oracle, _batch(81000 + n, 6, n, w_hi, c1, c2, kind))
+
+
+@pytest.mark.parametrize("c1,c2", [(768, 40), (769, 40), (40, 768), (40, 769), (1, 300), (300, 1), (127, 63), (128, 64), (129, 65)])
+def test_capacities_around_the_cells_and_the_limit(binding, oracle, c1, c2):
+    run(binding, oracle, _batch(82000 + c1 + c2, 4, 40, max(4, min(c1, c2) // 4), c1, c2))
+
+
+@pytest.mark.parametrize("n", [1023, 1024, 1025])
+def test_as_many_items_as_threads(binding, oracle, n):
+    run(binding, oracle, _batch(83000 + n, 2, n, 9, 70, 60))
+
+
+def test_links_that_hold_everything(binding, oracle):
+    """All items of value fit link 0; fit both links together; all but one do."""
+    kb = _batch(84000, 9, 30, 12, 400, 700)
+    total = kb.weights[:, 0].sum(axis=1)
+    kb.capacities[:, 0] = np.minimum(400, np.array([total[b] + (0, -1, -40)[b % 3] for b in range(9)]))
+    run(binding, oracle, kb)
+
+
+def test_faults_beside_good_instances(binding, oracle):
+    kb = _batch(85000, 6, 24, 30, 150, 150)
+    kb.weights[1, 1, 3] = 0
+    kb.values[2, 4] = -1
+    kb.capacities[3, 1] = -1
+    kb.n_items[4] = 0
+    run(binding, oracle, kb)
