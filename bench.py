@@ -448,6 +448,11 @@ def run_solver(args):
     traffic = traffic_source = None
     kernel = ("seq_bits_kernel" if by_sums else
               "seq_lds_kernel" if (seq and info.seq_path in (1, 2, 4)) else ("sg_stream" if seq else "jt_sweep_all"))
+    # two-link instances and stages on rows in global memory are settled by enumeration where that can be done: hardly
+    # any of the cells counted above is evaluated, the rate is an effective one and no roofline of cells applies
+    enumerated = not seq or (info.seq_path == 3 and calls[0].mode == 0)
+    if enumerated:
+        kernel = "seq_enum_kernel" if seq else "jt_enumerate"
     tf = os.path.join(ROOT, "profiles", f"{kernel}_{args.workload}_traffic.txt")
     if plain_run and os.path.exists(tf):
         try:
@@ -468,17 +473,18 @@ def run_solver(args):
         alu=dict(ops_per_cell=algo["ops_per_cell"], peak_lane_ops_per_s=PEAK_INT_LANE_OPS,
                  frac=(swept_step * args.steps * algo["ops_per_cell"] / sweep_s) / PEAK_INT_LANE_OPS
                  if sweep_s > 0 else 0.0))
-    if not seq:
-        # the table streams from HBM (the bound above); the LDS side of the same kernel, for the
-        # record: two shifted reads and one write per cell
-        roofline["lds"] = dict(bytes_per_cell=12.0, peak=PEAK_LDS_GBS,
-                               frac=(swept_step * args.steps * 12.0 / sweep_s / 1e9) / PEAK_LDS_GBS if sweep_s > 0 else 0.0)
+    if enumerated:
+        roofline = dict(bound="latency", achieved=0.0, peak=peak, unit="GB/s", frac=0.0, traffic=None, traffic_source=None,
+                        kernel=kernel, launches=launches, avg_launch_ms=roofline["avg_launch_ms"],
+                        swept_cell_updates_per_s=0.0, bytes_per_cell=0.0, alu=dict(roofline["alu"], frac=0.0))
     line = dict(
         metric="knapsack DP cell-updates/sec", value=value, unit="cell-updates/s", n_gpus=1,
         steps=args.steps, warmup=args.warmup, ms_per_step=ms_step, higher_is_better=True, scaling="weak",
         vs_baseline=None, dtype="int32", data="synthetic",
         config=dict(workload=desc,
-                    value_counts=("cells up to the capacity of the items the sweeps go through (cell_updates_swept_per_step), "
+                    value_counts=("cells that a sweep of the job would go through (cell_updates_swept_per_step): settled by "
+                                  "enumeration, hardly any is evaluated; " if enumerated else
+                                  "cells up to the capacity of the items the sweeps go through (cell_updates_swept_per_step), "
                                   + ("32 of them an instruction on the bit-set kernels; " if by_sums else
                                      "of which the streamed sweep computes a band; " if kernel == "sg_stream" else
                                      "every one evaluated; ")
@@ -514,8 +520,8 @@ def compact(line: dict) -> dict:
                              unit=r["unit"], frac=r["frac"], alu_frac=r["alu"]["frac"],
                              alu_ops_per_cell=r["alu"]["ops_per_cell"]),
                parity_vs_oracle=line["parity_vs_oracle"])
-    if "lds" in r:
-        out["roofline"][f"lds_frac_at_{r['lds']['bytes_per_cell']:g}_bytes_per_cell"] = r["lds"]["frac"]
+    if r["bound"] == "latency":   # settled by enumeration: what a sweep would go through
+        out["cell_updates_of_a_sweep_per_step"] = out.pop("cell_updates_evaluated_per_step")
     for key in ("instances_per_s", "candidate_iterations_per_s", "effective_cell_updates_per_s", "parity_checked"):
         if key in line:
             out[key] = line[key]

@@ -353,11 +353,12 @@ typedef struct {
     int64_t streamed_row_cells; /* SEQUENTIAL and CAPACITY_SWEEP with rows in global memory:
                               row cells read from plus row cells written to global memory
                               by the sweeps, summed over instances and stages (a pass over a
-                              row may serve seven items); 0 on the other paths             */
+                              row may serve seven items); stages settled by enumeration
+                              add nothing; 0 on the other paths                            */
     int64_t swept_cell_updates; /* rows in LDS (seq_path 1 or 2): cell-updates the sweeps
                               evaluated, C - w + 1 for every item a stage's sweep went
-                              through (stages settled without a sweep and the items after
-                              a full row add nothing), and the same count from the bit-set
+                              through (stages settled without a sweep, by enumeration for
+                              instance, and the items after a full row add nothing), and the same count from the bit-set
                               rows on those handles; 0 on the other paths                 */
 } deft_knapsack_profile_t;
 
