@@ -25,8 +25,8 @@
 // What bounds it: latency.  One workgroup owns an instance; a round is a chain of barriers (one for an item of each group
 // once the lists are long), its pairs are lookups in LDS at places of the lanes' own (a gather of 64 words meets each
 // bank about five times), and a launch lasts as long as its hardest instance.  Half of the instances of the two-link batch
-// are done after 100 us (prices 8, losses 4, three rounds of lists 12, sorting 9, pairs 35), the hardest after 0.5 to 1.9 ms;
-// about one of 3000 runs over.  The table sweep takes 6.36 ms: 256 instances, by the seed, 0.5 to 1.9 ms where none is left
+// are done after 100 us (prices 8, losses 4, three rounds of lists 12, sorting 9 to 13, pairs 37 to 48), the hardest after 0.64 to 1.94 ms;
+// about one of 3000 runs over.  The table sweep takes 6.36 ms: 256 instances, by the seed, 0.64 to 1.94 ms where none is left
 // to it, 6.1 where one is.  Few instances gain most: two of 64 items (C1 = 326, C2 = 112) 1.93 -> 0.07 ms.  Where the links hold
 // nearly everything there is next to no loss in any choice, and time for nothing is spent (175 instances of 39 items of up
 // to 35, 476 and 254: 1.15 -> 1.6 ms).

@@ -17,8 +17,8 @@
 // All quantities that decide are whole numbers: losses in units of 2^-F, rounded down by `coarse` bits in the lists.
 //
 // Bound by latency: one wavefront works through a few thousand dependent steps.  GPT-2 windows in 1 us units (148
-// items with priorities), us a stage, half of the stages and 97 of 100: price 2.2 and 2.3, losses and pool 4.5 and 5.6,
-// lists 2 and 11, pairs 4 and 16; the sweep of the same stage takes 2000.  Six items of a list are spelled
+// items with priorities), us a stage, half of the stages and 97 of 100: price 2.2 and 2.3, losses and pool 4.5 and 4.9,
+// lists 1 to 2 and 6 to 10, pairs 4 and 16; the sweep of the same stage takes 2000.  Six items of a list are spelled
 // out at once, a subset for every lane (a step for each of them: 4 us instead of 1); the price and the pool are found
 // by three candidates at a time from registers (by one from LDS: 4 and 5 us instead of 2 and 4).
 #pragma once
