@@ -45,7 +45,7 @@ constexpr int kEnumThreads = 1024;
 constexpr int kEnumWaves = kEnumThreads / 64;
 constexpr int kEnumItems = kEnumThreads;  // a thread per item
 constexpr int kEnumCapacity = 768;        // what P1 and P2 together (42 items) change on a link stays within 16 bits
-constexpr int kEnumOpen = 64;             // items that may have open choices, and choices open in the last round
+constexpr int kEnumOpen = 64;             // items that may have open choices (the listed ones), and choices open in the last round
 constexpr int kEnumRounds = 7;            // 16, 24, ..., 64 open choices
 // Shorter lists are swept at once: 248 instances of 8 items (C1 = 75, C2 = 253) 92 us, by enumeration 155; four of 19
 // items (138 and 407) 412 and 57.
@@ -96,6 +96,7 @@ struct EnumShared {
     int32_t q_default[2];                     // what the default choices of group Q's items take
     int32_t sum[4];
     int32_t threshold[kEnumRounds];
+    int32_t unlisted;                         // the least loss of a departure of an item that is not listed
     int32_t most[2];
     int32_t bound[4], bound_at[4];            // of a grid of prices, by quarters
     int32_t wave_sum[kEnumWaves];
@@ -177,7 +178,7 @@ __global__ void __launch_bounds__(kEnumThreads) jt_enumerate(BatchArgs a, State 
     if (tid < 4) s.sum[tid] = 0;
     if (tid < 2) s.most[tid] = 0;
     if (tid < kEnumRounds) s.threshold[tid] = kNever;
-    if (tid == 0) s.over = 0, s.least = kNever;
+    if (tid == 0) s.over = 0, s.least = s.unlisted = kNever;
     __syncthreads();
     const int waves_used = (n + 63) >> 6;
     if (wave < waves_used) {
@@ -347,6 +348,7 @@ __global__ void __launch_bounds__(kEnumThreads) jt_enumerate(BatchArgs a, State 
         };
         threshold(place_a, loss_a);
         threshold(place_b, loss_b);
+        if (rank == kEnumOpen) s.unlisted = loss_a;
         if (rank < kEnumOpen && loss_a < kNever) {
             auto takes = [&](int choice) { return choice == 1 ? w0 * 65536 : choice == 2 ? w1 : 0; };
             s.loss[0][rank] = loss_a;
@@ -417,9 +419,10 @@ __global__ void __launch_bounds__(kEnumThreads) jt_enumerate(BatchArgs a, State 
     for (int round = 0; round < kEnumRounds;) {
         int G = s.threshold[round] - 1;
         // What is left to look through is known: straight to it, unless the choices open then are so many that a better
-        // selection, met by a round before, will be worth its time.
+        // selection, met by a round before, will be worth its time, or some of them are of items that are not listed.
+        // (A round's own G leaves at most 64 choices open, and the items of those are listed.)
         const int choices = __popcll(__ballot(s.loss[0][lane] <= least)) + __popcll(__ballot(s.loss[1][lane] <= least));
-        const bool leap = may_leap && least > G && choices <= kLeapChoices;
+        const bool leap = may_leap && least > G && least < s.unlisted && choices <= kLeapChoices;
         if (leap || least <= G) G = least;
         if (G <= last_G) {
             ++round;

@@ -68,3 +68,51 @@ def test_faults_beside_good_instances(binding, oracle):
     kb.capacities[3, 1] = -1
     kb.n_items[4] = 0
     run(binding, oracle, kb)
+
+
+def _one_link(items, c, link, order=None):
+    """Items (weight, value) that fit `link` alone, capacity c there; in the order given or as listed."""
+    w, v = np.array(items, dtype=np.int64).T
+    if order is not None:
+        w, v = w[order], v[order]
+    weights = np.full((1, 2, len(w)), 50, dtype=np.int64)
+    weights[0, link] = w
+    caps = [[c, 1]] if link == 0 else [[1, c]]
+    return W.KnapsackBatch(name=f"one_link_{len(w)}_{c}_{link}", mode=W.MODE_JOINT2, batch=1, item_stride=len(w), knap_stride=2,
+                           n_items=np.array([len(w)], np.int32), n_knapsacks=np.array([2], np.int32),
+                           weights=weights.astype(np.int32), values=v[None].astype(np.int32),
+                           capacities=np.array(caps, np.int32))
+
+
+@pytest.mark.parametrize("link", [0, 1])
+def test_more_items_as_close_to_the_price_than_are_listed(binding, oracle, link):
+    """The best selection met first leaves more than 64 items to decide, none of them twice: the listed 64 are not all."""
+    first = [(5, 500)] * 10 + [(4, 570)] * 70 + [(3, 475)]
+    second = [(2, v) for v in range(251, 284)] + [(2, v) for v in range(117, 150)] + [(2, 200), (1, 5)]
+    r = np.random.Generator(np.random.PCG64(86000))
+    for items, c in ((first, 310), (second, 67)):
+        run(binding, oracle, _one_link(items, c, link))
+        for _ in range(3):
+            run(binding, oracle, _one_link(items, c, link, r.permutation(len(items))))
+
+
+@pytest.mark.parametrize("link", [0, 1])
+@pytest.mark.parametrize("either", [29, 30, 31, 32, 33, 34, 40])
+def test_as_many_items_to_decide_as_are_listed(binding, oracle, link, either):
+    """2 x either + 2 items around the listed 64, with distinct losses and with ties (the highest index gives way)."""
+    items = [(2, 251 + i) for i in range(either)] + [(2, 149 - i) for i in range(either)] + [(2, 200), (1, 5)]
+    ties = [(2, 251 + i // 4) for i in range(either)] + [(2, 149 - i // 4) for i in range(either)] + [(2, 200), (1, 5)]
+    for x in (items, ties):
+        run(binding, oracle, _one_link(x, 2 * either + 1, link))
+        run(binding, oracle, _one_link(x, 2 * either + 1, link, np.arange(len(x))[::-1]))
+
+
+@pytest.mark.parametrize("n", [65, 66, 80, 130, 300])
+def test_many_items_that_fit_one_link_only(binding, oracle, n):
+    kb = _batch(87000 + n, 8, n, 6, 200, 150)
+    kb.values[:] = 100 * kb.weights[:, 0] + np.random.Generator(np.random.PCG64(n)).integers(-60, 61, size=kb.values.shape)
+    kb.weights[:4, 1] = 151
+    kb.values[4:] = np.maximum(1, kb.values[4:])
+    kb.weights[4:, 1], kb.weights[4:, 0] = np.minimum(kb.weights[4:, 0], 150), 201
+    kb.values[:] = np.maximum(kb.values, 1)
+    run(binding, oracle, kb)
