@@ -742,7 +742,8 @@ seq_lds_kernel(BatchArgs a, LdsLayout lay, uint32_t *keep, int64_t keep_words_pe
                 int unplaced = 0;
                 int heaviest = 0;
                 int offered_weight = 0;  // per lane at most 64 items of at most 2^24 each
-                unsigned long long worth = 0;  // what is open and of some value, laid out like `placed`
+                unsigned long long worth = 0;  // what is offered and of some value, laid out like `placed`
+                int worth_weight = 0, worth_value = 0;
                 for (int i0 = 0; i0 < n; i0 += 64) {
                     const int i = i0 + tid;
                     const int w = item_w(i0, i);
@@ -752,7 +753,7 @@ seq_lds_kernel(BatchArgs a, LdsLayout lay, uint32_t *keep, int64_t keep_words_pe
                     if constexpr (POOL) {
                         if (pooled) {
                             pool_items[i] = make_int2(w, v);
-                            if (open && v > 0) worth |= 1ull << (i0 >> 6);
+                            if (f && v > 0) worth |= 1ull << (i0 >> 6), worth_weight += w, worth_value += v;
                         }
                     }
                     unplaced += __popcll(__ballot(open));
@@ -851,11 +852,17 @@ seq_lds_kernel(BatchArgs a, LdsLayout lay, uint32_t *keep, int64_t keep_words_pe
                     } else if constexpr (POOL) {
                         pool_sync();
                         PoolAnswer answer;
-                        const PoolOutcome outcome =
-                            pooled && (cnt >= kPoolItems || (int64_t)cnt * C >= kPoolCells) && pool_max(heaviest) <= offered_weight / 5
-                                ? pool_stage<true>(pool_items, reinterpret_cast<char *>(row) + pool_items_bytes(n), pool_room,
-                                                   kPoolEntries, n, C, worth, -1, tid, answer)
-                                : kPoolFailed;
+                        PoolOutcome outcome = kPoolFailed;
+                        if (pooled && (cnt >= kPoolItems || (int64_t)cnt * C >= kPoolCells) && pool_max(heaviest) <= offered_weight / 5) {
+                            worth_weight = wave_sum(min(worth_weight, (1 << 24) + 1));
+                            if (worth_weight <= C) {  // the others are worth nothing
+                                answer = PoolAnswer{wave_sum(worth_value), worth_weight, worth, 0};
+                                outcome = kPoolFound;
+                            } else {
+                                outcome = pool_stage<true>(pool_items, reinterpret_cast<char *>(row) + pool_items_bytes(n), pool_room,
+                                                           kPoolEntries, n, C, worth, -1, tid, answer);
+                            }
+                        }
                         if (outcome == kPoolFound || outcome == kPoolReduced) {
                             // (reduced: these are taken in any case)
                             placed |= answer.chosen;

@@ -82,3 +82,47 @@ def test_faults_beside_good_instances(binding, oracle):
     kb.values[6] = 2 ** 30
     kb.fill_order[7] = 0
     run(binding, oracle, kb, max_capacity=45000)
+
+
+def _stages(items, caps, name):
+    w, v = np.array(items, dtype=np.int64).T
+    return W._sequential(name, w[None], v[None], [caps])
+
+
+def _both_entry_points(binding, oracle, kb, max_capacity):
+    import torch
+    from tests.test_gpu_parity import assert_same
+    ref = run(binding, oracle, kb, max_capacity=max_capacity)
+    out = binding.solve_batch_static(binding.DeviceBatch(kb, torch.device("cuda", 0)), max_capacity)
+    torch.cuda.synchronize()
+    assert_same(kb, out, ref)
+
+
+GREATEST = 2 ** 31 - 1
+
+
+@pytest.mark.parametrize("weight", [GREATEST, GREATEST - 1, 2 ** 30, 2 ** 30 + 1, 14001, 20001])
+def test_items_heavier_than_every_window(binding, oracle, weight):
+    """They are never open, whatever they are worth: their weights do not add up in 32 bits, and they set no price."""
+    first = [(500, 0)] * 96 + [(10, 10), (700, 300)] + [(weight, 5)] * 3
+    second = [(1000, 0)] * 60 + [(weight, 9)] * 3
+    _both_entry_points(binding, oracle, _stages(first, [14000], "worthless_and_too_heavy"), 14000)
+    _both_entry_points(binding, oracle, _stages(second, [20000], "nothing_to_take"), 20000)
+    r = np.random.Generator(np.random.PCG64(76000))
+    for count in (1, 2, 4, 33):
+        kb = _batch(76000 + count, 6, 150, 13000, "priority")
+        for b in range(6):
+            at = r.choice(150, size=count, replace=False)
+            kb.weights[b, at], kb.values[b, at] = weight, r.integers(1, 1 << 22, size=count)
+        _both_entry_points(binding, oracle, kb, 20000)
+
+
+@pytest.mark.parametrize("kind", ["priority", "free"])
+def test_windows_that_some_items_do_not_fit(binding, oracle, kind):
+    """Windows from the largest to the smallest, the last ones smaller than many of the items still open."""
+    kb = _batch(77000, 12, 150, 13000, kind, m=6)
+    kb.capacities[:] = np.array([13000, 6000, 900, 250, 60, 15])
+    kb.fill_order = None
+    _both_entry_points(binding, oracle, kb, 13000)
+    kb.values[:, 10:] = 0                     # what is worth something fits, or nearly, beside what is not
+    _both_entry_points(binding, oracle, kb, 13000)
