@@ -706,11 +706,11 @@ seq_lds_kernel(BatchArgs a, LdsLayout lay, uint32_t *keep, int64_t keep_words_pe
         if (serial) {
             const int tid = sl;  // (the lane: this block addresses items as i0 + lane)
             int cnt = -1;
-            fixed_value = fixed_load = 0;
             for (; s < stages; ++s) {
                 const int j = stage_knapsack(s);
                 const int C = stage_capacity(j);
                 sweep_C = C;
+                fixed_value = fixed_load = 0;  // (the stage before may have been reduced to nothing)
                 OfferedItem *list = inst_lists + (size_t)s * list_stride;
                 if (levels) {
                     // Algorithm 1: the whole list is offered in generation order (an item heavier

@@ -126,3 +126,12 @@ def test_windows_that_some_items_do_not_fit(binding, oracle, kind):
     _both_entry_points(binding, oracle, kb, 13000)
     kb.values[:, 10:] = 0                     # what is worth something fits, or nearly, beside what is not
     _both_entry_points(binding, oracle, kb, 13000)
+
+
+def test_a_stage_reduced_to_nothing_before_one_that_is_swept(binding, oracle):
+    """What the first stage takes in any case is not part of the second one's answer."""
+    light, close = [(10, 10000)] * 40, [(w, w - 1 - (7 * i) % 60) for i, w in enumerate(range(311, 371))]
+    for caps in ([700, 340], [700, 340, 340], [700, 340, 700]):
+        _both_entry_points(binding, oracle, _stages(light + close, caps, f"reduced_{len(caps)}"), 7000)
+    kb = _batch(78000, 300, 100, 7000, "rates", m=4)
+    _both_entry_points(binding, oracle, kb, 7000)
