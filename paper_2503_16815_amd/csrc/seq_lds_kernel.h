@@ -654,14 +654,15 @@ seq_lds_kernel(BatchArgs a, LdsLayout lay, uint32_t *keep, int64_t keep_words_pe
         else if (vs >= (1ull << 31)) status = DEFT_ERR_OVERFLOW;
     }
     status = uniform(status);
-    if (tid == 0) {
-        for (int j = 0; j < a.knap_stride; ++j) { out_kv[j] = 0; out_kl[j] = 0; }
-        a.status[inst] = status;
+    // Cleared by the wavefront that stores the answers, whose stores stay in order: it settles stages before it meets
+    // the other wavefronts at a barrier.  Knapsack ids start at "none"; the capacity sweep's masks start empty.
+    if (serial) {
+        for (int j = sl; j < a.knap_stride; j += 64) { out_kv[j] = 0; out_kl[j] = 0; }
+        for (int i = sl; i < a.item_stride; i += 64) out_asg[i] = caps_sweep ? 0 : -1;
+        if (sl == 0) a.status[inst] = status;
     }
-    // knapsack ids start at "none"; the capacity sweep's masks start empty
-    for (int i = tid; i < a.item_stride; i += T) out_asg[i] = caps_sweep ? 0 : -1;
     if (status != DEFT_OK) {
-        if (tid == 0) a.total_value[inst] = 0;
+        if (serial && sl == 0) a.total_value[inst] = 0;
         return;
     }
 
