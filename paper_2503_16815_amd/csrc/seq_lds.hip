@@ -65,14 +65,18 @@ hipError_t seq_lds_prepare(SeqLdsPlan *plan)
 // 6 instances of 380 items at capacity 18914 630 and 70, 212 of 600 at 6695 646 and 103, 3082 of 55 at 20469 1189 and 400,
 // 2461 of 241 at 2529 390 and 180, 56 of 155 at 5108 110 and 40; 160 of 100 at 14000, values near the weights, 165 and 188,
 // 8 of those 153 and 82, 1000 of them 468 and 314.  Below the line 160 of 66 at 9000 94 and 121, 7 of 123 at 3537 104 and 119,
-// 476 of 402 at 699 264 and 287; calls of 16 to 24 us would pay 2 for the larger kernel.
+// 476 of 402 at 699 264 and 287; calls of 16 to 24 us would pay 2 for the larger kernel.  Nor where the row's LDS does not
+// hold the items and the shortest lists, so that no stage could be tried: 2048 of 700 items at 940, values the
+// weights or less than three above them, 0.99 ms, and 1.08 on the larger kernel.
 constexpr int64_t kPoolCallCells = 650000;
 
 hipError_t seq_lds_launch(const SeqLdsPlan &p, const BatchArgs &a, void *scratch, hipStream_t st,
                           unsigned long long *swept_cells)
 {
     const int64_t cells = (int64_t)a.item_stride * a.max_capacity;
-    if (cells >= kPoolCells || (a.item_stride >= 2 * kPoolItems && cells >= kPoolCallCells)) return seq_lds_pool_launch(p, a, scratch, st, swept_cells);
+    const bool room = (int64_t)p.row_cells * 4 >= pool_items_bytes(a.item_stride) + pool_space_bytes(a.item_stride, kPool);
+    if (room && (cells >= kPoolCells || (a.item_stride >= 2 * kPoolItems && cells >= kPoolCallCells)))
+        return seq_lds_pool_launch(p, a, scratch, st, swept_cells);
     return launch_variant<false>(p, a, scratch, st, swept_cells);
 }
 

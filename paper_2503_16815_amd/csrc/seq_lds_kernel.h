@@ -1094,8 +1094,15 @@ struct Variant {
     const void *fn;
 };
 
+// (a row of one wavefront's is too short for the items and lists of a stage by enumeration)
+template <int T, int K, int G, int WPE, bool REC, bool POOL>
+const void *variant_kernel()
+{
+    if constexpr (POOL && T == 64) return nullptr;
+    else return reinterpret_cast<const void *>(&seq_lds_kernel<T, K, G, WPE, REC, POOL>);
+}
 #define DEFT_VARIANT(T, K, G, WPE, GUARD) \
-    { T, K, G, GUARD, reinterpret_cast<const void *>(&seq_lds_kernel<T, K, G, WPE, REC, POOL>) }
+    { T, K, G, GUARD, variant_kernel<T, K, G, WPE, REC, POOL>() }
 template <bool REC, bool POOL = false>
 const Variant *variant_table()
 {
@@ -1132,7 +1139,9 @@ hipError_t launch_variant(const SeqLdsPlan &p, const BatchArgs &a, void *scratch
                           unsigned long long *swept_cells)
 {
     switch (p.variant) {
-    case 0: return launch_one<64, 16, 4, 5, REC, POOL>(p, a, scratch, st, swept_cells);
+    case 0:
+        if constexpr (POOL) return hipErrorInvalidValue;
+        else return launch_one<64, 16, 4, 5, REC, POOL>(p, a, scratch, st, swept_cells);
     case 1: return launch_one<256, 16, 4, 7, REC, POOL>(p, a, scratch, st, swept_cells);
     case 2: return launch_one<256, 32, 4, 4, REC, POOL>(p, a, scratch, st, swept_cells);
     case 3: return launch_one<512, 20, 1, 8, REC, POOL>(p, a, scratch, st, swept_cells);

@@ -6,6 +6,7 @@ namespace deft {
 
 hipError_t seq_lds_pool_prepare(const SeqLdsPlan &plan)
 {
+    if (plan.threads == 64) return hipSuccess;  // (no such kernel)
     int nb = 0;
     const hipError_t e = prepare_variant<false, true>(plan, &nb);
     if (e != hipSuccess) return e;
