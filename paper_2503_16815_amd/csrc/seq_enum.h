@@ -37,6 +37,19 @@ constexpr int kPoolNever = 1 << 30;
 constexpr int kPoolFirst = 1024; // the longest list before heavy items are gone through one by one
 constexpr int kPoolBins = 256;
 constexpr int kPoolSort = 6144;  // the fewest pairs that make it worth sorting one list by weight
+// Where an attempt ends early, so that what it cannot settle costs little on top of the sweep.  Values unrelated to
+// weights or priorities times them, 148 items on a long row: at most 2 items within one unit of value of the price, 4
+// selections as good as the best a stage.  Values of a few kinds: up to 64 of the pool and 39000 selections, gone
+// through one by one (128 instances of 60 items, C = 60000, the sweep 0.38 ms: 28.8 ms, now 0.39; values 1 to 3, 256 of 100, C = 100000,
+// 0.88 ms: 7.9, now 0.89; values within 2 of the weights, 128 of 60 0.40 ms: 2.9, now 0.41).
+constexpr int kPoolAlike = 16;   // REDUCE = false: with more items within one unit too many selections are as good
+// REDUCE: a stage whose items are mostly within one unit is reduced to hardly fewer, at 12 to 25 us.  Given up with two thirds
+// of them, in stages of fewer cells with half (values within 2 of the weights, 256 instances of 96 items, C = 7000: the sweep 112 us,
+// tried 162, now 114; 16 of 148, C = 38000 511, 602, now 518; values 1 to 3, about half within one unit, 16 of 148, C = 38000
+// 478, 174 without these limits, now 211).
+constexpr long long kPoolHope = 2400000;
+constexpr int kPoolTies = 16;    // more selections of the greatest value (0.4 us each)
+constexpr int kPoolSteps = 2048; // more steps through the fullest bin (40 ns each)
 
 // What a stage needs: the items' weights and values (64 at a time, padded), and space for their losses, the pool and lists.
 constexpr int kPoolEntryBytes = 16;
@@ -98,11 +111,13 @@ struct PoolAnswer {
 // together they weigh more than C.  `items`: weight and value of item i, whole chunks of 64.  `space`: `space_bytes`
 // of LDS, 16-byte aligned.  `entries`: how long the lists may get.
 // `least_value`: only selections of that value or more matter.
+// `deadline`: no round begins after it (by the wall clock).
 // REDUCE: where lists run over but a selection is known, the stage is reduced to the items that it leaves open.
-enum PoolOutcome { kPoolFailed, kPoolNone, kPoolFound, kPoolReduced };
+// kPoolHopeless: nor will it be settled with some of the items given.
+enum PoolOutcome { kPoolHopeless, kPoolFailed, kPoolNone, kPoolFound, kPoolReduced };
 template <bool REDUCE>
 __device__ __forceinline__ PoolOutcome pool_stage(const int2 *items, char *space, int space_bytes, int entries, int n, int C,
-                                                  unsigned long long offered, int least_value, int lane, PoolAnswer &answer)
+                                                  unsigned long long offered, int least_value, long long deadline, int lane, PoolAnswer &answer)
 {
     const int chunks = (n + 63) >> 6;
     // losses as floats, negative where the item is worth taking; in front of the lists
@@ -162,7 +177,7 @@ __device__ __forceinline__ PoolOutcome pool_stage(const int2 *items, char *space
     const long long price = (long long)ceilf(ldexpf(rate, F));
 
     // ---- losses -----------------------------------------------------------------------------------
-    int weight = 0, worth = 0, count = 0, greatest = 0;
+    int weight = 0, worth = 0, count = 0, alike = 0, greatest = 0;
     float weight_f = 0.0f;
     for (int c = 0; c < chunks; ++c) {
         const int2 it = items[c * 64 + lane];
@@ -175,7 +190,9 @@ __device__ __forceinline__ PoolOutcome pool_stage(const int2 *items, char *space
         loss_of[c * 64 + lane] = __float_as_int(take ? -loss : loss);
         greatest = max(greatest, in ? __float_as_int(loss) : 0);
         count += __popcll(__ballot(in));
+        alike += __popcll(__ballot(in && loss <= ldexpf(1.0f, F)));
     }
+    if (REDUCE ? alike * ((long long)count * C < kPoolHope ? 4 : 3) > count * 2 : alike > kPoolAlike) return kPoolHopeless;
     if (pool_sum(weight_f) > 1.0e9f) return kPoolFailed;
     weight = pool_sum(weight);
     worth = pool_sum(worth);
@@ -261,7 +278,7 @@ __device__ __forceinline__ PoolOutcome pool_stage(const int2 *items, char *space
     if (least < 0) return kPoolNone;
     int last_G = -1;
     bool may_leap = true;
-    for (int round = 0; round <= kPoolRounds;) {
+    for (int round = 0; round <= kPoolRounds && wall_clock64() < deadline;) {
         const int opened = 12 + 8 * round;
         int G = min(opened < held ? __builtin_amdgcn_readlane(s_loss, min(opened, 63)) - 1 : kPoolNever - 1, G_pool);
         const int left = (int)min(least >> coarse, (long long)kPoolNever);
@@ -333,6 +350,7 @@ __device__ __forceinline__ PoolOutcome pool_stage(const int2 *items, char *space
         const int4 *partners = list_b;
         int lightest = 0;
         float scale = 0.0f;
+        int fullest = 0;
         auto bin_of = [&](int w) { return (int)fminf((float)(w - lightest) * scale, (float)(kPoolBins - 1)); };
         if (sorted) {
             int least_w = INT_MAX, most_w = INT_MIN;
@@ -357,6 +375,7 @@ __device__ __forceinline__ PoolOutcome pool_stage(const int2 *items, char *space
             // bin b: where it begins, and the greatest value below it (four bins a lane)
             int4 counts = *reinterpret_cast<const int4 *>(&begin[lane * 4]), tops = *reinterpret_cast<const int4 *>(&top[lane * 4]);
             const int own_count = counts.x + counts.y + counts.z + counts.w, own_top = max(max(tops.x, tops.y), max(tops.z, tops.w));
+            fullest = pool_max(max(max(counts.x, counts.y), max(counts.z, counts.w)));
             int upto = own_count, best_upto = own_top;
 #pragma unroll
             for (int off = 1; off < 64; off <<= 1) {
@@ -379,7 +398,8 @@ __device__ __forceinline__ PoolOutcome pool_stage(const int2 *items, char *space
             pool_sync();
             partners = spare;
         }
-        int best = INT_MIN, load = 0;
+        if (fullest * ((size_a + 63) >> 6) > kPoolSteps) break;
+        int best = INT_MIN, load = 0, ties = 0;
         bool met = false;
         unsigned long long mask = 0;
 #pragma unroll 1
@@ -410,7 +430,7 @@ __device__ __forceinline__ PoolOutcome pool_stage(const int2 *items, char *space
                     best = max(best, both);
                     continue;
                 }
-                for (unsigned long long hits = __ballot(both == best && base + lane < size_a); hits; hits &= hits - 1) {
+                for (unsigned long long hits = __ballot(both == best && base + lane < size_a); hits && ties <= kPoolTies; hits &= hits - 1) {
                     const int i = __builtin_ctzll(hits);
                     const int i_room = __builtin_amdgcn_readlane(x_room, i), i_value = best - __builtin_amdgcn_readlane(x.y, i);
                     unsigned long long one = taken_mask;
@@ -418,13 +438,14 @@ __device__ __forceinline__ PoolOutcome pool_stage(const int2 *items, char *space
                         one ^= 1ull << __builtin_amdgcn_readlane(s_place, 2 * __builtin_ctz(bits));
                     for (int first = 0; first < size_b; first += 64) {
                         const int4 y = partners[min(first + lane, size_b - 1)];
-                        for (unsigned long long with = __ballot(first + lane < size_b && y.x <= i_room && y.y == i_value); with; with &= with - 1) {
+                        for (unsigned long long with = __ballot(first + lane < size_b && y.x <= i_room && y.y == i_value); with && ties <= kPoolTies; with &= with - 1) {
                             const int j = __builtin_ctzll(with);
                             unsigned long long other = one;
                             for (unsigned bits = (unsigned)__builtin_amdgcn_readlane(y.w, j); bits; bits &= bits - 1)
                                 other ^= 1ull << __builtin_amdgcn_readlane(s_place, 2 * __builtin_ctz(bits) + 1);
                             if (!met || other < mask) mask = other, load = C - i_room + __builtin_amdgcn_readlane(y.x, j);
                             met = true;
+                            ++ties;
                         }
                     }
                 }
@@ -440,6 +461,7 @@ __device__ __forceinline__ PoolOutcome pool_stage(const int2 *items, char *space
             if (G >= G_pool) break;
             continue;
         }
+        if (ties > kPoolTies) break;
         answer.value = worth + best;
         answer.load = load;
         unsigned long long chosen = 0;
@@ -486,7 +508,7 @@ __device__ __forceinline__ bool pool_before(unsigned long long x, unsigned long 
 // the time: the window's last quarter is not one any of them fits), all combinations of the heaviest ones are gone through,
 // each with a price of its own.
 __device__ __forceinline__ bool pool_solve(const int2 *items, char *space, int space_bytes, int entries, int n, int C,
-                                           unsigned long long offered, int lane, PoolAnswer &answer)
+                                           unsigned long long offered, long long deadline, int lane, PoolAnswer &answer)
 {
     constexpr int kHeavy = 3;
     unsigned long long rest = offered, pick[kHeavy] = {};
@@ -536,11 +558,9 @@ __device__ __forceinline__ bool pool_solve(const int2 *items, char *space, int s
             part.value = pool_sum(its_value);
         } else {
             const PoolOutcome outcome = pool_stage<false>(items, space, space_bytes, sub < 0 ? min(entries, kPoolFirst) : entries, n, room, fits,
-                                                   answer.value < 0 ? -1 : answer.value - value, lane, part);
-            if (outcome == kPoolFailed) {
-                if (sub >= 0) return false;
-                continue;
-            }
+                                                   answer.value < 0 ? -1 : answer.value - value, deadline, lane, part);
+            if (outcome == kPoolHopeless || (outcome == kPoolFailed && sub >= 0)) return false;
+            if (outcome == kPoolFailed) continue;
             if (outcome == kPoolNone) continue;
         }
         part.value += value;

@@ -695,7 +695,7 @@ seq_lds_kernel(BatchArgs a, LdsLayout lay, uint32_t *keep, int64_t keep_words_pe
     // (where the row's LDS holds the items and lists of some length)
     int2 *const pool_items = reinterpret_cast<int2 *>(row);
     const int pool_room = lay.row_cells * 4 - pool_items_bytes(n);
-    const bool pooled = POOL && !veqw && pool_room >= pool_space_bytes(n, kPool);
+    bool pooled = POOL && !veqw && pool_room >= pool_space_bytes(n, kPool);
     // A stage that is reduced: what is taken in any case, and the window left for the sweep (serial wavefront).
     int fixed_value = 0, fixed_load = 0, sweep_C = 0;
     int s = 0;
@@ -744,7 +744,6 @@ seq_lds_kernel(BatchArgs a, LdsLayout lay, uint32_t *keep, int64_t keep_words_pe
                 int heaviest = 0;
                 int offered_weight = 0;  // per lane at most 64 items of at most 2^24 each
                 unsigned long long worth = 0;  // what is offered and of some value, laid out like `placed`
-                int worth_weight = 0, worth_value = 0;
                 for (int i0 = 0; i0 < n; i0 += 64) {
                     const int i = i0 + tid;
                     const int w = item_w(i0, i);
@@ -754,7 +753,7 @@ seq_lds_kernel(BatchArgs a, LdsLayout lay, uint32_t *keep, int64_t keep_words_pe
                     if constexpr (POOL) {
                         if (pooled) {
                             pool_items[i] = make_int2(w, v);
-                            if (f && v > 0) worth |= 1ull << (i0 >> 6), worth_weight += w, worth_value += v;
+                            if (f && v > 0) worth |= 1ull << (i0 >> 6);
                         }
                     }
                     unplaced += __popcll(__ballot(open));
@@ -855,15 +854,21 @@ seq_lds_kernel(BatchArgs a, LdsLayout lay, uint32_t *keep, int64_t keep_words_pe
                         PoolAnswer answer;
                         PoolOutcome outcome = kPoolFailed;
                         if (pooled && (cnt >= kPoolItems || (int64_t)cnt * C >= kPoolCells) && pool_max(heaviest) <= offered_weight / 5) {
+                            int worth_weight = 0, worth_value = 0;
+                            for (int i0 = 0; i0 < n; i0 += 64) {
+                                const int2 it = pool_items[i0 + tid];
+                                if ((worth >> (i0 >> 6)) & 1ull) worth_weight += it.x, worth_value += it.y;
+                            }
                             worth_weight = wave_sum(min(worth_weight, (1 << 24) + 1));
                             if (worth_weight <= C) {  // the others are worth nothing
                                 answer = PoolAnswer{wave_sum(worth_value), worth_weight, worth, 0};
                                 outcome = kPoolFound;
                             } else {
                                 outcome = pool_stage<true>(pool_items, reinterpret_cast<char *>(row) + pool_items_bytes(n), pool_room,
-                                                           kPoolEntries, n, C, worth, -1, tid, answer);
+                                                           kPoolEntries, n, C, worth, -1, LLONG_MAX, tid, answer);
                             }
                         }
+                        if (outcome == kPoolHopeless) pooled = false;  // nor will the stages to come be settled
                         if (outcome == kPoolFound || outcome == kPoolReduced) {
                             // (reduced: these are taken in any case)
                             placed |= answer.chosen;
@@ -874,8 +879,8 @@ seq_lds_kernel(BatchArgs a, LdsLayout lay, uint32_t *keep, int64_t keep_words_pe
                                 out_kl[j] = answer.load;
                                 total += answer.value;
                             }
-                            cnt = -1;
                         }
+                        if (outcome == kPoolFound) cnt = -1;
                         if (outcome == kPoolReduced) {
                             fixed_value = answer.value;
                             fixed_load = answer.load;

@@ -135,3 +135,33 @@ def test_a_stage_reduced_to_nothing_before_one_that_is_swept(binding, oracle):
         _both_entry_points(binding, oracle, _stages(light + close, caps, f"reduced_{len(caps)}"), 7000)
     kb = _batch(78000, 300, 100, 7000, "rates", m=4)
     _both_entry_points(binding, oracle, kb, 7000)
+
+
+def _milliseconds(binding, kb, cap):
+    import torch
+    with binding.DeftKnapsack(max_batch=kb.batch, max_items=kb.item_stride, max_knapsacks=kb.knap_stride, max_capacity=cap, device=0) as h:
+        db = h.upload(kb)
+        h.solve_batch(db)
+        h.set_profiling(True)
+        best = np.inf
+        for _ in range(3):
+            h.solve_batch(db)
+            torch.cuda.synchronize()
+            best = min(best, h.get_profile().total_ms)
+        return best
+
+
+@pytest.mark.parametrize("kind", ["alike", "light", "near", "rates"])
+@pytest.mark.parametrize("n,cap", [(20, 45000), (60, 60000), (100, 100000)])
+def test_an_attempt_that_leads_nowhere_ends_early(binding, oracle, kind, n, cap):
+    """Many selections as good as the best: bit-exact, and at most a small multiple of the time that the sweep of such a
+    batch takes (values equal to weights are swept at once), where going through them took up to 75 times as long."""
+    kb = _batch(79000 + n, 64, n, cap, "rates" if kind == "near" else kind, m=2)
+    if kind == "near":
+        kb.values[:] = kb.weights + np.random.Generator(np.random.PCG64(n)).integers(0, 3, size=kb.weights.shape)
+    run(binding, oracle, kb.slice(0, 8), max_capacity=cap)
+    swept = _batch(79000 + n, 64, n, cap, "priority", m=2)
+    swept.values[:] = swept.weights
+    took, sweep = _milliseconds(binding, kb, cap), _milliseconds(binding, swept, cap)
+    print(f"{took:.3f} ms, sweep {sweep:.3f} ms", flush=True)
+    assert took < 4 * sweep + 0.2
