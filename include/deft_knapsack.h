@@ -358,8 +358,11 @@ typedef struct {
     int64_t swept_cell_updates; /* rows in LDS (seq_path 1 or 2): cell-updates the sweeps
                               evaluated, C - w + 1 for every item a stage's sweep went
                               through (stages settled without a sweep, by enumeration for
-                              instance, and the items after a full row add nothing), and the same count from the bit-set
-                              rows on those handles; 0 on the other paths                 */
+                              instance, and the items after a full row add nothing), and
+                              the same count from the bit-set rows on those handles.
+                              JOINT2: items times (C1 + 1) (C2 + 1) of the instances that
+                              enumeration left and their tables answered.  0 on the other
+                              paths                                                       */
 } deft_knapsack_profile_t;
 
 /* Turn HIP-event timing of solve calls on (1) or off (0); off by default.

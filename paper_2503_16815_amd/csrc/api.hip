@@ -50,6 +50,7 @@ struct deft_knapsack {
     void *glob_scratch = nullptr;
     unsigned long long *glob_streamed = nullptr;  // device counter read by get_profile
     unsigned long long *lds_swept = nullptr;      // device counter read by get_profile (LDS path)
+    unsigned long long *joint_swept = nullptr;    // device counter read by get_profile (two-link)
 
     // The bit-set kernels: promised - the handle's creator said that values are weights, and the
     // sequential-layout modes run on them alone; otherwise, where bits_ready, they answer the
@@ -80,6 +81,7 @@ void free_handle(deft_knapsack *h)
     if (h->glob_scratch) (void)hipFree(h->glob_scratch);
     if (h->glob_streamed) (void)hipFree(h->glob_streamed);
     if (h->lds_swept) (void)hipFree(h->lds_swept);
+    if (h->joint_swept) (void)hipFree(h->joint_swept);
     if (h->joint_scratch) (void)hipFree(h->joint_scratch);
     if (h->left) (void)hipFree(h->left);
     if (h->sim_buffers) (void)hipFree(h->sim_buffers);
@@ -211,11 +213,19 @@ extern "C" deft_status_t deft_knapsack_create(const deft_knapsack_config_t *cfg,
     if (st == DEFT_OK && want_joint) {
         h->joint_path = 1;
         joint_plan(cfg->max_c1, cfg->max_c2, cfg->max_items, cfg->max_batch, lds_wg, &h->joint_plan);
-        if (joint_prepare(h->joint_plan) != hipSuccess) {
+        st = alloc(&h->joint_scratch, h->joint_plan.scratch_bytes, &h->scratch_bytes);
+        if (st == DEFT_OK && joint_prepare(h->joint_plan, h->joint_scratch) != hipSuccess) {
             (void)hipGetLastError();
             st = DEFT_ERR_DEVICE;
-        } else {
-            st = alloc(&h->joint_scratch, h->joint_plan.scratch_bytes, &h->scratch_bytes);
+        }
+        if (st == DEFT_OK) {
+            void *c = nullptr;
+            st = alloc(&c, 8, &h->scratch_bytes);
+            h->joint_swept = static_cast<unsigned long long *>(c);
+            if (st == DEFT_OK && hipMemset(c, 0, 8) != hipSuccess) {
+                (void)hipGetLastError();
+                st = DEFT_ERR_DEVICE;
+            }
         }
     }
     if (st == DEFT_OK && greedy_prepare(cfg->max_items) != hipSuccess) {
@@ -326,7 +336,7 @@ extern "C" deft_status_t deft_knapsack_solve_batch(deft_knapsack_t *h, const def
         e = seq_lds_rec_launch(h->lds_plan, a, h->keep, st, swept);
         if (prof) prof->sweep_end(st);
     } else {
-        e = joint_launch(h->joint_plan, a, h->joint_scratch, st, prof);
+        e = joint_launch(h->joint_plan, a, h->joint_scratch, st, prof, prof ? h->joint_swept : nullptr);
     }
     if (prof) prof->end(st);
     if (e != hipSuccess) {
@@ -427,7 +437,7 @@ extern "C" deft_status_t deft_knapsack_set_profiling(deft_knapsack_t *h, int32_t
     if (!h) return DEFT_ERR_INVALID_ARG;
     h->profiling = enable != 0;
     h->prof.reset();
-    for (unsigned long long *counter : {h->glob_streamed, h->lds_swept}) {
+    for (unsigned long long *counter : {h->glob_streamed, h->lds_swept, h->joint_swept}) {
         if (!counter) continue;
         DeviceGuard g(h->cfg.device);
         if (!g.ok || hipMemset(counter, 0, 8) != hipSuccess) {
@@ -447,15 +457,14 @@ extern "C" deft_status_t deft_knapsack_get_profile(deft_knapsack_t *h, deft_knap
     out->streamed_row_cells = 0;
     out->swept_cell_updates = 0;
     if (rc != DEFT_OK) return rc;
-    for (int which = 0; which < 2; ++which) {
-        unsigned long long *counter = which == 0 ? h->glob_streamed : h->lds_swept;
+    for (unsigned long long *counter : {h->glob_streamed, h->lds_swept, h->joint_swept}) {
         if (!counter) continue;
         unsigned long long v = 0;
         if (hipMemcpy(&v, counter, 8, hipMemcpyDeviceToHost) != hipSuccess || hipMemset(counter, 0, 8) != hipSuccess) {
             (void)hipGetLastError();
             return DEFT_ERR_DEVICE;
         }
-        (which == 0 ? out->streamed_row_cells : out->swept_cell_updates) = (int64_t)v;
+        (counter == h->glob_streamed ? out->streamed_row_cells : out->swept_cell_updates) += (int64_t)v;
     }
     return rc;
 }

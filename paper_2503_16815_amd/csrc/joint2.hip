@@ -1,5 +1,5 @@
 // Joint two-link solve (Sec. III.C, Problem 2 with one weight per link).  Most instances are answered by enumeration
-// (joint2_enum.h); what follows is the table sweep, for those it leaves.  The
+// (joint2_enum.h); what follows is the table sweep, begun beside it, for those it leaves.  The
 // (C1+1) x (C2+1) table does not fit LDS, so it lives in global memory (two
 // copies, item q reads copy q & 1 and writes the other) and streams through an
 // LDS window once per item:
@@ -38,12 +38,12 @@ namespace {
 struct InstState {
     int32_t status, n, c1, c2;
 };
-constexpr int kAnswered = -1;  // status of an instance that the enumeration has answered: none of the codes that callers see
 
 struct Scratch {
     int32_t *tab;       // [batch][2][rows][pitch]
     uint64_t *choice;   // [batch][max_items][rows][pitch / 64][2]
     InstState *state;   // [batch]
+    int32_t *solved;    // [batch] kEnumerated, kSwept; 0 between calls
 };
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -57,11 +57,14 @@ Scratch carve(const JointPlan &p, void *base)
     s.choice = reinterpret_cast<uint64_t *>(c);
     c += align256((size_t)p.max_batch * p.max_items * p.rows * (p.pitch / 64) * 16);
     s.state = reinterpret_cast<InstState *>(c);
+    c += align256((size_t)p.max_batch * sizeof(InstState));
+    s.solved = reinterpret_cast<int32_t *>(c);
     return s;
 }
 
 constexpr int kSweepThreads = 1024;  // one workgroup per instance
 constexpr int kSweepWaves = kSweepThreads / 64;
+constexpr int kOtherLds = 64;        // beside the ring
 constexpr int kLoadWaves = 3;        // wavefronts that only move old rows from global memory into LDS
 constexpr int kComputeWaves = kSweepWaves - kLoadWaves;
 
@@ -90,14 +93,33 @@ typedef const __attribute__((address_space(1))) int32_t global_ci32;
 // A compute task is one row x 256 columns: lane l covers columns tile*256 + 64 j + l,
 // j = 0..3, so every global and LDS access of a wavefront is 64 consecutive words and the
 // ballot over j is the choice word of segment tile*4 + j.
-__global__ void __launch_bounds__(kSweepThreads)
-jt_sweep_all(BatchArgs a, const InstState *__restrict__ state, int32_t *tab, uint64_t *choice, int rows, int pitch,
-             int max_items, int ring_rows, int lds_pitch)
+// The instance may be solved by enumeration meanwhile: the sweep ends with the fourth block or the item then.
+// ring: [ring_rows][lds_pitch], row a lives in slot (a - base) % ring_rows
+__device__ __forceinline__ void jt_sweep(const BatchArgs &a, int inst, int32_t *solved, int32_t *tab, uint64_t *choice, int rows,
+                                         int pitch, int max_items, int ring_rows, int lds_pitch, int32_t *ring)
 {
-    extern __shared__ __align__(16) int32_t ring[];  // [ring_rows][lds_pitch], row a lives in slot (a - base) % ring_rows
-    const int inst = blockIdx.x;
-    const InstState st = state[inst];
-    if (st.status != DEFT_OK || st.n <= 0) return;
+    // Whether to go on, as one thread sees it, for all: told before a barrier, read behind it, and a barrier or more
+    // before the next word in the same place (one for blocks, one for items).
+    __shared__ int told[2];
+    InstState st;
+    st.status = check_instance(a, inst, true);
+    if (st.status != DEFT_OK) return;
+    st.n = a.n_items[inst];
+    st.c1 = a.capacities[(size_t)inst * a.knap_stride];
+    st.c2 = a.capacities[(size_t)inst * a.knap_stride + 1];
+    auto tell = [&](int place) {
+        if (threadIdx.x == 0) told[place] = __hip_atomic_load(&solved[inst], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    auto is_over = [&](int place) { return __builtin_amdgcn_readfirstlane(*(volatile int *)&told[place]) != 0; };
+    long long on_link0 = 0;
+    for (int i = threadIdx.x & 63; i < st.n; i += 64)
+        on_link0 += a.values[(size_t)inst * a.item_stride + i] > 0 ? a.weights[(size_t)inst * 2 * a.item_stride + i] : 0;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) on_link0 += __shfl_xor(on_link0, off);
+    tell(1);
+    __syncthreads();
+    if (is_over(1) || st.n <= 0) return;
+    if (on_link0 <= st.c1 && enum_takes(st.n, st.c1, st.c2)) return;  // everything fits there: answered at once
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const bool loader = wave < kLoadWaves;
@@ -178,11 +200,15 @@ jt_sweep_all(BatchArgs a, const InstState *__restrict__ state, int32_t *tab, uin
             barrier_after_lds_reads();
         }
         int slot_a0 = 0;  // (a0 - base) % ring_rows
-        for (int a0 = base; a0 < end; a0 += R) {
+        // (a return from within the loop makes every sweep 5 % longer)
+        int limit = end;
+        for (int a0 = base, block = 1; a0 < limit; a0 += R, ++block) {
+            const bool asks = (block & 3) == 0;
             int slot_next = slot_a0 + R;
             if (slot_next >= ring_rows) slot_next -= ring_rows;
             if (loader) {
                 if (a0 + R < end) load_rows(a0 + R, slot_next);
+                if (asks) tell(0);
                 barrier_after_loads();  // the next block is in the ring
             } else {
                 // One task.  IN_RING: the row-shifted operand comes from the ring; otherwise
@@ -302,20 +328,46 @@ jt_sweep_all(BatchArgs a, const InstState *__restrict__ state, int32_t *tab, uin
                 barrier_after_lds_reads();  // this block's slots may be reused
             }
             slot_a0 = slot_next;
+            if (asks && is_over(0)) limit = 0;
         }
+        if (limit == 0) return;
         // the next item reads what this one wrote (other wavefronts' rows included)
         __threadfence_block();
+        tell(1);
         __syncthreads();
+        if (is_over(1)) return;
     }
+    if (threadIdx.x == 0) __hip_atomic_fetch_or(&solved[inst], kSwept, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Workgroups [0, batch) enumerate, the same instances' [batch, 2 batch) sweep, as compute units become free: an instance
+// that is not solved early is worked at from both sides, and none waits for another.  With the sweeps behind all
+// enumerations a call took as long as the longest attempt and a sweep wherever one instance was left: of 360 kinds of calls (32 to
+// 256 instances of 16 to 150 items) 246 were slower than by the sweep alone, up to 2.8 times; now 64, up to 1.8 times (256
+// instances of 24 items whose values are the times on link 0, C1 = 468, C2 = 44: the sweep 0.48 ms, enumeration first 1.33, now
+// 0.88).  Where some instances are left it saves 10 to 60 % (256 of 64 items at 512 x 512 5.1 and 6.1 -> 4.4 and 4.1 ms), where
+// none is the sweeps' ends cost 2 to 15 % (other inputs 0.80 and 0.93 -> 0.82 and 0.98; 40 of 45 items 0.187 -> 0.215).
+__global__ void __launch_bounds__(kSweepThreads)
+jt_sweep_all(BatchArgs a, InstState *state, int32_t *solved, int32_t *tab, uint64_t *choice, int rows, int pitch, int max_items, int ring_rows, int lds_pitch)
+{
+    static_assert(kEnumThreads == kSweepThreads, "one launch");
+    extern __shared__ __align__(16) char lds[];
+    if ((int)blockIdx.x < a.batch) jt_enumerate(a, (int)blockIdx.x, state, solved, lds);
+    else jt_sweep(a, (int)blockIdx.x - a.batch, solved, tab, choice, rows, pitch, max_items, ring_rows, lds_pitch, reinterpret_cast<int32_t *>(lds));
 }
 
 __global__ void __launch_bounds__(64)
-jt_traceback(BatchArgs a, const InstState *__restrict__ state, const uint64_t *choice, int rows, int pitch, int max_items)
+jt_traceback(BatchArgs a, const InstState *__restrict__ state, int32_t *solved, const uint64_t *choice, int rows, int pitch, int max_items,
+             unsigned long long *swept_cells)
 {
     const int inst = blockIdx.x * 64 + threadIdx.x;
     if (inst >= a.batch) return;
     const InstState st = state[inst];
     if (st.status != DEFT_OK) return;
+    const int by = solved[inst];
+    solved[inst] = 0;  // for the next call
+    if (by & kEnumerated) return;
+    if (swept_cells) atomicAdd(swept_cells, (unsigned long long)st.n * (st.c1 + 1) * (st.c2 + 1));
     const int segs = pitch / 64;
     const int32_t *W0 = a.weights + (size_t)inst * 2 * a.item_stride;
     const int32_t *W1 = W0 + a.item_stride;
@@ -361,37 +413,39 @@ void joint_plan(int32_t max_c1, int32_t max_c2, int32_t max_items, int32_t max_b
     p->pitch = (max_c2 + 1 + 63) / 64 * 64;
     p->lds_pitch = (max_c2 + 1 + 3) / 4 * 4;  // rows stay 16-byte aligned for the 16-byte LDS-direct loads
     // as many LDS rows as fit, but no more than the table has (plus one block)
-    int64_t ring = (int64_t)lds_per_wg_bytes / ((int64_t)p->lds_pitch * 4);
+    int64_t ring = (int64_t)(lds_per_wg_bytes - kOtherLds) / ((int64_t)p->lds_pitch * 4);
     if (ring > p->rows) ring = p->rows;
     if (ring < 2) ring = 2;
     p->ring_rows = (int32_t)ring;
     p->lds_bytes = (int32_t)(ring * p->lds_pitch * 4);
+    if (p->lds_bytes < (int32_t)sizeof(EnumShared)) p->lds_bytes = (int32_t)sizeof(EnumShared);
     p->max_items = max_items;
     p->max_batch = max_batch;
     p->scratch_bytes = (int64_t)(align256((size_t)max_batch * 2 * p->rows * p->pitch * 4) +
                                  align256((size_t)max_batch * max_items * p->rows * (p->pitch / 64) * 16) +
-                                 align256((size_t)max_batch * sizeof(InstState)));
+                                 align256((size_t)max_batch * sizeof(InstState)) + align256((size_t)max_batch * 4));
 }
 
-hipError_t joint_prepare(const JointPlan &p)
+hipError_t joint_prepare(const JointPlan &p, void *scratch)
 {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&jt_enumerate<InstState>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(EnumShared));
+    hipError_t e = hipMemset(carve(p, scratch).solved, 0, (size_t)p.max_batch * 4);
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess) return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(&jt_sweep_all),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, p.lds_bytes);
+    // (the attribute belongs to the kernel, not to the handle: the most that any handle asks for)
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(&jt_sweep_all), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               160 * 1024 - kOtherLds);
 }
 
-hipError_t joint_launch(const JointPlan &p, const BatchArgs &a, void *scratch, hipStream_t st, Profiler *prof)
+hipError_t joint_launch(const JointPlan &p, const BatchArgs &a, void *scratch, hipStream_t st, Profiler *prof,
+                        unsigned long long *swept_cells)
 {
     const Scratch s = carve(p, scratch);
     if (prof) prof->sweep_begin(st);
-    hipLaunchKernelGGL(jt_enumerate<InstState>, dim3((unsigned)a.batch), dim3(kEnumThreads), sizeof(EnumShared), st, a, s.state, kAnswered);
-    hipLaunchKernelGGL(jt_sweep_all, dim3((unsigned)a.batch), dim3(kSweepThreads), (size_t)p.lds_bytes, st, a, s.state,
-                       s.tab, s.choice, p.rows, p.pitch, p.max_items, p.ring_rows, p.lds_pitch);
+    hipLaunchKernelGGL(jt_sweep_all, dim3(2 * (unsigned)a.batch), dim3(kSweepThreads), (size_t)p.lds_bytes, st, a, s.state,
+                       s.solved, s.tab, s.choice, p.rows, p.pitch, p.max_items, p.ring_rows, p.lds_pitch);
     if (prof) prof->sweep_end(st);
-    hipLaunchKernelGGL(jt_traceback, dim3((a.batch + 63) / 64), dim3(64), 0, st, a, s.state, s.choice, p.rows,
-                       p.pitch, p.max_items);
+    hipLaunchKernelGGL(jt_traceback, dim3((a.batch + 63) / 64), dim3(64), 0, st, a, s.state, s.solved, s.choice, p.rows,
+                       p.pitch, p.max_items, swept_cells);
     return hipGetLastError();
 }
 

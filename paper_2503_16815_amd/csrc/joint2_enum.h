@@ -17,19 +17,17 @@
 // P1 and P2 taken in pairs, each looking up the partners that leave little enough room on either link.  If
 // the best selection met loses no more than G, all better or equal ones have been met: it is the answer, and
 // among equals the one with the smallest choice number is the one that the DP's walk returns.  If lists
-// or time run over (0.42 of what the sweep is expected to take), the instance is left to the table sweep; so are instances in which the prices are zero
-// (everything fits one link or the other: all choices cost nothing).
+// or time run over (a share of what the sweep is expected to take), or the table sweep, which begins beside it when a compute unit is free, ends first,
+// the instance is left to that; so are instances in which the prices are zero (everything fits one link or the other: all
+// choices cost nothing).
 //
 // All quantities that decide are whole numbers: prices and losses in units of 2^-F, values as they are.
 //
 // What bounds it: latency.  One workgroup owns an instance; a round is a chain of barriers (one for an item of each group
-// once the lists are long), its pairs are lookups in LDS at places of the lanes' own (a gather of 64 words meets each
-// bank about five times), and a launch lasts as long as its hardest instance.  Half of the instances of the two-link batch
-// are done after 100 us (prices 8, losses 4, three rounds of lists 12, sorting 9 to 13, pairs 37 to 48), the hardest after 0.64 to 1.94 ms;
-// about one of 3000 runs over.  The table sweep takes 6.36 ms: 256 instances, by the seed, 0.64 to 1.94 ms where none is left
-// to it, 6.1 where one is.  Few instances gain most: two of 64 items (C1 = 326, C2 = 112) 1.93 -> 0.07 ms.  Where the links hold
-// nearly everything there is next to no loss in any choice, and time for nothing is spent (175 instances of 39 items of up
-// to 35, 476 and 254: 1.15 -> 1.6 ms).
+// once the lists are long), its pairs are lookups in LDS at places of the lanes' own, and a launch lasts as long as its hardest
+// instance.  Of the two-link batch half of the instances are solved after 85 us, the last one after 0.79 to 0.94 ms; by the input
+// one of some 300 to 1000 is left to the table sweep, and the call takes 4.1 to 4.4 ms then (all by the sweep: 6.36).  40 instances of 20 to 62
+// items 0.41 of the sweep, 256 0.53 (geometric means over 30 kinds each).
 // Tried and not kept: every lane noting ties as it meets them (two passes instead, the second only where several selections
 // are as good: 72 -> 5 ms), Q sorted by link 0 alone, or by link 1 in steps of 128 (cells of both: pairs / 3), no table of
 // least losses (it turns nine of ten pairs away before they are looked up).
@@ -41,6 +39,7 @@ namespace deft {
 
 namespace {
 
+constexpr int kEnumerated = 1, kSwept = 2;  // which side has come to its end (both may)
 constexpr int kEnumThreads = 1024;
 constexpr int kEnumWaves = kEnumThreads / 64;
 constexpr int kEnumItems = kEnumThreads;  // a thread per item
@@ -56,6 +55,8 @@ constexpr int kCells0 = 128, kCells1 = 64;  // that group Q is sorted by
 constexpr int kCells = kCells0 * kCells1;
 constexpr int kFilterPairs = 1 << 13;     // the fewest pairs that make the table of least losses worth its 3 us
 constexpr int kNever = 1 << 30;           // the loss of a choice that is out of the question
+constexpr int kEnumComputeUnits = 256, kEnumAlike = 20;
+constexpr int kLookTicks = 2000;          // of 10 ns, between looks at whether the sweep has come to its end
 constexpr int kPriceGrid = 16, kPriceRounds = 4;
 
 struct EnumResult {
@@ -143,14 +144,15 @@ __device__ __forceinline__ uint32_t enum_mask(const EnumShared &s, int l, uint32
     return l == 0 ? s.list.q_mask[q] : l == 1 ? s.list.p1_mask[pair >> 11] : s.list.p2_mask[pair & 2047];
 }
 
-// One workgroup per instance.  What it answers gets the status `answered` in `state`, which the kernels of the
-// table sweep skip like any fault; anything else is left to them with its outputs cleared.
+__device__ __forceinline__ bool enum_takes(int n, int c0, int c1) { return n <= kEnumItems && c0 <= kEnumCapacity && c1 <= kEnumCapacity; }
+
+// The whole workgroup's.  What it answers gets kEnumerated in `solved`; anything else is left to the table sweep with its outputs
+// cleared.  It gives up when the sweep has put kSwept there.
 template <class State>
-__global__ void __launch_bounds__(kEnumThreads) jt_enumerate(BatchArgs a, State *state, int answered)
+__device__ __forceinline__ void jt_enumerate(const BatchArgs &a, int inst, State *state, int32_t *solved, char *lds)
 {
-    extern __shared__ __align__(16) char lds_enum[];
-    EnumShared &s = *reinterpret_cast<EnumShared *>(lds_enum);
-    const int inst = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    EnumShared &s = *reinterpret_cast<EnumShared *>(lds);
+    const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int status = check_instance(a, inst, true);
     clear_outputs(a, inst, status);
@@ -165,7 +167,7 @@ __global__ void __launch_bounds__(kEnumThreads) jt_enumerate(BatchArgs a, State 
         st.c2 = c1;
         state[inst] = st;
     }
-    if (n == 0 || n > kEnumItems || c0 > kEnumCapacity || c1 > kEnumCapacity) return;
+    if (n == 0 || !enum_takes(n, c0, c1)) return;
 
     const long long began = wall_clock64();
 
@@ -187,16 +189,18 @@ __global__ void __launch_bounds__(kEnumThreads) jt_enumerate(BatchArgs a, State 
         const int most0 = enum_wave_max(__float_as_int(fits0 ? (float)v / (float)w0 : 0.0f));
         const int most1 = enum_wave_max(__float_as_int(fits1 ? (float)v / (float)w1 : 0.0f));
         const int wave_v = enum_wave_max(v), all0 = enum_wave_sum(v > 0 ? min(w0, c0 + 1) : 0);
+        const int all_w = enum_wave_sum(here ? min(w0, c0 + 1) : 0);
         if (lane == 0) {
             atomicMax(&s.most[0], most0);
             atomicMax(&s.most[1], most1);
             atomicMax(&s.sum[3], wave_v);
             atomicAdd(&s.sum[0], all0);
+            atomicAdd(&s.sum[1], all_w);
         }
     }
     __syncthreads();
     const bool all_on_link0 = s.sum[0] <= c0;  // every item of value fits there: the smallest of the best selections
-    const int most_v = s.sum[3];
+    const int most_v = s.sum[3], all_weight = s.sum[1];
     __syncthreads();
     if (tid < 4) s.sum[tid] = 0;
 
@@ -221,7 +225,7 @@ __global__ void __launch_bounds__(kEnumThreads) jt_enumerate(BatchArgs a, State 
         }
         if (tid == 0) {
             a.total_value[inst] = (long long)s.sum[0] + s.sum[1];
-            state[inst].status = answered;
+            __hip_atomic_fetch_or(&solved[inst], kEnumerated, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     };
     if (all_on_link0) {
@@ -311,14 +315,17 @@ __global__ void __launch_bounds__(kEnumThreads) jt_enumerate(BatchArgs a, State 
         s.all.loss[1][tid] = loss_b;
         s.all.place[0][tid] = s.all.place[1][tid] = s.all.place[2][tid] = 0;
         const int u0 = enum_wave_sum(dflt == 1 ? w0 : 0), u1 = enum_wave_sum(dflt == 2 ? w1 : 0);
+        const int near = __popcll(__ballot(loss_a < 1 << F)) + __popcll(__ballot(loss_b < 1 << F));
         if (lane == 0) {
             atomicAdd(&s.sum[0], u0);
             atomicAdd(&s.sum[1], u1);
+            atomicAdd(&s.sum[2], near);
         }
     }
     if (tid < kEnumOpen) s.loss[0][tid] = s.loss[1][tid] = kNever;
     __syncthreads();
     const int used0 = s.sum[0], used1 = s.sum[1];  // by the default choices
+    const int alike = s.sum[2];                    // departures within one unit of value
     int rank = kEnumItems;
     {
         // places among the lesser losses, and of both among all losses (ties in some order): every item's
@@ -398,8 +405,18 @@ __global__ void __launch_bounds__(kEnumThreads) jt_enumerate(BatchArgs a, State 
     // ---- rounds -----------------------------------------------------------------------------
     int least = kNever;  // what the best selection met so far loses
     int last_G = -1;
-// (a tick of the clock is 10 ns; the sweep takes about 10 us an item and a cell at 4 a ns: 0.42 of that)
-    const long long deadline = began + n * 420 + (long long)n * (c0 + 1) * (c1 + 1) / 95;
+    // What a sweep takes, in ticks of 10 ns: its rows times an item's, less those that hold everything or cannot be reached, a
+    // row 300 cells more than it has (within 25 % of nine sweeps of ten).  While there are compute units for the sweeps as well,
+    // an attempt may take as long as most of one; else the sweep begins only when some attempt ends.  Instances with more than
+    // kEnumAlike departures within one unit of value are solved late if at all (of values that are the times on link 0 one in
+    // ten, of unrelated values all have less).  Measured (calls against the sweep alone, the geometric mean over 150 kinds each of
+    // 32 and 256 instances): shares of 0.6, 0.45 and 0.12 0.800 and 0.974; 1, 0.5 and 0.15 0.815 and 0.975; 1, 0.4 and 0.4 0.829
+    // and 1.007; 0.25 for many leaves more of the calls to a sweep (256 of 20 to 64 items 0.62 of the sweep, 0.52 at 0.5).
+    const float held = fminf(1.0f, (float)(c0 + 1) / (float)max(all_weight, 1));
+    const long long sweep_ticks = n * 600 + (long long)((1.0f - held) * (float)((c0 + 1) * (c1 + 301)) * (float)n / 41.0f);
+    const int share = 2 * a.batch <= kEnumComputeUnits ? 60 : alike > kEnumAlike ? 12 : 50;
+    const long long deadline = began + sweep_ticks * share / 100;
+    long long look = began + sweep_ticks / 2;                   // (it does not before)
     const int group = wave < 10 ? 0 : wave < 13 ? 1 : 2;        // the list that this wavefront makes
     const int first_wave = group == 0 ? 0 : group == 1 ? 10 : 13, list_waves = group == 0 ? 10 : 3;
     const int limit = group == 0 ? kListQ : group == 1 ? kListP1 : kListP2;
@@ -772,7 +789,12 @@ __global__ void __launch_bounds__(kEnumThreads) jt_enumerate(BatchArgs a, State 
                         }
                     }
                 }
-                if (wall_clock64() > deadline) s.over = 1;
+                const long long now = wall_clock64();
+                if (now > deadline) s.over = 1;
+                if (now > look) {
+                    look = now + kLookTicks;
+                    if (__hip_atomic_load(&solved[inst], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) s.over = 1;
+                }
                 if (__builtin_amdgcn_readfirstlane(*(volatile int32_t *)&s.over)) break;
             }
             if (pass == 0) {

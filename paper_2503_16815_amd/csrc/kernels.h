@@ -148,9 +148,10 @@ struct JointPlan {
 };
 void joint_plan(int32_t max_c1, int32_t max_c2, int32_t max_items, int32_t max_batch, int32_t lds_per_wg_bytes,
                 JointPlan *plan);
-hipError_t joint_prepare(const JointPlan &plan);
+hipError_t joint_prepare(const JointPlan &plan, void *scratch);
+// `swept_cells` (device, may be null): every instance that is answered from its table adds the table's cells, an item.
 hipError_t joint_launch(const JointPlan &plan, const BatchArgs &args, void *scratch, hipStream_t stream,
-                        Profiler *prof);
+                        Profiler *prof, unsigned long long *swept_cells);
 
 // ---- the two task queues over several iterations (schedule_sim.hip) -------------
 // Arguments of one simulation call as the kernels see them (all device pointers).

@@ -116,3 +116,58 @@ def test_many_items_that_fit_one_link_only(binding, oracle, n):
     kb.weights[4:, 1], kb.weights[4:, 0] = np.minimum(kb.weights[4:, 0], 150), 201
     kb.values[:] = np.maximum(kb.values, 1)
     run(binding, oracle, kb)
+
+
+def _profiled(binding, oracle, batches, c1, c2):
+    """The batches one after the other on one handle, each against the oracle; the cells that the table sweep answered and ms."""
+    import torch
+    from tests.test_gpu_parity import assert_same
+    got = []
+    with binding.DeftKnapsack(max_batch=max(kb.batch for kb in batches), max_items=max(kb.item_stride for kb in batches),
+                              max_knapsacks=2, max_c1=c1, max_c2=c2, device=0) as h:
+        for kb in batches:
+            ref = oracle.solve_batch(kb, nthreads=16, c1_limit=c1, c2_limit=c2)
+            db = h.upload(kb)
+            best = np.inf
+            for _ in range(3):
+                h.set_profiling(True)
+                out = h.solve_batch(db)
+                torch.cuda.synchronize()
+                prof = h.get_profile()
+                assert_same(kb, out, ref)
+                best = min(best, prof.total_ms)
+            got.append((int(prof.swept_cell_updates), best))
+    return got
+
+
+def test_what_is_settled_and_what_is_left_to_the_table(binding, oracle):
+    """By the library's own count: unrelated values on links that hold a part are settled; where moving an item costs nothing
+    there is too much to look through; lists below the fewest are swept; all fits link 0.  One handle, calls in turn."""
+    settled = _batch(88000, 12, 49, 34, 339, 54, "free")
+    settled.weights[:, 1] = settled.weights[:, 0] * np.random.Generator(np.random.PCG64(88)).integers(3, 7, size=(12, 49))
+    settled.capacities[:] = (339, 54)
+    left = _batch(88001, 5, 64, 64, 400, 400, "ratio")
+    left.capacities[:] = (400, 400)
+    few = _batch(88002, 7, 15, 40, 90, 120, "free")
+    few.capacities[:] = (90, 120)
+    fits = _batch(88003, 9, 30, 5, 300, 300, "free")
+    fits.capacities[:] = (300, 300)
+    cells = [c for c, _ in _profiled(binding, oracle, [settled, left, settled, few, fits, left, fits], 400, 400)]
+    all_left, all_few = 5 * 64 * 401 * 401, 7 * 15 * 91 * 121
+    assert cells[1:2] + cells[3:] == [all_left, all_few, 0, all_left, 0]
+    assert max(cells[0], cells[2]) <= 49 * 340 * 55, "one instance may run late (attempts are bounded by time)"
+
+
+@pytest.mark.parametrize("batch", [8, 64])
+@pytest.mark.parametrize("n,w_hi", [(24, 100), (40, 70), (64, 64)])
+def test_attempts_do_not_hold_up_the_sweep(binding, oracle, batch, n, w_hi):
+    """Instances that are hardly ever settled (moving an item costs nothing): bit-exact, and about as fast as with
+    a link one unit beyond what enumeration takes, which is swept at once (behind all attempts: 1.4 to 2.3 times as long)."""
+    kb = _batch(89000 + n, batch, n, w_hi, 769, 700, "ratio")
+    kb.capacities[:] = (769, 700)
+    tried = kb.slice(0, batch)
+    tried.capacities = np.full_like(kb.capacities, 700)
+    tried.capacities[:, 0] = 768
+    (_, sweep), (_, took) = _profiled(binding, oracle, [kb, tried], 769, 700)
+    print(f"{took:.3f} ms, sweep {sweep:.3f} ms", flush=True)
+    assert took < 1.25 * sweep + 0.05
