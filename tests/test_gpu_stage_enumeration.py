@@ -165,3 +165,47 @@ def test_an_attempt_that_leads_nowhere_ends_early(binding, oracle, kind, n, cap)
     took, sweep = _milliseconds(binding, kb, cap), _milliseconds(binding, swept, cap)
     print(f"{took:.3f} ms, sweep {sweep:.3f} ms", flush=True)
     assert took < 4 * sweep + 0.2
+
+
+def _counted(binding, oracle, kb, cap):
+    """Bit-exact against the oracle, and what the sweeps went through by the library's own counts, as a share of what they
+    would without enumeration (rows in LDS), or in row cells (rows in global memory)."""
+    import torch
+    from tests.test_gpu_parity import assert_same
+    ref = oracle.solve_batch(kb, nthreads=16, cap_limit=cap)
+    with binding.DeftKnapsack(max_batch=kb.batch, max_items=kb.item_stride, max_knapsacks=kb.knap_stride, max_capacity=cap, device=0) as h:
+        db = h.upload(kb)
+        h.set_profiling(True)
+        out = h.solve_batch(db)
+        torch.cuda.synchronize()
+        prof = h.get_profile()
+        assert_same(kb, out, ref)
+        return int(prof.streamed_row_cells) if h.info().seq_path == 3 else int(prof.swept_cell_updates) / int(ref.touched_cells.sum())
+
+
+def _near(seed, n, cap):
+    kb = _batch(seed, 6, n, cap, "rates")
+    kb.values[:] = kb.weights + np.random.Generator(np.random.PCG64(n)).integers(0, 3, size=kb.weights.shape)
+    return kb
+
+
+@pytest.mark.parametrize("kind,n,cap,low,high", [
+    ("priority", 200, 13000, 0.0, 0.02), ("free", 300, 38900, 0.0, 0.02), ("great", 200, 13000, 0.0, 0.02),  # settled
+    ("light", 200, 13000, 0.05, 0.5), ("light", 300, 38900, 0.05, 0.5),                                      # reduced
+    ("heavy", 200, 13000, 0.4, 1.0),                                                                         # not tried
+    ("near", 200, 13000, 0.6, 1.0), ("rates", 300, 38900, 0.6, 1.0)])                                        # given up
+def test_stages_are_settled_reduced_or_left(binding, oracle, kind, n, cap, low, high):
+    kb = _near(90003, n, cap) if kind == "near" else _batch(90002, 6, n, cap, kind)
+    assert low <= _counted(binding, oracle, kb, cap) <= high
+
+
+def test_a_stage_is_reduced_to_nothing(binding, oracle):
+    items = [(10, 10000)] * 40 + [(w, w - 1 - (7 * i) % 60) for i, w in enumerate(range(311, 371))]
+    assert _counted(binding, oracle, _stages(items, [700], "nothing_left"), 7000) == 0
+    assert 0 < _counted(binding, oracle, _stages(items, [700, 340], "nothing_left_then_swept"), 7000) < 0.02
+
+
+@pytest.mark.parametrize("kind,settled", [("priority", True), ("great", True), ("heavy", True), ("alike", False), ("light", False), ("near", False)])
+def test_long_rows_are_settled_or_streamed(binding, oracle, kind, settled):
+    kb = _near(90003, 148, 45000) if kind == "near" else _batch(90001, 6, 148, 45000, kind)
+    assert (_counted(binding, oracle, kb, 45000) == 0) == settled
