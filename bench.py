@@ -452,7 +452,7 @@ def run_solver(args):
     # any of the cells counted above is evaluated, the rate is an effective one and no roofline of cells applies
     enumerated = not seq or (info.seq_path == 3 and calls[0].mode == 0)
     if enumerated:
-        kernel = "seq_enum_kernel" if seq else "jt_enumerate"
+        kernel = "seq_enum_kernel" if seq else "jt_sweep_all"   # (two links: enumeration and sweep are one launch)
     tf = os.path.join(ROOT, "profiles", f"{kernel}_{args.workload}_traffic.txt")
     if plain_run and os.path.exists(tf):
         try:
@@ -474,9 +474,12 @@ def run_solver(args):
                  frac=(swept_step * args.steps * algo["ops_per_cell"] / sweep_s) / PEAK_INT_LANE_OPS
                  if sweep_s > 0 else 0.0))
     if enumerated:
-        roofline = dict(bound="latency", achieved=0.0, peak=peak, unit="GB/s", frac=0.0, traffic=None, traffic_source=None,
+        # (what the library counted of the instances that were left: row cells streamed, or cells of their tables)
+        left = int(prof.streamed_row_cells if seq else prof.swept_cell_updates) // args.steps
+        roofline = dict(bound="latency", achieved=None, peak=peak, unit="GB/s", frac=None, traffic=None, traffic_source=None,
                         kernel=kernel, launches=launches, avg_launch_ms=roofline["avg_launch_ms"],
-                        swept_cell_updates_per_s=0.0, bytes_per_cell=0.0, alu=dict(roofline["alu"], frac=0.0))
+                        swept_cell_updates_per_s=None, bytes_per_cell=None, alu=dict(roofline["alu"], frac=None),
+                        cells_left_to_the_sweep_per_step=left)
     line = dict(
         metric="knapsack DP cell-updates/sec", value=value, unit="cell-updates/s", n_gpus=1,
         steps=args.steps, warmup=args.warmup, ms_per_step=ms_step, higher_is_better=True, scaling="weak",
@@ -522,6 +525,7 @@ def compact(line: dict) -> dict:
                parity_vs_oracle=line["parity_vs_oracle"])
     if r["bound"] == "latency":   # settled by enumeration: what a sweep would go through
         out["cell_updates_of_a_sweep_per_step"] = out.pop("cell_updates_evaluated_per_step")
+        out["cells_left_to_the_sweep_per_step"] = r["cells_left_to_the_sweep_per_step"]
     for key in ("instances_per_s", "candidate_iterations_per_s", "effective_cell_updates_per_s", "parity_checked"):
         if key in line:
             out[key] = line[key]

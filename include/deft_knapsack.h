@@ -49,7 +49,8 @@ enum {
  * workgroup, workgroups per compute unit) is chosen ONCE, here, from max_capacity
  * (and max_items, whose lists must fit the row's LDS), not per call: the host
  * never reads the capacities of a batch, which live in device memory.  Every call
- * on the handle runs that kernel, whatever capacities it holds, so a handle
+ * on the handle runs that kernel (or its form that tries stages by enumeration
+ * first, by the call's item_stride), whatever capacities it holds, so a handle
  * created for max_capacity 38911 solves capacity-900 instances on the
  * 1024-lane, one-workgroup-per-compute-unit kernel, several times slower than
  * a handle created for 1023 would.  Callers with mixed batches should keep one
@@ -337,7 +338,8 @@ typedef struct {
     int32_t seq_threads;       /* threads cooperating on one instance                      */
     int32_t seq_cells_per_thread;
     int32_t seq_lds_bytes;     /* LDS per workgroup                                        */
-    int32_t seq_workgroups_per_cu; /* co-resident workgroups reported by the runtime       */
+    int32_t seq_workgroups_per_cu; /* co-resident workgroups reported by the runtime (of
+                                  the form that only sweeps)                             */
     int32_t joint_path;        /* 0 none, 1 rows in global memory                          */
     int32_t compute_units;
 } deft_knapsack_info_t;

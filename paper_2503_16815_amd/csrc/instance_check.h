@@ -1,5 +1,5 @@
-// Per-instance input checks shared by the set-up kernels of the global-memory
-// paths.  Run by one 256-thread workgroup per instance.  Returns the instance's
+// Per-instance input checks shared by the kernels of the global-memory
+// paths.  Run by one workgroup, of any size, per instance.  Returns the instance's
 // deft_status_t (same value in every thread).  Precedence: invalid data, then
 // create-time limits, then value-sum overflow.
 #pragma once

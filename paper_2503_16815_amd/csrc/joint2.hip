@@ -343,7 +343,7 @@ __device__ __forceinline__ void jt_sweep(const BatchArgs &a, int inst, int32_t *
 // Workgroups [0, batch) enumerate, the same instances' [batch, 2 batch) sweep, as compute units become free: an instance
 // that is not solved early is worked at from both sides, and none waits for another.  With the sweeps behind all
 // enumerations a call took as long as the longest attempt and a sweep wherever one instance was left: of 360 kinds of calls (32 to
-// 256 instances of 16 to 150 items) 246 were slower than by the sweep alone, up to 2.8 times; now 64, up to 1.8 times (256
+// 256 instances of 16 to 150 items) 246 were slower than by the sweep alone, up to 2.8 times; now 61, up to 1.8 times (256
 // instances of 24 items whose values are the times on link 0, C1 = 468, C2 = 44: the sweep 0.48 ms, enumeration first 1.33, now
 // 0.88).  Where some instances are left it saves 10 to 60 % (256 of 64 items at 512 x 512 5.1 and 6.1 -> 4.4 and 4.1 ms), where
 // none is the sweeps' ends cost 2 to 15 % (other inputs 0.80 and 0.93 -> 0.82 and 0.98; 40 of 45 items 0.187 -> 0.215).

@@ -410,7 +410,8 @@ __device__ __forceinline__ void jt_enumerate(const BatchArgs &a, int inst, State
     // an attempt may take as long as most of one; else the sweep begins only when some attempt ends.  Instances with more than
     // kEnumAlike departures within one unit of value are solved late if at all (of values that are the times on link 0 one in
     // ten, of unrelated values all have less).  Measured (calls against the sweep alone, the geometric mean over 150 kinds each of
-    // 32 and 256 instances): shares of 0.6, 0.45 and 0.12 0.800 and 0.974; 1, 0.5 and 0.15 0.815 and 0.975; 1, 0.4 and 0.4 0.829
+    // 32 and 256 instances): shares of 0.6, 0.5 and 0.12 0.782 and 0.950; with sweeps that
+    // looked at every block whether to end 0.6, 0.45 and 0.12 0.800 and 0.974; 1, 0.5 and 0.15 0.815 and 0.975; 1, 0.4 and 0.4 0.829
     // and 1.007; 0.25 for many leaves more of the calls to a sweep (256 of 20 to 64 items 0.62 of the sweep, 0.52 at 0.5).
     const float held = fminf(1.0f, (float)(c0 + 1) / (float)max(all_weight, 1));
     const long long sweep_ticks = n * 600 + (long long)((1.0f - held) * (float)((c0 + 1) * (c1 + 301)) * (float)n / 41.0f);
