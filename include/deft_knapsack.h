@@ -265,8 +265,9 @@ deft_status_t deft_knapsack_solve_batch(deft_knapsack_t *h, const deft_knapsack_
  *   status      [batch]                 INVALID_ARG (time < 1, drop time < 0, window < 0),
  *                                       LIMIT (window above max_capacity), OVERFLOW; such a
  *                                       candidate's other outputs are 0
- * The call enqueues everything on `stream` and returns; its first use on a handle
- * allocates the queue state (sized for max_batch x max_items; OOM if that fails).
+ * The call enqueues everything on `stream` and returns: one launch where max_capacity is at
+ * most 65535.  Beyond that its first use on a handle allocates the queue state (sized for
+ * max_batch x max_items; OOM if that fails).
  * Host-side errors: INVALID_ARG (NULL, batch < 0, n_buckets < 1, iterations < 1), LIMIT
  * (above the create-time limits, iterations > 4096, max_knapsacks < 2, max_capacity == 0),
  * DEVICE.
@@ -361,7 +362,9 @@ typedef struct {
                               evaluated, C - w + 1 for every item a stage's sweep went
                               through (stages settled without a sweep, by enumeration for
                               instance, and the items after a full row add nothing), and
-                              the same count from the bit-set rows on those handles.
+                              the same count from the bit-set rows on those handles
+                              (there also for stages answered by what they leave out: the
+                              cells of the sweep that the answer stands for).
                               JOINT2: items times (C1 + 1) (C2 + 1) of the instances that
                               enumeration left and their tables answered.  0 on the other
                               paths                                                       */

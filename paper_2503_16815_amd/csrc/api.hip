@@ -361,7 +361,7 @@ extern "C" deft_status_t deft_knapsack_simulate_schedule(deft_knapsack_t *h, con
 
     DeviceGuard g(h->cfg.device);
     if (!g.ok) return DEFT_ERR_DEVICE;
-    if (!h->sim_buffers) {
+    if (!h->bits_ready && !h->sim_buffers) {
         const deft_status_t rc = alloc(&h->sim_buffers, schedule_sim_bytes(h->cfg.max_batch, h->cfg.max_items),
                                        &h->scratch_bytes);
         if (rc != DEFT_OK) return rc;
@@ -385,16 +385,15 @@ extern "C" deft_status_t deft_knapsack_simulate_schedule(deft_knapsack_t *h, con
 
     Profiler *prof = h->profiling ? &h->prof : nullptr;
     if (prof && !prof->begin(st)) return DEFT_ERR_DEVICE;
-    const auto solve = [&](const BatchArgs &x) -> hipError_t {
-        if (h->bits_ready) {  // a bucket's value is its communication time
-            if (prof) prof->sweep_begin(st);
-            const hipError_t rc = seq_bits_launch(h->bits_plan, x, st, prof && !subset_sum(h) ? h->lds_swept : nullptr);
-            if (prof) prof->sweep_end(st);
-            return rc;
-        }
-        return seq_global_launch(h->glob_plan, x, h->glob_scratch, st, prof, h->glob_streamed);
-    };
-    const hipError_t e = schedule_sim_launch(a, h->sim_buffers, st, solve);
+    hipError_t e;
+    if (h->bits_ready) {  // a bucket's value is its communication time
+        if (prof) prof->sweep_begin(st);
+        e = seq_bits_queues_launch(h->bits_plan, a, st, prof && !subset_sum(h) ? h->lds_swept : nullptr);
+        if (prof) prof->sweep_end(st);
+    } else {
+        const auto solve = [&](const BatchArgs &x) { return seq_global_launch(h->glob_plan, x, h->glob_scratch, st, prof, h->glob_streamed); };
+        e = schedule_sim_launch(a, h->sim_buffers, st, solve);
+    }
     if (prof) prof->end(st);
     if (e != hipSuccess) {
         (void)hipGetLastError();

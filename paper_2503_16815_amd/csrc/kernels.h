@@ -64,6 +64,13 @@ hipError_t seq_lds_rec_prepare(const SeqLdsPlan &plan);
 hipError_t seq_lds_rec_launch(const SeqLdsPlan &plan, const BatchArgs &args, void *scratch,
                               hipStream_t stream, unsigned long long *swept_cells);
 
+// Arguments of one simulation call as the kernels see them (all device pointers).
+struct ScheduleArgs {
+    int32_t batch, n_buckets, iterations, max_capacity;
+    const int32_t *comm_time, *drop_time, *forward_time, *backward_time;
+    int32_t *stage_case, *stage_count, *stage_time, *update_k, *tail, *status;
+};
+
 // ---- sequential layout, value = weight, one bit per cell (seq_bits_kernel.h) -----
 // One wavefront per instance; the reachable sums as a bit set in registers and LDS, the
 // selection from a bit-sliced "first item that reached this sum" table in registers.  No scratch.
@@ -82,7 +89,12 @@ hipError_t seq_bits_prepare(const SeqBitsPlan &plan);
 // DEFT_MODE_SEQUENTIAL, DEFT_MODE_RECURSIVE and DEFT_MODE_CAPACITY_SWEEP.
 // `swept_cells` (device, may be null): every stage adds the cell-updates its sweep evaluated.
 hipError_t seq_bits_launch(const SeqBitsPlan &plan, const BatchArgs &args, hipStream_t stream, unsigned long long *swept_cells);
-void *seq_bits_long_kernel(int variant);  // the kernels of the longer rows (seq_bits_long.hip)
+// The two task queues over several iterations (schedule_sim.hip has them for rows in global memory), one launch.
+hipError_t seq_bits_queues_launch(const SeqBitsPlan &plan, const ScheduleArgs &args, hipStream_t stream, unsigned long long *swept_cells);
+// The kernels that other translation units compile: of the longer rows, of the task queues, and of both.
+const void *seq_bits_long_kernel(int variant, bool queues);
+const void *seq_bits_queues_kernel(int variant);
+const void *seq_bits_long_queues_kernel(int variant);
 
 // ---- sequential mode by enumeration, ahead of rows in global memory (seq_enum.hip) ----------
 // Answers the instances it can (args.left 0) and flags the others (1).  No scratch.
@@ -154,12 +166,6 @@ hipError_t joint_launch(const JointPlan &plan, const BatchArgs &args, void *scra
                         Profiler *prof, unsigned long long *swept_cells);
 
 // ---- the two task queues over several iterations (schedule_sim.hip) -------------
-// Arguments of one simulation call as the kernels see them (all device pointers).
-struct ScheduleArgs {
-    int32_t batch, n_buckets, iterations, max_capacity;
-    const int32_t *comm_time, *drop_time, *forward_time, *backward_time;
-    int32_t *stage_case, *stage_count, *stage_time, *update_k, *tail, *status;
-};
 // Bytes of the handle-owned buffers (queue state and the per-stage solver problem).
 int64_t schedule_sim_bytes(int32_t max_batch, int32_t max_items);
 // Enqueues the whole simulation: per stage a set-up kernel, the solver (`solve` enqueues one

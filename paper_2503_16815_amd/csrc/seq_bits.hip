@@ -34,20 +34,10 @@ int bits_per_cu(const SeqBitsPlan &p, int64_t lds, int waves)
     return by_lds < by_regs ? by_lds : by_regs;
 }
 
-BitsKernel bits_kernel(const SeqBitsPlan &p)
+const void *bits_kernel(const SeqBitsPlan &p, bool queues)
 {
-    switch (p.variant) {
-    case 0: return &seq_bits_kernel<2, 6>;
-    case 1: return &seq_bits_kernel<2, 9>;
-    case 2: return &seq_bits_kernel<2, 12>;
-    case 3: return &seq_bits_kernel<5, 6>;
-    case 4: return &seq_bits_kernel<5, 9>;
-    case 5: return &seq_bits_kernel<5, 12>;
-    case 6: return &seq_bits_kernel<7, 6>;
-    case 7: return &seq_bits_kernel<7, 9>;
-    case 8: return &seq_bits_kernel<7, 12>;
-    default: return reinterpret_cast<BitsKernel>(seq_bits_long_kernel(p.variant));
-    }
+    if (p.variant >= 3 * kBitsShort) return seq_bits_long_kernel(p.variant, queues);
+    return queues ? seq_bits_queues_kernel(p.variant) : bits_kernel_of<0, kBitsShort, false>(p.variant);
 }
 
 }  // namespace
@@ -75,11 +65,17 @@ hipError_t seq_bits_prepare(const SeqBitsPlan &p)
 {
     // the attribute belongs to the kernel, not to the handle: the most any handle may ask for
     // (a compute unit's LDS less a small allowance)
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(bits_kernel(p)), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               160 * 1024 - 256);
+    for (const bool queues : {false, true}) {
+        const hipError_t e = hipFuncSetAttribute(bits_kernel(p, queues), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
-hipError_t seq_bits_launch(const SeqBitsPlan &p, const BatchArgs &a, hipStream_t st, unsigned long long *swept_cells)
+namespace {
+
+hipError_t bits_launch(const SeqBitsPlan &p, bool queues, const BatchArgs &a, const ScheduleArgs &q, hipStream_t st,
+                       unsigned long long *swept_cells)
 {
     const BitsLayout lay = bits_layout(p, a.mode == DEFT_MODE_CAPACITY_SWEEP);
     // Instances per workgroup: they share one copy of the walk's planes, the largest part of an
@@ -94,8 +90,28 @@ hipError_t seq_bits_launch(const SeqBitsPlan &p, const BatchArgs &a, hipStream_t
     }
     const size_t lds = (size_t)bits_lds_bytes(lay, waves);
     const unsigned grid = (unsigned)((a.batch + waves - 1) / waves);
-    hipLaunchKernelGGL(bits_kernel(p), dim3(grid), dim3(64 * waves), lds, st, a, lay, swept_cells);
+    hipLaunchKernelGGL(reinterpret_cast<BitsKernel>(const_cast<void *>(bits_kernel(p, queues))), dim3(grid), dim3(64 * waves), lds, st, a, q, lay, swept_cells);
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t seq_bits_launch(const SeqBitsPlan &p, const BatchArgs &a, hipStream_t st, unsigned long long *swept_cells)
+{
+    return bits_launch(p, false, a, ScheduleArgs{}, st, swept_cells);
+}
+
+hipError_t seq_bits_queues_launch(const SeqBitsPlan &p, const ScheduleArgs &q, hipStream_t st, unsigned long long *swept_cells)
+{
+    BatchArgs a{};
+    a.mode = DEFT_MODE_SEQUENTIAL;
+    a.batch = q.batch;
+    a.item_stride = q.n_buckets;
+    a.knap_stride = 2;
+    a.max_capacity = q.max_capacity;
+    a.weights = a.values = q.comm_time;  // the value of a bucket is its communication time
+    a.drop_time = q.drop_time;
+    return bits_launch(p, true, a, q, st, swept_cells);
 }
 
 }  // namespace deft

@@ -125,6 +125,16 @@ __device__ __forceinline__ int bits_wave_prefix_sum(int x, int lane)
 __device__ __forceinline__ int bits_wave_sum(int x) { return bits_wave_reduce(x, [](int a, int b) { return a + b; }); }
 __device__ __forceinline__ int bits_wave_max(int x) { return bits_wave_reduce(x, [](int a, int b) { return max(a, b); }); }
 
+}  // namespace
+
+}  // namespace deft
+
+#include "seq_excess.h"
+
+namespace deft {
+
+namespace {
+
 // LDS of a workgroup, in 32-bit words: [lock: 4][planes: plane_words] and per wavefront
 // [zeros: row_words][set: row_words][pad: 4][prefix: n_pad + 8][index: n_pad / 2][marks: mark_words].
 struct BitsLayout {
@@ -133,7 +143,8 @@ struct BitsLayout {
 // One instance's share of it.
 struct BitsLds {
     uint32_t *set;      // reachable sums, zeros below
-    int32_t *prefix;    // prefix[p]: weight of the stage's first p offered items
+    int32_t *prefix;    // prefix[p]: weight of the stage's first p offered items.  Outside a sweep and its walk: the
+                        // weight of every item that is still in the list, kGone for the others
     uint16_t *index;    // the item at position p of the stage's list
     uint32_t *marks;    // sequential modes: a byte per item, its knapsack (255: none); capacity sweep: a word per item
     uint32_t *planes;   // first[] of the walk in progress (shared by the workgroup)
@@ -410,10 +421,12 @@ __device__ __forceinline__ int bits_walk(const BitsLds &l, int lane, int G, int 
 }
 
 // K: words per lane (capacities up to 2048 K - 1).  NP: planes (lists of up to 2^NP items).
-// a.mode: DEFT_MODE_SEQUENTIAL, DEFT_MODE_RECURSIVE or DEFT_MODE_CAPACITY_SWEEP.
-template <int K, int NP>
+// a.mode: DEFT_MODE_SEQUENTIAL, DEFT_MODE_RECURSIVE or DEFT_MODE_CAPACITY_SWEEP.  QUEUES: the two task queues (q; the
+// candidates' times as a's weights and values), all stages of a candidate by its wavefront; its current queue is the
+// list as it stands after the stage before.
+template <int K, int NP, bool QUEUES>
 __global__ void __launch_bounds__(256, bits_waves_per_simd(K, NP))
-seq_bits_kernel(BatchArgs a, BitsLayout lay, unsigned long long *swept_cells)
+seq_bits_kernel(BatchArgs a, ScheduleArgs q, BitsLayout lay, unsigned long long *swept_cells)
 {
     extern __shared__ __align__(16) int32_t lds_bits[];
     const int lane_ = threadIdx.x & 63, lane = lane_;
@@ -433,25 +446,32 @@ seq_bits_kernel(BatchArgs a, BitsLayout lay, unsigned long long *swept_cells)
     }
     if (inst >= a.batch) return;  // (the whole wavefront; no barrier follows)
 
-    const bool levels = a.mode == DEFT_MODE_RECURSIVE, caps_sweep = a.mode == DEFT_MODE_CAPACITY_SWEEP;
+    constexpr bool queues = QUEUES;
+    const bool levels = !queues && a.mode == DEFT_MODE_RECURSIVE, caps_sweep = !queues && a.mode == DEFT_MODE_CAPACITY_SWEEP;
+    const bool drops = levels || queues;
     // Everything whose address follows from the instance number alone is fetched at once: the
     // kernel's entry is one memory round trip.  The weights stay in registers (lists of up to
     // 512 items; longer ones are read again per stage).
     constexpr int NCH = NP <= 6 ? 1 : NP <= 9 ? 8 : 1;
     const int32_t *__restrict__ W = a.weights + (size_t)inst * a.item_stride;
     const int32_t *__restrict__ V = a.values + (size_t)inst * a.item_stride;
-    const int32_t *cap = a.capacities + (size_t)inst * a.knap_stride;
+    const int32_t *drop = drops ? a.drop_time + (size_t)inst * a.item_stride : nullptr;
+    const int32_t *cap = queues ? nullptr : a.capacities + (size_t)inst * a.knap_stride;
     const int32_t *ord = a.fill_order ? a.fill_order + (size_t)inst * a.knap_stride : nullptr;
     int wreg[NCH], vreg[NCH];
+    uint32_t dreg_negative = 0;  // bit c: chunk c's drop time of this lane is negative
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
         const bool have = c * 64 + lane < a.item_stride;
         wreg[c] = have ? W[c * 64 + lane] : 0;
         vreg[c] = have ? V[c * 64 + lane] : 0;
+        // (an entry behind the list's end counts for nothing: looked at below, where the list's length is known)
+        if (drops && have && NP <= 9) dreg_negative |= (uint32_t)(drop[c * 64 + lane] < 0) << c;
     }
-    const int cap_raw = lane < a.knap_stride ? cap[lane] : 0;
+    const int cap_raw = queues ? (lane == 0 ? q.forward_time[inst] : lane == 1 ? q.backward_time[inst] : 0)
+                               : lane < a.knap_stride ? cap[lane] : 0;
     const int ord_raw = ord && lane < a.knap_stride ? ord[lane] : lane;
-    const int n = a.n_items[inst], m = a.n_knapsacks[inst];
+    const int n = queues ? q.n_buckets : a.n_items[inst], m = queues ? 2 : a.n_knapsacks[inst];
     for (int i = lane; i < lay.row_words; i += 64) zeros[i] = 0;
     // f(first item of the chunk, this lane's weight, this lane's value) for every 64 items
     auto chunks = [&](auto &&f) {
@@ -477,7 +497,7 @@ seq_bits_kernel(BatchArgs a, BitsLayout lay, unsigned long long *swept_cells)
             chunks([&](int i0, int w, int v) {
                 if (i0 + lane < n) {
                     bool bad = w < 1 || v < 0;
-                    if (levels) bad = bad || a.drop_time[(size_t)inst * a.item_stride + i0 + lane] < 0;
+                    if (drops) bad = bad || (NP <= 9 ? (dreg_negative >> (i0 >> 6)) & 1u : drop[i0 + lane] < 0);
                     if (bad) flags |= 1; else vs += (unsigned)v;
                     differs = differs || v != w;
                 }
@@ -510,7 +530,15 @@ seq_bits_kernel(BatchArgs a, BitsLayout lay, unsigned long long *swept_cells)
             if (not_mine) return;
         }
     }
-    int32_t *out_asg = a.assignment + (size_t)inst * a.item_stride;
+    int32_t *out_asg = queues ? nullptr : a.assignment + (size_t)inst * a.item_stride;
+    const size_t record0 = queues ? (size_t)inst * 2 * q.iterations : 0;
+    if (status != DEFT_OK && queues) {
+        for (int x = lane; x < 2 * q.iterations; x += 64) q.stage_case[record0 + x] = q.stage_count[record0 + x] = q.stage_time[record0 + x] = 0;
+        for (int x = lane; x < q.iterations; x += 64) q.update_k[record0 / 2 + x] = 0;
+        if (lane < 2) q.tail[(size_t)inst * 2 + lane] = 0;
+        if (lane == 0) q.status[inst] = status;
+        return;
+    }
     if (status != DEFT_OK) {
         for (int i = lane; i < a.item_stride; i += 64) out_asg[i] = caps_sweep ? 0 : -1;
         if (lane < a.knap_stride) {
@@ -523,105 +551,228 @@ seq_bits_kernel(BatchArgs a, BitsLayout lay, unsigned long long *swept_cells)
         }
         return;
     }
-    for (int i = lane; i < lay.mark_words; i += 64) l.marks[i] = caps_sweep ? 0u : 0xffffffffu;
+    for (int i = lane; i < lay.mark_words; i += 64) l.marks[i] = caps_sweep ? 0u : queues ? 0x7f7f7f7fu : 0xffffffffu;
     uint8_t *mark8 = reinterpret_cast<uint8_t *>(l.marks);
     const int cap_l = lane < m ? cap_raw : 0;
     const int ord_l = lane < m ? ord_raw : lane;
     int kv_l = 0, kl_l = 0;  // lane j: knapsack j's value and load
     long long total = 0;
     wave_lds_sync();
+    // Lists of more than 64 items: the list as it stands (seq_excess.h).
+    constexpr bool by_excess = NP > 6;
+    auto list_weights = [&]() {
+        if constexpr (by_excess) {
+            chunks([&](int i0, int w, int) {
+                const int i = i0 + lane;
+                if (i < n) l.prefix[i] = caps_sweep || mark8[i] == 0xff ? w : kGone;
+            });
+            wave_lds_sync();
+        }
+    };
+    auto list = [&](int i0) { return i0 + lane < n ? l.prefix[i0 + lane] : kGone; };
+    list_weights();
+    // Measurement only: C - w + 1 for every item that the row's sweep goes through, which is until it sees that C (every
+    // capacity of a capacity sweep) is reachable with item `last`; it looks after every eighth item, every second one
+    // of a list of at most 64.
+    auto count_cells = [&](int C, int j, int last, bool reached) {
+        int cnt = 0, sum = 0, upto = 0, weight = 0;
+        auto listed = [&](int i) { return i < n && W[i] <= C && (caps_sweep || mark8[i] == 0xff || mark8[i] == j); };
+        for (int i0 = 0; i0 < n; i0 += 64) {
+            const int i = i0 + lane;
+            const unsigned long long in = __builtin_amdgcn_ballot_w64(listed(i));
+            cnt += (int)__popcll(in);
+            upto += (int)__popcll(in & __builtin_amdgcn_ballot_w64(i <= last));
+            sum += bits_wave_sum(listed(i) ? W[i] : 0);
+        }
+        if (cnt == 0 || (!caps_sweep && (sum <= C || cnt <= kBitsEnumItems))) return;  // (settled without a sweep)
+        const int look = !caps_sweep && cnt <= 64 ? 2 : 8;
+        const int items = reached ? min(cnt, (upto + look - 1) / look * look) : cnt;
+        for (int i0 = 0, before = 0; i0 < n; i0 += 64) {
+            const bool in = listed(i0 + lane);
+            const unsigned long long mask = __builtin_amdgcn_ballot_w64(in);
+            weight += bits_wave_sum(in && before + (int)__popcll(mask & ((1ull << lane) - 1ull)) < items ? W[i0 + lane] : 0);
+            before += (int)__popcll(mask);
+        }
+        if (lane == 0) atomicAdd(swept_cells, (unsigned long long)items * (unsigned)(C + 1) - (unsigned long long)(unsigned)weight);
+    };
 
     BitsRows<K, NP> rows;
     const int cap_max = caps_sweep ? bits_wave_max(cap_l) : 0;
-    const int stages = caps_sweep ? min(m, 1) : m;
+    const int stages = queues ? 2 * q.iterations : m;
+    bool reached = true;
+    int furthest = -1;
+    // Task queues: items and time of the current queue, the iterations that it, the future queue and what is
+    // complete carry, and the time of all buckets.
+    int cur_items = 0, cur_time = 0, cur_k = 0, fut_k = 0, done_k = 0, all_time = 0;
+    if (queues) {
+        chunks([&](int i0, int w, int) { all_time += i0 + lane < n ? w : 0; });
+        all_time = bits_wave_sum(all_time);
+    }
     for (int s = 0; s < stages; ++s) {
-        const int j = __builtin_amdgcn_readlane(ord_l, s);
-        const int C = caps_sweep ? cap_max : __builtin_amdgcn_readlane(cap_l, j);
+        const int j = __builtin_amdgcn_readlane(ord_l, queues ? s & 1 : s);
+        int C = __builtin_amdgcn_readlane(cap_l, j);
         const int lane = bits_local(lane_);
-        // offered items: not yet placed and able to fit at all, ascending index
-        int cnt = 0, sum = 0;
-        bool all_placed = true;
-        if (lane == 0) l.prefix[0] = 0;
-        chunks([&](int i0, int w, int) {
-            const int i = i0 + lane;
-            const bool open = i < n && (caps_sweep || mark8[i] == 0xff);
-            const bool offered = open && w <= C;
-            all_placed = all_placed && __builtin_amdgcn_ballot_w64(open) == 0ull;
-            const unsigned long long mask = __builtin_amdgcn_ballot_w64(offered);
-            const int upto = sum + bits_wave_prefix_sum(offered ? w : 0, lane);  // (4096 weights of at most 65535)
-            if (offered) {
-                const int pos = cnt + __popcll(mask & ((1ull << lane) - 1ull));
-                l.prefix[pos + 1] = upto;
-                l.index[pos] = (uint16_t)i;
+        int case_now = 0, first_items = 0, first_time = 0;
+        if (queues) {
+            if (cur_items > 0 && (j == 0 || cur_time > C)) {
+                case_now = j + 1;  // Case 1 / Case 2: Problem 1 over the current queue
+            } else if (j == 1) {
+                // Case 3 (the current queue fits and goes first) / Case 4 (it is empty): Algorithm 1 over this iteration's
+                // buckets merged with the future queue, with what is left.  (Of its levels the whole list has
+                // the greatest value, and the level that is returned selects the same.)
+                case_now = cur_items > 0 ? 3 : 4;
+                first_items = cur_items;
+                first_time = cur_time;
+                C -= cur_time;
+                done_k += cur_k;
+                cur_k = fut_k + 1;
+                fut_k = 0;
+                cur_items = n;
+                cur_time = all_time;
+                for (int i = lane; i < lay.mark_words; i += 64) l.marks[i] = 0xffffffffu;
+                wave_lds_sync();
+                list_weights();
             }
-            cnt += __popcll(mask);
-            sum = __builtin_amdgcn_readlane(upto, 63);
-        });
-        if (all_placed && !levels) break;  // every item is placed: the remaining stages stay empty
-        wave_lds_sync();
-        int value = 0, last = -1;  // last: the list position whose item completed the value
-        if (cnt == 0) {
-            // nothing is offered
-        } else if (sum <= C && !caps_sweep) {
-            // everything offered fits together: the DP takes it all (every value is positive)
-            for (int p = lane; p < cnt; p += 64) mark8[l.index[p]] = (uint8_t)j;
-            value = sum;
-            last = cnt - 1;
-        } else if (cnt <= kBitsEnumItems && !caps_sweep) {
-            // A handful of items: lane x weighs the subset whose members are the set bits of x.  The
-            // DP with its walk returns the feasible subset of greatest value and, among
-            // equals, the one with the smallest such number.
-            int ws = 0;
-            for (int p = 0; p < cnt; ++p)
-                if ((lane >> p) & 1) ws += l.prefix[p + 1] - l.prefix[p];
-            const bool feasible = lane < (1 << cnt) && ws <= C;
-            value = bits_wave_max(feasible ? ws : -1);
-            const int pick = __builtin_ctzll(__builtin_amdgcn_ballot_w64(feasible && ws == value));  // (the empty set is feasible)
-            if (lane < cnt && ((pick >> lane) & 1)) mark8[l.index[lane]] = (uint8_t)j;
-            last = 31 - __builtin_clz(pick | 1);
-        } else {
-            const BitsSweep sw = bits_sweep<K, NP>(l, rows, lane, cnt, C, caps_sweep, cap_l);
-            const int steps = sw.q;
-            if (swept_cells && lane == 0) {
-                // measurement only: C - w + 1 per item the sweep went through
-                atomicAdd(swept_cells,
-                          (unsigned long long)sw.items * (unsigned)(C + 1) - (unsigned long long)(unsigned)l.prefix[sw.items]);
+            if (swept_cells) {
+                for (int i = lane; i < n; i += 64)
+                    if (mark8[i] != 0xff) mark8[i] = 0x7f;
+                wave_lds_sync();
             }
-            bits_publish<K, NP>(l, rows, lane, C);
-            if (!caps_sweep) {
-                value = sw.reached ? C : bits_top<K, NP>(rows, lane, C);
-                if (value > 0) last = min(bits_first<NP>(l.planes, value, steps), cnt - 1);
-                const int left = bits_walk<NP>(l, lane, 64, value, cnt, steps, [&](int p) { mark8[l.index[p]] = (uint8_t)j; });
-                if (left != 0) status = DEFT_ERR_DEVICE;  // (never expected)
-            } else {
-                // One sweep at the largest capacity answers every capacity: the largest reachable
-                // sum not above it, and the chain from that sum is the selection the DP would walk
-                // back there.  The lanes are dealt out to the capacities in groups, all walks run side
-                // by side, and an item's word collects the capacities at which it is taken.
-                int t = 0;
-                if (lane < m) {
-                    int wi = cap_l >> 5;
-                    uint32_t bits = l.set[wi] & (0xffffffffu >> (31 - (cap_l & 31)));
-                    while (bits == 0) bits = l.set[--wi];  // (word 0 holds the empty sum)
-                    t = wi * 32 + 31 - __builtin_clz(bits);
+        }
+        int value = 0, last = -1, got = 0;  // last: the item that completed the value
+        // (a capacity sweep: every capacity is a stage of its own over the whole list)
+        ExcessResult r = queues && case_now == 0 ? kExcessEmpty : kExcessNot;
+        if constexpr (by_excess) {
+            if (r == kExcessNot) {
+                r = excess_stage<NP>(list, lane, n, C, value, last, [&](int i0, unsigned long long in) {
+                    got += (int)__popcll(in);
+                    if ((in >> lane) & 1ull) {
+                        if (caps_sweep) {
+                            l.marks[i0 + lane] |= 1u << s;
+                        } else {
+                            mark8[i0 + lane] = (uint8_t)j;
+                            l.prefix[i0 + lane] = kGone;
+                        }
+                    }
+                });
+                if (r == kExcessEmpty && !levels && !caps_sweep && !queues) break;  // every item is placed: the remaining stages stay empty
+            }
+            // (a capacity sweep: every capacity is a stage of its own over the whole list)
+            reached = reached && value == C;
+            furthest = max(furthest, last);
+            if (swept_cells && r == kExcessDone && (!caps_sweep || s + 1 == stages))
+                count_cells(caps_sweep ? cap_max : C, j, caps_sweep ? furthest : last, !caps_sweep || reached);
+        }
+        if (r == kExcessNot) {
+            // the row's own sweep, over a list in LDS (in the place of the weights); for all capacities of a capacity sweep at once
+            if (caps_sweep) C = cap_max;
+            int cnt = 0, sum = 0;
+            bool all_placed = true;
+            if (lane == 0) l.prefix[0] = 0;
+            chunks([&](int i0, int w, int) {
+                const int i = i0 + lane;
+                const bool open = i < n && (caps_sweep || mark8[i] == 0xff), offered = open && w <= C;
+                if constexpr (!by_excess) all_placed = all_placed && __builtin_amdgcn_ballot_w64(open) == 0ull;
+                const unsigned long long mask = __builtin_amdgcn_ballot_w64(offered);
+                const int upto = sum + bits_wave_prefix_sum(offered ? w : 0, lane);  // (4096 weights of at most 65535)
+                if (offered) {
+                    const int pos = cnt + __popcll(mask & ((1ull << lane) - 1ull));
+                    l.prefix[pos + 1] = upto;
+                    l.index[pos] = (uint16_t)i;
                 }
-                kv_l = kl_l = t;
-                int G = 64;
-                while (G > 1 && 64 / G < m) G >>= 1;
-                const int x = lane / G;  // this group's capacity
-                int t_group = __shfl(t, x);
-                if (x >= m) t_group = 0;
-                const int left = bits_walk<NP>(l, lane, G, t_group, cnt, steps,
-                                               [&](int p) { atomicOr(&l.marks[l.index[p]], 1u << x); });
-                if (__builtin_amdgcn_ballot_w64(left != 0) != 0ull) status = DEFT_ERR_DEVICE;  // (never expected)
+                cnt += __popcll(mask);
+                sum = __builtin_amdgcn_readlane(upto, 63);
+            });
+            if constexpr (!by_excess) {
+                if (all_placed && !levels && !queues) break;  // every item is placed: the remaining stages stay empty
             }
-            bits_release(l, lane);
+            wave_lds_sync();
+            if (cnt == 0) {
+                // nothing is offered
+            } else if (!by_excess && sum <= C && !caps_sweep) {
+                // everything offered fits together: the DP takes it all (every value is positive)
+                for (int p = lane; p < cnt; p += 64) mark8[l.index[p]] = (uint8_t)j;
+                value = sum;
+                last = l.index[cnt - 1];
+            } else if (cnt <= kBitsEnumItems && !caps_sweep) {
+                // A handful of items: lane x weighs the subset whose members are the set bits of x.  The
+                // DP with its walk returns the feasible subset of greatest value and, among
+                // equals, the one with the smallest such number.
+                int ws = 0;
+                for (int p = 0; p < cnt; ++p)
+                    if ((lane >> p) & 1) ws += l.prefix[p + 1] - l.prefix[p];
+                const bool feasible = lane < (1 << cnt) && ws <= C;
+                value = bits_wave_max(feasible ? ws : -1);
+                const int pick = __builtin_ctzll(__builtin_amdgcn_ballot_w64(feasible && ws == value));  // (the empty set is feasible)
+                if (lane < cnt && ((pick >> lane) & 1)) mark8[l.index[lane]] = (uint8_t)j;
+                last = l.index[31 - __builtin_clz(pick | 1)];
+            } else {
+                const BitsSweep sw = bits_sweep<K, NP>(l, rows, lane, cnt, C, caps_sweep, cap_l);
+                const int steps = sw.q;
+                if (swept_cells && lane == 0) {
+                    // measurement only: C - w + 1 per item the sweep went through
+                    atomicAdd(swept_cells,
+                              (unsigned long long)sw.items * (unsigned)(C + 1) - (unsigned long long)(unsigned)l.prefix[sw.items]);
+                }
+                bits_publish<K, NP>(l, rows, lane, C);
+                if (!caps_sweep) {
+                    value = sw.reached ? C : bits_top<K, NP>(rows, lane, C);
+                    if (value > 0) last = l.index[min(bits_first<NP>(l.planes, value, steps), cnt - 1)];
+                    const int left = bits_walk<NP>(l, lane, 64, value, cnt, steps, [&](int p) { mark8[l.index[p]] = (uint8_t)j; });
+                    if (left != 0) status = DEFT_ERR_DEVICE;  // (never expected)
+                } else {
+                    // One sweep at the largest capacity answers every capacity: the largest reachable
+                    // sum not above it, and the chain from that sum is the selection the DP would walk
+                    // back there.  The lanes are dealt out to the capacities in groups, all walks run side
+                    // by side, and an item's word collects the capacities at which it is taken.
+                    int t = 0;
+                    if (lane < m) {
+                        int wi = cap_l >> 5;
+                        uint32_t bits = l.set[wi] & (0xffffffffu >> (31 - (cap_l & 31)));
+                        while (bits == 0) bits = l.set[--wi];  // (word 0 holds the empty sum)
+                        t = wi * 32 + 31 - __builtin_clz(bits);
+                    }
+                    kv_l = kl_l = t;
+                    int G = 64;
+                    while (G > 1 && 64 / G < m) G >>= 1;
+                    const int x = lane / G;  // this group's capacity
+                    int t_group = __shfl(t, x);
+                    if (x >= m) t_group = 0;
+                    const int left = bits_walk<NP>(l, lane, G, t_group, cnt, steps,
+                                                   [&](int p) { atomicOr(&l.marks[l.index[p]], 1u << x); });
+                    if (__builtin_amdgcn_ballot_w64(left != 0) != 0ull) status = DEFT_ERR_DEVICE;  // (never expected)
+                }
+                bits_release(l, lane);
+            }
+            wave_lds_sync();
+            if (caps_sweep) break;
+            if (s + 1 < stages) list_weights();
+            if (queues) {
+                int open = 0;
+                for (int i = lane; i < n; i += 64) open += mark8[i] == 0xff;
+                got = cur_items - bits_wave_sum(open);
+            }
         }
         wave_lds_sync();
-        if (!caps_sweep) {
-            if (lane == j) kv_l = kl_l = value;
-            total += value;
+        if (queues) {
+            cur_items -= got;
+            cur_time -= value;
+            if (case_now == 2) fut_k += 1;  // the new buckets wait in the future queue
+            if (case_now != 0 && cur_items == 0) {
+                done_k += cur_k;
+                cur_k = 0;
+            }
+            if (lane == 0) {
+                q.stage_case[record0 + s] = case_now;
+                q.stage_count[record0 + s] = case_now != 0 ? first_items + got : 0;
+                q.stage_time[record0 + s] = case_now != 0 ? first_time + value : 0;
+                if (j == 1) q.update_k[(record0 + s) / 2] = done_k;  // everything complete is applied in one update
+            }
+            if (j == 1) done_k = 0;
+            continue;
         }
+        if (lane == j) kv_l = kl_l = value;
+        total += value;
         if (levels) {
             // Algorithm 1: level d keeps the first n - d items and the remaining time R less the drop
             // times of the others.  The levels' answers are nested (fewer items, less time), so the
@@ -637,14 +788,12 @@ seq_bits_kernel(BatchArgs a, BitsLayout lay, unsigned long long *swept_cells)
             if (value > 0) {
                 length = n;
                 remain = C;
-                const int beyond = l.index[last];
-                const int32_t *drop = a.drop_time + (size_t)inst * a.item_stride;
                 int behind = 0;
                 for (int i0 = (n - 1) & ~63; i0 >= 0; i0 -= 64) {
                     const int e = i0 + lane;
                     const int x = bits_wave_suffix_sum(e < n ? min(drop[e], kOver) : 0, lane);
                     const int time_left = C - min(x + behind, kOver);
-                    const unsigned long long hit = __builtin_amdgcn_ballot_w64(e > beyond && e < n && time_left >= value);
+                    const unsigned long long hit = __builtin_amdgcn_ballot_w64(e > last && e < n && time_left >= value);
                     if (hit == 0ull) break;
                     length = i0 + __builtin_ctzll(hit);
                     remain = __builtin_amdgcn_readlane(time_left, __builtin_ctzll(hit));
@@ -657,6 +806,11 @@ seq_bits_kernel(BatchArgs a, BitsLayout lay, unsigned long long *swept_cells)
                 kl_l = remain;
             }
         }
+    }
+    if (queues) {
+        if (lane < 2) q.tail[(size_t)inst * 2 + lane] = lane == 0 ? cur_k : fut_k;
+        if (lane == 0) q.status[inst] = status;
+        return;
     }
     if (caps_sweep) total = bits_wave_max(kv_l);
 
@@ -681,7 +835,24 @@ constexpr int kBitsWords[] = {2, 5, 7, 10, 14, 20, 32};
 constexpr int kNumBitsWords = 7;
 constexpr int kBitsPlanes[] = {6, 9, 12};
 
-typedef void (*BitsKernel)(BatchArgs, BitsLayout, unsigned long long *);
+typedef void (*BitsKernel)(BatchArgs, ScheduleArgs, BitsLayout, unsigned long long *);
+
+// The kernel of a variant (3 times the index in kBitsWords, plus the index in kBitsPlanes), among those of the
+// word counts W .. END - 1 that a translation unit compiles.
+template <int W, int END, bool QUEUES>
+const void *bits_kernel_of(int variant)
+{
+    if constexpr (W < END) {
+        constexpr int K = kBitsWords[W];
+        if (variant / 3 != W) return bits_kernel_of<W + 1, END, QUEUES>(variant);
+        const BitsKernel fn = variant % 3 == 0   ? &seq_bits_kernel<K, kBitsPlanes[0], QUEUES>
+                              : variant % 3 == 1 ? &seq_bits_kernel<K, kBitsPlanes[1], QUEUES>
+                                                 : &seq_bits_kernel<K, kBitsPlanes[2], QUEUES>;
+        return reinterpret_cast<const void *>(fn);
+    }
+    return nullptr;
+}
+constexpr int kBitsShort = 3;  // word counts of the shorter rows
 
 }  // namespace
 
