@@ -16,6 +16,7 @@ BitsLayout bits_layout(const SeqBitsPlan &p, bool caps_sweep)
     lay.n_pad = p.n_pad;
     lay.mark_words = caps_sweep ? p.n_pad : p.n_pad / 4;
     lay.plane_words = p.row_words * bits_plane_stride(p.planes);
+    lay.share = 1;
     lay.wave_words = 2 * p.row_words + 4 + (p.n_pad + 8) + p.n_pad / 2 + lay.mark_words;
     return lay;
 }
@@ -77,7 +78,22 @@ namespace {
 hipError_t bits_launch(const SeqBitsPlan &p, bool queues, const BatchArgs &a, const ScheduleArgs &q, hipStream_t st,
                        unsigned long long *swept_cells)
 {
-    const BitsLayout lay = bits_layout(p, a.mode == DEFT_MODE_CAPACITY_SWEEP);
+    BitsLayout lay = bits_layout(p, a.mode == DEFT_MODE_CAPACITY_SWEEP);
+    // A capacity sweep of lists that are answered capacity by capacity (more than 64 items): as many wavefronts an
+    // instance, up to four, as the whole batch leaves room for.  1024 instances of 314 items and eleven capacities: one
+    // TT1 us, three TT3.
+    if (a.mode == DEFT_MODE_CAPACITY_SWEEP && p.planes > 6) {
+        const int64_t lds = bits_lds_bytes(lay, 1);
+        for (int share = 4; share > 1; --share) {
+            const int by_lds = kLdsGranulesPerCu / (int)((lds + kLdsGranule - 1) / kLdsGranule);
+            const int by_regs = 4 * bits_waves_per_simd(p.words_per_lane, p.planes) / share;
+            if (share > a.knap_stride || (int64_t)(by_lds < by_regs ? by_lds : by_regs) * p.compute_units < a.batch) continue;
+            lay.share = share;
+            hipLaunchKernelGGL(reinterpret_cast<BitsKernel>(const_cast<void *>(bits_kernel(p, false))), dim3((unsigned)a.batch),
+                               dim3(64 * share), (size_t)lds, st, a, q, lay, swept_cells);
+            return hipGetLastError();
+        }
+    }
     // Instances per workgroup: they share one copy of the walk's planes, the largest part of an
     // instance's LDS, but walk one at a time.  So: as few as still let the whole batch run at
     // once, else as many as put the most instances on a compute unit.

@@ -139,6 +139,7 @@ namespace {
 // [zeros: row_words][set: row_words][pad: 4][prefix: n_pad + 8][index: n_pad / 2][marks: mark_words].
 struct BitsLayout {
     int32_t row_words, n_pad, mark_words, plane_words, wave_words;
+    int32_t share;  // wavefronts of an instance (capacity sweep; else 1): they share its part, and deal its capacities out
 };
 // One instance's share of it.
 struct BitsLds {
@@ -431,11 +432,12 @@ seq_bits_kernel(BatchArgs a, ScheduleArgs q, BitsLayout lay, unsigned long long 
     extern __shared__ __align__(16) int32_t lds_bits[];
     const int lane_ = threadIdx.x & 63, lane = lane_;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int inst = (int)blockIdx.x * (int)(blockDim.x >> 6) + wave;
+    const int share = QUEUES ? 1 : lay.share;
+    const int inst = share > 1 ? (int)blockIdx.x : (int)blockIdx.x * (int)(blockDim.x >> 6) + wave;
     BitsLds l;
     l.lock = lds_bits;
     l.planes = reinterpret_cast<uint32_t *>(lds_bits) + 4;
-    uint32_t *zeros = l.planes + lay.plane_words + (size_t)wave * lay.wave_words;
+    uint32_t *zeros = l.planes + lay.plane_words + (size_t)(share > 1 ? 0 : wave) * lay.wave_words;
     l.set = zeros + lay.row_words;
     l.prefix = reinterpret_cast<int32_t *>(l.set + lay.row_words + 4);
     l.index = reinterpret_cast<uint16_t *>(l.prefix + lay.n_pad + 8);
@@ -515,10 +517,9 @@ seq_bits_kernel(BatchArgs a, ScheduleArgs q, BitsLayout lay, unsigned long long 
                 if ((int)(__popc((uint32_t)seen_lo) + __popc((uint32_t)seen_hi)) != m) flags |= 1;
             }
         }
-        // (a lane adds at most 64 values below 2^31: three 16-bit pieces keep the sums in range)
-        const unsigned long long total_v = (unsigned long long)(unsigned)bits_wave_sum((int)(vs & 0xffffu)) +
-                                           ((unsigned long long)(unsigned)bits_wave_sum((int)((vs >> 16) & 0xffffu)) << 16) +
-                                           ((unsigned long long)(unsigned)bits_wave_sum((int)(vs >> 32)) << 32);
+        // (a lane adds at most 64 values below 2^31: two pieces, of 24 and 13 bits, keep the sums in range)
+        const unsigned long long total_v = (unsigned long long)(unsigned)bits_wave_sum((int)(vs & 0xffffffu)) +
+                                           ((unsigned long long)(unsigned)bits_wave_sum((int)(vs >> 24)) << 24);
         if (__builtin_amdgcn_ballot_w64((flags & 1) != 0) != 0ull) status = DEFT_ERR_INVALID_ARG;
         else if (__builtin_amdgcn_ballot_w64((flags & 2) != 0) != 0ull) status = DEFT_ERR_LIMIT;
         else if (total_v >= (1ull << 31)) status = DEFT_ERR_OVERFLOW;
@@ -571,6 +572,13 @@ seq_bits_kernel(BatchArgs a, ScheduleArgs q, BitsLayout lay, unsigned long long 
     };
     auto list = [&](int i0) { return i0 + lane < n ? l.prefix[i0 + lane] : kGone; };
     list_weights();
+    // Where wavefronts share an instance: [0 .. 30] the values, then whether a capacity is left over, the furthest last
+    // item + 1, whether a capacity was not reached (in the place of the walk's planes).
+    uint32_t *shared = l.planes;
+    if (share > 1) {
+        if (wave == 0 && lane < 34 && lane > 30) shared[lane] = 0;
+        __syncthreads();
+    }
     // Measurement only: C - w + 1 for every item that the row's sweep goes through, which is until it sees that C (every
     // capacity of a capacity sweep) is reachable with item `last`; it looks after every eighth item, every second one
     // of a list of at most 64.
@@ -608,8 +616,25 @@ seq_bits_kernel(BatchArgs a, ScheduleArgs q, BitsLayout lay, unsigned long long 
         chunks([&](int i0, int w, int) { all_time += i0 + lane < n ? w : 0; });
         all_time = bits_wave_sum(all_time);
     }
-    for (int s = 0; s < stages; ++s) {
-        const int j = __builtin_amdgcn_readlane(ord_l, queues ? s & 1 : s);
+    bool to_row = false;
+    for (int s = share > 1 ? wave : 0;; s += share) {
+        if (s >= stages) {
+            if (share == 1) break;
+            // what the instance's other wavefronts have answered
+            if (lane == 0) {
+                atomicMax(&shared[32], (uint32_t)(furthest + 1));
+                if (!reached) shared[33] = 1u;
+            }
+            __syncthreads();
+            if (wave != 0) return;
+            if (shared[31] == 0u) {
+                kv_l = kl_l = lane < m ? (int)shared[lane] : 0;
+                if (swept_cells && m > 0) count_cells(cap_max, 0, (int)shared[32] - 1, shared[33] == 0u);
+                break;
+            }
+            to_row = true;
+        }
+        const int j = __builtin_amdgcn_readlane(ord_l, queues ? s & 1 : min(s, 63));
         int C = __builtin_amdgcn_readlane(cap_l, j);
         const int lane = bits_local(lane_);
         int case_now = 0, first_items = 0, first_time = 0;
@@ -643,12 +668,12 @@ seq_bits_kernel(BatchArgs a, ScheduleArgs q, BitsLayout lay, unsigned long long 
         // (a capacity sweep: every capacity is a stage of its own over the whole list)
         ExcessResult r = queues && case_now == 0 ? kExcessEmpty : kExcessNot;
         if constexpr (by_excess) {
-            if (r == kExcessNot) {
+            if (r == kExcessNot && !to_row) {
                 r = excess_stage<NP>(list, lane, n, C, value, last, [&](int i0, unsigned long long in) {
                     got += (int)__popcll(in);
                     if ((in >> lane) & 1ull) {
                         if (caps_sweep) {
-                            l.marks[i0 + lane] |= 1u << s;
+                            atomicOr(&l.marks[i0 + lane], 1u << s);
                         } else {
                             mark8[i0 + lane] = (uint8_t)j;
                             l.prefix[i0 + lane] = kGone;
@@ -660,6 +685,11 @@ seq_bits_kernel(BatchArgs a, ScheduleArgs q, BitsLayout lay, unsigned long long 
             // (a capacity sweep: every capacity is a stage of its own over the whole list)
             reached = reached && value == C;
             furthest = max(furthest, last);
+            if (share > 1 && !to_row) {
+                if (lane == 0) shared[r == kExcessNot ? 31 : s] = r == kExcessNot ? 1u : (uint32_t)value;
+                if (r == kExcessNot) s = stages;
+                continue;
+            }
             if (swept_cells && r == kExcessDone && (!caps_sweep || s + 1 == stages))
                 count_cells(caps_sweep ? cap_max : C, j, caps_sweep ? furthest : last, !caps_sweep || reached);
         }
