@@ -37,7 +37,7 @@ int bits_per_cu(const SeqBitsPlan &p, int64_t lds, int waves)
 
 const void *bits_kernel(const SeqBitsPlan &p, bool queues)
 {
-    if (p.variant >= 3 * kBitsShort) return seq_bits_long_kernel(p.variant, queues);
+    if (p.variant >= 4 * kBitsShort) return seq_bits_long_kernel(p.variant, queues);
     return queues ? seq_bits_queues_kernel(p.variant) : bits_kernel_of<0, kBitsShort, false>(p.variant);
 }
 
@@ -48,8 +48,8 @@ bool seq_bits_plan(int32_t max_capacity, int32_t max_items, int32_t lds_per_wg_b
     for (int i = 0; i < kNumBitsWords; ++i) {
         const int K = kBitsWords[i];
         if ((int64_t)max_capacity > (int64_t)K * 2048 - 1) continue;
-        const int which = max_items <= 64 ? 0 : max_items <= 512 ? 1 : 2, grain = bits_grain(K);
-        p->variant = 3 * i + which;
+        const int which = max_items <= 64 ? 0 : max_items < kBitsExcessItems ? 1 : max_items <= 512 ? 2 : 3, grain = bits_grain(K);
+        p->variant = 4 * i + which;
         p->words_per_lane = K;
         p->planes = kBitsPlanes[which];
         p->row_words = (max_capacity / 2048 + grain) / grain * grain * 64;
@@ -75,22 +75,21 @@ hipError_t seq_bits_prepare(const SeqBitsPlan &p)
 
 namespace {
 
-hipError_t bits_launch(const SeqBitsPlan &p, bool queues, const BatchArgs &a, const ScheduleArgs &q, hipStream_t st,
-                       unsigned long long *swept_cells)
+template <bool QUEUES>
+hipError_t bits_launch(const SeqBitsPlan &p, const BatchArgs &a, const BitsQueueArgs<QUEUES> &q, hipStream_t st, unsigned long long *swept_cells)
 {
+    const auto kernel = reinterpret_cast<BitsKernel<QUEUES>>(const_cast<void *>(bits_kernel(p, QUEUES)));
     BitsLayout lay = bits_layout(p, a.mode == DEFT_MODE_CAPACITY_SWEEP);
-    // A capacity sweep of lists that are answered capacity by capacity (more than 64 items): as many wavefronts an
-    // instance, up to four, as the whole batch leaves room for.  1024 instances of 314 items and eleven capacities: one
-    // TT1 us, three TT3.
-    if (a.mode == DEFT_MODE_CAPACITY_SWEEP && p.planes > 6) {
+    // A capacity sweep of lists that are answered capacity by capacity: as many wavefronts an instance, up to four, as the
+    // whole batch leaves room for.  1024 instances of 314 items and eleven capacities: one 79 us, three 38.
+    if (a.mode == DEFT_MODE_CAPACITY_SWEEP && a.item_stride >= kBitsExcessCapsItems) {
         const int64_t lds = bits_lds_bytes(lay, 1);
         for (int share = 4; share > 1; --share) {
             const int by_lds = kLdsGranulesPerCu / (int)((lds + kLdsGranule - 1) / kLdsGranule);
             const int by_regs = 4 * bits_waves_per_simd(p.words_per_lane, p.planes) / share;
             if (share > a.knap_stride || (int64_t)(by_lds < by_regs ? by_lds : by_regs) * p.compute_units < a.batch) continue;
             lay.share = share;
-            hipLaunchKernelGGL(reinterpret_cast<BitsKernel>(const_cast<void *>(bits_kernel(p, false))), dim3((unsigned)a.batch),
-                               dim3(64 * share), (size_t)lds, st, a, q, lay, swept_cells);
+            hipLaunchKernelGGL(kernel, dim3((unsigned)a.batch), dim3(64 * share), (size_t)lds, st, a, q, lay, swept_cells);
             return hipGetLastError();
         }
     }
@@ -106,7 +105,7 @@ hipError_t bits_launch(const SeqBitsPlan &p, bool queues, const BatchArgs &a, co
     }
     const size_t lds = (size_t)bits_lds_bytes(lay, waves);
     const unsigned grid = (unsigned)((a.batch + waves - 1) / waves);
-    hipLaunchKernelGGL(reinterpret_cast<BitsKernel>(const_cast<void *>(bits_kernel(p, queues))), dim3(grid), dim3(64 * waves), lds, st, a, q, lay, swept_cells);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * waves), lds, st, a, q, lay, swept_cells);
     return hipGetLastError();
 }
 
@@ -114,7 +113,7 @@ hipError_t bits_launch(const SeqBitsPlan &p, bool queues, const BatchArgs &a, co
 
 hipError_t seq_bits_launch(const SeqBitsPlan &p, const BatchArgs &a, hipStream_t st, unsigned long long *swept_cells)
 {
-    return bits_launch(p, false, a, ScheduleArgs{}, st, swept_cells);
+    return bits_launch<false>(p, a, BitsNoArgs{}, st, swept_cells);
 }
 
 hipError_t seq_bits_queues_launch(const SeqBitsPlan &p, const ScheduleArgs &q, hipStream_t st, unsigned long long *swept_cells)
@@ -127,7 +126,7 @@ hipError_t seq_bits_queues_launch(const SeqBitsPlan &p, const ScheduleArgs &q, h
     a.max_capacity = q.max_capacity;
     a.weights = a.values = q.comm_time;  // the value of a bucket is its communication time
     a.drop_time = q.drop_time;
-    return bits_launch(p, true, a, q, st, swept_cells);
+    return bits_launch<true>(p, a, q, st, swept_cells);
 }
 
 }  // namespace deft

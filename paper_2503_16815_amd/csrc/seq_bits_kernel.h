@@ -50,10 +50,17 @@
 
 #include "instance_check.h"
 
+#include <type_traits>
+
 namespace deft {
 
 namespace {
 
+// Shorter lists are swept at once (81 items, 1735 of them: by what their stages leave out 27.4 -> 36 us; 93 items 13.9 -> 16.7), and
+// so are capacity sweeps of fewer than 129 items: one capacity that is not answered by itself sends the others along (101
+// items, nine of them with eight capacities: 18.8 -> 26.7).  Handles for shorter lists have kernels without it, whose sweep
+// has the registers (66 items: 17.7 against 20.8 us).
+constexpr int kBitsExcessItems = 97, kBitsExcessCapsItems = 129;
 constexpr int kBitsEnumItems = 6;  // stages offered at most this many items are settled by enumeration
 
 // words-per-lane counts are compiled for; a block of items works on a multiple of bits_grain(K) slots
@@ -421,18 +428,26 @@ __device__ __forceinline__ int bits_walk(const BitsLds &l, int lane, int G, int 
     return t;
 }
 
+// The task queues' arguments, of the kernels that solve those.
+struct BitsNoArgs {
+    int32_t n_buckets, iterations;
+};
+template <bool QUEUES>
+using BitsQueueArgs = std::conditional_t<QUEUES, ScheduleArgs, BitsNoArgs>;
+
 // K: words per lane (capacities up to 2048 K - 1).  NP: planes (lists of up to 2^NP items).
 // a.mode: DEFT_MODE_SEQUENTIAL, DEFT_MODE_RECURSIVE or DEFT_MODE_CAPACITY_SWEEP.  QUEUES: the two task queues (q; the
 // candidates' times as a's weights and values), all stages of a candidate by its wavefront; its current queue is the
 // list as it stands after the stage before.
-template <int K, int NP, bool QUEUES>
+template <int K, int NP, bool QUEUES, bool EXCESS>
 __global__ void __launch_bounds__(256, bits_waves_per_simd(K, NP))
-seq_bits_kernel(BatchArgs a, ScheduleArgs q, BitsLayout lay, unsigned long long *swept_cells)
+seq_bits_kernel(BatchArgs a, BitsQueueArgs<QUEUES> q, BitsLayout lay, unsigned long long *swept_cells)
 {
     extern __shared__ __align__(16) int32_t lds_bits[];
     const int lane_ = threadIdx.x & 63, lane = lane_;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int share = QUEUES ? 1 : lay.share;
+    constexpr bool by_excess = EXCESS;  // stages by what they leave out (seq_excess.h)
+    const int share = QUEUES || !by_excess ? 1 : lay.share;
     const int inst = share > 1 ? (int)blockIdx.x : (int)blockIdx.x * (int)(blockDim.x >> 6) + wave;
     BitsLds l;
     l.lock = lds_bits;
@@ -460,18 +475,22 @@ seq_bits_kernel(BatchArgs a, ScheduleArgs q, BitsLayout lay, unsigned long long 
     const int32_t *drop = drops ? a.drop_time + (size_t)inst * a.item_stride : nullptr;
     const int32_t *cap = queues ? nullptr : a.capacities + (size_t)inst * a.knap_stride;
     const int32_t *ord = a.fill_order ? a.fill_order + (size_t)inst * a.knap_stride : nullptr;
-    int wreg[NCH], vreg[NCH];
-    uint32_t dreg_negative = 0;  // bit c: chunk c's drop time of this lane is negative
+    int wreg[NCH], vreg[NCH], dreg[NCH];
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
         const bool have = c * 64 + lane < a.item_stride;
         wreg[c] = have ? W[c * 64 + lane] : 0;
         vreg[c] = have ? V[c * 64 + lane] : 0;
-        // (an entry behind the list's end counts for nothing: looked at below, where the list's length is known)
-        if (drops && have && NP <= 9) dreg_negative |= (uint32_t)(drop[c * 64 + lane] < 0) << c;
+        dreg[c] = 0;
     }
-    const int cap_raw = queues ? (lane == 0 ? q.forward_time[inst] : lane == 1 ? q.backward_time[inst] : 0)
-                               : lane < a.knap_stride ? cap[lane] : 0;
+    if (drops && NP <= 9) {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+            if (c * 64 + lane < a.item_stride) dreg[c] = drop[c * 64 + lane];
+    }
+    int cap_raw;
+    if constexpr (queues) cap_raw = lane == 0 ? q.forward_time[inst] : lane == 1 ? q.backward_time[inst] : 0;
+    else cap_raw = lane < a.knap_stride ? cap[lane] : 0;
     const int ord_raw = ord && lane < a.knap_stride ? ord[lane] : lane;
     const int n = queues ? q.n_buckets : a.n_items[inst], m = queues ? 2 : a.n_knapsacks[inst];
     for (int i = lane; i < lay.row_words; i += 64) zeros[i] = 0;
@@ -499,7 +518,7 @@ seq_bits_kernel(BatchArgs a, ScheduleArgs q, BitsLayout lay, unsigned long long 
             chunks([&](int i0, int w, int v) {
                 if (i0 + lane < n) {
                     bool bad = w < 1 || v < 0;
-                    if (drops) bad = bad || (NP <= 9 ? (dreg_negative >> (i0 >> 6)) & 1u : drop[i0 + lane] < 0);
+                    if (drops) bad = bad || (NP <= 9 ? dreg[i0 >> 6 & (NCH - 1)] : drop[i0 + lane]) < 0;
                     if (bad) flags |= 1; else vs += (unsigned)v;
                     differs = differs || v != w;
                 }
@@ -533,12 +552,14 @@ seq_bits_kernel(BatchArgs a, ScheduleArgs q, BitsLayout lay, unsigned long long 
     }
     int32_t *out_asg = queues ? nullptr : a.assignment + (size_t)inst * a.item_stride;
     const size_t record0 = queues ? (size_t)inst * 2 * q.iterations : 0;
-    if (status != DEFT_OK && queues) {
-        for (int x = lane; x < 2 * q.iterations; x += 64) q.stage_case[record0 + x] = q.stage_count[record0 + x] = q.stage_time[record0 + x] = 0;
-        for (int x = lane; x < q.iterations; x += 64) q.update_k[record0 / 2 + x] = 0;
-        if (lane < 2) q.tail[(size_t)inst * 2 + lane] = 0;
-        if (lane == 0) q.status[inst] = status;
-        return;
+    if constexpr (queues) {
+        if (status != DEFT_OK) {
+            for (int x = lane; x < 2 * q.iterations; x += 64) q.stage_case[record0 + x] = q.stage_count[record0 + x] = q.stage_time[record0 + x] = 0;
+            for (int x = lane; x < q.iterations; x += 64) q.update_k[record0 / 2 + x] = 0;
+            if (lane < 2) q.tail[(size_t)inst * 2 + lane] = 0;
+            if (lane == 0) q.status[inst] = status;
+            return;
+        }
     }
     if (status != DEFT_OK) {
         for (int i = lane; i < a.item_stride; i += 64) out_asg[i] = caps_sweep ? 0 : -1;
@@ -559,8 +580,7 @@ seq_bits_kernel(BatchArgs a, ScheduleArgs q, BitsLayout lay, unsigned long long 
     int kv_l = 0, kl_l = 0;  // lane j: knapsack j's value and load
     long long total = 0;
     wave_lds_sync();
-    // Lists of more than 64 items: the list as it stands (seq_excess.h).
-    constexpr bool by_excess = NP > 6;
+    // the list as it stands
     auto list_weights = [&]() {
         if constexpr (by_excess) {
             chunks([&](int i0, int w, int) {
@@ -571,7 +591,18 @@ seq_bits_kernel(BatchArgs a, ScheduleArgs q, BitsLayout lay, unsigned long long 
         }
     };
     auto list = [&](int i0) { return i0 + lane < n ? l.prefix[i0 + lane] : kGone; };
-    list_weights();
+    // (Where items heavier than a quarter of the window hold more than half of the time, the excess is mostly out of reach.)
+    bool long_list = EXCESS && n >= (caps_sweep ? kBitsExcessCapsItems : kBitsExcessItems);
+    if (long_list) {
+        const int quarter = bits_wave_max(cap_l) >> 2;
+        int light = 0, heavy = 0;
+        chunks([&](int i0, int w, int) {
+            if (i0 + lane < n && w <= quarter) light += w;
+            else if (i0 + lane < n && w <= 4 * quarter + 3) heavy += w;
+        });
+        long_list = bits_wave_sum(light) > bits_wave_sum(heavy);
+    }
+    if (long_list) list_weights();
     // Where wavefronts share an instance: [0 .. 30] the values, then whether a capacity is left over, the furthest last
     // item + 1, whether a capacity was not reached (in the place of the walk's planes).
     uint32_t *shared = l.planes;
@@ -656,7 +687,7 @@ seq_bits_kernel(BatchArgs a, ScheduleArgs q, BitsLayout lay, unsigned long long 
                 cur_time = all_time;
                 for (int i = lane; i < lay.mark_words; i += 64) l.marks[i] = 0xffffffffu;
                 wave_lds_sync();
-                list_weights();
+                if (long_list) list_weights();
             }
             if (swept_cells) {
                 for (int i = lane; i < n; i += 64)
@@ -668,8 +699,8 @@ seq_bits_kernel(BatchArgs a, ScheduleArgs q, BitsLayout lay, unsigned long long 
         // (a capacity sweep: every capacity is a stage of its own over the whole list)
         ExcessResult r = queues && case_now == 0 ? kExcessEmpty : kExcessNot;
         if constexpr (by_excess) {
-            if (r == kExcessNot && !to_row) {
-                r = excess_stage<NP>(list, lane, n, C, value, last, [&](int i0, unsigned long long in) {
+            if (r == kExcessNot && !to_row && long_list) {
+                r = excess_stage<NP>(list, lane, n, C, caps_sweep, value, last, [&](int i0, unsigned long long in) {
                     got += (int)__popcll(in);
                     if ((in >> lane) & 1ull) {
                         if (caps_sweep) {
@@ -702,7 +733,7 @@ seq_bits_kernel(BatchArgs a, ScheduleArgs q, BitsLayout lay, unsigned long long 
             chunks([&](int i0, int w, int) {
                 const int i = i0 + lane;
                 const bool open = i < n && (caps_sweep || mark8[i] == 0xff), offered = open && w <= C;
-                if constexpr (!by_excess) all_placed = all_placed && __builtin_amdgcn_ballot_w64(open) == 0ull;
+                all_placed = all_placed && __builtin_amdgcn_ballot_w64(open) == 0ull;
                 const unsigned long long mask = __builtin_amdgcn_ballot_w64(offered);
                 const int upto = sum + bits_wave_prefix_sum(offered ? w : 0, lane);  // (4096 weights of at most 65535)
                 if (offered) {
@@ -713,17 +744,15 @@ seq_bits_kernel(BatchArgs a, ScheduleArgs q, BitsLayout lay, unsigned long long 
                 cnt += __popcll(mask);
                 sum = __builtin_amdgcn_readlane(upto, 63);
             });
-            if constexpr (!by_excess) {
-                if (all_placed && !levels && !queues) break;  // every item is placed: the remaining stages stay empty
-            }
+            if (all_placed && !levels && !queues && !caps_sweep) break;  // every item is placed: the remaining stages stay empty
             wave_lds_sync();
             if (cnt == 0) {
                 // nothing is offered
-            } else if (!by_excess && sum <= C && !caps_sweep) {
+            } else if (sum <= C && !caps_sweep) {
                 // everything offered fits together: the DP takes it all (every value is positive)
                 for (int p = lane; p < cnt; p += 64) mark8[l.index[p]] = (uint8_t)j;
                 value = sum;
-                last = l.index[cnt - 1];
+                if (levels) last = l.index[cnt - 1];
             } else if (cnt <= kBitsEnumItems && !caps_sweep) {
                 // A handful of items: lane x weighs the subset whose members are the set bits of x.  The
                 // DP with its walk returns the feasible subset of greatest value and, among
@@ -735,7 +764,7 @@ seq_bits_kernel(BatchArgs a, ScheduleArgs q, BitsLayout lay, unsigned long long 
                 value = bits_wave_max(feasible ? ws : -1);
                 const int pick = __builtin_ctzll(__builtin_amdgcn_ballot_w64(feasible && ws == value));  // (the empty set is feasible)
                 if (lane < cnt && ((pick >> lane) & 1)) mark8[l.index[lane]] = (uint8_t)j;
-                last = l.index[31 - __builtin_clz(pick | 1)];
+                if (levels) last = l.index[31 - __builtin_clz(pick | 1)];
             } else {
                 const BitsSweep sw = bits_sweep<K, NP>(l, rows, lane, cnt, C, caps_sweep, cap_l);
                 const int steps = sw.q;
@@ -747,7 +776,7 @@ seq_bits_kernel(BatchArgs a, ScheduleArgs q, BitsLayout lay, unsigned long long 
                 bits_publish<K, NP>(l, rows, lane, C);
                 if (!caps_sweep) {
                     value = sw.reached ? C : bits_top<K, NP>(rows, lane, C);
-                    if (value > 0) last = l.index[min(bits_first<NP>(l.planes, value, steps), cnt - 1)];
+                    if (levels && value > 0) last = l.index[min(bits_first<NP>(l.planes, value, steps), cnt - 1)];
                     const int left = bits_walk<NP>(l, lane, 64, value, cnt, steps, [&](int p) { mark8[l.index[p]] = (uint8_t)j; });
                     if (left != 0) status = DEFT_ERR_DEVICE;  // (never expected)
                 } else {
@@ -776,7 +805,7 @@ seq_bits_kernel(BatchArgs a, ScheduleArgs q, BitsLayout lay, unsigned long long 
             }
             wave_lds_sync();
             if (caps_sweep) break;
-            if (s + 1 < stages) list_weights();
+            if (long_list && s + 1 < stages) list_weights();
             if (queues) {
                 int open = 0;
                 for (int i = lane; i < n; i += 64) open += mark8[i] == 0xff;
@@ -784,7 +813,7 @@ seq_bits_kernel(BatchArgs a, ScheduleArgs q, BitsLayout lay, unsigned long long 
             }
         }
         wave_lds_sync();
-        if (queues) {
+        if constexpr (queues) {
             cur_items -= got;
             cur_time -= value;
             if (case_now == 2) fut_k += 1;  // the new buckets wait in the future queue
@@ -837,7 +866,7 @@ seq_bits_kernel(BatchArgs a, ScheduleArgs q, BitsLayout lay, unsigned long long 
             }
         }
     }
-    if (queues) {
+    if constexpr (queues) {
         if (lane < 2) q.tail[(size_t)inst * 2 + lane] = lane == 0 ? cur_k : fut_k;
         if (lane == 0) q.status[inst] = status;
         return;
@@ -863,21 +892,23 @@ seq_bits_kernel(BatchArgs a, ScheduleArgs q, BitsLayout lay, unsigned long long 
 // 2^NP items).
 constexpr int kBitsWords[] = {2, 5, 7, 10, 14, 20, 32};
 constexpr int kNumBitsWords = 7;
-constexpr int kBitsPlanes[] = {6, 9, 12};
+constexpr int kBitsPlanes[] = {6, 9, 9, 12};  // (the second: lists too short for seq_excess.h)
 
-typedef void (*BitsKernel)(BatchArgs, ScheduleArgs, BitsLayout, unsigned long long *);
+template <bool QUEUES>
+using BitsKernel = void (*)(BatchArgs, BitsQueueArgs<QUEUES>, BitsLayout, unsigned long long *);
 
-// The kernel of a variant (3 times the index in kBitsWords, plus the index in kBitsPlanes), among those of the
+// The kernel of a variant (4 times the index in kBitsWords, plus the index in kBitsPlanes), among those of the
 // word counts W .. END - 1 that a translation unit compiles.
 template <int W, int END, bool QUEUES>
 const void *bits_kernel_of(int variant)
 {
     if constexpr (W < END) {
         constexpr int K = kBitsWords[W];
-        if (variant / 3 != W) return bits_kernel_of<W + 1, END, QUEUES>(variant);
-        const BitsKernel fn = variant % 3 == 0   ? &seq_bits_kernel<K, kBitsPlanes[0], QUEUES>
-                              : variant % 3 == 1 ? &seq_bits_kernel<K, kBitsPlanes[1], QUEUES>
-                                                 : &seq_bits_kernel<K, kBitsPlanes[2], QUEUES>;
+        if (variant / 4 != W) return bits_kernel_of<W + 1, END, QUEUES>(variant);
+        const BitsKernel<QUEUES> fn = variant % 4 == 0   ? &seq_bits_kernel<K, kBitsPlanes[0], QUEUES, false>
+                              : variant % 4 == 1 ? &seq_bits_kernel<K, kBitsPlanes[1], QUEUES, false>
+                              : variant % 4 == 2 ? &seq_bits_kernel<K, kBitsPlanes[2], QUEUES, true>
+                                                 : &seq_bits_kernel<K, kBitsPlanes[3], QUEUES, true>;
         return reinterpret_cast<const void *>(fn);
     }
     return nullptr;

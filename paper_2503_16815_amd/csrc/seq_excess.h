@@ -24,11 +24,12 @@ namespace {
 
 constexpr int kGone = 0x7fffffff;    // the weight of an item that is not in the list any more
 constexpr int kExcessCells = 2048;   // sums the wide set holds: a word a lane
-// Fewer items up to C than this have too few sums for C to be among them: the attempt would be in vain (of 517 stages
-// drawn from all sizes 122).  Where C is not reachable with items 0 .. p the next p is tried: six in all, which cost
-// little where the 64 lowest sums answer, and one that the wide set says no to counts for four.
-constexpr int kExcessFewest = 16, kExcessTries = 6, kExcessWideTries = 3;
-constexpr int kExcessHeavy = 512;  // excesses that are held against the weight of what is lighter first
+// Fewer items up to C than this have few light ones, and the row's sweep is as quick.  Where C is not reachable with items
+// 0 .. p the next p is tried, six in all (that costs little where the 64 lowest sums say so).
+constexpr int kExcessFewest = 48, kExcessTries = 6;
+// Windows from which on what the 64 lowest sums and the run in the items' order do not show is looked for further (the runs
+// lightest first, the wide set): below, the row's own sweep is as quick.
+constexpr int kExcessThorough = 2048;
 
 enum ExcessResult { kExcessEmpty, kExcessDone, kExcessNot };
 enum ExcessAnswer { kExcessYes, kExcessNo, kExcessUnsure };
@@ -51,7 +52,7 @@ __device__ __forceinline__ void excess_spare(ExcessSpared &x, int lane, int chun
 // weight, lightest items first, which makes them as long as they get.  What that does not show either is left open
 // (kExcessUnsure), with the walk as far as it came: E is what is left, `limit` the item to go on below.
 template <class List>
-__device__ __forceinline__ ExcessAnswer excess_narrow(List &&list, int lane, int C, int &limit, int &E, ExcessSpared &spared)
+__device__ __forceinline__ ExcessAnswer excess_narrow(List &&list, int lane, int C, bool thorough, int &limit, int &E, ExcessSpared &spared)
 {
     const unsigned long long mask = E >= 63 ? ~0ull : (2ull << E) - 1ull;
     unsigned long long set = 1ull;
@@ -93,6 +94,7 @@ __device__ __forceinline__ ExcessAnswer excess_narrow(List &&list, int lane, int
         lacking -= more;
     }
     bool closely = shown == kGone;
+    if (closely && !thorough) return kExcessUnsure;
     int shift = 0, length = 32;  // closely: lane x: the run of the items up to begin + (x + 1 << shift)
     for (;;) {
         if (closely) {
@@ -152,7 +154,7 @@ __device__ __forceinline__ ExcessAnswer excess_narrow(List &&list, int lane, int
             excess_spare(spared, lane, i0 >> 6, out);
         }
         if (E == 0) return kExcessYes;
-        if (closely) return kExcessUnsure;
+        if (closely || !thorough) return kExcessUnsure;
         closely = true;
     }
 }
@@ -229,10 +231,12 @@ __device__ __forceinline__ ExcessAnswer excess_wide(List &&list, int lane, int p
 
 // One stage: the items of the list, n at most, of weight at most C.  kExcessEmpty: no item is in the list any more.
 // kExcessDone: answered; take(first item, mask) was called for every 64 items of the selection, `value` is its weight,
-// `last` its last item (-1: none).  kExcessNot: not answered, nothing taken.
+// `last` its last item (-1: none).  kExcessNot: not answered, nothing taken.  `persistent`: the row's sweep costs more than
+// this stage's.
 template <int NP, class List, class Take>
-__device__ __forceinline__ ExcessResult excess_stage(List &&list, int lane, int n, int C, int &value, int &last, Take &&take)
+__device__ __forceinline__ ExcessResult excess_stage(List &&list, int lane, int n, int C, bool persistent, int &value, int &last, Take &&take)
 {
+    const bool thorough = persistent || C >= kExcessThorough;
     int sum = 0, items = 0, p = -1, E = 0;
     value = 0;
     last = -1;
@@ -264,21 +268,21 @@ __device__ __forceinline__ ExcessResult excess_stage(List &&list, int lane, int 
         if (E > 0 && items < kExcessFewest) return kExcessNot;
         ExcessAnswer answer = kExcessYes;
         for (int attempt = 0; E > 0; ++attempt) {
-            int light = 0;  // (a heavy item that took the list past C: often all that is lighter weighs less than the excess)
-            if (E >= kExcessHeavy) {
+            // Where all that is lighter than the excess weighs less than that, the items that follow do not help for long: each adds
+            // to both.
+            if (E > 63) {
+                int light = 0;
                 for (int i0 = 0; i0 < p && light < E; i0 += 64) {
                     const int w = list(i0);
                     light += bits_wave_sum(i0 + lane < p && w <= min(E, C) ? w : 0);
                 }
+                if (light < E) return kExcessNot;
             }
-            answer = kExcessNo;
-            if (E < kExcessHeavy || light >= E) {
-                int limit = p, left = E;
-                answer = excess_narrow(list, lane, C, limit, left, spared);
-                if (answer == kExcessUnsure && left < kExcessCells) {
-                    answer = excess_wide<NP>(list, lane, limit, C, left, spared);
-                    attempt += kExcessWideTries;
-                }
+            int limit = p, left = E;
+            answer = excess_narrow(list, lane, C, thorough, limit, left, spared);
+            if (answer == kExcessUnsure && left < kExcessCells && thorough) {
+                answer = excess_wide<NP>(list, lane, limit, C, left, spared);
+                if (answer == kExcessNo && !persistent) return kExcessNot;
             }
             if (answer != kExcessNo || attempt + 1 >= kExcessTries) break;
             int next = -1;
