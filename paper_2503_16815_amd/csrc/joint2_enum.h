@@ -16,8 +16,11 @@
 // loss up to G in LDS: the combinations of group Q sorted by roughly what they take of link 1, then of link 0, those of
 // P1 and P2 taken in pairs, each looking up the partners that leave little enough room on either link.  If
 // the best selection met loses no more than G, all better or equal ones have been met: it is the answer, and
-// among equals the one with the smallest choice number is the one that the DP's walk returns.  If lists
-// or time run over (a share of what the sweep is expected to take), or the table sweep, which begins beside it when a compute unit is free, ends first,
+// among equals the one with the smallest choice number is the one that the DP's walk returns.  Where a list runs over,
+// smaller steps and other groups are tried, then Q is made in parts, one after the other: the choices of its items of
+// least loss (up to four, three choices each) are a part's own, so a part is half of the list or less, and P1 and P2 stay as
+// they are.  (Of 24 two-link batches of 256 ten had an instance whose lists ran over so that it was left, and took 2.8 to 4.4 ms; five have
+// now, the others take 1.1 to 2.4 ms.)  If lists or time run over (a share of what the sweep is expected to take), or the table sweep, which begins beside it when a compute unit is free, ends first,
 // the instance is left to that; so are instances in which the prices are zero (everything fits one link or the other: all
 // choices cost nothing).
 //
@@ -25,8 +28,8 @@
 //
 // What bounds it: latency.  One workgroup owns an instance; a round is a chain of barriers (one for an item of each group
 // once the lists are long), its pairs are lookups in LDS at places of the lanes' own, and a launch lasts as long as its hardest
-// instance.  Of the two-link batch half of the instances are solved after 85 us, the last one after 0.79 to 0.94 ms; by the input
-// one of some 300 to 1000 is left to the table sweep, and the call takes 4.1 to 4.4 ms then (all by the sweep: 6.36).  40 instances of 20 to 62
+// instance.  Of the two-link batch half of the instances are solved after 85 us, the last one after 0.6 to 1.3 ms, 1.1 to 2.4 where lists run over; by the input
+// one of some 1200 is left to the table sweep, and the call takes 3.9 to 4.4 ms then (all by the sweep: 6.36).  40 instances of 20 to 62
 // items 0.41 of the sweep, 256 0.53 (geometric means over 30 kinds each).
 // Tried and not kept: every lane noting ties as it meets them (two passes instead, the second only where several selections
 // are as good: 72 -> 5 ms), Q sorted by link 0 alone, or by link 1 in steps of 128 (cells of both: pairs / 3), no table of
@@ -50,6 +53,7 @@ constexpr int kEnumRounds = 7;            // 16, 24, ..., 64 open choices
 // items (138 and 407) 412 and 57.
 constexpr int kEnumFewest = 16;
 constexpr int kLeapChoices = 64, kReach = 2;
+constexpr int kBranches = 4;              // items whose choices Q is split up by, at most, where it runs over
 constexpr int kListQ = 5120, kListP1 = 2048, kListP2 = 1536;
 constexpr int kCells0 = 128, kCells1 = 64;  // that group Q is sorted by
 constexpr int kCells = kCells0 * kCells1;
@@ -60,8 +64,8 @@ constexpr int kLookTicks = 2000;          // of 10 ns, between looks at whether 
 constexpr int kPriceGrid = 16, kPriceRounds = 4;
 
 struct EnumResult {
-    int q;                      // places in Q (-1: no result) and in P1 and P2 (11 bits each)
-    uint32_t pair;
+    int q;                      // -1: no result
+    uint32_t q_mask, pair;      // what it takes of Q, its places in P1 and P2 (11 bits each)
     unsigned long long lo, hi;  // the choices of the open items, two bits each by item index
 };
 
@@ -108,8 +112,8 @@ struct EnumShared {
     EnumResult result[kEnumWaves];
     unsigned long long default_lo, default_hi;
     unsigned long long flip_lo[3][32], flip_hi[3][32];  // what a mask bit changes of them
-    int32_t over, least, q;                   // least: what the best selection met so far loses
-    uint32_t pair;
+    int32_t over, least;                      // least: what the best selection met so far loses
+    uint32_t q_mask, pair;
 };
 
 static_assert(sizeof(EnumShared) + 64 <= 160 * 1024, "a compute unit's LDS");  // (check_instance has some words of its own)
@@ -139,9 +143,9 @@ __device__ __forceinline__ bool enum_before(const EnumResult &x, const EnumResul
     return x.hi != y.hi ? x.hi < y.hi : x.lo < y.lo;
 }
 // The departures of a combination that group l makes.
-__device__ __forceinline__ uint32_t enum_mask(const EnumShared &s, int l, uint32_t pair, int q)
+__device__ __forceinline__ uint32_t enum_mask(const EnumShared &s, int l, uint32_t pair, uint32_t q_mask)
 {
-    return l == 0 ? s.list.q_mask[q] : l == 1 ? s.list.p1_mask[pair >> 11] : s.list.p2_mask[pair & 2047];
+    return l == 0 ? q_mask : l == 1 ? s.list.p1_mask[pair >> 11] : s.list.p2_mask[pair & 2047];
 }
 
 __device__ __forceinline__ bool enum_takes(int n, int c0, int c1) { return n <= kEnumItems && c0 <= kEnumCapacity && c1 <= kEnumCapacity; }
@@ -370,12 +374,13 @@ __device__ __forceinline__ void jt_enumerate(const BatchArgs &a, int inst, State
         }
     }
     __syncthreads();
-    // Three groups: of every ten items by loss, four to Q, three each to P1 and P2; where Q runs over so, about
-    // a third each.
-    auto make_groups = [&](bool even) {
+    // Three groups: of every ten items by loss, four to Q, three each to P1 and P2; where a list runs over so, about
+    // a third each (split 1); where P1 or P2 still does, as at first again (2) and then half of them to Q (3), which is
+    // made in parts then.
+    auto make_groups = [&](int split) {
         const bool open = s.loss[0][lane] < kNever;
-        const int five = lane % 5, ten = lane % 10, three = lane % 20 == 19 ? 0 : lane % 3;
-        const int group = even ? three : five == 0 || five == 3 ? 0 : five == 1 || ten == 4 ? 1 : 2;
+        const int five = lane % 5, ten = lane % 10, three = lane % 20 == 19 ? 0 : lane % 3, four = lane % 4;
+        const int group = split == 3 ? (four & 1) * ((four + 1) >> 1) : split == 1 ? three : five == 0 || five == 3 ? 0 : five == 1 || ten == 4 ? 1 : 2;
 #pragma unroll
         for (int l = 0; l < 3; ++l) {
             const unsigned long long mask = __ballot(open && group == l);
@@ -384,7 +389,7 @@ __device__ __forceinline__ void jt_enumerate(const BatchArgs &a, int inst, State
         }
     };
     if (wave == 0) {
-        make_groups(false);
+        make_groups(0);
         const bool open = s.loss[0][lane] < kNever;
         int by_index = 0;
         const int item = open ? s.item[lane] : kEnumItems;
@@ -433,7 +438,8 @@ __device__ __forceinline__ void jt_enumerate(const BatchArgs &a, int inst, State
     auto row_of = [&](int on0) { return min(on0 >> cell0, kCells0 - 1) * kCells1; };
     auto column_of = [&](int on1) { return min(on1 >> cell1, kCells1 - 1); };
 
-    bool may_leap = true, even = false;
+    bool may_leap = true;
+    int split = 0, branches = 0;
     for (int round = 0; round < kEnumRounds;) {
         int G = s.threshold[round] - 1;
         // What is left to look through is known: straight to it, unless the choices open then are so many that a better
@@ -446,18 +452,17 @@ __device__ __forceinline__ void jt_enumerate(const BatchArgs &a, int inst, State
             ++round;
             continue;
         }
-        auto retry = [&]() {  // a list has run over: in smaller steps, or other groups
+        auto retry = [&](bool q_over) {  // a list has run over: in smaller steps, other groups, or Q in parts
             if (leap) {
                 may_leap = false;
-            } else {
-                if (wave == 0) {
-                    if (even) {
-                        if (lane == 0) s.over = 1;
-                    } else {
-                        make_groups(true);
-                    }
-                }
-                even = true;
+            } else if (split == 0 || (!q_over && split < 3)) {
+                ++split;
+                branches = split == 1 ? 0 : max(branches, 1);
+                if (wave == 0) make_groups(split);
+            } else if (q_over && branches < kBranches) {
+                ++branches;
+            } else if (tid == 0) {
+                s.over = 1;
             }
             __syncthreads();
         };
@@ -472,346 +477,260 @@ __device__ __forceinline__ void jt_enumerate(const BatchArgs &a, int inst, State
         const int first_u = s.use[0][r], second_u = s.use[1][r];
         const unsigned long long both = __ballot(second_l <= G);
         const int second_b = count + enum_below(both, lane);
-        int have = 1, place = count - 1;
-        // One item into the list, by `waves` wavefronts of which this is number `w`: entries [0, have) are followed
-        // by what they make with the item's departures.  to(more) is where this wavefront's go.
-        auto grow = [&](int p, int w, int waves, auto &&to) {
-            const int loss1 = __builtin_amdgcn_readlane(first_l, p), loss2 = __builtin_amdgcn_readlane(second_l, p);
-            const int use1 = __builtin_amdgcn_readlane(first_u, p), use2 = __builtin_amdgcn_readlane(second_u, p);
-            const int bit2 = __builtin_amdgcn_readlane(second_b, p);
-            const bool twice = loss2 <= G;
-            for (int base = w * 64; base < have; base += waves * 64) {
-                const int e = base + lane;
-                const int loss = e < have ? l_loss[e] : kNever, use = e < have ? l_use[e] : 0;
-                const uint32_t mask = e < have ? l_mask[e] : 0;
-                const bool one = loss <= G - loss1, two = twice && loss <= G - loss2;
-                const unsigned long long ones = __ballot(one), twos = __ballot(two);
-                const int at = to(__popcll(ones) + __popcll(twos));
-                const int at1 = at + enum_below(ones, lane), at2 = at + __popcll(ones) + enum_below(twos, lane);
-                if (one && at1 < limit) {
-                    l_loss[at1] = loss + loss1;
-                    l_use[at1] = use + use1;
-                    l_mask[at1] = mask | 1u << p;
-                }
-                if (two && at2 < limit) {
-                    l_loss[at2] = loss + loss2;
-                    l_use[at2] = use + use2;
-                    l_mask[at2] = mask | 1u << bit2;
-                }
-            }
-        };
-        // The greatest losses first (they combine with little, so the lists stay short for long).  A short list is
-        // its first wavefront's alone.
-        if (wave == first_wave) {
-            auto means = [&](int bit, int option) {
-                const int at = s.by_index[r];
-                const unsigned long long flip = (unsigned long long)(option ^ s.dflt[r]) << (2 * (at & 31));
-                s.meaning[group][bit] = (uint16_t)(r << 2 | option);
-                s.flip_lo[group][bit] = at < 32 ? flip : 0ull;
-                s.flip_hi[group][bit] = at < 32 ? 0ull : flip;
-            };
-            const int bits = count + __popcll(both);
-            if (bits > 32) {
-                if (lane == 0) s.over = 1;
-            } else {
-                if (mine) means(lane, s.option[0][r]);
-                if (second_l <= G) means(second_b, s.option[1][r]);
-                if (group == 0) {
-                    const int u = mine ? s.taken[r] : 0, u0 = enum_wave_sum(u >> 16), u1 = enum_wave_sum(u & 0xffff);
-                    if (lane == 0) s.q_default[0] = u0, s.q_default[1] = u1;
-                }
-                if (lane == 0) {
-                    l_loss[0] = 0;
-                    l_use[0] = 0;
-                    l_mask[0] = 0;
-                }
-                while (place >= 0 && have <= 64 * list_waves) {
-                    int next = have;
-                    __builtin_amdgcn_wave_barrier();
-                    grow(place, 0, 1, [&](int more) {
-                        const int at = next;
-                        next += more;
-                        return at;
-                    });
-                    __builtin_amdgcn_wave_barrier();
-                    have = next;
-                    --place;
-                    if (have > limit) break;
-                }
-                if (lane == 0) s.size[group] = have, s.places[group] = place, s.bits[group] = bits;
-            }
-        }
-        for (int i = tid; i < kEnumOpen * 3; i += kEnumThreads) s.appended[i / 3][i % 3] = 0;
-        __syncthreads();
-        if (s.over) return;
-        int size[3], steps = 0;
-        bool over = false;
-#pragma unroll
-        for (int l = 0; l < 3; ++l) {
-            size[l] = s.size[l];
-            over = over || size[l] > (l == 0 ? kListQ : l == 1 ? kListP1 : kListP2);
-            steps = max(steps, s.places[l] + 1);
-        }
-        if (over) {
-            retry();
-            if (s.over) return;
-            continue;
-        }
-        place = s.places[group];
-        // A longer one is made by all of the group's wavefronts, a barrier per item.
-        for (int step = 0; step < steps; ++step) {
-            have = group == 0 ? size[0] : group == 1 ? size[1] : size[2];
-            if (place - step >= 0) {
-                grow(place - step, wave - first_wave, list_waves, [&](int more) {
-                    int at = 0;
-                    if (more > 0) {
-                        if (lane == 0) at = have + atomicAdd(&s.appended[step][group], more);
-                        at = __builtin_amdgcn_readfirstlane(at);
-                    }
-                    return at;
-                });
-            }
-            __syncthreads();
-#pragma unroll
-            for (int l = 0; l < 3; ++l) {
-                size[l] += s.appended[step][l];
-                over = over || size[l] > (l == 0 ? kListQ : l == 1 ? kListP1 : kListP2);
-            }
-            if (over) break;
-        }
-        if (over) {
-            retry();
-            if (s.over) return;
-            continue;
-        }
-        last_G = G;
-        ++round;
-        // Q: sorted by cells (a counting sort in place, by way of registers).
-        for (int i = tid; i <= kCells / 2; i += kEnumThreads) s.list.begin[i] = 0;
-        constexpr int kMine = (kListQ + kEnumThreads - 1) / kEnumThreads;
-        int q_cell[kMine], q_loss[kMine], q_used[kMine];
-        uint32_t q_mask[kMine];
-        __syncthreads();
-#pragma unroll
-        for (int x = 0; x < kMine; ++x) {
-            const int e = tid + x * kEnumThreads;
-            q_cell[x] = -1;
-            if (e < size[0]) {
-                const int use = s.list.q_use[e], ua = s.q_default[0] + use_a(use), ub = s.q_default[1] + use_b(use);
-                if (ua <= c0 && ub <= c1) {
-                    const int cell = row_of(ua) + column_of(ub), half = (cell & 1) * 16;
-                    q_cell[x] = (int)(atomicAdd(&s.list.begin[cell >> 1], 1u << half) >> half & 0xffffu) << 16 | cell;
-                    q_loss[x] = s.list.q_loss[e];
-                    q_used[x] = ua << 16 | ub;
-                    q_mask[x] = s.list.q_mask[e];
-                }
-            }
-        }
-        __syncthreads();
-        {
-            constexpr int kWords = kCells / 2 / kEnumThreads;
-            uint32_t word[kWords];
-            int sum = 0;
-#pragma unroll
-            for (int x = 0; x < kWords; ++x) {
-                word[x] = s.list.begin[tid * kWords + x];
-                sum += (int)(word[x] & 0xffffu) + (int)(word[x] >> 16);
-            }
-            int upto = sum;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const int y = __shfl_up(upto, off);
-                if (lane >= off) upto += y;
-            }
-            if (lane == 63) s.wave_sum[wave] = upto;
-            __syncthreads();
-            int begin = upto - sum;
-#pragma unroll 1
-            for (int x = 0; x < wave; ++x) begin += s.wave_sum[x];
-#pragma unroll
-            for (int x = 0; x < kWords; ++x) {
-                const int lo = begin, hi = begin + (int)(word[x] & 0xffffu);
-                s.list.begin[tid * kWords + x] = (uint32_t)hi << 16 | (uint32_t)lo;
-                begin = hi + (int)(word[x] >> 16);
-            }
-            if (tid == kEnumThreads - 1) s.list.begin[kCells / 2] = (uint32_t)begin;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int x = 0; x < kMine; ++x) {
-            if (q_cell[x] >= 0) {
-                const int at = begin16[q_cell[x] & 0xffff] + (q_cell[x] >> 16);  // (its cell, and its place there)
-                s.list.q_loss[at] = q_loss[x];
-                s.list.q_use[at] = q_used[x];
-                s.list.q_mask[at] = q_mask[x];
-            }
-        }
-        __syncthreads();
-        // What a partner loses at least, the room that it leaves included, where a pair leaves room in a cell: the least loss
-        // in the cell, or in one below it plus the price of the room that is certainly left then.  16 bits, rounded
-        // down.
-        const bool filtered = size[1] * size[2] >= kFilterPairs;
-        const int coarse = max(0, 18 - __builtin_clz(G | 1));  // G in 14 bits
-        if (filtered) {
-            constexpr int kRows = kCells0 / kEnumWaves, kFar = 0xffff;
-            const int one0 = min(l0 >> coarse, kFar), one1 = min(l1 >> coarse, kFar);
-            const int wide0 = (int)min(((long long)l0 << cell0) >> coarse, (long long)kFar);
-            const int wide1 = (int)min(((long long)l1 << cell1) >> coarse, (long long)kFar);
-            int row[kRows], last = kFar;
-#pragma unroll
-            for (int x = 0; x < kRows; ++x) {
-                const int cell = (wave * kRows + x) * kCells1 + lane, end = begin16[cell + 1];
-                int own = kNever;
-                for (int k = begin16[cell]; k < end; ++k) own = min(own, s.list.q_loss[k]);
-                own = min(own >> coarse, kFar);
-                int least_below = own - wide1 * lane;
-#pragma unroll
-                for (int off = 1; off < 64; off <<= 1) {
-                    const int y = __shfl_up(least_below, off);
-                    if (lane >= off) least_below = min(least_below, y);
-                }
-                const int below = __shfl_up(least_below + wide1 * lane, 1);
-                row[x] = lane > 0 ? min(own, below + one1) : own;
-                last = min(row[x], last + wide0);
-            }
-            s.edge[wave][lane] = last;
-            __syncthreads();
-            int below = kFar;
-#pragma unroll 1
-            for (int x = 0; x < wave; ++x) below = min(s.edge[x][lane], below + wide0 * kRows);
-#pragma unroll
-            for (int x = 0; x < kRows; ++x) {
-                s.list.least[wave * kRows + x][lane] = (uint16_t)min(row[x], min(below + one0, kFar));
-                below = min(row[x], below + wide0);
-            }
-            __syncthreads();
-        }
-
-        // Pairs of P1 and P2 that some partner may suit: collected 64 at a time, then every lane looks its partners up.  If
-        // this settles the matter but several selections are as good, once more, for the one whose choices, two
-        // bits each with the last item's on top, make the smallest number.  (One loop for everything: the code is run
-        // a few times, and fetching it is a good part of what that takes.)
-        const int room0 = c0 - used0 + s.q_default[0], room1 = c1 - used1 + s.q_default[1];
+        // Q in parts: the choices of its `branches` items of least loss are the part's, three to an item (one group's items are
+        // any of them, so a part is its combinations with those choices).
+        int turns = 1;
+        for (int b = 0; b < branches; ++b) turns *= 3;
+        const int q_count = __popcll(s.members[0] & opened), stop = group == 0 ? branches : 0;
         // (the first rounds look beyond G, for a selection that says how far the others have to)
         const int known = least < kNever ? least : (int)min(kReach * (long long)G, (long long)kNever - 1);
         int best = known + 1, copies = 0;  // what this lane's best selection loses, and whether it has met it twice
-        EnumResult chosen{-1, 0, 0, 0};
-        uint32_t *queue = s.list.queue[wave];
-        const int chunks = (size[2] + 63) >> 6;
-        bool several = false;
+        EnumResult chosen{-1, 0, 0, 0, 0};
+        bool several = false, again = false;
+        int size[3] = {0, 0, 0};
 #pragma unroll 1
-        for (int pass = 0; pass < 2; ++pass) {
-            int queued = 0;
-            // a tile: sixteen of P1, one after the other, with 64 of P2
-            int first1 = 0, chunk = wave, x = 16, i2 = 0, left0_2 = 0, left1_2 = 0, a1 = 0, b1 = 0, spare2 = 0, loss1 = 0;
-            bool more = true;
-            while (true) {
-                const int limit = min(min(known, best), *(volatile int32_t *)&s.least);  // no selection that loses more matters
-                if (more && queued < 64) {
-                    if (x == 16) {
-                        while (chunk >= chunks) chunk -= chunks, first1 += 16;
-                        if (first1 >= size[1]) {
-                            more = false;
-                            continue;
-                        }
-                        i2 = chunk * 64 + lane;
-                        chunk += kEnumWaves;
-                        const int i1 = first1 + (lane & 15);
-                        const int use2 = s.list.p2_use[i2], use1 = i1 < size[1] ? s.list.p1_use[i1] : 0;
-                        left0_2 = room0 - use_a(use2), left1_2 = room1 - use_b(use2), a1 = use_a(use1), b1 = use_b(use1);
-                        spare2 = i2 < size[2] ? __builtin_amdgcn_readfirstlane(limit) - s.list.p2_loss[i2] : -1;
-                        loss1 = i1 < size[1] ? s.list.p1_loss[i1] : kNever;
-                        // (first1 stays the tile's until chunk runs over)
-                        x = 0;
-                    }
-                    bool valid[2];
-                    int at_least[2], spare[2];
-#pragma unroll
-                    for (int y = 0; y < 2; ++y) {
-                        spare[y] = spare2 - __builtin_amdgcn_readlane(loss1, x + y);
-                        const int left0 = left0_2 - __builtin_amdgcn_readlane(a1, x + y);
-                        const int left1 = left1_2 - __builtin_amdgcn_readlane(b1, x + y);
-                        valid[y] = (spare[y] | left0 | left1) >= 0;
-                        at_least[y] = filtered ? (&s.list.least[0][0])[row_of(max(left0, 0)) + column_of(max(left1, 0))] : 0;
-                    }
-#pragma unroll
-                    for (int y = 0; y < 2; ++y) {
-                        valid[y] = valid[y] && at_least[y] <= spare[y] >> coarse;
-                        const unsigned long long mask = __ballot(valid[y]);
-                        if (valid[y]) queue[queued + enum_below(mask, lane)] = (uint32_t)(first1 + x + y) << 11 | (uint32_t)i2;
-                        queued += __popcll(mask);
-                    }
-                    __builtin_amdgcn_wave_barrier();
-                    x += 2;
-                    continue;
-                }
-                if (queued == 0) break;
-                const bool valid = lane < queued;
-                const uint32_t pair = queue[lane], rest = queue[64 + lane], rest2 = queue[128 + lane];
-                __builtin_amdgcn_wave_barrier();
-                queue[lane] = rest;
-                queue[64 + lane] = rest2;
-                queued = max(queued - 64, 0);
-                if (valid) {
-                    const int p1 = pair >> 11, p2 = pair & 2047;
-                    const int use = s.list.p1_use[p1] + s.list.p2_use[p2], loss = s.list.p1_loss[p1] + s.list.p2_loss[p2];
-                    const int left0 = room0 - use_a(use), left1 = room1 - use_b(use), spare = limit - loss;
-                    // room left on a link costs its price: no partner may leave more of it than what is spare pays for
-                    const int slack0 = l0 > 0 ? (int)fminf((float)spare * per0, 65535.0f) + 1 : 65536;
-                    const int slack1 = l1 > 0 ? (int)fminf((float)spare * per1, 65535.0f) + 1 : 65536;
-                    const int to0 = row_of(left0), from1 = column_of(max(left1 - slack1, 0)), to1 = column_of(left1) + 1;
-                    for (int row = spare >= 0 ? row_of(max(left0 - slack0, 0)) : kCells; row <= to0; row += kCells1) {
-                        const int end = begin16[row + to1];
-                        for (int k = begin16[row + from1]; k < end; ++k) {
-                            const int its_loss = s.list.q_loss[k];
-                            if (its_loss > spare) continue;
-                            const int used = s.list.q_use[k], room_a = left0 - (used >> 16), room_b = left1 - (used & 0xffff);
-                            if ((room_a | room_b | (slack0 - room_a) | (slack1 - room_b)) < 0) continue;
-                            const long long more_lost = (long long)l0 * room_a + (long long)l1 * room_b + its_loss;
-                            if (more_lost > spare) continue;
-                            const int lost = loss + (int)more_lost;
-                            if (pass == 0) {
-                                copies = lost < best ? 0 : lost == best ? 1 : copies;
-                                if (lost < best) chosen.q = k, chosen.pair = pair, best = lost;
-                            } else if (lost == least) {
-                                EnumResult other{k, pair, s.default_lo, s.default_hi};
-#pragma unroll 1
-                                for (int l = 0; l < 3; ++l) {
-                                    const uint32_t mask = enum_mask(s, l, pair, k);
-#pragma unroll
-                                    for (int at = 0; at < 8; ++at) {
-                                        const ulonglong2 flips = s.flips[l][at][mask >> (at * 4) & 15];
-                                        other.lo ^= flips.x;
-                                        other.hi ^= flips.y;
-                                    }
-                                }
-                                if (enum_before(other, chosen)) chosen = other;
-                            }
-                        }
-                    }
-                }
-                const long long now = wall_clock64();
-                if (now > deadline) s.over = 1;
-                if (now > look) {
-                    look = now + kLookTicks;
-                    if (__hip_atomic_load(&solved[inst], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) s.over = 1;
-                }
-                if (__builtin_amdgcn_readfirstlane(*(volatile int32_t *)&s.over)) break;
+        for (int pass = 0, part = 0;;) {
+            int part_loss = 0, part_use = 0;
+            uint32_t part_mask = 0;
+            for (int b = 0, digits = part, second = q_count; b < branches; ++b, digits /= 3) {
+                const int at = s.order[0][b], digit = b < q_count ? digits % 3 : digits % 3 == 0 ? 0 : 3;
+                const bool twice = b < q_count && s.loss[1][at] <= G;
+                if (digit == 1) part_loss = min(part_loss + s.loss[0][at], kNever), part_use += s.use[0][at], part_mask |= 1u << b;
+                if (digit == 2 && twice) part_loss = min(part_loss + s.loss[1][at], kNever), part_use += s.use[1][at], part_mask |= 1u << second;
+                if (digit == 3 || (digit == 2 && !twice)) part_loss = kNever;
+                second += twice ? 1 : 0;
             }
-            if (pass == 0) {
-                if (best <= known) atomicMin(&s.least, best);
+            part_loss = __builtin_amdgcn_readfirstlane(part_loss);
+            const bool first_turn = pass == 0 && part == 0;
+            if (part_loss <= G && (pass == 0 || turns > 1)) {
+                int have = 1, place = count - 1;
+                // One item into the list, by `waves` wavefronts of which this is number `w`: entries [0, have) are followed
+                // by what they make with the item's departures.  to(more) is where this wavefront's go.
+                auto grow = [&](int p, int w, int waves, auto &&to) {
+                    const int loss1 = __builtin_amdgcn_readlane(first_l, p), loss2 = __builtin_amdgcn_readlane(second_l, p);
+                    const int use1 = __builtin_amdgcn_readlane(first_u, p), use2 = __builtin_amdgcn_readlane(second_u, p);
+                    const int bit2 = __builtin_amdgcn_readlane(second_b, p);
+                    const bool twice = loss2 <= G;
+                    for (int base = w * 64; base < have; base += waves * 64) {
+                        const int e = base + lane;
+                        const int loss = e < have ? l_loss[e] : kNever, use = e < have ? l_use[e] : 0;
+                        const uint32_t mask = e < have ? l_mask[e] : 0;
+                        const bool one = loss <= G - loss1, two = twice && loss <= G - loss2;
+                        const unsigned long long ones = __ballot(one), twos = __ballot(two);
+                        const int at = to(__popcll(ones) + __popcll(twos));
+                        const int at1 = at + enum_below(ones, lane), at2 = at + __popcll(ones) + enum_below(twos, lane);
+                        if (one && at1 < limit) {
+                            l_loss[at1] = loss + loss1;
+                            l_use[at1] = use + use1;
+                            l_mask[at1] = mask | 1u << p;
+                        }
+                        if (two && at2 < limit) {
+                            l_loss[at2] = loss + loss2;
+                            l_use[at2] = use + use2;
+                            l_mask[at2] = mask | 1u << bit2;
+                        }
+                    }
+                };
+                // The greatest losses first (they combine with little, so the lists stay short for long).  A short list is
+                // its first wavefront's alone.
+                if (wave == first_wave && (first_turn || group == 0)) {
+                    auto means = [&](int bit, int option) {
+                        const int at = s.by_index[r];
+                        const unsigned long long flip = (unsigned long long)(option ^ s.dflt[r]) << (2 * (at & 31));
+                        s.meaning[group][bit] = (uint16_t)(r << 2 | option);
+                        s.flip_lo[group][bit] = at < 32 ? flip : 0ull;
+                        s.flip_hi[group][bit] = at < 32 ? 0ull : flip;
+                    };
+                    const int bits = count + __popcll(both);
+                    if (bits > 32) {
+                        if (lane == 0) s.over = 1;
+                    } else {
+                        if (mine) means(lane, s.option[0][r]);
+                        if (second_l <= G) means(second_b, s.option[1][r]);
+                        if (group == 0) {
+                            const int u = mine ? s.taken[r] : 0, u0 = enum_wave_sum(u >> 16), u1 = enum_wave_sum(u & 0xffff);
+                            if (lane == 0) s.q_default[0] = u0, s.q_default[1] = u1;
+                        }
+                        if (lane == 0) {
+                            l_loss[0] = group == 0 ? part_loss : 0;
+                            l_use[0] = group == 0 ? part_use : 0;
+                            l_mask[0] = group == 0 ? part_mask : 0;
+                        }
+                        while (place >= stop && have <= 64 * list_waves) {
+                            int next = have;
+                            __builtin_amdgcn_wave_barrier();
+                            grow(place, 0, 1, [&](int more) {
+                                const int at = next;
+                                next += more;
+                                return at;
+                            });
+                            __builtin_amdgcn_wave_barrier();
+                            have = next;
+                            --place;
+                            if (have > limit) break;
+                        }
+                        if (lane == 0) s.size[group] = have, s.places[group] = place, s.bits[group] = bits;
+                    }
+                }
+                for (int i = tid; i < kEnumOpen * 3; i += kEnumThreads) s.appended[i / 3][i % 3] = 0;
                 __syncthreads();
                 if (s.over) return;
-                least = s.least;
-                if (least > G) break;
-                // nothing is better, and nothing as good has not been met
-                const int met = __popcll(__ballot(best == least)) + __popcll(__ballot(best == least && copies != 0));
-                if (lane == 0) s.wave_sum[wave] = met;
-                if (best == least) s.q = chosen.q, s.pair = chosen.pair;  // (whichever, where there are several)
+                int steps = 0;
+                bool over = false;
+        #pragma unroll
+                for (int l = 0; l < 3; ++l) {
+                    if (l > 0 && !first_turn) continue;
+                    size[l] = s.size[l];
+                    over = over || size[l] > (l == 0 ? kListQ : l == 1 ? kListP1 : kListP2);
+                    steps = max(steps, s.places[l] + 1 - (l == 0 ? branches : 0));
+                }
+                if (over) {
+                    again = true;
+                    break;
+                }
+                place = first_turn || group == 0 ? s.places[group] : -1;
+                // A longer one is made by all of the group's wavefronts, a barrier per item.
+                for (int step = 0; step < steps; ++step) {
+                    have = group == 0 ? size[0] : group == 1 ? size[1] : size[2];
+                    if (place - step >= stop) {
+                        grow(place - step, wave - first_wave, list_waves, [&](int more) {
+                            int at = 0;
+                            if (more > 0) {
+                                if (lane == 0) at = have + atomicAdd(&s.appended[step][group], more);
+                                at = __builtin_amdgcn_readfirstlane(at);
+                            }
+                            return at;
+                        });
+                    }
+                    __syncthreads();
+        #pragma unroll
+                    for (int l = 0; l < 3; ++l) {
+                        size[l] += s.appended[step][l];
+                        over = over || size[l] > (l == 0 ? kListQ : l == 1 ? kListP1 : kListP2);
+                    }
+                    if (over) break;
+                }
+                if (over) {
+                    again = true;
+                    break;
+                }
+                // Q: sorted by cells (a counting sort in place, by way of registers).
+                for (int i = tid; i <= kCells / 2; i += kEnumThreads) s.list.begin[i] = 0;
+                constexpr int kMine = (kListQ + kEnumThreads - 1) / kEnumThreads;
+                int q_cell[kMine], q_loss[kMine], q_used[kMine];
+                uint32_t q_mask[kMine];
+                __syncthreads();
+        #pragma unroll
+                for (int x = 0; x < kMine; ++x) {
+                    const int e = tid + x * kEnumThreads;
+                    q_cell[x] = -1;
+                    if (e < size[0]) {
+                        const int use = s.list.q_use[e], ua = s.q_default[0] + use_a(use), ub = s.q_default[1] + use_b(use);
+                        if (ua <= c0 && ub <= c1) {
+                            const int cell = row_of(ua) + column_of(ub), half = (cell & 1) * 16;
+                            q_cell[x] = (int)(atomicAdd(&s.list.begin[cell >> 1], 1u << half) >> half & 0xffffu) << 16 | cell;
+                            q_loss[x] = s.list.q_loss[e];
+                            q_used[x] = ua << 16 | ub;
+                            q_mask[x] = s.list.q_mask[e];
+                        }
+                    }
+                }
+                __syncthreads();
+                {
+                    constexpr int kWords = kCells / 2 / kEnumThreads;
+                    uint32_t word[kWords];
+                    int sum = 0;
+        #pragma unroll
+                    for (int x = 0; x < kWords; ++x) {
+                        word[x] = s.list.begin[tid * kWords + x];
+                        sum += (int)(word[x] & 0xffffu) + (int)(word[x] >> 16);
+                    }
+                    int upto = sum;
+        #pragma unroll
+                    for (int off = 1; off < 64; off <<= 1) {
+                        const int y = __shfl_up(upto, off);
+                        if (lane >= off) upto += y;
+                    }
+                    if (lane == 63) s.wave_sum[wave] = upto;
+                    __syncthreads();
+                    int begin = upto - sum;
+        #pragma unroll 1
+                    for (int x = 0; x < wave; ++x) begin += s.wave_sum[x];
+        #pragma unroll
+                    for (int x = 0; x < kWords; ++x) {
+                        const int lo = begin, hi = begin + (int)(word[x] & 0xffffu);
+                        s.list.begin[tid * kWords + x] = (uint32_t)hi << 16 | (uint32_t)lo;
+                        begin = hi + (int)(word[x] >> 16);
+                    }
+                    if (tid == kEnumThreads - 1) s.list.begin[kCells / 2] = (uint32_t)begin;
+                }
+                __syncthreads();
+        #pragma unroll
+                for (int x = 0; x < kMine; ++x) {
+                    if (q_cell[x] >= 0) {
+                        const int at = begin16[q_cell[x] & 0xffff] + (q_cell[x] >> 16);  // (its cell, and its place there)
+                        s.list.q_loss[at] = q_loss[x];
+                        s.list.q_use[at] = q_used[x];
+                        s.list.q_mask[at] = q_mask[x];
+                    }
+                }
+                __syncthreads();
+                // What a partner loses at least, the room that it leaves included, where a pair leaves room in a cell: the least loss
+                // in the cell, or in one below it plus the price of the room that is certainly left then.  16 bits, rounded
+                // down.
+                const bool filtered = size[1] * size[2] >= kFilterPairs;
+                const int coarse = max(0, 18 - __builtin_clz(G | 1));  // G in 14 bits
+                if (filtered) {
+                    constexpr int kRows = kCells0 / kEnumWaves, kFar = 0xffff;
+                    const int one0 = min(l0 >> coarse, kFar), one1 = min(l1 >> coarse, kFar);
+                    const int wide0 = (int)min(((long long)l0 << cell0) >> coarse, (long long)kFar);
+                    const int wide1 = (int)min(((long long)l1 << cell1) >> coarse, (long long)kFar);
+                    int row[kRows], last = kFar;
+        #pragma unroll
+                    for (int x = 0; x < kRows; ++x) {
+                        const int cell = (wave * kRows + x) * kCells1 + lane, end = begin16[cell + 1];
+                        int own = kNever;
+                        for (int k = begin16[cell]; k < end; ++k) own = min(own, s.list.q_loss[k]);
+                        own = min(own >> coarse, kFar);
+                        int least_below = own - wide1 * lane;
+        #pragma unroll
+                        for (int off = 1; off < 64; off <<= 1) {
+                            const int y = __shfl_up(least_below, off);
+                            if (lane >= off) least_below = min(least_below, y);
+                        }
+                        const int below = __shfl_up(least_below + wide1 * lane, 1);
+                        row[x] = lane > 0 ? min(own, below + one1) : own;
+                        last = min(row[x], last + wide0);
+                    }
+                    s.edge[wave][lane] = last;
+                    __syncthreads();
+                    int below = kFar;
+        #pragma unroll 1
+                    for (int x = 0; x < wave; ++x) below = min(s.edge[x][lane], below + wide0 * kRows);
+        #pragma unroll
+                    for (int x = 0; x < kRows; ++x) {
+                        s.list.least[wave * kRows + x][lane] = (uint16_t)min(row[x], min(below + one0, kFar));
+                        below = min(row[x], below + wide0);
+                    }
+                    __syncthreads();
+                }
+
+            }
+
+            // Pairs of P1 and P2 that some partner may suit: collected 64 at a time, then every lane looks its partners up.  If
+            // this settles the matter but several selections are as good, once more, for the one whose choices, two
+            // bits each with the last item's on top, make the smallest number.  (One loop for everything: the code is run
+            // a few times, and fetching it is a good part of what that takes.)
+            const bool filtered = size[1] * size[2] >= kFilterPairs;
+            const int coarse = max(0, 18 - __builtin_clz(G | 1));  // (as above)
+            const int room0 = c0 - used0 + s.q_default[0], room1 = c1 - used1 + s.q_default[1];
+            uint32_t *queue = s.list.queue[wave];
+            const int chunks = (size[2] + 63) >> 6;
+            if (pass == 1) {  // (in the place of what the table of least losses was made with)
                 if (tid < 3 * 8 * 16) {
                     const int l = tid >> 7, at = tid >> 4 & 7, bits = tid & 15;
                     ulonglong2 flips = make_ulonglong2(0ull, 0ull);
-#pragma unroll
+        #pragma unroll
                     for (int b = 0; b < 4; ++b) {
                         if ((bits >> b & 1) != 0 && at * 4 + b < s.bits[l]) {
                             flips.x ^= s.flip_lo[l][at * 4 + b];
@@ -821,21 +740,142 @@ __device__ __forceinline__ void jt_enumerate(const BatchArgs &a, int inst, State
                     s.flips[l][at][bits] = flips;
                 }
                 __syncthreads();
-                int all = 0;
-#pragma unroll 4
-                for (int w = 0; w < kEnumWaves; ++w) all += s.wave_sum[w];
-                several = all > 1;
-                if (!several) break;
-                chosen.q = -1;
-                best = least;
             }
+            if (part_loss <= G) {
+                int queued = 0;
+                // a tile: sixteen of P1, one after the other, with 64 of P2
+                int first1 = 0, chunk = wave, x = 16, i2 = 0, left0_2 = 0, left1_2 = 0, a1 = 0, b1 = 0, spare2 = 0, loss1 = 0;
+                bool more = true;
+                while (true) {
+                    const int limit = min(min(known, best), *(volatile int32_t *)&s.least);  // no selection that loses more matters
+                    if (more && queued < 64) {
+                        if (x == 16) {
+                            while (chunk >= chunks) chunk -= chunks, first1 += 16;
+                            if (first1 >= size[1]) {
+                                more = false;
+                                continue;
+                            }
+                            i2 = chunk * 64 + lane;
+                            chunk += kEnumWaves;
+                            const int i1 = first1 + (lane & 15);
+                            const int use2 = s.list.p2_use[i2], use1 = i1 < size[1] ? s.list.p1_use[i1] : 0;
+                            left0_2 = room0 - use_a(use2), left1_2 = room1 - use_b(use2), a1 = use_a(use1), b1 = use_b(use1);
+                            spare2 = i2 < size[2] ? __builtin_amdgcn_readfirstlane(limit) - s.list.p2_loss[i2] : -1;
+                            loss1 = i1 < size[1] ? s.list.p1_loss[i1] : kNever;
+                            // (first1 stays the tile's until chunk runs over)
+                            x = 0;
+                        }
+                        bool valid[2];
+                        int at_least[2], spare[2];
+    #pragma unroll
+                        for (int y = 0; y < 2; ++y) {
+                            spare[y] = spare2 - __builtin_amdgcn_readlane(loss1, x + y);
+                            const int left0 = left0_2 - __builtin_amdgcn_readlane(a1, x + y);
+                            const int left1 = left1_2 - __builtin_amdgcn_readlane(b1, x + y);
+                            valid[y] = (spare[y] | left0 | left1) >= 0;
+                            at_least[y] = filtered ? (&s.list.least[0][0])[row_of(max(left0, 0)) + column_of(max(left1, 0))] : 0;
+                        }
+    #pragma unroll
+                        for (int y = 0; y < 2; ++y) {
+                            valid[y] = valid[y] && at_least[y] <= spare[y] >> coarse;
+                            const unsigned long long mask = __ballot(valid[y]);
+                            if (valid[y]) queue[queued + enum_below(mask, lane)] = (uint32_t)(first1 + x + y) << 11 | (uint32_t)i2;
+                            queued += __popcll(mask);
+                        }
+                        __builtin_amdgcn_wave_barrier();
+                        x += 2;
+                        continue;
+                    }
+                    if (queued == 0) break;
+                    const bool valid = lane < queued;
+                    const uint32_t pair = queue[lane], rest = queue[64 + lane], rest2 = queue[128 + lane];
+                    __builtin_amdgcn_wave_barrier();
+                    queue[lane] = rest;
+                    queue[64 + lane] = rest2;
+                    queued = max(queued - 64, 0);
+                    if (valid) {
+                        const int p1 = pair >> 11, p2 = pair & 2047;
+                        const int use = s.list.p1_use[p1] + s.list.p2_use[p2], loss = s.list.p1_loss[p1] + s.list.p2_loss[p2];
+                        const int left0 = room0 - use_a(use), left1 = room1 - use_b(use), spare = limit - loss;
+                        // room left on a link costs its price: no partner may leave more of it than what is spare pays for
+                        const int slack0 = l0 > 0 ? (int)fminf((float)spare * per0, 65535.0f) + 1 : 65536;
+                        const int slack1 = l1 > 0 ? (int)fminf((float)spare * per1, 65535.0f) + 1 : 65536;
+                        const int to0 = row_of(left0), from1 = column_of(max(left1 - slack1, 0)), to1 = column_of(left1) + 1;
+                        for (int row = spare >= 0 ? row_of(max(left0 - slack0, 0)) : kCells; row <= to0; row += kCells1) {
+                            const int end = begin16[row + to1];
+                            for (int k = begin16[row + from1]; k < end; ++k) {
+                                const int its_loss = s.list.q_loss[k];
+                                if (its_loss > spare) continue;
+                                const int used = s.list.q_use[k], room_a = left0 - (used >> 16), room_b = left1 - (used & 0xffff);
+                                if ((room_a | room_b | (slack0 - room_a) | (slack1 - room_b)) < 0) continue;
+                                const long long more_lost = (long long)l0 * room_a + (long long)l1 * room_b + its_loss;
+                                if (more_lost > spare) continue;
+                                const int lost = loss + (int)more_lost;
+                                if (pass == 0) {
+                                    copies = lost < best ? 0 : lost == best ? 1 : copies;
+                                    if (lost < best) chosen.q = 0, chosen.q_mask = s.list.q_mask[k], chosen.pair = pair, best = lost;
+                                } else if (lost == least) {
+                                    EnumResult other{0, s.list.q_mask[k], pair, s.default_lo, s.default_hi};
+    #pragma unroll 1
+                                    for (int l = 0; l < 3; ++l) {
+                                        const uint32_t mask = enum_mask(s, l, pair, other.q_mask);
+    #pragma unroll
+                                        for (int at = 0; at < 8; ++at) {
+                                            const ulonglong2 flips = s.flips[l][at][mask >> (at * 4) & 15];
+                                            other.lo ^= flips.x;
+                                            other.hi ^= flips.y;
+                                        }
+                                    }
+                                    if (enum_before(other, chosen)) chosen = other;
+                                }
+                            }
+                        }
+                    }
+                    const long long now = wall_clock64();
+                    if (now > deadline) s.over = 1;
+                    if (now > look) {
+                        look = now + kLookTicks;
+                        if (__hip_atomic_load(&solved[inst], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) s.over = 1;
+                    }
+                    if (__builtin_amdgcn_readfirstlane(*(volatile int32_t *)&s.over)) break;
+                }
+                if (pass == 0 && best <= known) atomicMin(&s.least, best);
+                __syncthreads();
+                if (s.over) return;
+            }
+            if (++part < turns) continue;
+            part = 0;
+            if (pass == 1) break;
+            least = s.least;
+            if (least > G) break;
+            // nothing is better, and nothing as good has not been met
+            const int met = __popcll(__ballot(best == least)) + __popcll(__ballot(best == least && copies != 0));
+            if (lane == 0) s.wave_sum[wave] = met;
+            if (best == least) s.q_mask = chosen.q_mask, s.pair = chosen.pair;  // (whichever, where there are several)
+            __syncthreads();
+            int all = 0;
+    #pragma unroll 4
+            for (int w = 0; w < kEnumWaves; ++w) all += s.wave_sum[w];
+            several = all > 1;
+            if (!several) break;
+            chosen.q = -1;
+            best = least;
+            pass = 1;
         }
+        if (again) {
+            retry(size[0] > kListQ);
+            if (s.over) return;
+            continue;
+        }
+        last_G = G;
+        ++round;
         if (least <= G) {
             if (several) {
 #pragma unroll 1
                 for (int off = 1; off < 64; off <<= 1) {
                     EnumResult other;
                     other.q = __shfl_xor(chosen.q, off);
+                    other.q_mask = __shfl_xor(chosen.q_mask, off);
                     other.pair = __shfl_xor(chosen.pair, off);
                     other.lo = __shfl_xor(chosen.lo, off);
                     other.hi = __shfl_xor(chosen.hi, off);
@@ -848,7 +888,7 @@ __device__ __forceinline__ void jt_enumerate(const BatchArgs &a, int inst, State
 #pragma unroll 1
                     for (int w = 1; w < kEnumWaves; ++w)
                         if (enum_before(s.result[w], chosen)) chosen = s.result[w];
-                    s.q = chosen.q;
+                    s.q_mask = chosen.q_mask;
                     s.pair = chosen.pair;
                 }
                 __syncthreads();
@@ -858,7 +898,7 @@ __device__ __forceinline__ void jt_enumerate(const BatchArgs &a, int inst, State
             __syncthreads();
             if (tid < 96) {
                 const int l = tid >> 5, b = tid & 31;
-                if (enum_mask(s, l, s.pair, s.q) >> b & 1u) s.choice[s.meaning[l][b] >> 2] = (uint8_t)(s.meaning[l][b] & 3);
+                if (enum_mask(s, l, s.pair, s.q_mask) >> b & 1u) s.choice[s.meaning[l][b] >> 2] = (uint8_t)(s.meaning[l][b] & 3);
             }
             finish([&]() { return rank < kEnumOpen && loss_a < kNever ? (int)s.choice[rank] : dflt; });
             return;

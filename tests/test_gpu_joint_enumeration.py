@@ -171,3 +171,16 @@ def test_attempts_do_not_hold_up_the_sweep(binding, oracle, batch, n, w_hi):
     (_, sweep), (_, took) = _profiled(binding, oracle, [kb, tried], 769, 700)
     print(f"{took:.3f} ms, sweep {sweep:.3f} ms", flush=True)
     assert took < 1.25 * sweep + 0.05
+
+
+@pytest.mark.parametrize("seed,v_hi", [(102, 1000), (103, 1000), (106, 1000), (108, 1000), (109, 60), (110, 25)])
+def test_lists_that_run_over_are_made_in_parts(binding, oracle, seed, v_hi):
+    """64 items on links of 512: of 256 such instances some have more combinations than a list holds, in one or more of the
+    groups; with few values many selections are as good, in several parts."""
+    r = np.random.Generator(np.random.PCG64(seed))
+    w0 = r.integers(1, 65, size=(256, 64))
+    w1 = w0 * r.integers(3, 7, size=w0.shape)
+    kb = W.hetero_joint(batch=256, n=64, c1=512, c2=512)
+    kb.weights[:] = np.stack([w0, w1], axis=1)
+    kb.values[:] = r.integers(1, v_hi + 1, size=w0.shape)
+    run(binding, oracle, kb)
