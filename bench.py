@@ -3,8 +3,9 @@
 
 A step is one pass of the whole hot path (validation, every stage's DP sweep,
 keep-table stream, traceback, outputs) over one synthetic batch resident in
-HBM.  Prints ONE JSON line: DP cell-updates/s (the cell-updates the kernels
-evaluate; the job's count as the CPU oracle performs it is beside it),
+HBM.  Prints ONE JSON line: DP cell-updates/s (the cells that the sweeps go
+through, or would where a stage is answered without one, which the line says;
+the job's count as the CPU oracle performs it is beside it),
 instances/s, the LDS roofline of the sweep kernel from HIP events on the launch
 stream, and the CPU oracle timed on this machine's host cores.  The default run
 (ResNet-101 shape) also measures, in the same process, every other
@@ -144,7 +145,7 @@ def calibration_copy(dev) -> None:
 
 def run_schedule(args):
     """The task-queue simulation (Sec. III.B, Cases 1-4) on the ResNet-101 shape: a step is one
-    call simulating every candidate for 8 iterations (16 stages, each one solver launch).
+    call simulating every candidate for 8 iterations (16 stages, one launch).
     Returns (line, parity)."""
     import torch
     from oracle import oracle
@@ -193,18 +194,14 @@ def run_schedule(args):
     # them for its sample and the per-candidate mean is applied to the batch
     cells_step = float(ref.sweep_cells.mean()) * sb.batch
     ms_step = (t1 - t0) * 1e3 / args.steps
-    sweep_s = float(prof.sweep_ms) * 1e-3
     launches = int(prof.sweep_launches)
-    swept_step = int(prof.swept_cell_updates) // args.steps   # counted by the library: what the sweeps evaluated
-    # every stage runs on the bit-set kernels, 12 LDS bytes and about four vector instructions per 32
-    # cells; on a handle that promises a subset-sum problem they count nothing, and the one-sweep cells
+    swept_step = int(prof.swept_cell_updates) // args.steps   # counted by the library: the sweeps the answers stand for
+    # every stage runs on the bit-set kernels, most of them without a sweep (seq_excess.h), so no roofline of cells
+    # applies; on a handle that promises a subset-sum problem they count nothing, and the one-sweep cells
     # the oracle's sample gives stand in
     bitset = bool(getattr(args, "subset_sum", False))
-    bytes_per_cell, ops_per_cell = 0.375, 0.125
     if bitset:
         swept_step = int(cells_step)
-    achieved = swept_step * args.steps * bytes_per_cell / sweep_s / 1e9 if sweep_s > 0 else 0.0
-    ops = swept_step * args.steps * ops_per_cell / sweep_s if sweep_s > 0 else 0.0
     upd = got["update_k"]
     line = dict(
         metric="knapsack DP cell-updates/sec", value=swept_step / (ms_step * 1e-3), unit="cell-updates/s", n_gpus=1,
@@ -217,7 +214,8 @@ def run_schedule(args):
                                 if bitset else ""),
                     value_counts=("one-sweep cell-updates per stage as estimated from the oracle's sample (the bit-set "
                                   "kernels count none)" if bitset else
-                                  "cell-updates the sweeps evaluate (counted by the library)"),
+                                  "cells that the stages' sweeps would go through (counted by the library): most are "
+                                  "answered by what they leave out, without one"),
                     candidates_per_step=sb.batch, iterations=sb.iterations,
                     one_sweep_cell_updates_per_step_estimated_from_sample=cells_step,
                     cell_updates_swept_per_step=swept_step, seq_path=int(info.seq_path),
@@ -228,13 +226,11 @@ def run_schedule(args):
         parity_checked=f"{len(rows)} of {sb.batch} candidates (every candidate: tests/test_gpu_schedule.py)",
         profile=dict(total_ms_per_step=float(prof.total_ms) / args.steps,
                      sweep_ms_per_step=float(prof.sweep_ms) / args.steps),
-        roofline=dict(bound="lds", achieved=achieved, peak=PEAK_LDS_GBS, unit="GB/s", frac=achieved / PEAK_LDS_GBS,
-                      traffic=None, kernel="seq_bits_kernel",
-                      bytes_per_cell=bytes_per_cell, launches=launches,
-                      avg_launch_ms=float(prof.sweep_ms) / max(launches, 1),
-                      swept_cell_updates_per_s=swept_step * args.steps / sweep_s if sweep_s > 0 else 0.0,
-                      alu=dict(ops_per_cell=ops_per_cell, peak_lane_ops_per_s=PEAK_INT_LANE_OPS,
-                               frac=ops / PEAK_INT_LANE_OPS)),
+        roofline=dict(bound="latency", achieved=None, peak=PEAK_LDS_GBS, unit="GB/s", frac=None,
+                      traffic=None, kernel="seq_bits_kernel", bytes_per_cell=None, launches=launches,
+                      avg_launch_ms=float(prof.sweep_ms) / max(launches, 1), swept_cell_updates_per_s=None,
+                      cells_left_to_the_sweep_per_step=None,
+                      alu=dict(ops_per_cell=None, peak_lane_ops_per_s=PEAK_INT_LANE_OPS, frac=None)),
         cpu_baseline=None if args.no_cpu else dict(
             value=float(ref.sweep_cells.sum()) / t_cpu, unit="cell-updates/s", cores=int(ref.threads), kind="oracle",
             sample=f"{len(rows)} of the {sb.batch} candidates, all {sb.iterations} iterations, {t_cpu:.2f} s wall "
@@ -451,6 +447,8 @@ def run_solver(args):
     # two-link instances and stages on rows in global memory are settled by enumeration where that can be done: hardly
     # any of the cells counted above is evaluated, the rate is an effective one and no roofline of cells applies
     enumerated = not seq or (info.seq_path == 3 and calls[0].mode == 0)
+    # subset-sum stages of long lists are answered by what they leave out: the count is that of the sweeps this stands for
+    by_excess = by_sums and calls[0].item_stride >= 97
     if enumerated:
         kernel = "seq_enum_kernel" if seq else "jt_sweep_all"   # (two links: enumeration and sweep are one launch)
     tf = os.path.join(ROOT, "profiles", f"{kernel}_{args.workload}_traffic.txt")
@@ -473,9 +471,9 @@ def run_solver(args):
         alu=dict(ops_per_cell=algo["ops_per_cell"], peak_lane_ops_per_s=PEAK_INT_LANE_OPS,
                  frac=(swept_step * args.steps * algo["ops_per_cell"] / sweep_s) / PEAK_INT_LANE_OPS
                  if sweep_s > 0 else 0.0))
-    if enumerated:
+    if enumerated or by_excess:
         # (what the library counted of the instances that were left: row cells streamed, or cells of their tables)
-        left = int(prof.streamed_row_cells if seq else prof.swept_cell_updates) // args.steps
+        left = None if by_excess else int(prof.streamed_row_cells if seq else prof.swept_cell_updates) // args.steps
         roofline = dict(bound="latency", achieved=None, peak=peak, unit="GB/s", frac=None, traffic=None, traffic_source=None,
                         kernel=kernel, launches=launches, avg_launch_ms=roofline["avg_launch_ms"],
                         swept_cell_updates_per_s=None, bytes_per_cell=None, alu=dict(roofline["alu"], frac=None),
@@ -487,6 +485,8 @@ def run_solver(args):
         config=dict(workload=desc,
                     value_counts=("cells that a sweep of the job would go through (cell_updates_swept_per_step): settled by "
                                   "enumeration, hardly any is evaluated; " if enumerated else
+                                  "cells that the sweeps of the job would go through (cell_updates_swept_per_step): most "
+                                  "stages are answered by what they leave out, without one; " if by_excess else
                                   "cells up to the capacity of the items the sweeps go through (cell_updates_swept_per_step), "
                                   + ("32 of them an instruction on the bit-set kernels; " if by_sums else
                                      "of which the streamed sweep computes a band; " if kernel == "sg_stream" else
@@ -523,7 +523,7 @@ def compact(line: dict) -> dict:
                              unit=r["unit"], frac=r["frac"], alu_frac=r["alu"]["frac"],
                              alu_ops_per_cell=r["alu"]["ops_per_cell"]),
                parity_vs_oracle=line["parity_vs_oracle"])
-    if r["bound"] == "latency":   # settled by enumeration: what a sweep would go through
+    if r["bound"] == "latency":   # settled without a sweep: what a sweep would go through
         out["cell_updates_of_a_sweep_per_step"] = out.pop("cell_updates_evaluated_per_step")
         out["cells_left_to_the_sweep_per_step"] = r["cells_left_to_the_sweep_per_step"]
     for key in ("instances_per_s", "candidate_iterations_per_s", "effective_cell_updates_per_s", "parity_checked"):
