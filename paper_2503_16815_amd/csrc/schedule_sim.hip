@@ -1,5 +1,6 @@
 // The two task queues of Sec. III.B (Cases 1-4) simulated over several iterations for a
-// batch of candidate schedules, entirely on the device: per stage a small kernel turns
+// batch of candidate schedules, where rows live in global memory (windows above 65535; shorter ones: one launch of
+// seq_bits_kernel.h), entirely on the device: per stage a small kernel turns
 // each candidate's queue state into one knapsack problem (the list, the window, and
 // whether the stage is a plain knapsack or Algorithm 1), the solver runs on all candidates
 // at once, and a second small kernel applies the answer to the queues and
