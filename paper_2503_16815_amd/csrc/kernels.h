@@ -75,7 +75,8 @@ struct ScheduleArgs {
 // One wavefront per instance; the reachable sums as a bit set in registers and LDS, the
 // selection from a bit-sliced "first item that reached this sum" table in registers.  No scratch.
 struct SeqBitsPlan {
-    int32_t variant;         // index into the compiled (words per lane, planes) table
+    int32_t variant;         // index into the compiled (words per lane, planes) table; it, planes and n_pad are those of
+                             // the longest lists: a launch takes those of the call's
     int32_t words_per_lane;  // K: capacities up to 2048 K - 1
     int32_t planes;          // NP: lists of up to 2^NP items
     int32_t row_words;       // 64 x the slots max_capacity needs

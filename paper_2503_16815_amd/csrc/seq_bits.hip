@@ -26,6 +26,23 @@ int64_t bits_lds_bytes(const BitsLayout &lay, int waves)
     return ((int64_t)4 + lay.plane_words + (int64_t)waves * lay.wave_words) * 4;
 }
 
+// The planes that a call's lists of up to `items` need (index in kBitsPlanes).  By the call and not by the handle, whose lists
+// may be longer elsewhere: planes cost registers and LDS, and stages by what they leave out cost the row's sweep its
+// registers where they are never tried.  8192 instances on a handle for 314 items, us with the handle's kernel and the call's: 80 items
+// SEQUENTIAL 121 and 94, RECURSIVE 96 and 68, CAPACITY_SWEEP 106 and 80; 38 items 61 and 43; a sweep of 128 items 130 and 102.
+int bits_which(int items, bool caps_sweep)
+{
+    return items <= 64 ? 0 : items < (caps_sweep ? kBitsExcessCapsItems : kBitsExcessItems) ? 1 : items <= 512 ? 2 : 3;
+}
+
+void bits_lists(SeqBitsPlan *p, int items, bool caps_sweep)
+{
+    const int which = bits_which(items, caps_sweep);
+    p->variant = p->variant / 4 * 4 + which;
+    p->planes = kBitsPlanes[which];
+    p->n_pad = (items + 7) & ~7;
+}
+
 // Instances a compute unit holds when `waves` of them share a workgroup (0: they do not fit).
 int bits_per_cu(const SeqBitsPlan &p, int64_t lds, int waves)
 {
@@ -48,12 +65,11 @@ bool seq_bits_plan(int32_t max_capacity, int32_t max_items, int32_t lds_per_wg_b
     for (int i = 0; i < kNumBitsWords; ++i) {
         const int K = kBitsWords[i];
         if ((int64_t)max_capacity > (int64_t)K * 2048 - 1) continue;
-        const int which = max_items <= 64 ? 0 : max_items < kBitsExcessItems ? 1 : max_items <= 512 ? 2 : 3, grain = bits_grain(K);
-        p->variant = 4 * i + which;
+        const int grain = bits_grain(K);
+        p->variant = 4 * i;
         p->words_per_lane = K;
-        p->planes = kBitsPlanes[which];
+        bits_lists(p, max_items, false);
         p->row_words = (max_capacity / 2048 + grain) / grain * grain * 64;
-        p->n_pad = (max_items + 7) & ~7;
         p->lds_limit = lds_per_wg_bytes - 256;
         p->compute_units = compute_units;
         p->lds_bytes = (int32_t)bits_lds_bytes(bits_layout(*p, true), 1);
@@ -66,9 +82,11 @@ hipError_t seq_bits_prepare(const SeqBitsPlan &p)
 {
     // the attribute belongs to the kernel, not to the handle: the most any handle may ask for
     // (a compute unit's LDS less a small allowance)
-    for (const bool queues : {false, true}) {
-        const hipError_t e = hipFuncSetAttribute(bits_kernel(p, queues), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256);
-        if (e != hipSuccess) return e;
+    for (SeqBitsPlan q = p; q.variant >= p.variant / 4 * 4; --q.variant) {  // (shorter lists have kernels of their own)
+        for (const bool queues : {false, true}) {
+            const hipError_t e = hipFuncSetAttribute(bits_kernel(q, queues), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256);
+            if (e != hipSuccess) return e;
+        }
     }
     return hipSuccess;
 }
@@ -76,8 +94,9 @@ hipError_t seq_bits_prepare(const SeqBitsPlan &p)
 namespace {
 
 template <bool QUEUES>
-hipError_t bits_launch(const SeqBitsPlan &p, const BatchArgs &a, const BitsQueueArgs<QUEUES> &q, hipStream_t st, unsigned long long *swept_cells)
+hipError_t bits_launch(SeqBitsPlan p, const BatchArgs &a, const BitsQueueArgs<QUEUES> &q, hipStream_t st, unsigned long long *swept_cells)
 {
+    bits_lists(&p, a.item_stride, a.mode == DEFT_MODE_CAPACITY_SWEEP);
     const auto kernel = reinterpret_cast<BitsKernel<QUEUES>>(const_cast<void *>(bits_kernel(p, QUEUES)));
     BitsLayout lay = bits_layout(p, a.mode == DEFT_MODE_CAPACITY_SWEEP);
     // A capacity sweep of lists that are answered capacity by capacity: as many wavefronts an instance, up to four, as the

@@ -58,7 +58,7 @@ namespace {
 
 // Shorter lists are swept at once (81 items, 1735 of them: by what their stages leave out 27.4 -> 36 us; 93 items 13.9 -> 16.7), and
 // so are capacity sweeps of fewer than 129 items: one capacity that is not answered by itself sends the others along (101
-// items, nine of them with eight capacities: 18.8 -> 26.7).  Handles for shorter lists have kernels without it, whose sweep
+// items, nine of them with eight capacities: 18.8 -> 26.7).  Calls of shorter lists run on kernels without it, whose sweep
 // has the registers (66 items: 17.7 against 20.8 us).
 constexpr int kBitsExcessItems = 97, kBitsExcessCapsItems = 129;
 constexpr int kBitsEnumItems = 6;  // stages offered at most this many items are settled by enumeration

@@ -63,3 +63,41 @@ def test_uneven_workgroups(binding, oracle, batch):
     run(binding, oracle, kb, flags=FLAG)
     kc = W.random_capacity_sweep(33500 + batch, batch=min(batch, 300), n_max=90, m_max=5, w_hi=60, v_hi=9, cap_hi=2500, ties=True)
     run(binding, oracle, kc, flags=FLAG)
+
+
+@pytest.mark.parametrize("mode", ["sequential", "algorithm1", "capacities"])
+def test_short_lists_on_a_handle_for_long_ones(binding, oracle, mode):
+    """The kernel goes by the call's lists: the same outputs, and about as fast, as on a handle for lists no longer (with
+    the kernels of the longer lists 1.13 to 1.41 times as long)."""
+    import torch
+    r = np.random.Generator(np.random.PCG64(34000))
+    B, n, cap = 8192, 80, 12000
+    x = r.lognormal(0.0, 1.0, size=(B, n))
+    w = np.maximum(1, np.rint(x * (2.2 * cap / x.sum(axis=1, keepdims=True)))).astype(np.int32)
+    full = lambda v: np.full(B, v, np.int32)  # noqa: E731
+    kb = W._sequential("short_lists", w, w.copy(), np.tile(np.array([[cap, cap * 4 // 10] * 2], np.int32), (B, 1)))
+    if mode == "algorithm1":
+        kb = W.KnapsackBatch(name=mode, mode=W.MODE_RECURSIVE, batch=B, item_stride=n, knap_stride=2, n_items=full(n),
+                             n_knapsacks=full(1), weights=w, values=w.copy(), capacities=kb.capacities[:, :2].copy(),
+                             fill_order=None, drop_time=(w // 3).astype(np.int32))
+    if mode == "capacities":
+        caps = np.rint(cap / 1.35 * (1 + 0.05 * np.tile(np.arange(8), (B, 1)))).astype(np.int32)
+        kb = W.KnapsackBatch(name=mode, mode=W.MODE_CAPACITY_SWEEP, batch=B, item_stride=n, knap_stride=8, n_items=full(n),
+                             n_knapsacks=full(8), weights=w, values=w.copy(), capacities=caps, fill_order=None, drop_time=None)
+    took, outs = [], []
+    for max_items in (n, 314, 700):
+        with binding.DeftKnapsack(max_batch=B, max_items=max_items, max_knapsacks=8, max_capacity=cap, flags=FLAG) as h:
+            db = h.upload(kb)
+            best = np.inf
+            for _ in range(12):
+                h.set_profiling(True)
+                o = h.solve_batch(db)
+                torch.cuda.synchronize()
+                best = min(best, h.get_profile().sweep_ms)
+            took.append(best)
+            outs.append([getattr(o, k).cpu().numpy().copy() for k in ("status", "total_value", "knap_value", "knap_load", "assignment")])
+    print(f"{mode}: {took} ms", flush=True)
+    for got in outs[1:]:
+        assert all(np.array_equal(a, b) for a, b in zip(got, outs[0]))
+    run(binding, oracle, kb.slice(0, 64), max_capacity=cap, max_items=314, flags=FLAG)
+    assert max(took[1:]) < 1.08 * took[0]
