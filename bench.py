@@ -195,30 +195,23 @@ def run_schedule(args):
     cells_step = float(ref.sweep_cells.mean()) * sb.batch
     ms_step = (t1 - t0) * 1e3 / args.steps
     launches = int(prof.sweep_launches)
-    swept_step = int(prof.swept_cell_updates) // args.steps   # counted by the library: the sweeps the answers stand for
     # every stage runs on the bit-set kernels, most of them without a sweep (seq_excess.h), so no roofline of cells
-    # applies; on a handle that promises a subset-sum problem they count nothing, and the one-sweep cells
-    # the oracle's sample gives stand in
-    bitset = bool(getattr(args, "subset_sum", False))
-    if bitset:
-        swept_step = int(cells_step)
+    # applies; the library counts what was swept all the same
+    left_step = int(prof.streamed_row_cells) // args.steps
     upd = got["update_k"]
     line = dict(
-        metric="knapsack DP cell-updates/sec", value=swept_step / (ms_step * 1e-3), unit="cell-updates/s", n_gpus=1,
+        metric="knapsack DP cell-updates/sec", value=cells_step / (ms_step * 1e-3), unit="cell-updates/s", n_gpus=1,
         steps=args.steps, warmup=args.warmup, ms_per_step=ms_step, higher_is_better=True, scaling="weak",
         vs_baseline=None, dtype="int32", data="synthetic",
         config=dict(workload=f"task-queue simulation (Cases 1-4), ResNet-101-shaped: {sb.batch} candidates x "
                              f"{sb.n_buckets} buckets x {sb.iterations} iterations, windows 5900 / 11800 +-10%"
                              + (" [handle promises values equal to weights]" if promised else "")
-                             + (" [bit-set rows; cell-updates as the oracle's sample counts them for one sweep per stage]"
-                                if bitset else ""),
-                    value_counts=("one-sweep cell-updates per stage as estimated from the oracle's sample (the bit-set "
-                                  "kernels count none)" if bitset else
-                                  "cells that the stages' sweeps would go through (counted by the library): most are "
-                                  "answered by what they leave out, without one"),
+                             + (" [handle promises a subset-sum problem]" if getattr(args, "subset_sum", False) else ""),
+                    value_counts="one-sweep cell-updates per stage as estimated from the oracle's sample: most stages are "
+                                 "answered by what they leave out, without a sweep (cells_left_to_the_sweep_per_step: counted)",
                     candidates_per_step=sb.batch, iterations=sb.iterations,
                     one_sweep_cell_updates_per_step_estimated_from_sample=cells_step,
-                    cell_updates_swept_per_step=swept_step, seq_path=int(info.seq_path),
+                    cell_updates_swept_per_step=int(cells_step), seq_path=int(info.seq_path),
                     threads_per_instance=int(info.seq_threads), cells_per_thread=int(info.seq_cells_per_thread),
                     updates_per_iteration_mean=float((upd > 0).mean()),
                     buckets_per_iteration_mean=float(got["stage_count"].sum(axis=(1, 2)).mean() / sb.iterations)),
@@ -229,7 +222,7 @@ def run_schedule(args):
         roofline=dict(bound="latency", achieved=None, peak=PEAK_LDS_GBS, unit="GB/s", frac=None,
                       traffic=None, kernel="seq_bits_kernel", bytes_per_cell=None, launches=launches,
                       avg_launch_ms=float(prof.sweep_ms) / max(launches, 1), swept_cell_updates_per_s=None,
-                      cells_left_to_the_sweep_per_step=None,
+                      cells_left_to_the_sweep_per_step=left_step,
                       alu=dict(ops_per_cell=None, peak_lane_ops_per_s=PEAK_INT_LANE_OPS, frac=None)),
         cpu_baseline=None if args.no_cpu else dict(
             value=float(ref.sweep_cells.sum()) / t_cpu, unit="cell-updates/s", cores=int(ref.threads), kind="oracle",
@@ -447,8 +440,10 @@ def run_solver(args):
     # two-link instances and stages on rows in global memory are settled by enumeration where that can be done: hardly
     # any of the cells counted above is evaluated, the rate is an effective one and no roofline of cells applies
     enumerated = not seq or (info.seq_path == 3 and calls[0].mode == 0)
-    # subset-sum stages of long lists are answered by what they leave out: the count is that of the sweeps this stands for
-    by_excess = by_sums and calls[0].item_stride >= 97
+    # subset-sum stages of long lists are answered by what they leave out, mostly: the count is that of the sweeps this stands
+    # for, and the library counts what was swept all the same
+    left = int(prof.streamed_row_cells if seq else prof.swept_cell_updates) // args.steps
+    by_excess = by_sums and 2 * left < swept_step
     if enumerated:
         kernel = "seq_enum_kernel" if seq else "jt_sweep_all"   # (two links: enumeration and sweep are one launch)
     tf = os.path.join(ROOT, "profiles", f"{kernel}_{args.workload}_traffic.txt")
@@ -472,8 +467,7 @@ def run_solver(args):
                  frac=(swept_step * args.steps * algo["ops_per_cell"] / sweep_s) / PEAK_INT_LANE_OPS
                  if sweep_s > 0 else 0.0))
     if enumerated or by_excess:
-        # (what the library counted of the instances that were left: row cells streamed, or cells of their tables)
-        left = None if by_excess else int(prof.streamed_row_cells if seq else prof.swept_cell_updates) // args.steps
+        # (left: cells that were swept, row cells streamed, or cells of the tables of the instances that were left)
         roofline = dict(bound="latency", achieved=None, peak=peak, unit="GB/s", frac=None, traffic=None, traffic_source=None,
                         kernel=kernel, launches=launches, avg_launch_ms=roofline["avg_launch_ms"],
                         swept_cell_updates_per_s=None, bytes_per_cell=None, alu=dict(roofline["alu"], frac=None),

@@ -357,14 +357,19 @@ typedef struct {
                               row cells read from plus row cells written to global memory
                               by the sweeps, summed over instances and stages (a pass over a
                               row may serve seven items); stages settled by enumeration
-                              add nothing; 0 on the other paths                            */
+                              add nothing.  Bit-set rows (values that are weights on rows
+                              in LDS, handles with a flag, simulate_schedule up to 65535):
+                              cell-updates that their sweeps evaluated, C - w + 1 an item;
+                              most stages of long lists are answered without a sweep and
+                              add nothing.  0 on the other paths                           */
     int64_t swept_cell_updates; /* rows in LDS (seq_path 1 or 2): cell-updates the sweeps
                               evaluated, C - w + 1 for every item a stage's sweep went
                               through (stages settled without a sweep, by enumeration for
-                              instance, and the items after a full row add nothing), and
-                              the same count from the bit-set rows on those handles
-                              (there also for stages answered by what they leave out: the
-                              cells of the sweep that the answer stands for).
+                              instance, and the items after a full row add nothing).  Of
+                              solve calls' instances that the bit-set rows answered on
+                              those handles: the same count of what a sweep goes through,
+                              whether there was one or not (streamed_row_cells says what
+                              was swept); nothing of simulate_schedule.
                               JOINT2: items times (C1 + 1) (C2 + 1) of the instances that
                               enumeration left and their tables answered.  0 on the other
                               paths                                                       */

@@ -20,6 +20,7 @@ constexpr int32_t kMaxCapacity = 1 << 24;
 constexpr int32_t kMaxJointCapacity = 4095;
 constexpr int32_t kMaxIterations = 4096;
 constexpr int32_t kMaxValuesAreWeightsCapacity = 26623;
+constexpr int kBitsWords = kBitsCounters * kBitsCounterStride;
 constexpr int32_t kMaxSubsetSumCapacity = 65535;  // the longest bit-set row that is compiled
 
 struct DeviceGuard {
@@ -57,6 +58,7 @@ struct deft_knapsack {
     // instances of which that holds and flag the others in `left` for the kernels with rows of values.
     bool bits_ready = false, promised = false;
     SeqBitsPlan bits_plan{};
+    unsigned long long *bits_swept = nullptr;  // device counters read by get_profile
     int32_t *left = nullptr;      // [max_batch]; rows in global memory: for the enumeration ahead of them
 
     void *sim_buffers = nullptr;  // task-queue simulation: allocated by its first call
@@ -83,6 +85,7 @@ void free_handle(deft_knapsack *h)
     if (h->lds_swept) (void)hipFree(h->lds_swept);
     if (h->joint_swept) (void)hipFree(h->joint_swept);
     if (h->joint_scratch) (void)hipFree(h->joint_scratch);
+    if (h->bits_swept) (void)hipFree(h->bits_swept);
     if (h->left) (void)hipFree(h->left);
     if (h->sim_buffers) (void)hipFree(h->sim_buffers);
     h->prof.destroy();
@@ -104,6 +107,16 @@ deft_status_t alloc(void **p, int64_t bytes, int64_t *total)
     }
     *total += bytes;
     return DEFT_OK;
+}
+
+deft_status_t alloc_counter(unsigned long long **p, int words, int64_t *total)
+{
+    void *c = nullptr;
+    const deft_status_t st = alloc(&c, (int64_t)words * 8, total);
+    *p = static_cast<unsigned long long *>(c);
+    if (st != DEFT_OK || hipMemset(c, 0, (size_t)words * 8) == hipSuccess) return st;
+    (void)hipGetLastError();
+    return DEFT_ERR_DEVICE;
 }
 
 }  // namespace
@@ -161,6 +174,7 @@ extern "C" deft_status_t deft_knapsack_create(const deft_knapsack_config_t *cfg,
         } else {
             h->bits_ready = true;
             h->promised = cfg->flags != 0;
+            st = alloc_counter(&h->bits_swept, kBitsWords, &h->scratch_bytes);
         }
     }
     if (st == DEFT_OK && want_seq) {
@@ -175,15 +189,7 @@ extern "C" deft_status_t deft_knapsack_create(const deft_knapsack_config_t *cfg,
                 st = alloc(&c, (int64_t)cfg->max_batch * 4, &h->scratch_bytes);
                 h->left = static_cast<int32_t *>(c);
             }
-            if (st == DEFT_OK) {
-                void *c = nullptr;
-                st = alloc(&c, 8, &h->scratch_bytes);
-                h->lds_swept = static_cast<unsigned long long *>(c);
-                if (st == DEFT_OK && hipMemset(c, 0, 8) != hipSuccess) {
-                    (void)hipGetLastError();
-                    st = DEFT_ERR_DEVICE;
-                }
-            }
+            if (st == DEFT_OK) st = alloc_counter(&h->lds_swept, 1, &h->scratch_bytes);
         } else {
             (void)hipGetLastError();
             h->seq_path = 3;
@@ -199,15 +205,7 @@ extern "C" deft_status_t deft_knapsack_create(const deft_knapsack_config_t *cfg,
                 (void)hipGetLastError();
                 st = DEFT_ERR_DEVICE;
             }
-            if (st == DEFT_OK) {
-                void *c = nullptr;
-                st = alloc(&c, 8, &h->scratch_bytes);
-                h->glob_streamed = static_cast<unsigned long long *>(c);
-                if (st == DEFT_OK && hipMemset(c, 0, 8) != hipSuccess) {
-                    (void)hipGetLastError();
-                    st = DEFT_ERR_DEVICE;
-                }
-            }
+            if (st == DEFT_OK) st = alloc_counter(&h->glob_streamed, 1, &h->scratch_bytes);
         }
     }
     if (st == DEFT_OK && want_joint) {
@@ -218,15 +216,7 @@ extern "C" deft_status_t deft_knapsack_create(const deft_knapsack_config_t *cfg,
             (void)hipGetLastError();
             st = DEFT_ERR_DEVICE;
         }
-        if (st == DEFT_OK) {
-            void *c = nullptr;
-            st = alloc(&c, 8, &h->scratch_bytes);
-            h->joint_swept = static_cast<unsigned long long *>(c);
-            if (st == DEFT_OK && hipMemset(c, 0, 8) != hipSuccess) {
-                (void)hipGetLastError();
-                st = DEFT_ERR_DEVICE;
-            }
-        }
+        if (st == DEFT_OK) st = alloc_counter(&h->joint_swept, 1, &h->scratch_bytes);
     }
     if (st == DEFT_OK && greedy_prepare(cfg->max_items) != hipSuccess) {
         (void)hipGetLastError();
@@ -308,7 +298,7 @@ extern "C" deft_status_t deft_knapsack_solve_batch(deft_knapsack_t *h, const def
     if (by_sums) {
         a.left = h->left;
         if (prof) prof->sweep_begin(st);
-        e = seq_bits_launch(h->bits_plan, a, st, swept);
+        e = seq_bits_launch(h->bits_plan, a, st, prof ? h->bits_swept : nullptr);
         if (prof) prof->sweep_end(st);
     }
     if (e != hipSuccess || (by_sums && h->promised)) {
@@ -339,6 +329,11 @@ extern "C" deft_status_t deft_knapsack_solve_batch(deft_knapsack_t *h, const def
         e = joint_launch(h->joint_plan, a, h->joint_scratch, st, prof, prof ? h->joint_swept : nullptr);
     }
     if (prof) prof->end(st);
+    if (e == hipSuccess && by_sums && swept) {
+        a.left = h->left;
+        e = bits_count_launch(a, st, swept);
+        prof->counted(st);
+    }
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return DEFT_ERR_DEVICE;
@@ -388,7 +383,7 @@ extern "C" deft_status_t deft_knapsack_simulate_schedule(deft_knapsack_t *h, con
     hipError_t e;
     if (h->bits_ready) {  // a bucket's value is its communication time
         if (prof) prof->sweep_begin(st);
-        e = seq_bits_queues_launch(h->bits_plan, a, st, prof && !subset_sum(h) ? h->lds_swept : nullptr);
+        e = seq_bits_queues_launch(h->bits_plan, a, st, prof ? h->bits_swept : nullptr);
         if (prof) prof->sweep_end(st);
     } else {
         const auto solve = [&](const BatchArgs &x) { return seq_global_launch(h->glob_plan, x, h->glob_scratch, st, prof, h->glob_streamed); };
@@ -436,10 +431,10 @@ extern "C" deft_status_t deft_knapsack_set_profiling(deft_knapsack_t *h, int32_t
     if (!h) return DEFT_ERR_INVALID_ARG;
     h->profiling = enable != 0;
     h->prof.reset();
-    for (unsigned long long *counter : {h->glob_streamed, h->lds_swept, h->joint_swept}) {
+    for (unsigned long long *counter : {h->glob_streamed, h->bits_swept, h->lds_swept, h->joint_swept}) {
         if (!counter) continue;
         DeviceGuard g(h->cfg.device);
-        if (!g.ok || hipMemset(counter, 0, 8) != hipSuccess) {
+        if (!g.ok || hipMemset(counter, 0, counter == h->bits_swept ? kBitsWords * 8 : 8) != hipSuccess) {
             (void)hipGetLastError();
             return DEFT_ERR_DEVICE;
         }
@@ -456,14 +451,16 @@ extern "C" deft_status_t deft_knapsack_get_profile(deft_knapsack_t *h, deft_knap
     out->streamed_row_cells = 0;
     out->swept_cell_updates = 0;
     if (rc != DEFT_OK) return rc;
-    for (unsigned long long *counter : {h->glob_streamed, h->lds_swept, h->joint_swept}) {
+    for (unsigned long long *counter : {h->glob_streamed, h->bits_swept, h->lds_swept, h->joint_swept}) {
         if (!counter) continue;
-        unsigned long long v = 0;
-        if (hipMemcpy(&v, counter, 8, hipMemcpyDeviceToHost) != hipSuccess || hipMemset(counter, 0, 8) != hipSuccess) {
+        unsigned long long v[kBitsWords] = {};
+        const size_t bytes = counter == h->bits_swept ? sizeof(v) : 8;
+        if (hipMemcpy(v, counter, bytes, hipMemcpyDeviceToHost) != hipSuccess || hipMemset(counter, 0, bytes) != hipSuccess) {
             (void)hipGetLastError();
             return DEFT_ERR_DEVICE;
         }
-        (counter == h->glob_streamed ? out->streamed_row_cells : out->swept_cell_updates) += (int64_t)v;
+        int64_t &sum = counter == h->glob_streamed || counter == h->bits_swept ? out->streamed_row_cells : out->swept_cell_updates;
+        for (int i = 0; i < kBitsWords; i += kBitsCounterStride) sum += (int64_t)v[i];
     }
     return rc;
 }

@@ -603,43 +603,16 @@ seq_bits_kernel(BatchArgs a, BitsQueueArgs<QUEUES> q, BitsLayout lay, unsigned l
         long_list = bits_wave_sum(light) > bits_wave_sum(heavy);
     }
     if (long_list) list_weights();
-    // Where wavefronts share an instance: [0 .. 30] the values, then whether a capacity is left over, the furthest last
-    // item + 1, whether a capacity was not reached (in the place of the walk's planes).
+    // Where wavefronts share an instance: [0 .. 30] the values, then whether a capacity is left over (in the place of the
+    // walk's planes).
     uint32_t *shared = l.planes;
     if (share > 1) {
-        if (wave == 0 && lane < 34 && lane > 30) shared[lane] = 0;
+        if (threadIdx.x == 31) shared[31] = 0;
         __syncthreads();
     }
-    // Measurement only: C - w + 1 for every item that the row's sweep goes through, which is until it sees that C (every
-    // capacity of a capacity sweep) is reachable with item `last`; it looks after every eighth item, every second one
-    // of a list of at most 64.
-    auto count_cells = [&](int C, int j, int last, bool reached) {
-        int cnt = 0, sum = 0, upto = 0, weight = 0;
-        auto listed = [&](int i) { return i < n && W[i] <= C && (caps_sweep || mark8[i] == 0xff || mark8[i] == j); };
-        for (int i0 = 0; i0 < n; i0 += 64) {
-            const int i = i0 + lane;
-            const unsigned long long in = __builtin_amdgcn_ballot_w64(listed(i));
-            cnt += (int)__popcll(in);
-            upto += (int)__popcll(in & __builtin_amdgcn_ballot_w64(i <= last));
-            sum += bits_wave_sum(listed(i) ? W[i] : 0);
-        }
-        if (cnt == 0 || (!caps_sweep && (sum <= C || cnt <= kBitsEnumItems))) return;  // (settled without a sweep)
-        const int look = !caps_sweep && cnt <= 64 ? 2 : 8;
-        const int items = reached ? min(cnt, (upto + look - 1) / look * look) : cnt;
-        for (int i0 = 0, before = 0; i0 < n; i0 += 64) {
-            const bool in = listed(i0 + lane);
-            const unsigned long long mask = __builtin_amdgcn_ballot_w64(in);
-            weight += bits_wave_sum(in && before + (int)__popcll(mask & ((1ull << lane) - 1ull)) < items ? W[i0 + lane] : 0);
-            before += (int)__popcll(mask);
-        }
-        if (lane == 0) atomicAdd(swept_cells, (unsigned long long)items * (unsigned)(C + 1) - (unsigned long long)(unsigned)weight);
-    };
-
     BitsRows<K, NP> rows;
     const int cap_max = caps_sweep ? bits_wave_max(cap_l) : 0;
     const int stages = queues ? 2 * q.iterations : m;
-    bool reached = true;
-    int furthest = -1;
     // Task queues: items and time of the current queue, the iterations that it, the future queue and what is
     // complete carry, and the time of all buckets.
     int cur_items = 0, cur_time = 0, cur_k = 0, fut_k = 0, done_k = 0, all_time = 0;
@@ -651,16 +624,10 @@ seq_bits_kernel(BatchArgs a, BitsQueueArgs<QUEUES> q, BitsLayout lay, unsigned l
     for (int s = share > 1 ? wave : 0;; s += share) {
         if (s >= stages) {
             if (share == 1) break;
-            // what the instance's other wavefronts have answered
-            if (lane == 0) {
-                atomicMax(&shared[32], (uint32_t)(furthest + 1));
-                if (!reached) shared[33] = 1u;
-            }
-            __syncthreads();
+            __syncthreads();  // (the instance's other wavefronts have answered theirs)
             if (wave != 0) return;
             if (shared[31] == 0u) {
                 kv_l = kl_l = lane < m ? (int)shared[lane] : 0;
-                if (swept_cells && m > 0) count_cells(cap_max, 0, (int)shared[32] - 1, shared[33] == 0u);
                 break;
             }
             to_row = true;
@@ -689,11 +656,6 @@ seq_bits_kernel(BatchArgs a, BitsQueueArgs<QUEUES> q, BitsLayout lay, unsigned l
                 wave_lds_sync();
                 if (long_list) list_weights();
             }
-            if (swept_cells) {
-                for (int i = lane; i < n; i += 64)
-                    if (mark8[i] != 0xff) mark8[i] = 0x7f;
-                wave_lds_sync();
-            }
         }
         int value = 0, last = -1, got = 0;  // last: the item that completed the value
         // (a capacity sweep: every capacity is a stage of its own over the whole list)
@@ -713,16 +675,11 @@ seq_bits_kernel(BatchArgs a, BitsQueueArgs<QUEUES> q, BitsLayout lay, unsigned l
                 });
                 if (r == kExcessEmpty && !levels && !caps_sweep && !queues) break;  // every item is placed: the remaining stages stay empty
             }
-            // (a capacity sweep: every capacity is a stage of its own over the whole list)
-            reached = reached && value == C;
-            furthest = max(furthest, last);
             if (share > 1 && !to_row) {
                 if (lane == 0) shared[r == kExcessNot ? 31 : s] = r == kExcessNot ? 1u : (uint32_t)value;
                 if (r == kExcessNot) s = stages;
                 continue;
             }
-            if (swept_cells && r == kExcessDone && (!caps_sweep || s + 1 == stages))
-                count_cells(caps_sweep ? cap_max : C, j, caps_sweep ? furthest : last, !caps_sweep || reached);
         }
         if (r == kExcessNot) {
             // the row's own sweep, over a list in LDS (in the place of the weights); for all capacities of a capacity sweep at once
@@ -770,7 +727,7 @@ seq_bits_kernel(BatchArgs a, BitsQueueArgs<QUEUES> q, BitsLayout lay, unsigned l
                 const int steps = sw.q;
                 if (swept_cells && lane == 0) {
                     // measurement only: C - w + 1 per item the sweep went through
-                    atomicAdd(swept_cells,
+                    atomicAdd(swept_cells + (inst & (kBitsCounters - 1)) * kBitsCounterStride,
                               (unsigned long long)sw.items * (unsigned)(C + 1) - (unsigned long long)(unsigned)l.prefix[sw.items]);
                 }
                 bits_publish<K, NP>(l, rows, lane, C);

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 from paper_2503_16815_amd import workloads as W
-from tests.test_gpu_parity import binding, run  # noqa: F401  (binding is a fixture)
+from tests.test_gpu_parity import assert_same as assert_same_outputs, binding, run  # noqa: F401  (binding is a fixture)
 from tests.test_gpu_schedule import assert_same, simulate
 
 pytestmark = pytest.mark.gpu
@@ -84,3 +84,65 @@ def test_excesses_by_construction(binding, oracle, excess):
             caps.append([int(x[:81].sum()) - excess, 900])
     w = np.array(w, np.int32)
     run(binding, oracle, W._sequential(f"by_construction_{excess}", w, w.copy(), np.array(caps, np.int32)), flags=FLAG)
+
+
+def _swept(binding, kb_or_sb, flags, **limits):
+    """Outputs of one profiled call, the cell-updates that the rows' sweeps evaluated, the kernel's time with profiling on and, by
+    events, without (us, best of ten)."""
+    import torch
+    queues = isinstance(kb_or_sb, W.ScheduleBatch)
+    with binding.DeftKnapsack(max_batch=kb_or_sb.batch, flags=flags, **limits) as h:
+        x = binding.DeviceSchedules(kb_or_sb, h.device) if queues else h.upload(kb_or_sb)
+        call = (lambda: binding.simulate_schedule(h, x)) if queues else (lambda: h.solve_batch(x))
+        plain = profiled = np.inf
+        for _ in range(10):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            call()
+            b.record()
+            torch.cuda.synchronize()
+            plain = min(plain, 1e3 * a.elapsed_time(b))
+        h.set_profiling(True)
+        for _ in range(10):
+            out = call()
+            torch.cuda.synchronize()
+            prof = h.get_profile()
+            profiled = min(profiled, 1e3 * prof.sweep_ms)
+        return out, int(prof.streamed_row_cells), profiled, plain
+
+
+@pytest.mark.parametrize("kind,n,low,high", [
+    ("lognormal", 96, 0.3, 1.0), ("lognormal", 97, 0.05, 0.3), ("lognormal", 300, 0.0, 0.04), ("lognormal", 700, 0.0, 0.01),
+    ("light", 300, 0.0, 0.04), ("jumps", 512, 0.0, 0.03), ("late_light", 300, 0.01, 0.15),    # beyond 63: runs, looked at closely
+    ("heavy", 300, 0.05, 0.3), ("thirds", 300, 0.05, 0.3),                                    # the wide set, or not answered
+    ("two", 300, 0.5, 1.0)])                                                                  # sums that there are few of
+def test_which_way_stages_go(binding, oracle, kind, n, low, high):
+    """By the library's own count: the share of the oracle's cells that the rows' sweeps evaluate."""
+    r = np.random.Generator(np.random.PCG64(51000 + n + 1000 * KINDS.index(kind)))
+    w = _weights(r, kind, 40, n).astype(np.int64)
+    caps = (w.sum(axis=1, keepdims=True) * r.uniform(0.03, 0.6, size=(40, 3))).astype(np.int64).clip(1, 65535)
+    kb = W._sequential(f"which_way_{kind}_{n}", w, w.copy(), caps)
+    ref = oracle.solve_batch(kb, nthreads=16)
+    out, swept, _, _ = _swept(binding, kb, FLAG, max_items=n, max_knapsacks=3, max_capacity=int(caps.max()))
+    assert_same_outputs(kb, out, ref)
+    share = swept / int(ref.touched_cells.sum())
+    print(f"{kind} {n}: {share:.3f}", flush=True)
+    assert low <= share <= high
+
+
+@pytest.mark.parametrize("flags", [0, 1, FLAG])
+def test_paper_shapes_are_answered_without_a_sweep(binding, flags):
+    """The ResNet-101 shapes in every mode: hardly any cell is swept, and counting does not change the kernel's time."""
+    for kb, most in ((W.resnet101_sweep(), 0.01), (W.backward_stage_shaped(), 0.01), (W.inflation_sweep_shaped(), 0.01),
+                     (W.resnet101_schedules(), 0.02)):
+        queues = isinstance(kb, W.ScheduleBatch)
+        if queues:
+            cap, n, m = int(max(kb.backward_time.max(), kb.forward_time.max())), kb.n_buckets, 2
+            cells = float((kb.iterations * np.maximum(0, kb.backward_time[:, None] - kb.comm_time + 1)).sum())
+        else:
+            cap, n, m = int(kb.capacities.max()), kb.item_stride, kb.knap_stride
+            cells = float(np.maximum(0, kb.capacities[:, :1] - kb.weights + 1).sum())
+        _, swept, profiled, plain = _swept(binding, kb, flags, max_items=n, max_knapsacks=m, max_capacity=cap)
+        print(f"{kb.name}: {swept / cells:.4f}, {profiled:.1f} us profiled, {plain:.1f} us", flush=True)
+        assert swept <= most * cells
+        assert profiled < 1.2 * plain + 5
