@@ -20,7 +20,7 @@ constexpr int32_t kMaxCapacity = 1 << 24;
 constexpr int32_t kMaxJointCapacity = 4095;
 constexpr int32_t kMaxIterations = 4096;
 constexpr int32_t kMaxValuesAreWeightsCapacity = 26623;
-constexpr int kBitsWords = kBitsCounters * kBitsCounterStride;
+constexpr int kBitsCounterWords = kBitsCounters * kBitsCounterStride;
 constexpr int32_t kMaxSubsetSumCapacity = 65535;  // the longest bit-set row that is compiled
 
 struct DeviceGuard {
@@ -174,7 +174,7 @@ extern "C" deft_status_t deft_knapsack_create(const deft_knapsack_config_t *cfg,
         } else {
             h->bits_ready = true;
             h->promised = cfg->flags != 0;
-            st = alloc_counter(&h->bits_swept, kBitsWords, &h->scratch_bytes);
+            st = alloc_counter(&h->bits_swept, kBitsCounterWords, &h->scratch_bytes);
         }
     }
     if (st == DEFT_OK && want_seq) {
@@ -434,7 +434,7 @@ extern "C" deft_status_t deft_knapsack_set_profiling(deft_knapsack_t *h, int32_t
     for (unsigned long long *counter : {h->glob_streamed, h->bits_swept, h->lds_swept, h->joint_swept}) {
         if (!counter) continue;
         DeviceGuard g(h->cfg.device);
-        if (!g.ok || hipMemset(counter, 0, counter == h->bits_swept ? kBitsWords * 8 : 8) != hipSuccess) {
+        if (!g.ok || hipMemset(counter, 0, counter == h->bits_swept ? kBitsCounterWords * 8 : 8) != hipSuccess) {
             (void)hipGetLastError();
             return DEFT_ERR_DEVICE;
         }
@@ -453,14 +453,14 @@ extern "C" deft_status_t deft_knapsack_get_profile(deft_knapsack_t *h, deft_knap
     if (rc != DEFT_OK) return rc;
     for (unsigned long long *counter : {h->glob_streamed, h->bits_swept, h->lds_swept, h->joint_swept}) {
         if (!counter) continue;
-        unsigned long long v[kBitsWords] = {};
+        unsigned long long v[kBitsCounterWords] = {};
         const size_t bytes = counter == h->bits_swept ? sizeof(v) : 8;
         if (hipMemcpy(v, counter, bytes, hipMemcpyDeviceToHost) != hipSuccess || hipMemset(counter, 0, bytes) != hipSuccess) {
             (void)hipGetLastError();
             return DEFT_ERR_DEVICE;
         }
         int64_t &sum = counter == h->glob_streamed || counter == h->bits_swept ? out->streamed_row_cells : out->swept_cell_updates;
-        for (int i = 0; i < kBitsWords; i += kBitsCounterStride) sum += (int64_t)v[i];
+        for (int i = 0; i < kBitsCounterWords; i += kBitsCounterStride) sum += (int64_t)v[i];
     }
     return rc;
 }

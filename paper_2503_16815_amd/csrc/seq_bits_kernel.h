@@ -68,8 +68,8 @@ constexpr int bits_grain(int k) { return k <= 7 ? 1 : k <= 14 ? 2 : 4; }
 constexpr int bits_plane_stride(int np) { return np | 1; }  // odd: a lane's planes are spread over the LDS banks
 // Wavefronts per SIMD the register budget is held to: planes, set, and about fifty others.  That leaves out the
 // two shifted words per slot of the item in progress, so most builds beyond five words or six planes
-// spill, some of it in the item loop (7 words, 9 planes: 72 registers, 118 MB of scratch traffic for 4096
-// instances of 314 items; 20 and 9: 359; 32 and 9: 723).  Against the array of cells in LDS these builds are
+// spill, some of it in the item loop (7 words, 9 planes: 62 registers; 20 and 9: 350; 32 and 9: 727; with stages by what
+// they leave out the sweep has a frame of its own, bits_row_function).  Against the array of cells in LDS these builds were
 // quicker all the same, 2048 instances of 300 items in two windows: 20000 cells 0.58 -> 0.087 ms, 40000 cells
 // 2.07 -> 0.32, 65535 cells 5.95 -> 0.66.
 constexpr int bits_waves_per_simd(int k, int np)
@@ -428,6 +428,94 @@ __device__ __forceinline__ int bits_walk(const BitsLds &l, int lane, int G, int 
     return t;
 }
 
+// One stage by the row's sweep and its walk, or walks, over the list in LDS.
+struct BitsStage {
+    int cnt, C, j;  // items listed; the capacity (of a capacity sweep: the largest); the knapsack
+    int m, goal;    // capacity sweep: capacities, and the lane's
+    int levels, caps_sweep;
+};
+struct BitsAnswer {
+    int value;   // of a capacity sweep: the lane's
+    int last;    // Algorithm 1: the item that completed the value (-1: none)
+    int failed;  // (never expected)
+};
+template <int K, int NP>
+__device__ __forceinline__ BitsAnswer bits_row(const BitsLds &l, int lane, const BitsStage &g, unsigned long long *swept_cells)
+{
+    BitsRows<K, NP> rows;
+    BitsAnswer r{0, -1, 0};
+    const BitsSweep sw = bits_sweep<K, NP>(l, rows, lane, g.cnt, g.C, g.caps_sweep != 0, g.goal);
+    const int steps = sw.q;
+    if (swept_cells && lane == 0) {
+        // measurement only: C - w + 1 per item the sweep went through
+        atomicAdd(swept_cells,
+                  (unsigned long long)sw.items * (unsigned)(g.C + 1) - (unsigned long long)(unsigned)l.prefix[sw.items]);
+    }
+    bits_publish<K, NP>(l, rows, lane, g.C);
+    if (!g.caps_sweep) {
+        uint8_t *mark8 = reinterpret_cast<uint8_t *>(l.marks);
+        r.value = sw.reached ? g.C : bits_top<K, NP>(rows, lane, g.C);
+        if (g.levels && r.value > 0) r.last = l.index[min(bits_first<NP>(l.planes, r.value, steps), g.cnt - 1)];
+        r.failed = bits_walk<NP>(l, lane, 64, r.value, g.cnt, steps, [&](int p) { mark8[l.index[p]] = (uint8_t)g.j; }) != 0;
+    } else {
+        // One sweep at the largest capacity answers every capacity: the largest reachable
+        // sum not above it, and the chain from that sum is the selection the DP would walk
+        // back there.  The lanes are dealt out to the capacities in groups, all walks run side
+        // by side, and an item's word collects the capacities at which it is taken.
+        if (lane < g.m) {
+            int wi = g.goal >> 5;
+            uint32_t bits = l.set[wi] & (0xffffffffu >> (31 - (g.goal & 31)));
+            while (bits == 0) bits = l.set[--wi];  // (word 0 holds the empty sum)
+            r.value = wi * 32 + 31 - __builtin_clz(bits);
+        }
+        int G = 64;
+        while (G > 1 && 64 / G < g.m) G >>= 1;
+        const int x = lane / G;  // this group's capacity
+        int t_group = __shfl(r.value, x);
+        if (x >= g.m) t_group = 0;
+        const int left = bits_walk<NP>(l, lane, G, t_group, g.cnt, steps,
+                                       [&](int p) { atomicOr(&l.marks[l.index[p]], 1u << x); });
+        r.failed = __builtin_amdgcn_ballot_w64(left != 0) != 0ull;
+    }
+    bits_release(l, lane);
+    return r;
+}
+
+// The same as a function of its own, for kernels with stages by what they leave out: what the compiler keeps in
+// registers for those it took from the row's sweep, whose item loop spilled twice as much (7 words and 9 planes: 131
+// registers in place of 64).  900 lists of 334 items of which three hold 85 % of the time, windows of 11700 and 5900 cells: 117 us in kernels
+// without those stages, 149 inlined, 94 so; 24000 and 12000: 155, 194 (230 before), 154.  A call saves and restores up
+// to a hundred registers, a microsecond or so: where the sweep fits the registers anyhow it stays inlined (up to 60 words of set and planes:
+// 2013 lists of 150 items in windows of 9000 cells 44 us, 46 by calls; and the task queues, 114 and 127).
+// LDS pointers go as offsets: as generic ones they would be loaded from by flat instructions.
+template <class T>
+__device__ __forceinline__ int bits_lds_offset(T *p)
+{
+    return (int)(uint32_t)(uintptr_t)(__attribute__((address_space(3))) T *)p;
+}
+template <class T>
+__device__ __forceinline__ T *bits_lds_pointer(int offset)
+{
+    return (T *)(__attribute__((address_space(3))) T *)(uintptr_t)(uint32_t)__builtin_amdgcn_readfirstlane(offset);
+}
+template <int K, int NP>
+__device__ __noinline__ BitsAnswer bits_row_function(int set, int prefix, int index, int marks, int planes, int lock, int cnt, int C, int j,
+                                                     int m, int goal, int levels, int caps_sweep, unsigned long long *swept_cells)
+{
+    const auto uniform = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
+    const BitsLds l{bits_lds_pointer<uint32_t>(set), bits_lds_pointer<int32_t>(prefix), bits_lds_pointer<uint16_t>(index),
+                    bits_lds_pointer<uint32_t>(marks), bits_lds_pointer<uint32_t>(planes), bits_lds_pointer<int32_t>(lock)};
+    const BitsStage g{uniform(cnt), uniform(C), uniform(j), uniform(m), goal, uniform(levels), uniform(caps_sweep)};
+    return bits_row<K, NP>(l, threadIdx.x & 63, g, swept_cells);
+}
+template <int K, int NP>
+__device__ __forceinline__ BitsAnswer bits_row_call(const BitsLds &l, const BitsStage &g, unsigned long long *swept_cells)
+{
+    return bits_row_function<K, NP>(bits_lds_offset(l.set), bits_lds_offset(l.prefix), bits_lds_offset(l.index), bits_lds_offset(l.marks),
+                                    bits_lds_offset(l.planes), bits_lds_offset(l.lock), g.cnt, g.C, g.j, g.m, g.goal, g.levels,
+                                    g.caps_sweep, swept_cells);
+}
+
 // The task queues' arguments, of the kernels that solve those.
 struct BitsNoArgs {
     int32_t n_buckets, iterations;
@@ -610,7 +698,6 @@ seq_bits_kernel(BatchArgs a, BitsQueueArgs<QUEUES> q, BitsLayout lay, unsigned l
         if (threadIdx.x == 31) shared[31] = 0;
         __syncthreads();
     }
-    BitsRows<K, NP> rows;
     const int cap_max = caps_sweep ? bits_wave_max(cap_l) : 0;
     const int stages = queues ? 2 * q.iterations : m;
     // Task queues: items and time of the current queue, the iterations that it, the future queue and what is
@@ -723,42 +810,15 @@ seq_bits_kernel(BatchArgs a, BitsQueueArgs<QUEUES> q, BitsLayout lay, unsigned l
                 if (lane < cnt && ((pick >> lane) & 1)) mark8[l.index[lane]] = (uint8_t)j;
                 if (levels) last = l.index[31 - __builtin_clz(pick | 1)];
             } else {
-                const BitsSweep sw = bits_sweep<K, NP>(l, rows, lane, cnt, C, caps_sweep, cap_l);
-                const int steps = sw.q;
-                if (swept_cells && lane == 0) {
-                    // measurement only: C - w + 1 per item the sweep went through
-                    atomicAdd(swept_cells + (inst & (kBitsCounters - 1)) * kBitsCounterStride,
-                              (unsigned long long)sw.items * (unsigned)(C + 1) - (unsigned long long)(unsigned)l.prefix[sw.items]);
-                }
-                bits_publish<K, NP>(l, rows, lane, C);
-                if (!caps_sweep) {
-                    value = sw.reached ? C : bits_top<K, NP>(rows, lane, C);
-                    if (levels && value > 0) last = l.index[min(bits_first<NP>(l.planes, value, steps), cnt - 1)];
-                    const int left = bits_walk<NP>(l, lane, 64, value, cnt, steps, [&](int p) { mark8[l.index[p]] = (uint8_t)j; });
-                    if (left != 0) status = DEFT_ERR_DEVICE;  // (never expected)
-                } else {
-                    // One sweep at the largest capacity answers every capacity: the largest reachable
-                    // sum not above it, and the chain from that sum is the selection the DP would walk
-                    // back there.  The lanes are dealt out to the capacities in groups, all walks run side
-                    // by side, and an item's word collects the capacities at which it is taken.
-                    int t = 0;
-                    if (lane < m) {
-                        int wi = cap_l >> 5;
-                        uint32_t bits = l.set[wi] & (0xffffffffu >> (31 - (cap_l & 31)));
-                        while (bits == 0) bits = l.set[--wi];  // (word 0 holds the empty sum)
-                        t = wi * 32 + 31 - __builtin_clz(bits);
-                    }
-                    kv_l = kl_l = t;
-                    int G = 64;
-                    while (G > 1 && 64 / G < m) G >>= 1;
-                    const int x = lane / G;  // this group's capacity
-                    int t_group = __shfl(t, x);
-                    if (x >= m) t_group = 0;
-                    const int left = bits_walk<NP>(l, lane, G, t_group, cnt, steps,
-                                                   [&](int p) { atomicOr(&l.marks[l.index[p]], 1u << x); });
-                    if (__builtin_amdgcn_ballot_w64(left != 0) != 0ull) status = DEFT_ERR_DEVICE;  // (never expected)
-                }
-                bits_release(l, lane);
+                const BitsStage g{cnt, C, j, m, cap_l, levels, caps_sweep};
+                unsigned long long *counter = swept_cells ? swept_cells + (inst & (kBitsCounters - 1)) * kBitsCounterStride : nullptr;
+                BitsAnswer r;
+                if constexpr (EXCESS && !QUEUES && K * (NP + 1) > 60) r = bits_row_call<K, NP>(l, g, counter);
+                else r = bits_row<K, NP>(l, lane, g, counter);
+                if (caps_sweep) kv_l = kl_l = r.value;
+                else value = r.value;
+                if (levels) last = r.last;
+                if (r.failed) status = DEFT_ERR_DEVICE;  // (never expected)
             }
             wave_lds_sync();
             if (caps_sweep) break;

@@ -146,3 +146,35 @@ def test_paper_shapes_are_answered_without_a_sweep(binding, flags):
         print(f"{kb.name}: {swept / cells:.4f}, {profiled:.1f} us profiled, {plain:.1f} us", flush=True)
         assert swept <= most * cells
         assert profiled < 1.2 * plain + 5
+
+
+def _us_of_lists(binding, weights, caps):
+    import torch
+    kb = W._sequential("lists", weights, weights.copy(), caps)
+    with binding.DeftKnapsack(max_batch=kb.batch, max_items=kb.item_stride, max_knapsacks=kb.knap_stride,
+                              max_capacity=int(caps.max()), flags=FLAG) as h:
+        db = h.upload(kb)
+        best = np.inf
+        for _ in range(12):
+            h.set_profiling(True)
+            h.solve_batch(db)
+            torch.cuda.synchronize()
+            best = min(best, 1e3 * h.get_profile().sweep_ms)
+    return best
+
+
+@pytest.mark.parametrize("cap", [8000, 11700, 17000, 24000, 34000, 58000])
+def test_the_rows_sweep_keeps_its_speed(binding, cap):
+    """Lists of which three items hold most, which the rows sweep: one item more, and so on the kernels that have stages by
+    what they leave out, costs no more than its share and the call (its registers in the sweep: up to 1.58 times as long)."""
+    r = np.random.Generator(np.random.PCG64(54000 + cap))
+    B, n = 900, 97
+    x = r.lognormal(0.0, 0.8, size=(B, n))
+    x[:, 40:43] = 0
+    x *= 0.15 / x.sum(axis=1, keepdims=True)
+    x[:, 40:43] = 0.85 / 3 * r.uniform(0.9, 1.1, size=(B, 3))
+    w = np.maximum(1, np.rint(1.35 * cap * x)).astype(np.int32)
+    caps = np.tile(np.array([[cap, cap // 2] * 2], np.int32), (B, 1))
+    without, with_ = _us_of_lists(binding, w[:, :96].copy(), caps), _us_of_lists(binding, w, caps)
+    print(f"{cap}: 96 items {without:.1f} us, 97 items {with_:.1f} us", flush=True)
+    assert with_ < 1.15 * without
