@@ -679,16 +679,21 @@ seq_bits_kernel(BatchArgs a, BitsQueueArgs<QUEUES> q, BitsLayout lay, unsigned l
         }
     };
     auto list = [&](int i0) { return i0 + lane < n ? l.prefix[i0 + lane] : kGone; };
-    // (Where items heavier than a quarter of the window hold more than half of the time, the excess is mostly out of reach.)
+    // (Where items heavier than a quarter of the window hold more than half of the time, the excess is mostly out of reach, and where
+    // too few items of the list's mean weight fill the window it is not tried.)
     bool long_list = EXCESS && n >= (caps_sweep ? kBitsExcessCapsItems : kBitsExcessItems);
     if (long_list) {
-        const int quarter = bits_wave_max(cap_l) >> 2;
-        int light = 0, heavy = 0;
+        const int most = bits_wave_max(cap_l), quarter = most >> 2;
+        int light = 0, heavy = 0, items = 0;
         chunks([&](int i0, int w, int) {
-            if (i0 + lane < n && w <= quarter) light += w;
-            else if (i0 + lane < n && w <= 4 * quarter + 3) heavy += w;
+            const bool in = i0 + lane < n && w <= most;
+            items += (int)__popcll(__builtin_amdgcn_ballot_w64(in));
+            light += in && w <= quarter ? w : 0;
+            heavy += in && w > quarter ? w : 0;
         });
-        long_list = bits_wave_sum(light) > bits_wave_sum(heavy);
+        light = bits_wave_sum(light);
+        heavy = bits_wave_sum(heavy);
+        long_list = light > heavy && items * most / kExcessFewest >= light + heavy;  // (4096 items of 65535)
     }
     if (long_list) list_weights();
     // Where wavefronts share an instance: [0 .. 30] the values, then whether a capacity is left over (in the place of the
