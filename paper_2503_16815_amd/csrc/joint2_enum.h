@@ -112,7 +112,7 @@ struct EnumShared {
     EnumResult result[kEnumWaves];
     unsigned long long default_lo, default_hi;
     unsigned long long flip_lo[3][32], flip_hi[3][32];  // what a mask bit changes of them
-    int32_t over, least;                      // least: what the best selection met so far loses
+    int32_t over, late, least;                // least: what the best selection met so far loses
     uint32_t q_mask, pair;
 };
 
@@ -184,7 +184,7 @@ __device__ __forceinline__ void jt_enumerate(const BatchArgs &a, int inst, State
     if (tid < 4) s.sum[tid] = 0;
     if (tid < 2) s.most[tid] = 0;
     if (tid < kEnumRounds) s.threshold[tid] = kNever;
-    if (tid == 0) s.over = 0, s.least = s.unlisted = kNever;
+    if (tid == 0) s.over = s.late = 0, s.least = s.unlisted = kNever;
     __syncthreads();
     const int waves_used = (n + 63) >> 6;
     if (wave < waves_used) {
@@ -423,6 +423,15 @@ __device__ __forceinline__ void jt_enumerate(const BatchArgs &a, int inst, State
     const int share = 2 * a.batch <= kEnumComputeUnits ? 60 : alike > kEnumAlike ? 12 : 50;
     const long long deadline = began + sweep_ticks * share / 100;
     long long look = began + sweep_ticks / 2;                   // (it does not before)
+    // Looked at wherever a list begins (a part, a round) and by every wavefront for 64 pairs looked up: a part whose pairs are
+    // all passed over takes up to 60 us, and there are up to 81.  (Looked at for pairs alone, attempts of 392 of 600 kinds of calls ended
+    // late, by up to 13.7 ms where they were allowed 0.23.)
+    auto late = [&]() {
+        const long long now = wall_clock64();
+        if (now <= look) return now > deadline;
+        look = now + kLookTicks;
+        return now > deadline || __hip_atomic_load(&solved[inst], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+    };
     const int group = wave < 10 ? 0 : wave < 13 ? 1 : 2;        // the list that this wavefront makes
     const int first_wave = group == 0 ? 0 : group == 1 ? 10 : 13, list_waves = group == 0 ? 10 : 3;
     const int limit = group == 0 ? kListQ : group == 1 ? kListP1 : kListP2;
@@ -502,7 +511,9 @@ __device__ __forceinline__ void jt_enumerate(const BatchArgs &a, int inst, State
             }
             part_loss = __builtin_amdgcn_readfirstlane(part_loss);
             const bool first_turn = pass == 0 && part == 0;
-            if (part_loss <= G && (pass == 0 || turns > 1)) {
+            // No selection counts that loses more than the best one met so far, by this part or one before.
+            const int cut = __builtin_amdgcn_readfirstlane(min(G, s.least));
+            if (part_loss <= cut && (pass == 0 || turns > 1)) {
                 int have = 1, place = count - 1;
                 // One item into the list, by `waves` wavefronts of which this is number `w`: entries [0, have) are followed
                 // by what they make with the item's departures.  to(more) is where this wavefront's go.
@@ -510,12 +521,12 @@ __device__ __forceinline__ void jt_enumerate(const BatchArgs &a, int inst, State
                     const int loss1 = __builtin_amdgcn_readlane(first_l, p), loss2 = __builtin_amdgcn_readlane(second_l, p);
                     const int use1 = __builtin_amdgcn_readlane(first_u, p), use2 = __builtin_amdgcn_readlane(second_u, p);
                     const int bit2 = __builtin_amdgcn_readlane(second_b, p);
-                    const bool twice = loss2 <= G;
+                    const bool twice = loss2 <= cut;
                     for (int base = w * 64; base < have; base += waves * 64) {
                         const int e = base + lane;
                         const int loss = e < have ? l_loss[e] : kNever, use = e < have ? l_use[e] : 0;
                         const uint32_t mask = e < have ? l_mask[e] : 0;
-                        const bool one = loss <= G - loss1, two = twice && loss <= G - loss2;
+                        const bool one = loss <= cut - loss1, two = twice && loss <= cut - loss2;
                         const unsigned long long ones = __ballot(one), twos = __ballot(two);
                         const int at = to(__popcll(ones) + __popcll(twos));
                         const int at1 = at + enum_below(ones, lane), at2 = at + __popcll(ones) + enum_below(twos, lane);
@@ -573,8 +584,9 @@ __device__ __forceinline__ void jt_enumerate(const BatchArgs &a, int inst, State
                     }
                 }
                 for (int i = tid; i < kEnumOpen * 3; i += kEnumThreads) s.appended[i / 3][i % 3] = 0;
+                if (tid == kEnumThreads - 1) s.late = late() ? 1 : 0;  // (of a wavefront that makes no short list)
                 __syncthreads();
-                if (s.over) return;
+                if (s.over | s.late) return;
                 int steps = 0;
                 bool over = false;
         #pragma unroll
@@ -741,7 +753,7 @@ __device__ __forceinline__ void jt_enumerate(const BatchArgs &a, int inst, State
                 }
                 __syncthreads();
             }
-            if (part_loss <= G) {
+            if (part_loss <= cut) {
                 int queued = 0;
                 // a tile: sixteen of P1, one after the other, with 64 of P2
                 int first1 = 0, chunk = wave, x = 16, i2 = 0, left0_2 = 0, left1_2 = 0, a1 = 0, b1 = 0, spare2 = 0, loss1 = 0;
@@ -831,12 +843,7 @@ __device__ __forceinline__ void jt_enumerate(const BatchArgs &a, int inst, State
                             }
                         }
                     }
-                    const long long now = wall_clock64();
-                    if (now > deadline) s.over = 1;
-                    if (now > look) {
-                        look = now + kLookTicks;
-                        if (__hip_atomic_load(&solved[inst], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) s.over = 1;
-                    }
+                    if (late()) s.over = 1;
                     if (__builtin_amdgcn_readfirstlane(*(volatile int32_t *)&s.over)) break;
                 }
                 if (pass == 0 && best <= known) atomicMin(&s.least, best);
