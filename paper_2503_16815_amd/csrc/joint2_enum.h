@@ -464,6 +464,9 @@ __device__ __forceinline__ void jt_enumerate(const BatchArgs &a, int inst, State
         auto retry = [&](bool q_over) {  // a list has run over: in smaller steps, other groups, or Q in parts
             if (leap) {
                 may_leap = false;
+            } else if (split > 0 && alike > kEnumAlike) {
+                // (solved late if at all; by parts none was, and 32 instances of 39 items at 103 x 316 took 0.92 ms, 0.71 so)
+                if (tid == 0) s.over = 1;
             } else if (split == 0 || (!q_over && split < 3)) {
                 ++split;
                 branches = split == 1 ? 0 : max(branches, 1);
