@@ -192,3 +192,21 @@ def test_lists_too_heavy_for_the_excess_are_swept_at_once(binding, cap):
     without, with_ = _us_of_lists(binding, w[:, :96].copy(), caps), _us_of_lists(binding, w, caps)
     print(f"{cap}: 96 items {without:.1f} us, 97 items {with_:.1f} us", flush=True)
     assert with_ < 1.11 * without
+
+
+@pytest.mark.parametrize("cap,limit", [(8000, 42), (11700, 46)])
+def test_a_hopeless_excess_is_left_soon(binding, oracle, cap, limit):
+    """Of 1500 lists of 140 items a few end on an item of half of the window: not looked for at length (us as measured: 36 and 40;
+    with all that there is 50 and 51, in kernels without stages by excess 32 and 39)."""
+    B, n = 1500, 140
+    r = np.random.Generator(np.random.PCG64(7))
+    x = r.lognormal(0.0, 1.2, size=(B, n))
+    w = np.maximum(1, np.rint(x * ((1.8 * cap + n) / x.sum(axis=1, keepdims=True)))).astype(np.int32)
+    back = np.rint(cap * r.uniform(0.9, 1.1, size=B)).astype(np.int32)
+    kb = W.KnapsackBatch(name="hopeless", mode=W.MODE_RECURSIVE, batch=B, item_stride=n, knap_stride=2, n_items=np.full(B, n, np.int32),
+                         n_knapsacks=np.ones(B, np.int32), weights=w, values=w.copy(), capacities=np.stack([back, 0 * back], axis=1),
+                         fill_order=None, drop_time=np.rint(w / w.sum(axis=1, keepdims=True) * back[:, None]).astype(np.int32))
+    out, _, took, _ = _swept(binding, kb, FLAG, max_items=n, max_knapsacks=2, max_capacity=int(back.max()))
+    print(f"{cap}: {took:.1f} us", flush=True)
+    assert_same_outputs(kb, out, oracle.solve_batch(kb, nthreads=16))
+    assert took < limit
