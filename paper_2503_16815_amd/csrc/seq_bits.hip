@@ -17,6 +17,8 @@ BitsLayout bits_layout(const SeqBitsPlan &p, bool caps_sweep)
     lay.mark_words = caps_sweep ? p.n_pad : p.n_pad / 4;
     lay.plane_words = p.row_words * bits_plane_stride(p.planes);
     lay.share = 1;
+    lay.fewest = lay.sure = kBitsExcessItems;
+    lay.light = 0;
     lay.wave_words = 2 * p.row_words + 4 + (p.n_pad + 8) + p.n_pad / 2 + lay.mark_words;
     return lay;
 }
@@ -26,18 +28,15 @@ int64_t bits_lds_bytes(const BitsLayout &lay, int waves)
     return ((int64_t)4 + lay.plane_words + (int64_t)waves * lay.wave_words) * 4;
 }
 
-// The planes that a call's lists of up to `items` need (index in kBitsPlanes).  By the call and not by the handle, whose lists
-// may be longer elsewhere: planes cost registers and LDS, and stages by what they leave out cost the row's sweep its
-// registers where they are never tried.  8192 instances on a handle for 314 items, us with the handle's kernel and the call's: 80 items
+// The planes that a call's lists of up to `items` need (index in kBitsPlanes); `fewest`: from so many on, stages by what they
+// leave out.  By the call and not by the handle, whose lists may be longer elsewhere: planes cost registers and LDS, and those
+// stages cost the row's sweep its registers where they are never tried.  8192 instances on a handle for 314 items, us with the handle's kernel and the call's: 80 items
 // SEQUENTIAL 121 and 94, RECURSIVE 96 and 68, CAPACITY_SWEEP 106 and 80; 38 items 61 and 43; a sweep of 128 items 130 and 102.
-int bits_which(int items, bool caps_sweep)
-{
-    return items <= 64 ? 0 : items < (caps_sweep ? kBitsExcessCapsItems : kBitsExcessItems) ? 1 : items <= 512 ? 2 : 3;
-}
+int bits_which(int items, int fewest) { return items <= 64 ? 0 : items > 512 ? 3 : items < fewest ? 1 : 2; }
 
-void bits_lists(SeqBitsPlan *p, int items, bool caps_sweep)
+void bits_lists(SeqBitsPlan *p, int items, int fewest)
 {
-    const int which = bits_which(items, caps_sweep);
+    const int which = bits_which(items, fewest);
     p->variant = p->variant / 4 * 4 + which;
     p->planes = kBitsPlanes[which];
     p->n_pad = (items + 7) & ~7;
@@ -68,7 +67,7 @@ bool seq_bits_plan(int32_t max_capacity, int32_t max_items, int32_t lds_per_wg_b
         const int grain = bits_grain(K);
         p->variant = 4 * i;
         p->words_per_lane = K;
-        bits_lists(p, max_items, false);
+        bits_lists(p, max_items, kBitsExcessItems);
         p->row_words = (max_capacity / 2048 + grain) / grain * grain * 64;
         p->lds_limit = lds_per_wg_bytes - 256;
         p->compute_units = compute_units;
@@ -96,20 +95,35 @@ namespace {
 template <bool QUEUES>
 hipError_t bits_launch(SeqBitsPlan p, const BatchArgs &a, const BitsQueueArgs<QUEUES> &q, hipStream_t st, unsigned long long *swept_cells)
 {
-    bits_lists(&p, a.item_stride, a.mode == DEFT_MODE_CAPACITY_SWEEP);
-    const auto kernel = reinterpret_cast<BitsKernel<QUEUES>>(const_cast<void *>(bits_kernel(p, QUEUES)));
-    BitsLayout lay = bits_layout(p, a.mode == DEFT_MODE_CAPACITY_SWEEP);
-    // A capacity sweep of lists that are answered capacity by capacity: as many wavefronts an instance, up to four, as the
-    // whole batch leaves room for.  1024 instances of 314 items and eleven capacities: one 79 us, three 38.
-    if (a.mode == DEFT_MODE_CAPACITY_SWEEP && a.item_stride >= kBitsExcessCapsItems) {
-        const int64_t lds = bits_lds_bytes(lay, 1);
-        for (int share = 4; share > 1; --share) {
-            const int by_lds = kLdsGranulesPerCu / (int)((lds + kLdsGranule - 1) / kLdsGranule);
+    const bool caps_sweep = a.mode == DEFT_MODE_CAPACITY_SWEEP;
+    bits_lists(&p, a.item_stride, kBitsExcessItems);
+    BitsLayout lay = bits_layout(p, caps_sweep);
+    const auto launch = [&](unsigned blocks, int waves) {
+        const auto kernel = reinterpret_cast<BitsKernel<QUEUES>>(const_cast<void *>(bits_kernel(p, QUEUES)));
+        const size_t lds = (size_t)bits_lds_bytes(lay, lay.share > 1 ? 1 : waves);
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(64 * waves), lds, st, a, q, lay, swept_cells);
+        return hipGetLastError();
+    };
+    if (caps_sweep && a.item_stride >= kBitsExcessItems) {
+        // Lists that are answered capacity by capacity: as many wavefronts an instance, up to four, as the whole batch leaves
+        // room for.  1024 instances of 314 items and eleven capacities: one 79 us, three 38.
+        const int by_lds = kLdsGranulesPerCu / (int)((bits_lds_bytes(lay, 1) + kLdsGranule - 1) / kLdsGranule);
+        int share = a.knap_stride < 4 ? a.knap_stride : 4;
+        for (; share > 1; --share) {
             const int by_regs = 4 * bits_waves_per_simd(p.words_per_lane, p.planes) / share;
-            if (share > a.knap_stride || (int64_t)(by_lds < by_regs ? by_lds : by_regs) * p.compute_units < a.batch) continue;
+            if ((int64_t)(by_lds < by_regs ? by_lds : by_regs) * p.compute_units >= a.batch) break;
+        }
+        const BitsExcessCaps by = bits_excess_caps((a.knap_stride + share - 1) / share, p.words_per_lane);
+        lay.fewest = by.fewest;
+        lay.sure = by.sure;
+        lay.light = by.light;
+        if (a.item_stride >= by.fewest && share > 1) {
             lay.share = share;
-            hipLaunchKernelGGL(kernel, dim3((unsigned)a.batch), dim3(64 * share), (size_t)lds, st, a, q, lay, swept_cells);
-            return hipGetLastError();
+            return launch((unsigned)a.batch, share);
+        }
+        if (a.item_stride < by.fewest) {
+            bits_lists(&p, a.item_stride, by.fewest);
+            lay = bits_layout(p, caps_sweep);
         }
     }
     // Instances per workgroup: they share one copy of the walk's planes, the largest part of an
@@ -122,10 +136,7 @@ hipError_t bits_launch(SeqBitsPlan p, const BatchArgs &a, const BitsQueueArgs<QU
         if (held > most) most = held, waves = w;
         if ((int64_t)held * p.compute_units >= a.batch) break;
     }
-    const size_t lds = (size_t)bits_lds_bytes(lay, waves);
-    const unsigned grid = (unsigned)((a.batch + waves - 1) / waves);
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * waves), lds, st, a, q, lay, swept_cells);
-    return hipGetLastError();
+    return launch((unsigned)((a.batch + waves - 1) / waves), waves);
 }
 
 }  // namespace

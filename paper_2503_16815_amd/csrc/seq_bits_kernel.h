@@ -56,11 +56,26 @@ namespace deft {
 
 namespace {
 
-// Shorter lists are swept at once (81 items, 1735 of them: by what their stages leave out 27.4 -> 36 us; 93 items 13.9 -> 16.7), and
-// so are capacity sweeps of fewer than 129 items: one capacity that is not answered by itself sends the others along (101
-// items, nine of them with eight capacities: 18.8 -> 26.7).  Calls of shorter lists run on kernels without it, whose sweep
-// has the registers (66 items: 17.7 against 20.8 us).
-constexpr int kBitsExcessItems = 97, kBitsExcessCapsItems = 129;
+// Shorter lists are swept at once (81 items, 1735 of them: by what their stages leave out 27.4 -> 36 us; 93 items 13.9 -> 16.7).
+// Calls of shorter lists run on kernels without it, whose sweep has the registers (66 items: 17.7 against 20.8 us).
+constexpr int kBitsExcessItems = 97;
+// In a capacity sweep one sweep answers all capacities, and one capacity that is not answered by itself sends the others
+// along, which takes both.  What pays goes by the items, the capacities a wavefront has in turn, the words of a row, and the
+// items of up to 32 that the lowest sums are made of: lists of `fewest` items are tried if they have `light` of those, lists of
+// `sure` items in any case.  Time by kernels without stages by what they leave out = 1 (eleven capacities, lognormal times,
+// sigma 0.7 to 1.2): up to three capacities in turn, rows of up to 7 words 130 items 0.55 to 1.12, 160 0.42 to 0.97; 10 words 130
+// items 0.90 and 1.48, 160 0.38 to 0.93; 14 and 20 words 160 items 0.42 to 1.40, 200 0.24 to 0.99.  More of them: up to 5 words 160 items
+// 0.85 to 1.59, 200 0.82 to 1.43, 250 0.57 to 0.86; 7 words and more with some 20 to 38 light items 1.01 to 2.23, with 48 to 90 0.38 to
+// 1.04.  Over 381 calls (130 to 450 items, 5 to 6000 lists) 0.60 in the geometric mean, 19 slower by 5 % or more, up to 1.38 times; from 129 items on
+// in any case 0.66, 103 and 2.3; with 28 and 40 light items 27 and 17 slower, and 25 and 35 slower than so.
+struct BitsExcessCaps {
+    int fewest, sure, light;
+};
+constexpr BitsExcessCaps bits_excess_caps(int capacities, int words)
+{
+    const int few = 129 + 12 * (words > 7 ? words - 7 : 0);
+    return capacities <= 3 ? BitsExcessCaps{129, few < 200 ? few : 200, 32} : words < 7 ? BitsExcessCaps{225, 225, 0} : BitsExcessCaps{160, 300, 36};
+}
 constexpr int kBitsEnumItems = 6;  // stages offered at most this many items are settled by enumeration
 
 // words-per-lane counts are compiled for; a block of items works on a multiple of bits_grain(K) slots
@@ -146,6 +161,7 @@ namespace {
 // [zeros: row_words][set: row_words][pad: 4][prefix: n_pad + 8][index: n_pad / 2][marks: mark_words].
 struct BitsLayout {
     int32_t row_words, n_pad, mark_words, plane_words, wave_words;
+    int32_t fewest, sure, light;  // items of a list whose stages are tried by what they leave out: if so many are light, and in any case
     int32_t share;  // wavefronts of an instance (capacity sweep; else 1): they share its part, and deal its capacities out
 };
 // One instance's share of it.
@@ -681,19 +697,20 @@ seq_bits_kernel(BatchArgs a, BitsQueueArgs<QUEUES> q, BitsLayout lay, unsigned l
     auto list = [&](int i0) { return i0 + lane < n ? l.prefix[i0 + lane] : kGone; };
     // (Where items heavier than a quarter of the window hold more than half of the time, the excess is mostly out of reach, and where
     // too few items of the list's mean weight fill the window it is not tried.)
-    bool long_list = EXCESS && n >= (caps_sweep ? kBitsExcessCapsItems : kBitsExcessItems);
+    bool long_list = EXCESS && n >= lay.fewest;
     if (long_list) {
         const int most = bits_wave_max(cap_l), quarter = most >> 2;
-        int light = 0, heavy = 0, items = 0;
+        int light = 0, heavy = 0, items = 0, tiny = 0;
         chunks([&](int i0, int w, int) {
             const bool in = i0 + lane < n && w <= most;
             items += (int)__popcll(__builtin_amdgcn_ballot_w64(in));
+            tiny += (int)__popcll(__builtin_amdgcn_ballot_w64(in && w <= 32));
             light += in && w <= quarter ? w : 0;
             heavy += in && w > quarter ? w : 0;
         });
         light = bits_wave_sum(light);
         heavy = bits_wave_sum(heavy);
-        long_list = light > heavy && items * most / kExcessFewest >= light + heavy;  // (4096 items of 65535)
+        long_list = light > heavy && items * most / kExcessFewest >= light + heavy && (n >= lay.sure || tiny >= lay.light);  // (4096 items of 65535)
     }
     if (long_list) list_weights();
     // Where wavefronts share an instance: [0 .. 30] the values, then whether a capacity is left over (in the place of the
