@@ -3,13 +3,15 @@
 
 A step is one pass of the whole hot path (validation, every stage's DP sweep,
 keep-table stream, traceback, outputs) over one synthetic batch resident in
-HBM.  Prints ONE JSON line: DP cell-updates/s (the cells that the sweeps go
+HBM.  Prints ONE JSON line on stdout: DP cell-updates/s (the cells that the sweeps go
 through, or would where a stage is answered without one, which the line says;
 the job's count as the CPU oracle performs it is beside it),
 instances/s, the LDS roofline of the sweep kernel from HIP events on the launch
 stream, and the CPU oracle timed on this machine's host cores.  The default run
 (ResNet-101 shape) also measures, in the same process, every other
-configuration (`per_config`) and the device's LDS / HBM rates (`peaks`).
+configuration, of which that line has the times, and the device's LDS / HBM rates.
+The whole record, with each configuration's own line (`per_config`) and the rates
+(`peaks`), goes to stderr as a second JSON line.
 """
 from __future__ import annotations
 
@@ -528,6 +530,34 @@ def compact(line: dict) -> dict:
     return out
 
 
+LINE_CHARS = 1900   # of the line on stdout: short enough to be read from the end of a log
+
+
+def summary(line: dict) -> dict:
+    """The record that goes to stdout: what was measured and on what, without the long texts."""
+    pick = lambda d, keys: {k: d[k] for k in keys if k in d}  # noqa: E731
+    short = lambda x: float(f"{x:.5g}") if isinstance(x, float) else x  # noqa: E731
+    out = pick(line, ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline",
+                      "dtype", "data"))
+    out["config"] = pick(line["config"], ("workload", "instances_per_step", "candidates_per_step", "cell_updates_per_step",
+                                          "cell_updates_swept_per_step"))
+    out["config"]["value_counts"] = ("cells of the sweeps that answers stand for"
+                                     if line["roofline"]["bound"] == "latency" else "cells swept")
+    for key in ("instances_per_s", "candidate_iterations_per_s", "effective_cell_updates_per_s", "parity_vs_oracle",
+                "parity_vs_oracle_every_config"):
+        if key in line:
+            out[key] = short(line[key])
+    out["roofline"] = {k: short(v) for k, v in pick(line["roofline"], (
+        "bound", "kernel", "achieved", "peak", "unit", "frac", "traffic", "avg_launch_ms", "cells_left_to_the_sweep_per_step")).items()}
+    if line.get("cpu_baseline"):
+        out["cpu_baseline"] = {k: short(v) for k, v in pick(line["cpu_baseline"], ("value", "unit", "cores", "kind", "sample")).items()}
+        if "single_thread" in line["cpu_baseline"]:
+            out["cpu_baseline"]["single_thread_value"] = short(line["cpu_baseline"]["single_thread"]["value"])
+    if "per_config" in line:
+        out["ms_per_step_of"] = {k: float(f"{v['ms_per_step']:.4g}") for k, v in line["per_config"].items()}
+    return out
+
+
 def measured_peaks() -> dict:
     """Nominal peaks used for the rooflines beside what the library's calibration kernels reach
     on this device (LDS: the sweep's access mix; HBM: a 1 GiB copy)."""
@@ -621,7 +651,8 @@ def main() -> int:
         line["per_config"] = per_config
         line["parity_vs_oracle_every_config"] = bool(parity)
         line["peaks"] = measured_peaks()
-    print(json.dumps(line))
+    print(json.dumps(line), file=sys.stderr)
+    print(json.dumps(summary(line)))
     return 0 if parity else 3
 
 

@@ -56,3 +56,31 @@ def test_counts_never_exceed_the_oracles(oracle):
     r = oracle.solve_batch(kb)
     settled, full = bench.cells_not_swept(kb, r, True)
     assert 0 < settled and 0 <= full and settled + full < int(r.touched_cells.sum())
+
+
+def test_the_line_is_short_enough_to_be_read_from_a_log(oracle):
+    """The record on stdout has what the run is judged by and stays within its length with every configuration in it."""
+    import json
+    names = ("tiny", "resnet101_one_call_per_k", "vgg19", "gpt2", "hetero", "backward", "inflation", "schedule")
+    names += tuple(f"{n}_{kind}" for kind in ("promised", "bitset")
+                   for n in ("resnet101", "resnet101_one_call_per_k", "vgg19", "backward", "inflation", "schedule"))
+    third = 1.0 / 3
+    text = "x" * 160
+    line = dict(metric="knapsack DP cell-updates/sec", value=2.4e14 + third, unit="cell-updates/s", n_gpus=1, steps=20, warmup=5, ms_per_step=third,
+                higher_is_better=True, scaling="weak", vs_baseline=None, dtype="int32", data="synthetic",
+                config=dict(workload=text, value_counts=text, instances_per_step=4096, cell_updates_per_step=22347957584,
+                            cell_updates_swept_per_step=9617333988, seq_path=2),
+                effective_cell_updates_per_s=5.6e14 + third, instances_per_s=1e8 + third, parity_vs_oracle=True,
+                parity_vs_oracle_every_config=True, profile=dict(total_ms_per_step=third, sweep_ms_per_step=third),
+                roofline=dict(bound="latency", achieved=1e4 + third, peak=78643.2, unit="GB/s", frac=third, traffic=third, traffic_source=text,
+                              kernel="seq_bits_kernel", launches=20, avg_launch_ms=third, cells_left_to_the_sweep_per_step=10 ** 10),
+                cpu_baseline=dict(value=5.4e10 + third, unit="cell-updates/s", cores=16, kind="oracle", sample=text,
+                                  single_thread=dict(value=4.1e9 + third, sample=text)),
+                per_config={n: dict(ms_per_step=third, value=third) for n in names}, peaks=dict(nominal=text))
+    out = bench.summary(line)
+    assert len(json.dumps(out)) <= bench.LINE_CHARS
+    for key in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline", "dtype",
+                "data", "config", "roofline", "cpu_baseline", "parity_vs_oracle_every_config"):
+        assert key in out
+    assert out["value"] == line["value"] and out["ms_per_step"] == line["ms_per_step"]
+    assert set(out["ms_per_step_of"]) == set(names)
