@@ -153,9 +153,7 @@ deft_status_t deft_knapsack_create(const deft_knapsack_config_t *cfg, deft_knaps
  * with a larger knapsack capacity, up to ten times):
  *   SEQUENTIAL layout, but capacities[b][0 .. n_knapsacks-1] are capacities of ONE knapsack,
  *   in any order; each is Problem 1 over the whole item list, solved exactly as a
- *   SEQUENTIAL stage (same tie rule).  One DP sweep at the largest capacity answers all of
- *   them: the value at capacity c is cell c of the final row and the selection is walked
- *   back from (last item, c).  n_knapsacks <= 31.
+ *   SEQUENTIAL stage (same tie rule).  n_knapsacks <= 31.
  *     knap_value[j], knap_load[j]  value and weight scheduled at capacities[b][j]
  *     assignment[i]                bit j set iff item i is scheduled at capacities[b][j]
  *                                  (0 = nowhere; also for slots >= n_items and faulted
@@ -265,9 +263,11 @@ deft_status_t deft_knapsack_solve_batch(deft_knapsack_t *h, const deft_knapsack_
  *   status      [batch]                 INVALID_ARG (time < 1, drop time < 0, window < 0),
  *                                       LIMIT (window above max_capacity), OVERFLOW; such a
  *                                       candidate's other outputs are 0
- * The call enqueues everything on `stream` and returns: one launch where max_capacity is at
- * most 65535.  Beyond that its first use on a handle allocates the queue state (sized for
- * max_batch x max_items; OOM if that fails).
+ * The call enqueues everything on `stream` and returns.  Where lists of max_items fit a
+ * compute unit's LDS beside a row of max_capacity bits it is one launch and nothing is
+ * allocated: max_capacity up to 65535 and, from 57344 on, max_items up to 4064.  Beyond that
+ * the first use on a handle allocates the queue state (sized for max_batch x max_items; OOM
+ * if that fails).
  * Host-side errors: INVALID_ARG (NULL, batch < 0, n_buckets < 1, iterations < 1), LIMIT
  * (above the create-time limits, iterations > 4096, max_knapsacks < 2, max_capacity == 0),
  * DEVICE.
