@@ -227,3 +227,54 @@ def test_capacity_sweeps_by_the_quicker_way(binding, oracle, n, batch, sigma, li
     print(f"{n} items, {batch}: {took:.1f} us, {swept} cells swept", flush=True)
     assert_same_outputs(kb, out, oracle.solve_batch(kb, nthreads=16))
     assert took < limit
+
+
+@pytest.mark.parametrize("n,m,batch,max_capacity", [
+    (300, 1, 40, 14000), (300, 2, 40, 14000), (300, 3, 24, 30000),       # one to three wavefronts an instance
+    (314, 11, 70, 14000), (314, 11, 900, 14000), (314, 11, 1500, 14000), (314, 5, 2500, 9000),   # four, and as few as the batch leaves room for
+    (320, 4, 300, 65535),                                                # one, several instances sharing the planes
+    (700, 11, 30, 14000), (700, 2, 300, 65535), (513, 31, 9, 30000),     # lists beyond 512 items
+    (128, 3, 9, 14000), (129, 3, 9, 14000), (159, 11, 3000, 9000), (160, 11, 3000, 9000), (224, 11, 3000, 4000), (225, 11, 3000, 4000)])
+def test_capacity_sweeps_dealt_out(binding, oracle, n, m, batch, max_capacity):
+    """Some capacities answered by themselves before one sends the instance to the row; short lists beside long ones."""
+    r = np.random.Generator(np.random.PCG64(57000 + n + 100 * m + batch))
+    w = np.concatenate([_weights(r, kind, -(-batch // 4), n) for kind in ("lognormal", "thirds", "heavy", "late_light")])[:batch]
+    r.shuffle(w)
+    w = np.minimum(w, max_capacity).astype(np.int32)
+    n_items = np.where(r.random(batch) < 0.3, r.integers(1, n + 1, size=batch), n).astype(np.int32)
+    caps = (w.sum(axis=1, keepdims=True) * r.uniform(0.05, 0.6, size=(batch, 1)) * (1 + 0.05 * np.arange(m)[None, :])).astype(np.int64)
+    caps = r.permuted(caps.clip(0, max_capacity), axis=1).astype(np.int32)
+    n_caps = np.where(r.random(batch) < 0.2, r.integers(0, m + 1, size=batch), m).astype(np.int32)
+    kb = W.KnapsackBatch(name=f"dealt_out_{n}_{m}", mode=W.MODE_CAPACITY_SWEEP, batch=batch, item_stride=n, knap_stride=m, n_items=n_items,
+                         n_knapsacks=n_caps, weights=w, values=w.copy(), capacities=caps, fill_order=None, drop_time=None)
+    run(binding, oracle, kb, max_capacity=max_capacity, flags=FLAG)
+
+
+@pytest.mark.parametrize("cap", [9000, 20000, 30000, 60000])
+@pytest.mark.parametrize("n", [40, 90, 97, 150, 600])
+def test_queues_of_every_kernel(binding, oracle, n, cap):
+    """Windows of the longer rows, lists of each plane count, with and without stages by what they leave out."""
+    r = np.random.Generator(np.random.PCG64(58000 + n + cap))
+    batch = 12 if n < 600 else 5
+    w = np.maximum(1, np.rint(r.lognormal(0.0, 1.1, size=(batch, n)))).astype(np.float64)
+    w = np.maximum(1, np.rint(w * (1.7 * cap / w.sum(axis=1, keepdims=True)))).astype(np.int32)
+    back = np.rint(cap * r.uniform(0.7, 1.0, size=batch)).astype(np.int32)
+    sb = W.ScheduleBatch(name=f"queues_{n}_{cap}", batch=batch, n_buckets=n, iterations=4, comm_time=w,
+                         drop_time=np.rint(w * 0.5).astype(np.int32), forward_time=(back * 0.45).astype(np.int32), backward_time=back)
+    assert_same(simulate(binding, sb, cap), oracle.simulate_batch(sb, cap_limit=cap, nthreads=16))
+
+
+@pytest.mark.parametrize("max_items", [4064, 4065])
+def test_queues_around_the_longest_lists_beside_a_row(binding, oracle, max_items):
+    """One launch, and beyond that stage by stage with queue state in global memory, on a handle's first call and the next."""
+    import torch
+    sb = W.random_schedules(59000, batch=7, n=40, iterations=5, w_hi=5000, t_hi=900, f_hi=25000, b_hi=60000)
+    want = oracle.simulate_batch(sb, cap_limit=60000, nthreads=7)
+    with binding.DeftKnapsack(max_batch=7, max_items=max_items, max_knapsacks=2, max_capacity=60000) as h:
+        ds = binding.DeviceSchedules(sb, h.device)
+        before = h.info().scratch_bytes
+        for _ in range(2):
+            out = binding.simulate_schedule(h, ds)
+            torch.cuda.synchronize()
+            assert_same({k: getattr(out, k).cpu().numpy() for k in ("stage_case", "stage_count", "stage_time", "update_k", "tail", "status")}, want)
+        assert (h.info().scratch_bytes == before) == (max_items == 4064)

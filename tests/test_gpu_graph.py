@@ -60,3 +60,46 @@ def test_two_handles_on_two_streams_at_once(binding, oracle):
         sg.synchronize()
         assert_same(ka, oa, ra)
         assert_same(kg, og, rg)
+
+
+def test_subset_sum_stages_and_queues_replayed_from_a_graph(binding, oracle):
+    """Lists of 600 items on the longest bit-set rows: stages without a sweep, stages of heavy lists that are swept by a function
+    with a frame in scratch memory, and the task queues, each in a graph."""
+    import torch
+    from tests.test_gpu_schedule import FIELDS, assert_same as assert_same_schedule
+    r = np.random.Generator(np.random.PCG64(5200))
+    batches = []
+    for kind in range(3):
+        x = r.lognormal(0.0, 1.0, size=(24, 600))
+        if kind:
+            x[::kind, 100:103] = 1.7 * x.sum(axis=1)[::kind, None]      # three items hold most: swept
+        w = np.maximum(1, np.rint(x * (90000 / x.sum(axis=1, keepdims=True)))).astype(np.int32)
+        batches.append(W._sequential(f"graph_{kind}", w, w.copy(), np.tile(np.array([[60000, 25000]], np.int32), (24, 1))))
+    refs = [oracle.solve_batch(kb, nthreads=16) for kb in batches]
+    sb = [W.random_schedules(5300 + s, batch=9, n=150, iterations=4, w_hi=300, t_hi=100, f_hi=8000, b_hi=18000) for s in range(2)]
+    want = [oracle.simulate_batch(s, cap_limit=60000, nthreads=9) for s in sb]
+    with binding.DeftKnapsack(max_batch=24, max_items=600, max_knapsacks=2, max_capacity=60000, flags=2) as h:
+        db, ds = h.upload(batches[0]), binding.DeviceSchedules(sb[0], h.device)
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            h.solve_batch(db)
+            out = binding.simulate_schedule(h, ds)
+        side.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            h.solve_batch(db, torch.cuda.current_stream())
+            out = binding.simulate_schedule(h, ds, torch.cuda.current_stream())
+        for rep in range(4):
+            kb, ref, s, expected = batches[rep % 3], refs[rep % 3], sb[rep % 2], want[rep % 2]
+            for name in ("weights", "values", "capacities"):
+                getattr(db, name).copy_(torch.from_numpy(np.ascontiguousarray(getattr(kb, name), np.int32)))
+            for name in ("comm_time", "drop_time", "forward_time", "backward_time"):
+                getattr(ds, name).copy_(torch.from_numpy(np.ascontiguousarray(getattr(s, name), np.int32)))
+            for t in (db.out.total_value, db.out.assignment, db.out.knap_value, db.out.knap_load, db.out.status, out.stage_case, out.tail):
+                t.fill_(-7)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert_same(kb, db.out, ref)
+            assert_same_schedule({k: getattr(out, k).cpu().numpy() for k in FIELDS}, expected)

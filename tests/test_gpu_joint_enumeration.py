@@ -211,3 +211,19 @@ def test_lists_that_run_over_are_made_in_parts(binding, oracle, seed, v_hi):
     kb.weights[:] = np.stack([w0, w1], axis=1)
     kb.values[:] = r.integers(1, v_hi + 1, size=w0.shape)
     run(binding, oracle, kb)
+
+
+def test_parts_settle_what_lists_that_run_over_left(binding, oracle):
+    """One instance of each of these inputs has lists that run over: made in parts they settle it (without parts one a call
+    is left to its table).  An attempt that runs late may leave one."""
+    batches = []
+    for seed in (102, 103, 106, 108):
+        r = np.random.Generator(np.random.PCG64(seed))
+        w0 = r.integers(1, 65, size=(256, 64))
+        kb = W.hetero_joint(batch=256, n=64, c1=512, c2=512)
+        kb.weights[:] = np.stack([w0, w0 * r.integers(3, 7, size=w0.shape)], axis=1)
+        kb.values[:] = r.integers(1, 1001, size=w0.shape)
+        batches.append(kb)
+    left = [cells // (64 * 513 * 513) for cells, _ in _profiled(binding, oracle, batches, 512, 512)]
+    print(f"left: {left}", flush=True)
+    assert sum(left) <= 1
