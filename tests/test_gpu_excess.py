@@ -229,6 +229,27 @@ def test_capacity_sweeps_by_the_quicker_way(binding, oracle, n, batch, sigma, li
     assert took < limit
 
 
+def _capacity_sweep(w, caps):
+    B, n = w.shape
+    return W.KnapsackBatch(name="sweep", mode=W.MODE_CAPACITY_SWEEP, batch=B, item_stride=n, knap_stride=caps.shape[1],
+                           n_items=np.full(B, n, np.int32), n_knapsacks=np.full(B, caps.shape[1], np.int32), weights=w, values=w.copy(),
+                           capacities=caps, fill_order=None, drop_time=None)
+
+
+def test_a_capacity_sweep_looks_closely(binding, oracle):
+    """One instance of these ends on an item that is most of its window; its excess is found, and nothing is swept."""
+    B, n = 454, 348
+    r = np.random.Generator(np.random.PCG64(11))
+    x = r.lognormal(0.0, 1.2, size=(B, n))
+    w = np.maximum(1, np.rint(x * (8707 / x.sum(axis=1, keepdims=True)))).astype(np.int32)
+    back = np.rint(3748 * r.uniform(0.9, 1.1, size=B))
+    kb = _capacity_sweep(w, np.rint(back[:, None] * np.array([[1.0, 1.05]])).astype(np.int32))
+    out, swept, took, _ = _swept(binding, kb, FLAG, max_items=n, max_knapsacks=2, max_capacity=int(kb.capacities.max()))
+    print(f"{took:.1f} us, {swept} cells swept", flush=True)
+    assert_same_outputs(kb, out, oracle.solve_batch(kb, nthreads=16))
+    assert swept == 0
+
+
 @pytest.mark.parametrize("n,m,batch,max_capacity", [
     (300, 1, 40, 14000), (300, 2, 40, 14000), (300, 3, 24, 30000),       # one to three wavefronts an instance
     (314, 11, 70, 14000), (314, 11, 900, 14000), (314, 11, 1500, 14000), (314, 5, 2500, 9000),   # four, and as few as the batch leaves room for
