@@ -17,8 +17,7 @@ BitsLayout bits_layout(const SeqBitsPlan &p, bool caps_sweep)
     lay.mark_words = caps_sweep ? p.n_pad : p.n_pad / 4;
     lay.plane_words = p.row_words * bits_plane_stride(p.planes);
     lay.share = 1;
-    lay.fewest = lay.sure = kBitsExcessItems;
-    lay.light = 0;
+    lay.turns = 1;
     lay.wave_words = 2 * p.row_words + 4 + (p.n_pad + 8) + p.n_pad / 2 + lay.mark_words;
     return lay;
 }
@@ -113,16 +112,14 @@ hipError_t bits_launch(SeqBitsPlan p, const BatchArgs &a, const BitsQueueArgs<QU
             const int by_regs = 4 * bits_waves_per_simd(p.words_per_lane, p.planes) / share;
             if ((int64_t)(by_lds < by_regs ? by_lds : by_regs) * p.compute_units >= a.batch) break;
         }
-        const BitsExcessCaps by = bits_excess_caps((a.knap_stride + share - 1) / share, p.words_per_lane);
-        lay.fewest = by.fewest;
-        lay.sure = by.sure;
-        lay.light = by.light;
-        if (a.item_stride >= by.fewest && share > 1) {
-            lay.share = share;
+        lay.turns = (int16_t)((a.knap_stride + share - 1) / share);
+        const int fewest = bits_tried_caps(lay.turns, p.words_per_lane).fewest;
+        if (a.item_stride >= fewest && share > 1) {
+            lay.share = (int16_t)share;
             return launch((unsigned)a.batch, share);
         }
-        if (a.item_stride < by.fewest) {
-            bits_lists(&p, a.item_stride, by.fewest);
+        if (a.item_stride < fewest) {
+            bits_lists(&p, a.item_stride, fewest);
             lay = bits_layout(p, caps_sweep);
         }
     }

@@ -68,13 +68,13 @@ constexpr int kBitsExcessItems = 97;
 // 0.85 to 1.59, 200 0.82 to 1.43, 250 0.57 to 0.86; 7 words and more with some 20 to 38 light items 1.01 to 2.23, with 48 to 90 0.38 to
 // 1.04.  Over 381 calls (130 to 450 items, 5 to 6000 lists) 0.60 in the geometric mean, 19 slower by 5 % or more, up to 1.38 times; from 129 items on
 // in any case 0.66, 103 and 2.3; with 28 and 40 light items 27 and 17 slower, and 25 and 35 slower than so.
-struct BitsExcessCaps {
-    int fewest, sure, light;
+struct BitsTried {
+    int fewest, sure, light;  // items of a list whose stages are tried by what they leave out: if so many are light, and in any case
 };
-constexpr BitsExcessCaps bits_excess_caps(int capacities, int words)
+constexpr BitsTried bits_tried_caps(int capacities, int words)
 {
     const int few = 129 + 12 * (words > 7 ? words - 7 : 0);
-    return capacities <= 3 ? BitsExcessCaps{129, few < 200 ? few : 200, 32} : words < 7 ? BitsExcessCaps{225, 225, 0} : BitsExcessCaps{160, 300, 36};
+    return capacities <= 3 ? BitsTried{129, few < 200 ? few : 200, 32} : words < 7 ? BitsTried{225, 225, 0} : BitsTried{160, 300, 36};
 }
 constexpr int kBitsEnumItems = 6;  // stages offered at most this many items are settled by enumeration
 
@@ -161,8 +161,8 @@ namespace {
 // [zeros: row_words][set: row_words][pad: 4][prefix: n_pad + 8][index: n_pad / 2][marks: mark_words].
 struct BitsLayout {
     int32_t row_words, n_pad, mark_words, plane_words, wave_words;
-    int32_t fewest, sure, light;  // items of a list whose stages are tried by what they leave out: if so many are light, and in any case
-    int32_t share;  // wavefronts of an instance (capacity sweep; else 1): they share its part, and deal its capacities out
+    int16_t share;  // wavefronts of an instance (capacity sweep; else 1): they share its part, and deal its capacities out
+    int16_t turns;  // capacities that a wavefront has in turn then
 };
 // One instance's share of it.
 struct BitsLds {
@@ -538,6 +538,9 @@ struct BitsNoArgs {
 };
 template <bool QUEUES>
 using BitsQueueArgs = std::conditional_t<QUEUES, ScheduleArgs, BitsNoArgs>;
+// The arguments and the workgroup's size behind them (12 bytes on) end within three cache lines: a fourth is fetched by itself, 0.2 us
+// of a call's 8 to 12.
+static_assert(sizeof(BatchArgs) + sizeof(BitsNoArgs) + sizeof(BitsLayout) + sizeof(void *) + 14 <= 192, "kernel arguments");
 
 // K: words per lane (capacities up to 2048 K - 1).  NP: planes (lists of up to 2^NP items).
 // a.mode: DEFT_MODE_SEQUENTIAL, DEFT_MODE_RECURSIVE or DEFT_MODE_CAPACITY_SWEEP.  QUEUES: the two task queues (q; the
@@ -697,7 +700,8 @@ seq_bits_kernel(BatchArgs a, BitsQueueArgs<QUEUES> q, BitsLayout lay, unsigned l
     auto list = [&](int i0) { return i0 + lane < n ? l.prefix[i0 + lane] : kGone; };
     // (Where items heavier than a quarter of the window hold more than half of the time, the excess is mostly out of reach, and where
     // too few items of the list's mean weight fill the window it is not tried.)
-    bool long_list = EXCESS && n >= lay.fewest;
+    const BitsTried tried = caps_sweep ? bits_tried_caps(lay.turns, K) : BitsTried{kBitsExcessItems, kBitsExcessItems, 0};
+    bool long_list = EXCESS && n >= tried.fewest;
     if (long_list) {
         const int most = bits_wave_max(cap_l), quarter = most >> 2;
         int light = 0, heavy = 0, items = 0, tiny = 0;
@@ -710,7 +714,7 @@ seq_bits_kernel(BatchArgs a, BitsQueueArgs<QUEUES> q, BitsLayout lay, unsigned l
         });
         light = bits_wave_sum(light);
         heavy = bits_wave_sum(heavy);
-        long_list = light > heavy && items * most / kExcessFewest >= light + heavy && (n >= lay.sure || tiny >= lay.light);  // (4096 items of 65535)
+        long_list = light > heavy && items * most / kExcessFewest >= light + heavy && (n >= tried.sure || tiny >= tried.light);  // (4096 items of 65535)
     }
     if (long_list) list_weights();
     // Where wavefronts share an instance: [0 .. 30] the values, then whether a capacity is left over (in the place of the
