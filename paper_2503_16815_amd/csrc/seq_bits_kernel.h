@@ -60,21 +60,21 @@ namespace {
 // Calls of shorter lists run on kernels without it, whose sweep has the registers (66 items: 17.7 against 20.8 us).
 constexpr int kBitsExcessItems = 97;
 // In a capacity sweep one sweep answers all capacities, and one capacity that is not answered by itself sends the others
-// along, which takes both.  What pays goes by the items, the capacities a wavefront has in turn, the words of a row, and the
-// items of up to 32 that the lowest sums are made of: lists of `fewest` items are tried if they have `light` of those, lists of
-// `sure` items in any case.  Time by kernels without stages by what they leave out = 1 (eleven capacities, lognormal times,
-// sigma 0.7 to 1.2): up to three capacities in turn, rows of up to 7 words 130 items 0.55 to 1.12, 160 0.42 to 0.97; 10 words 130
-// items 0.90 and 1.48, 160 0.38 to 0.93; 14 and 20 words 160 items 0.42 to 1.40, 200 0.24 to 0.99.  More of them: up to 5 words 160 items
-// 0.85 to 1.59, 200 0.82 to 1.43, 250 0.57 to 0.86; 7 words and more with some 20 to 38 light items 1.01 to 2.23, with 48 to 90 0.38 to
-// 1.04.  Over 381 calls (130 to 450 items, 5 to 6000 lists) 0.60 in the geometric mean, 19 slower by 5 % or more, up to 1.38 times; from 129 items on
-// in any case 0.66, 103 and 2.3; with 28 and 40 light items 27 and 17 slower, and 25 and 35 slower than so.
+// along, which takes both.  What pays goes by how many items of mean weight fill the smallest window, and by the capacities that a wavefront has
+// in turn.  Time by the row alone = 1, 2100 calls (129 to 420 items, 1 to 2500 lists, one to eleven capacities), every list tried: one
+// capacity in turn 1.27 where 40 to 48 items fill it, 0.97 to 54, 0.93 to 60, 0.74 to 66; two 1.33, 1.13, 1.03, 0.80; three 1.49,
+// 1.28, 1.19, 0.89; four to six 1.5 up to 66, 1.24 to 75, 0.85 from there on; more 1.9 up to 75, 1.58 to 85, 0.97.  Lists that are
+// not tried take some 2 us longer on these kernels (14 -> 16), so from four in turn on shorter ones get kernels without them, and rows of 7
+// words and more ask for 36 items of up to 32 besides, which the lowest sums are made of, or lists of 300 (200 items without, 1500 lists, eleven
+// capacities: 98 us by the row, 184 tried).
 struct BitsTried {
-    int fewest, sure, light;  // items of a list whose stages are tried by what they leave out: if so many are light, and in any case
+    int fewest, fill;  // items of a list whose stages are tried by what they leave out, and of its mean weight in the window
+    int sure, light;   // fewer items than `sure`: if so many are light
 };
 constexpr BitsTried bits_tried_caps(int capacities, int words)
 {
-    const int few = 129 + 12 * (words > 7 ? words - 7 : 0);
-    return capacities <= 3 ? BitsTried{129, few < 200 ? few : 200, 32} : words < 7 ? BitsTried{225, 225, 0} : BitsTried{160, 300, 36};
+    const int fill = 48 + 6 * (capacities - 1);
+    return capacities <= 3 ? BitsTried{129, fill, 129, 0} : words < 7 ? BitsTried{225, fill, 225, 0} : BitsTried{160, fill, 300, 36};
 }
 constexpr int kBitsEnumItems = 6;  // stages offered at most this many items are settled by enumeration
 
@@ -699,11 +699,12 @@ seq_bits_kernel(BatchArgs a, BitsQueueArgs<QUEUES> q, BitsLayout lay, unsigned l
     };
     auto list = [&](int i0) { return i0 + lane < n ? l.prefix[i0 + lane] : kGone; };
     // (Where items heavier than a quarter of the window hold more than half of the time, the excess is mostly out of reach, and where
-    // too few items of the list's mean weight fill the window it is not tried.)
-    const BitsTried tried = caps_sweep ? bits_tried_caps(lay.turns, K) : BitsTried{kBitsExcessItems, kBitsExcessItems, 0};
+    // too few items of the list's mean weight fill the window, a capacity sweep's smallest one, it is not tried.)
+    const BitsTried tried = caps_sweep ? bits_tried_caps(lay.turns, K) : BitsTried{kBitsExcessItems, kExcessFewest, kBitsExcessItems, 0};
     bool long_list = EXCESS && n >= tried.fewest;
     if (long_list) {
         const int most = bits_wave_max(cap_l), quarter = most >> 2;
+        const int window = caps_sweep ? min(most, -bits_wave_max(cap_l > 0 ? -cap_l : -0x7fffffff)) : most;
         int light = 0, heavy = 0, items = 0, tiny = 0;
         chunks([&](int i0, int w, int) {
             const bool in = i0 + lane < n && w <= most;
@@ -714,7 +715,7 @@ seq_bits_kernel(BatchArgs a, BitsQueueArgs<QUEUES> q, BitsLayout lay, unsigned l
         });
         light = bits_wave_sum(light);
         heavy = bits_wave_sum(heavy);
-        long_list = light > heavy && items * most / kExcessFewest >= light + heavy && (n >= tried.sure || tiny >= tried.light);  // (4096 items of 65535)
+        long_list = light > heavy && items * window / tried.fill >= light + heavy && (n >= tried.sure || tiny >= tried.light);  // (4096 items of 65535)
     }
     if (long_list) list_weights();
     // Where wavefronts share an instance: [0 .. 30] the values, then whether a capacity is left over (in the place of the

@@ -236,6 +236,26 @@ def _capacity_sweep(w, caps):
                            capacities=caps, fill_order=None, drop_time=None)
 
 
+@pytest.mark.parametrize("batch,m,cap,fill,sigma", [(300, 8, 6000, 44, 0.7), (300, 11, 3000, 40, 0.9), (2000, 3, 11000, 42, 0.6)])
+def test_capacity_sweeps_whose_smallest_window_a_few_items_fill(binding, oracle, batch, m, cap, fill, sigma):
+    """Some forty items fill it: swept at once.  One item more, and so on the kernels with stages by what they leave out, takes as
+    measured 1.10, 1.09 and 1.03 times as long (with every capacity tried 2.0, 1.9 and 1.5 times)."""
+    r = np.random.Generator(np.random.PCG64(61000))
+    n = 129
+    x = r.lognormal(0.0, sigma, size=(batch, n))
+    w = np.maximum(1, np.rint(x * (cap * n / fill / x.sum(axis=1, keepdims=True)))).astype(np.int32)
+    caps = np.rint(cap * r.uniform(0.95, 1.05, size=(batch, 1)) * (1 + 0.05 * np.arange(m)[None, :])).astype(np.int32)
+    took = []
+    for items in (128, 129):
+        kb = _capacity_sweep(w[:, :items].copy(), caps)
+        out, _, us, _ = _swept(binding, kb, FLAG, max_items=items, max_knapsacks=m, max_capacity=int(caps.max()))
+        took.append(us)
+        if batch == 300:
+            assert_same_outputs(kb, out, oracle.solve_batch(kb, nthreads=16))
+    print(f"{batch} x {m}: 128 items {took[0]:.1f} us, 129 items {took[1]:.1f} us", flush=True)
+    assert took[1] < 1.25 * took[0]
+
+
 def test_a_capacity_sweep_looks_closely(binding, oracle):
     """One instance of these ends on an item that is most of its window; its excess is found, and nothing is swept."""
     B, n = 454, 348
