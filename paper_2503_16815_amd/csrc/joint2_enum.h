@@ -18,18 +18,19 @@
 // the best selection met loses no more than G, all better or equal ones have been met: it is the answer, and
 // among equals the one with the smallest choice number is the one that the DP's walk returns.  Where a list runs over,
 // smaller steps and other groups are tried, then Q is made in parts, one after the other: the choices of its items of
-// least loss (up to four, three choices each) are a part's own, so a part is half of the list or less, and P1 and P2 stay as
-// they are.  (Of 24 two-link batches of 256 ten had an instance whose lists ran over so that it was left, and took 2.8 to 4.4 ms; five have
-// now, the others take 1.1 to 2.4 ms.)  If lists or time run over (a share of what the sweep is expected to take), or the table sweep, which begins beside it when a compute unit is free, ends first,
-// the instance is left to that; so are instances in which the prices are zero (everything fits one link or the other: all
-// choices cost nothing).
+// least loss (up to four, three choices each) are a part's own, and P1 and P2 stay as they are.  (The part of the best choices is the
+// largest: of an item it keeps half of the list at least where one departure is open, a third where both are.)  If lists or time
+// run over (a share of what the sweep is expected to take), or the table sweep, which begins beside it when a compute unit is free, ends
+// first, the instance is left to that; so are instances in which the prices are zero (everything fits one link or the other:
+// all choices cost nothing).
 //
 // All quantities that decide are whole numbers: prices and losses in units of 2^-F, values as they are.
 //
 // What bounds it: latency.  One workgroup owns an instance; a round is a chain of barriers (one for an item of each group
 // once the lists are long), its pairs are lookups in LDS at places of the lanes' own, and a launch lasts as long as its hardest
-// instance.  Of the two-link batch half of the instances are solved after 85 us, the last one after 0.6 to 1.3 ms, 1.1 to 2.4 where lists run over; by the input
-// one of some 1200 is left to the table sweep, and the call takes 3.9 to 4.4 ms then (all by the sweep: 6.36).  40 instances of 20 to 62
+// instance.  Of the two-link batch half of the instances are solved after 85 us, the last one after 0.6 to 1.3 ms, 1.1 to 2.4 where lists run
+// over (2.8 to 4.4 without parts); by the input one of some 1200 is left to the table sweep, and the call takes 3.9 to 4.4 ms then (all
+// by the sweep: 6.36).  40 instances of 20 to 62
 // items 0.41 of the sweep, 256 0.53 (geometric means over 30 kinds each).
 // Tried and not kept: every lane noting ties as it meets them (two passes instead, the second only where several selections
 // are as good: 72 -> 5 ms), Q sorted by link 0 alone, or by link 1 in steps of 128 (cells of both: pairs / 3), no table of
@@ -498,8 +499,9 @@ __device__ __forceinline__ void jt_enumerate(const BatchArgs &a, int inst, State
         const int known = least < kNever ? least : (int)min(kReach * (long long)G, (long long)kNever - 1);
         int best = known + 1, copies = 0;  // what this lane's best selection loses, and whether it has met it twice
         EnumResult chosen{-1, 0, 0, 0, 0};
-        bool several = false, again = false;
+        bool several = false, again = false, filtered = false;
         int size[3] = {0, 0, 0};
+        const int coarse = max(0, 18 - __builtin_clz(G | 1));  // G in 14 bits
 #pragma unroll 1
         for (int pass = 0, part = 0;;) {
             int part_loss = 0, part_use = 0;
@@ -693,8 +695,7 @@ __device__ __forceinline__ void jt_enumerate(const BatchArgs &a, int inst, State
                 // What a partner loses at least, the room that it leaves included, where a pair leaves room in a cell: the least loss
                 // in the cell, or in one below it plus the price of the room that is certainly left then.  16 bits, rounded
                 // down.
-                const bool filtered = size[1] * size[2] >= kFilterPairs;
-                const int coarse = max(0, 18 - __builtin_clz(G | 1));  // G in 14 bits
+                filtered = size[1] * size[2] >= kFilterPairs;
                 if (filtered) {
                     constexpr int kRows = kCells0 / kEnumWaves, kFar = 0xffff;
                     const int one0 = min(l0 >> coarse, kFar), one1 = min(l1 >> coarse, kFar);
@@ -736,8 +737,6 @@ __device__ __forceinline__ void jt_enumerate(const BatchArgs &a, int inst, State
             // this settles the matter but several selections are as good, once more, for the one whose choices, two
             // bits each with the last item's on top, make the smallest number.  (One loop for everything: the code is run
             // a few times, and fetching it is a good part of what that takes.)
-            const bool filtered = size[1] * size[2] >= kFilterPairs;
-            const int coarse = max(0, 18 - __builtin_clz(G | 1));  // (as above)
             const int room0 = c0 - used0 + s.q_default[0], room1 = c1 - used1 + s.q_default[1];
             uint32_t *queue = s.list.queue[wave];
             const int chunks = (size[2] + 63) >> 6;
