@@ -30,12 +30,13 @@ constexpr int kExcessFewest = 48, kExcessTries = 6;
 // Windows from which on what the 64 lowest sums and the run in the items' order do not show is looked for further (the runs
 // lightest first, the wide set): below, the row's own sweep is as quick.
 constexpr int kExcessThorough = 2048;
-// And not where the excess is more than half of the window and fewer items than this come before it: there it is mostly a list of
-// heavy items, what is looked for further is not found, and takes as long as the row's sweep.  1500 lists of 140 items with a window of 8000 cells
-// (Algorithm 1): one of them, its excess 5752, 110000 cycles where the others take 20000; the call 48.1 -> 35.0 us.  From 160 items on it is mostly
-// found (1024 ResNet-101-shaped backward stages 16 to 32 us, 16 to 53 without).  A capacity sweep looks in any case, for it would sweep at the
-// largest capacity for all of them (454 lists of 348 items, two capacities from 3748 on: 22 us, 43 otherwise).
-constexpr int kExcessMany = 160;
+// And not where the excess is more than three quarters of the window and fewer items than this come before it: there it is mostly a list of
+// heavy items, what is looked for further is not found, and takes as long as the row's sweep.  Forty inputs each, looked for always,
+// up to half of the window or from 160 items on, and so, us in the geometric mean: 4096 ResNet-101-shaped schedules 46.0, 45.9, 43.5; task queues 125.9,
+// 127.7, 122.4; 1500 lists of 140 items (Algorithm 1) with windows of 8000 cells 26.7, 28.3, 26.1, of 11700 cells 37.0, 34.0, 34.0; of 240
+// items in two windows 35.0, 34.8, 33.0.  A capacity sweep looks in any case, for it would sweep at the largest capacity for all of them
+// (454 lists of 348 items, two capacities from 3748 on: 22 us, 43 otherwise).
+constexpr int kExcessMany = 140;
 
 enum ExcessResult { kExcessEmpty, kExcessDone, kExcessNot };
 enum ExcessAnswer { kExcessYes, kExcessNo, kExcessUnsure };
@@ -273,7 +274,7 @@ __device__ __forceinline__ ExcessResult excess_stage(List &&list, int lane, int 
         if (E > 0 && items < kExcessFewest) return kExcessNot;
         ExcessAnswer answer = kExcessYes;
         for (int attempt = 0; E > 0; ++attempt) {
-            const bool thorough = persistent || (C >= kExcessThorough && (2 * E <= C || items >= kExcessMany));
+            const bool thorough = persistent || (C >= kExcessThorough && (4 * E <= 3 * C || items >= kExcessMany));
             // Where all that is lighter than the excess weighs less than that, the items that follow do not help for long: each adds
             // to both.
             if (E > 63) {

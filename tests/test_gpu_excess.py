@@ -194,22 +194,32 @@ def test_lists_too_heavy_for_the_excess_are_swept_at_once(binding, cap):
     assert with_ < 1.11 * without
 
 
-@pytest.mark.parametrize("cap,limit", [(8000, 45), (11700, 48)])
-def test_a_hopeless_excess_is_left_soon(binding, oracle, cap, limit):
-    """Of 1500 lists of 140 items a few end on an item of half of the window: not looked for at length (us as measured: 36 and 40;
-    with all that there is 50 and 51, in kernels without stages by excess 32 and 39)."""
-    B, n = 1500, 140
-    r = np.random.Generator(np.random.PCG64(7))
-    x = r.lognormal(0.0, 1.2, size=(B, n))
-    w = np.maximum(1, np.rint(x * ((1.8 * cap + n) / x.sum(axis=1, keepdims=True)))).astype(np.int32)
-    back = np.rint(cap * r.uniform(0.9, 1.1, size=B)).astype(np.int32)
-    kb = W.KnapsackBatch(name="hopeless", mode=W.MODE_RECURSIVE, batch=B, item_stride=n, knap_stride=2, n_items=np.full(B, n, np.int32),
-                         n_knapsacks=np.ones(B, np.int32), weights=w, values=w.copy(), capacities=np.stack([back, 0 * back], axis=1),
-                         fill_order=None, drop_time=np.rint(w / w.sum(axis=1, keepdims=True) * back[:, None]).astype(np.int32))
-    out, _, took, _ = _swept(binding, kb, FLAG, max_items=n, max_knapsacks=2, max_capacity=int(back.max()))
-    print(f"{cap}: {took:.1f} us", flush=True)
-    assert_same_outputs(kb, out, oracle.solve_batch(kb, nthreads=16))
-    assert took < limit
+@pytest.mark.parametrize("cap,limit", [(8000, 0.97), (11700, 1.035)])
+def test_how_long_a_large_excess_is_looked_for(binding, oracle, cap, limit):
+    """Of 1500 lists of 140 items a few end on an item of half of the window and more.  Against their first 96 items, which the rows sweep,
+    in the geometric mean over twelve inputs, as measured: 0.90 and 0.99; looked for at length always 0.92 and 1.08, only where the
+    excess is half of the window at most 1.07 and 1.03."""
+    B, ratios = 1500, []
+    for seed in range(12):
+        r = np.random.Generator(np.random.PCG64(seed))
+        x = r.lognormal(0.0, 1.2, size=(B, 140))
+        w = np.maximum(1, np.rint(x * ((1.8 * cap + 140) / x.sum(axis=1, keepdims=True)))).astype(np.int32)
+        back = np.rint(cap * r.uniform(0.9, 1.1, size=B)).astype(np.int32)
+        drop = np.rint(w / w.sum(axis=1, keepdims=True) * back[:, None])
+        took = []
+        for n in (96, 140):
+            kb = W.KnapsackBatch(name="large_excess", mode=W.MODE_RECURSIVE, batch=B, item_stride=n, knap_stride=2,
+                                 n_items=np.full(B, n, np.int32), n_knapsacks=np.ones(B, np.int32), weights=w[:, :n].copy(),
+                                 values=w[:, :n].copy(), capacities=np.stack([back, 0 * back], axis=1), fill_order=None,
+                                 drop_time=drop[:, :n].copy())
+            out, _, us, _ = _swept(binding, kb, FLAG, max_items=n, max_knapsacks=2, max_capacity=int(back.max()))
+            took.append(us)
+        if seed == 7:   # (one of them is swept after it was looked for)
+            assert_same_outputs(kb, out, oracle.solve_batch(kb, nthreads=16))
+        ratios.append(took[1] / took[0])
+    mean = float(np.exp(np.mean(np.log(ratios))))
+    print(f"{cap}: {mean:.3f}, {min(ratios):.2f} to {max(ratios):.2f}", flush=True)
+    assert mean < limit
 
 
 @pytest.mark.parametrize("n,batch,sigma,limit", [(140, 1500, 1.0, 100), (200, 1500, 0.7, 140), (200, 60, 1.0, 35), (314, 1500, 1.0, 100)])
