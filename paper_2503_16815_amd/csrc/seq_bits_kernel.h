@@ -27,7 +27,7 @@
 // item reached a fresh sum, took half of the kernel - the fresh words are few and found by
 // ballots, bit by bit - and its LDS held a compute unit to eight instances.  The ResNet-101-shaped
 // sweep of 4096 schedules took 0.469 ms with it and one lookup per taken item in the walk, and
-// 0.096 ms so; stages of such lists are now mostly answered without a sweep, seq_excess.h: 0.042 ms.)
+// 0.096 ms so; stages of such lists are now mostly answered without a sweep, seq_excess.h: 0.033 to 0.046 ms.)
 //
 // What bounds the sweep: a chain of one LDS write and one LDS read per item (1024 instances, a wavefront per SIMD:
 // vector units busy 27 % of the cycles, LDS 16 %, the wavefront waiting 43 %) and, with the compute unit full
