@@ -59,7 +59,7 @@ def test_counts_never_exceed_the_oracles(oracle):
 
 
 def test_the_line_is_short_enough_to_be_read_from_a_log(oracle):
-    """The record on stdout has what the run is judged by and stays within its length with every configuration in it."""
+    """The record on stdout has the metric, its configuration and every time, and stays within its length with every configuration in it."""
     import json
     names = ("tiny", "resnet101_one_call_per_k", "vgg19", "gpt2", "hetero", "backward", "inflation", "schedule")
     names += tuple(f"{n}_{kind}" for kind in ("promised", "bitset")
